@@ -148,19 +148,23 @@ template <bool HALVES> __device__ __forceinline__ void lanes_add_runs_to_slots(f
     }
 }
 
-// One sub-stream as its lane sees it.  Stream words travel memory -> blk -> LDS ring -> next -> buf.
+// One sub-stream as its lane sees it.  Stream words travel memory -> blk -> LDS ring -> r.
 // The ring of a wave is 4 KiB, 4 KiB aligned; ring word j of the lane sits at byte
-// (j % 16) * 256 + lane * 4 of it, so the lanes of a wave never collide on a bank and the slot bits
-// (0xF00) can be OR-ed into the lane's base address.
+// (j % 16) * 256 + lane * 4 of it, so the lanes of a wave never collide on a bank.  Positions and block counts are
+// kept times 8 (a block is 128 bits = 1024 units): bits 8-11 of a position are then the slot of its word as they
+// stand, and bits 10-11 of a block count the slot of the block's first word.
+// Huffman positions are kept one bit early (kLead): a window that begins there is "the next 11 bits, times 2" under a
+// mask, which is the byte offset of the table entry, so a look-up needs no shift of its own.
+template <int CODEC> struct Lead { static constexpr uint32_t kBits = CODEC == DC_CODEC_TANS ? 0 : 1; };
 struct Stream {
-    uint64_t buf;   // LSB-first bit buffer
-    uint32_t state; // 256 * (words taken out of the ring) + (valid bits in buf, at most 64)
-    uint32_t next;  // the word that follows buf
-    uint32_t tk10;  // 1024 * (blocks asked for so far, f of the placement rule)
-    uint32_t nb10;  // 1024 * (blocks of the stream)
-    uint32_t npend[2]; // -1024: blk[p] holds a block asked for at the last step of parity p, not yet in the ring; else 0
+    uint32_t pos;     // 8 * (position in bits - kLead)
+    uint32_t asked;   // 1024 * (blocks asked for so far, f of the placement rule)
+    uint32_t end;     // 1024 * (blocks of the stream)
+    uint32_t r[4];    // the words at the position and behind it: all a half group can need
     uint32_t x4;      // tANS: 4 * state = byte offset of the state's table entry
     u32x4 blk[2];     // a block travels for two steps: asked for at step h, put into the ring at step h + 2
+    uint32_t slot[2]; // where in the ring blk[p] goes
+    bool pend[2];     // whether blk[p] is a block of this stream (asked for at the last step of parity p)
 };
 
 // What the lanes of one stream set share: where the block region of the set's area stands.
@@ -174,19 +178,24 @@ struct Region {
 // 16 bytes at an address that is a multiple of 4 only
 typedef uint32_t u32x4_align4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// Block number b of a stream goes to ring words 4b .. 4b+3.
-__device__ __forceinline__ void push_block(uint32_t block10, const u32x4 &blk, uint32_t ring_lane)
+// A block goes to the four ring words from `slot` on (block number b of a stream: ring words 4b .. 4b+3).
+__device__ __forceinline__ void push_block(uint32_t slot, const u32x4 &blk)
 {
-    lds_u32 *w = (lds_u32 *)(uintptr_t)((block10 & 0xF00u) | ring_lane);
+    lds_u32 *w = (lds_u32 *)(uintptr_t)slot;
     w[0] = blk[0];
     w[64] = blk[1];
     w[128] = blk[2];
     w[192] = blk[3];
 }
 
-__device__ __forceinline__ uint32_t ring_word(uint32_t state, uint32_t ring_lane)
+// The four words from the position on.  KEEP_FIRST: the word at the position is only read when the position has
+// moved to another word, because its slot may have been given to a later block since (see stream_step).
+template <bool KEEP_FIRST> __device__ __forceinline__ void read_window(Stream &s, uint32_t before, uint32_t ring_lane)
 {
-    return lds_load32((state & 0xF00u) | ring_lane);
+    const uint32_t first = lds_load32((s.pos & 0xF00u) | ring_lane);
+    s.r[0] = KEEP_FIRST && ((s.pos ^ before) < 256u) ? s.r[0] : first;
+#pragma unroll
+    for (uint32_t k = 1; k < 4; k++) s.r[k] = lds_load32(((s.pos + 256u * k) & 0xF00u) | ring_lane);
 }
 
 // The lanes with `want` each take the next block of the region, in lane order.
@@ -196,52 +205,44 @@ __device__ __forceinline__ void take_blocks(Stream &s, Region &rg, bool want, u3
     const uint64_t m = __ballot(want) & rg.lanes;
     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     if (want) {
-        uint32_t off = (rg.next_block + rank) * kBlockBytes;
-        const uint32_t limit = rg.max_off & ~15u;
-        off = off < limit ? off : limit;
-        dst = *reinterpret_cast<const u32x4 *>(rg.payload8 + off);
-        s.tk10 += 1024;
+        dst = *reinterpret_cast<const u32x4 *>(rg.payload8 + (rg.next_block + rank) * kBlockBytes);
+        s.asked += 1024;
     }
     rg.next_block += (uint32_t)__popcll(m);
     if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
 }
 
-// The same inside the decode loop: every lane loads; a lane without `want` loads, and drops, a block that a
-// lane below it asks for, or the one after the last asked for (the address is inside the payload in any case).
-// A load that is always issued lets the wait for an earlier load be exact (it counts the loads issued
-// since), so a block can stay in flight across the next step's load.  npend = -1024 where the lane asked.
-template <bool UNIFORM>
-__device__ __forceinline__ void take_blocks_all_load(Stream &s, Region &rg, bool want, u32x4 &dst, uint32_t &npend)
-{
-    const uint64_t m = __ballot(want) & rg.lanes;
-    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    uint32_t off = (rg.next_block + rank) * kBlockBytes;
-    const uint32_t limit = rg.max_off & ~15u;
-    off = off < limit ? off : limit;
-    dst = *reinterpret_cast<const u32x4 *>(rg.payload8 + off);
-    npend = want ? 0xFFFFFC00u : 0u;
-    s.tk10 -= npend;
-    rg.next_block += (uint32_t)__popcll(m);
-    if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
-}
-
 // One step of the placement rule (before every half group; P = the step's parity): the block asked for two
-// steps before goes into the ring, then the lanes short of look-ahead ask for their next block.  With
-// used = 32*(words taken) - 32 - avail stream bits used so far, the rule's
-// 128*f - used < DC_LOOKAHEAD_BITS reads, times 8, tk10 < state + 8*(DC_LOOKAHEAD_BITS - 32) - 9*avail.
-// Why two steps are safe: before its decision at a step a stream has at least DC_LOOKAHEAD_BITS - 88 bits
-// placed beyond its position, at least DC_LOOKAHEAD_BITS - 48 if it asked at the step before; the blocks
-// asked for at this step and the one before are the only ones not in the ring, so at least
-// DC_LOOKAHEAD_BITS - 176 = 216 bits are, and half a group reads at most 88 + 96 + 31 = 215 bits ahead.
-template <bool UNIFORM, int P>
+// steps before goes into the ring, then the lanes short of look-ahead ask for their next block.  The rule's
+// 128*f - c < DC_LOOKAHEAD_BITS reads, times 8, asked < pos + 8*DC_LOOKAHEAD_BITS.
+// Every lane loads; a lane that asks for nothing loads, and drops, a block that a lane below it asks for, or the
+// one after the last asked for (stream_fetch has checked that the region and one block more lie inside the blob).
+// A load that is always issued lets the wait for an earlier load be exact (it counts the loads issued
+// since), so a block can stay in flight across the next step's load.
+//
+// The words of half group h are read when half group h - 1 is done, before step h, so that the step's arithmetic runs
+// while they come.  Why they are there: a stream has at least DC_LOOKAHEAD_BITS - 88 = 304 bits placed beyond its
+// position before its decision at any step, or all of its blocks; the ring lacks what was asked for at steps h - 1
+// and h - 2; so beyond the position of h it holds at least 304 - 2*88 = 128 bits, and half a group uses at most 88.
+// Why their slots are still theirs: block b goes into the slot of block b - 4 two steps after a position beyond
+// 128*b - DC_LOOKAHEAD_BITS = 128*(b - 3) - 8, and is there from the next read on, three half groups after that
+// position.  24 Huffman codes take at least 24 bits, so the position has left block b - 4.  tANS fields may be
+// empty: its last 7 bits may still be needed then, but they lie in one word, which the lane has held since its
+// position entered that word (KEEP_FIRST).
+template <bool UNIFORM, int P, int CODEC>
 __device__ __forceinline__ void stream_step(Stream &s, Region &rg, uint32_t ring_lane)
 {
-    if (s.npend[P]) push_block(s.tk10 - 1024 + s.npend[1 - P], s.blk[P], ring_lane);
-    const uint32_t avail = s.state & 0xFFu;
-    // tk10 below both bounds: the look-ahead's (at least 2368, so no wrap) and the stream's blocks
-    const uint32_t bound = s.state + 8u * (DC_LOOKAHEAD_BITS - 32) + (uint32_t)__mul24((int)avail, -9);
-    const bool want = s.tk10 < (bound < s.nb10 ? bound : s.nb10);
-    take_blocks_all_load<UNIFORM>(s, rg, want, s.blk[P], s.npend[P]);
+    if (s.pend[P]) push_block(s.slot[P], s.blk[P]);
+    const uint32_t bound = s.pos + 8u * (DC_LOOKAHEAD_BITS + Lead<CODEC>::kBits);
+    const bool want = s.asked < (bound < s.end ? bound : s.end);
+    const uint64_t m = UNIFORM ? __ballot(want) : __ballot(want) & rg.lanes;
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    s.blk[P] = *reinterpret_cast<const u32x4 *>(rg.payload8 + (rg.next_block + rank) * kBlockBytes);
+    s.slot[P] = (s.asked & 0xC00u) | ring_lane;
+    s.asked += want ? 1024u : 0u;
+    s.pend[P] = want;
+    rg.next_block += (uint32_t)__popcll(m);
+    if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
 }
 
 // Start of a sub-stream.  Block 0 of a stream is short: its first pad = 16 - hb bytes do not exist and
@@ -249,8 +250,8 @@ __device__ __forceinline__ void stream_step(Stream &s, Region &rg, uint32_t ring
 // loads the 20 bytes from the 4-byte boundary at or before the place where block 0 would start and
 // shifts them down, so the ring holds block 0 with foreign bytes in front, and starts reading behind
 // them.  Then step 0 of the rule runs for the three further times (a stream takes a block while it
-// has blocks left and fewer than DC_LOOKAHEAD_BITS bits beyond its position 8*pad), and buf and next
-// are loaded.  (The step at the head of the decode loop is the fifth time; a tANS stream has read its
+// has blocks left and fewer than DC_LOOKAHEAD_BITS bits beyond its position 8*pad), and the first words
+// are read.  (The step at the head of the decode loop is the fifth time; a tANS stream has read its
 // first state by then.)
 // What stream_fetch has asked memory for and stream_start puts into the ring.
 struct StreamFetch {
@@ -269,7 +270,7 @@ template <bool UNIFORM>
 __device__ __forceinline__ void stream_fetch(Stream &s, Region &rg, uint32_t field, StreamFetch &f)
 {
     // header field of the stream: blocks in all, and the bytes of block 0 less one
-    const uint32_t nb = field & 0xFFFu;
+    uint32_t nb = field & 0xFFFu;
     const uint32_t hb = nb ? ((field >> 12) & 15u) + 1 : 0;
     const uint32_t pad = nb ? kBlockBytes - hb : 0;
     const uint32_t whole_incl = lanes_prefix_sum<!UNIFORM>(nb ? nb - 1 : 0);
@@ -279,9 +280,16 @@ __device__ __forceinline__ void stream_fetch(Stream &s, Region &rg, uint32_t fie
         const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)whole_incl, 31);
         whole_total = (threadIdx.x & 32u) ? whole_total : lower;
     }
-    s.nb10 = nb << 10;
-    s.tk10 = 0;
-    s.npend[0] = s.npend[1] = 0;
+    // The set's lanes take whole_total blocks in all, whatever the payload holds, and look one block further at most.
+    // A region that the blob does not hold (a corrupt payload) is not read: its streams have no blocks then.
+    if (rg.next_block + whole_total > rg.max_off / kBlockBytes) {
+        nb = 0;
+        rg.next_block = 0;
+    }
+    s.end = nb << 10;
+    s.asked = 0;
+    s.pend[0] = s.pend[1] = false;
+    s.slot[0] = s.slot[1] = 0;
     f.pad = pad;
     f.has_head = nb != 0;
     f.shift = 0;
@@ -292,112 +300,58 @@ __device__ __forceinline__ void stream_fetch(Stream &s, Region &rg, uint32_t fie
         f.v = *reinterpret_cast<const u32x4_align4 *>(p);
         f.v4 = *reinterpret_cast<const uint32_t *>(p + 16);
         f.shift = at & 3u;
-        s.tk10 = 1024;
+        s.asked = 1024;
     }
 #pragma unroll
     for (int t = 0; t < 3; t++) {
-        f.got[t] = s.tk10 < s.nb10 && s.tk10 < ((8u * pad + DC_LOOKAHEAD_BITS) << 3); // 128 f < c + look-ahead, times 8
+        f.got[t] = s.asked < s.end && s.asked < ((8u * pad + DC_LOOKAHEAD_BITS) << 3); // 128 f < c + look-ahead, times 8
         take_blocks<UNIFORM>(s, rg, f.got[t], f.b[t]);
     }
 }
 
-// Second half: block 0 shifted into place and the further blocks go into the ring, and buf and next are loaded.
-__device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, uint32_t ring_lane)
+// Second half: block 0 shifted into place and the further blocks go into the ring, and the first words are read.
+// A tANS stream reads its first state, its first 11 bits, and the words after them.
+template <int CODEC> __device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, uint32_t ring_lane)
 {
     if (f.has_head) {
         const u32x4 b0 = {__builtin_amdgcn_alignbyte(f.v[1], f.v[0], f.shift), __builtin_amdgcn_alignbyte(f.v[2], f.v[1], f.shift),
                           __builtin_amdgcn_alignbyte(f.v[3], f.v[2], f.shift), __builtin_amdgcn_alignbyte(f.v4, f.v[3], f.shift)};
-        push_block(0, b0, ring_lane);
+        push_block(ring_lane, b0);
     }
 #pragma unroll
     for (int t = 0; t < 3; t++)
-        if (f.got[t]) push_block((t + 1) << 10, f.b[t], ring_lane);
-    // the stream begins `pad` bytes into block 0
-    const uint32_t skip = f.pad >> 2, bits = 8u * (f.pad & 3u);
-    const uint32_t lo = ring_word(skip << 8, ring_lane);
-    const uint32_t hi = ring_word((skip + 1) << 8, ring_lane);
-    s.buf = ((uint64_t)lo | ((uint64_t)hi << 32)) >> bits;
-    s.next = ring_word((skip + 2) << 8, ring_lane);
-    s.state = ((skip + 3) << 8) + 64 - bits;
-}
-
-// Takes the look-ahead word into the buffer when at most 32 bits are valid.  After it at least 32 bits
-// are valid, and exactly 32 only if the buffer was empty: enough for two codes of 11 bits.
-__device__ __forceinline__ void refill(Stream &s, uint32_t ring_lane)
-{
-    if ((s.state & 0xFFu) <= 32) {
-        s.buf |= (uint64_t)s.next << (s.state & 63u);
-        s.next = ring_word(s.state, ring_lane);
-        s.state += 256 + 32;
+        if (f.got[t]) push_block(ring_lane + ((t + 1) << 10), f.b[t]);
+    s.pos = 64u * f.pad - 8u * Lead<CODEC>::kBits; // the stream begins `pad` bytes into block 0
+    read_window<false>(s, 0, ring_lane);
+    s.x4 = 0;
+    if (CODEC == DC_CODEC_TANS) {
+        const uint32_t before = s.pos;
+        s.x4 = (__builtin_amdgcn_alignbit(s.r[1], s.r[0], s.pos >> 3) & (kTableEntries - 1)) << 2;
+        s.pos += 8u * kPeekBits;
+        read_window<true>(s, before, ring_lane);
     }
 }
 
-// Three codes of 11 bits need 33 bits.  A buffer that was empty holds 32 after one refill (the three codes
-// before it used all 33 bits it had: rare, but it happens); the second call then takes one more word.
-__device__ __forceinline__ void refill33(Stream &s, uint32_t ring_lane)
-{
-    refill(s, ring_lane);
-    refill(s, ring_lane);
-}
-
-// Table entry = (length - 1) | symbol << 8: the field a 32-bit shift reads (its low 5 bits) is the
-// amount that turns "the next 11 bits, times 2" (the byte offset of the next table entry) into a
-// single shift and mask.
-__device__ __forceinline__ uint32_t table_entry(uint32_t tbl, uint32_t window_times_2)
-{
-    return lds_load16(tbl + (window_times_2 & (2 * kTableEntries - 2)));
-}
-
-// The next N (2 or 3) symbols; at least 11*N bits are valid in buf.  With m_i = length_i - 1:
-// the offsets of the three entries are (lo << 1), (lo >> m_0) and (buf >> (m_0 + m_1 + 1)), each masked
-// to 0xFFE; the bits used are sum(m_i) + N.
-template <int N> __device__ __forceinline__ void symbols(Stream &s, uint32_t tbl, uint32_t *e)
-{
-    const uint32_t lo = (uint32_t)s.buf, hi = (uint32_t)(s.buf >> 32);
-    e[0] = table_entry(tbl, lo << 1);
-    e[1] = table_entry(tbl, lo >> (e[0] & 31u));
-    uint32_t used = e[0] + e[1] + 1;
-    if (N == 3) {
-        e[2] = table_entry(tbl, __builtin_amdgcn_alignbit(hi, lo, used));
-        used += e[2] + 1;
-    }
-    used += 1;
-    s.buf >>= (used & 63u);
-    s.state -= used & 0xFFu;
-}
-
-// tANS.  Table entry of a state = nb | value << 8 | (4 * base) << 16, where nb is the width of the state's
+// The next two symbols out of the 32 bits of w (at most 22, and the lead, are used): their table entries, symbol in
+// byte 1.  Returns the bits used in its low byte.
+// Huffman: entry = length | symbol << 8; w begins one bit early, so the byte offsets of the entries are w and
+// w >> length_0 under the mask.
+// tANS: table entry of a state = nb | value << 8 | (4 * base) << 16, where nb is the width of the state's
 // field and base the next state before the field is added; bits 4-7 are 0, so that the low five bits of an
-// entry (and of a sum of two) can be used as a field width or offset as they are, and the low byte of a sum
-// of three is the number of bits used.  The next N (2 or 3) symbols; at least 11*N bits are valid in buf.
-template <int N> __device__ __forceinline__ void tans_symbols(Stream &s, uint32_t tbl, uint32_t *e)
+// entry can be used as a field width or offset as they are.
+template <int CODEC> __device__ __forceinline__ uint32_t two_symbols(uint32_t w, uint32_t &x4, uint32_t tbl, uint32_t e[2])
 {
-    const uint32_t lo = (uint32_t)s.buf, hi = (uint32_t)(s.buf >> 32);
-    e[0] = lds_load32(tbl + s.x4);
-    uint32_t x4 = (e[0] >> 16) + (__builtin_amdgcn_ubfe(lo, 0u, e[0]) << 2);
-    e[1] = lds_load32(tbl + x4);
-    x4 = (e[1] >> 16) + (__builtin_amdgcn_ubfe(lo, e[0], e[1]) << 2);
-    uint32_t used = e[0] + e[1];
-    if (N == 3) {
-        e[2] = lds_load32(tbl + x4);
-        x4 = (e[2] >> 16) + (__builtin_amdgcn_ubfe(__builtin_amdgcn_alignbit(hi, lo, used), 0u, e[2]) << 2);
-        used += e[2];
+    constexpr uint32_t kOffsetMask = 2 * kTableEntries - 2;
+    if (CODEC == DC_CODEC_TANS) {
+        e[0] = lds_load32(tbl + x4);
+        x4 = (e[0] >> 16) + (__builtin_amdgcn_ubfe(w, 0u, e[0]) << 2);
+        e[1] = lds_load32(tbl + x4);
+        x4 = (e[1] >> 16) + (__builtin_amdgcn_ubfe(w, e[0], e[1]) << 2);
+    } else {
+        e[0] = lds_load16(tbl + (w & kOffsetMask));
+        e[1] = lds_load16(tbl + ((w >> (e[0] & 31u)) & kOffsetMask));
     }
-    s.x4 = x4;
-    s.buf >>= (used & 63u);
-    s.state -= used & 0xFFu;
-}
-
-// One tANS symbol at a time, for the ragged end of a chunk.
-__device__ __forceinline__ uint32_t tans_decode1(Stream &s, uint32_t tbl, uint32_t ring_lane)
-{
-    refill(s, ring_lane);
-    const uint32_t e = lds_load32(tbl + s.x4);
-    const uint32_t nb = e & 15u;
-    s.x4 = (e >> 16) + (__builtin_amdgcn_ubfe((uint32_t)s.buf, 0u, nb) << 2);
-    s.buf >>= nb;
-    s.state -= nb;
-    return (e >> 8) & 0xFFu;
+    return e[0] + e[1];
 }
 
 // bytes 1 of four entries -> one little-endian word of four symbols
@@ -408,44 +362,44 @@ __device__ __forceinline__ uint32_t pack4(uint32_t e0, uint32_t e1, uint32_t e2,
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
-// Symbols [8*HALF, 8*HALF + 8) of a group: 3 + 2 + 3 symbols.  Only the first batch can meet an empty buffer
-// (the batch before it, the last of the half group before, may have used all 33 bits it had) and needs the second
-// refill; the two symbols leave at least 10 of the 32 bits their refill guarantees, so one refill gives the
-// last three their 33.
-template <int HALF, int CODEC>
-__device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_lane, uint32_t out[4])
+// Half a group: 8 symbols, at most 88 bits, out of the four words in r.  The words are shifted down once by the position
+// inside its word (96 bits are left, the lead among them) and then by the bits every pair of symbols has used, so that every pair starts at
+// bit 0 of w0: no lane waits for another's refill, and nothing is conditional.  A lane past its stream's last symbol
+// decodes on over what the ring holds (it has no blocks left to ask for, so its position no longer matters) and its
+// symbols are dropped where they would be stored.
+template <int CODEC>
+__device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_lane, uint32_t out[2])
 {
     uint32_t e[8];
-    refill33(s, ring_lane);
-    if (CODEC == DC_CODEC_TANS) tans_symbols<3>(s, tbl, e); else symbols<3>(s, tbl, e);
-    refill(s, ring_lane);
-    if (CODEC == DC_CODEC_TANS) tans_symbols<2>(s, tbl, e + 3); else symbols<2>(s, tbl, e + 3);
-    refill(s, ring_lane);
-    if (CODEC == DC_CODEC_TANS) tans_symbols<3>(s, tbl, e + 5); else symbols<3>(s, tbl, e + 5);
-    out[2 * HALF] = pack4(e[0], e[1], e[2], e[3]);
-    out[2 * HALF + 1] = pack4(e[4], e[5], e[6], e[7]);
+    const uint32_t o = s.pos >> 3; // shifts read the low 5 bits
+    uint32_t w0 = __builtin_amdgcn_alignbit(s.r[1], s.r[0], o);
+    uint32_t w1 = __builtin_amdgcn_alignbit(s.r[2], s.r[1], o);
+    uint32_t w2 = __builtin_amdgcn_alignbit(s.r[3], s.r[2], o);
+    const uint32_t u0 = two_symbols<CODEC>(w0, s.x4, tbl, e);
+    w0 = __builtin_amdgcn_alignbit(w1, w0, u0);
+    w1 = __builtin_amdgcn_alignbit(w2, w1, u0);
+    w2 >>= u0 & 31u;
+    const uint32_t u1 = two_symbols<CODEC>(w0, s.x4, tbl, e + 2);
+    w0 = __builtin_amdgcn_alignbit(w1, w0, u1);
+    w1 = __builtin_amdgcn_alignbit(w2, w1, u1);
+    const uint32_t u2 = two_symbols<CODEC>(w0, s.x4, tbl, e + 4);
+    w0 = __builtin_amdgcn_alignbit(w1, w0, u2);
+    const uint32_t u3 = two_symbols<CODEC>(w0, s.x4, tbl, e + 6);
+    const uint32_t before = s.pos;
+    s.pos += ((u0 + u1 + u2 + u3) & 0xFFu) << 3;
+    read_window<CODEC == DC_CODEC_TANS>(s, before, ring_lane);
+    out[0] = pack4(e[0], e[1], e[2], e[3]);
+    out[1] = pack4(e[4], e[5], e[6], e[7]);
 }
 
 // One whole group of 16 symbols with the two steps of the placement rule that precede its halves.
 template <bool UNIFORM, int CODEC = DC_CODEC_HUFFMAN>
-__device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, bool has_group,
-                                         uint32_t out[4])
+__device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t out[4])
 {
-    stream_step<UNIFORM, 0>(s, rg, ring_lane);
-    if (has_group) decode8<0, CODEC>(s, tbl, ring_lane, out);
-    stream_step<UNIFORM, 1>(s, rg, ring_lane);
-    if (has_group) decode8<1, CODEC>(s, tbl, ring_lane, out);
-}
-
-// One symbol at a time, for the ragged end of a chunk.
-__device__ __forceinline__ uint32_t decode1(Stream &s, uint32_t tbl, uint32_t ring_lane)
-{
-    refill(s, ring_lane);
-    const uint32_t e = table_entry(tbl, (uint32_t)s.buf << 1);
-    const uint32_t used = (e & 15u) + 1;
-    s.buf >>= used;
-    s.state -= used;
-    return e >> 8;
+    stream_step<UNIFORM, 0, CODEC>(s, rg, ring_lane);
+    decode8<CODEC>(s, tbl, ring_lane, out);
+    stream_step<UNIFORM, 1, CODEC>(s, rg, ring_lane);
+    decode8<CODEC>(s, tbl, ring_lane, out + 2);
 }
 
 __device__ __forceinline__ uint32_t bf16x2(float a, float b)
@@ -808,12 +762,11 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
                     if (r == (uint32_t)q) before[q] += 1u << sh;
                 const uint32_t run = 1u << (kPeekBits - l);
                 const uint32_t start = first_of[l] + rank * run;
-                const uint16_t entry = (uint16_t)((l - 1) | ((ct * SPL + s) << 8));
+                const uint16_t entry = (uint16_t)(l | ((ct * SPL + s) << 8)); // never 0: 0 means "no mark"
                 // also at the first slot of every later wave that the run reaches into, so that no
                 // wave needs a mark from another wave's slots
-                // (marks hold entry + 1, so that 0 means "no mark")
                 for (uint32_t p = start; p < start + run && p < (uint32_t)kTableEntries; p += kTableEntries / WAVES)
-                    marks[p] = (uint16_t)(entry + 1);
+                    marks[p] = entry;
             }
         }
         __syncthreads();
@@ -841,23 +794,15 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         for (int i = 0; i < EPT / 2; i++) {
             const uint32_t lo = w[i] & 0xFFFFu, hi = w[i] >> 16;
             cur = lo ? lo : cur;
-            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)(cur - 1);
+            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)cur;
             cur = hi ? hi : cur;
-            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i + 1)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)(cur - 1);
+            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i + 1)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)cur;
         }
         __syncthreads();
     }
 
     // ---- sub-stream set-up, second half: the ring is free now
-    if (huff) {
-        stream_start(st, sf, ring_lane);
-        if (CODEC == DC_CODEC_TANS) {
-            // the first state: the stream's first 11 bits (at least 40 bits are valid after the set-up)
-            st.x4 = ((uint32_t)st.buf & (kTableEntries - 1)) << 2;
-            st.buf >>= kPeekBits;
-            st.state -= kPeekBits;
-        }
-    }
+    if (huff) stream_start<CODEC>(st, sf, ring_lane);
 
     const uint32_t round_bytes = 16 * S;
     const uint32_t full_rounds = raw / round_bytes;
@@ -867,20 +812,23 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         uint8_t *d8 = static_cast<uint8_t *>(a.dst) + dst_pos + ct * 16;
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, true, w);
+            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
             store16_stream(d8 + (size_t)r * round_bytes, w[0], w[1], w[2], w[3]);
         }
         if (rem) {
-            // last, partial round: lanes hold 16, fewer or no symbols; bytes are written one by one
+            // last, partial round: lanes hold 16, fewer (one lane of the chunk) or no symbols
             const uint32_t start = ct * 16;
             const uint32_t n = rem > start ? (rem - start < 16 ? rem - start : 16) : 0;
             uint8_t *d = d8 + (size_t)full_rounds * round_bytes;
-            stream_step<UNI, 0>(st, rg, ring_lane);
-            for (uint32_t i = 0; i < (n < 8 ? n : 8); i++)
-                d[i] = (uint8_t)(CODEC == DC_CODEC_TANS ? tans_decode1(st, tbl_addr, ring_lane) : decode1(st, tbl_addr, ring_lane));
-            stream_step<UNI, 1>(st, rg, ring_lane);
-            for (uint32_t i = 8; i < n; i++)
-                d[i] = (uint8_t)(CODEC == DC_CODEC_TANS ? tans_decode1(st, tbl_addr, ring_lane) : decode1(st, tbl_addr, ring_lane));
+            uint32_t w[4];
+            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            if (n == 16) {
+                store16_stream(d, w[0], w[1], w[2], w[3]);
+            } else if (n) {
+#pragma unroll
+                for (uint32_t i = 0; i < 15; i++)
+                    if (i < n) d[i] = (uint8_t)(w[i / 4] >> (8 * (i % 4)));
+            }
         }
         leave_record(DC_TRACE_DECODED);
         return;
@@ -960,7 +908,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         float s_a = scale_of(row_a), s_b = scale_of(row_b);
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, true, w);
+            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, r, true, true);
             next_round();
             s_a = scale_of(row_a);
@@ -969,7 +917,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         if (rem) {
             const uint32_t base = full_rounds * round_bytes;
             uint32_t w[4] = {0, 0, 0, 0};
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, raw >= base + ct * 16 + 16, w);
+            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, full_rounds, raw >= base + ct_a * 16 + 16, raw >= base + ct_b * 16 + 16);
         }
         return;
@@ -999,7 +947,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             const bool whole = raw >= start + 16;
             uint32_t w[4] = {0, 0, 0, 0};
             if (huff) {
-                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, whole, w);
+                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
             } else if (whole) {
                 const u32x4 v = load16_stream(payload8 + start);
                 w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
@@ -1050,7 +998,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             const bool whole = raw >= start + 16;
             uint32_t w[4] = {0, 0, 0, 0};
             if (huff) {
-                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, whole, w);
+                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
             } else if (whole) {
                 const u32x4 v = load16_stream(payload8 + start);
                 w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
