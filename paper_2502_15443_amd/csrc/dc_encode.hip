@@ -8,7 +8,7 @@
 //                     16-byte blocks in the order of the format's placement rule.
 // For the container's second coder (tANS) dc_tans_model_kernel takes the place of dc_codes_kernel: byte
 // histogram, frequencies normalised to 2048 by the format's rule, the states of every value, and every
-// sub-stream coded backwards once, which leaves one 16-bit item (field and width) per byte in the
+// sub-stream coded backwards once, which leaves one 32-bit item (fields and width) per two bytes in the
 // workspace; dc_emit_kernel then writes those items forwards where it would write codes.
 // The stored format is in include/dc.h.
 #include <hip/hip_runtime.h>
@@ -41,7 +41,7 @@ struct EncArgs {
     uint32_t *comp; // [n_chunks] bytes of the coded payload
     uint16_t *freq;  // tANS: [n_chunks][256] normalised frequencies
     uint16_t *first; // tANS: [n_chunks][S] first state of every sub-stream
-    uint16_t *items; // tANS: [n_chunks * chunk_bytes] per byte: field | width << 12
+    uint32_t *items; // tANS: [n_chunks * chunk_bytes / 2] per two bytes: width of both fields | both fields << 8
     // results
     uint8_t *blob;
     uint64_t blob_cap;
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
 
     // ---- every sub-stream coded from its last symbol to its first: X = 2048; per symbol the smallest n with
     // (X >> n) < 2q, the field X mod 2^n, then X = 2048 + the state of the value numbered X >> n.  The items
-    // (field | n << 12) land in the workspace at the positions of their bytes.
+    // (two symbols each: width | fields << 8) land in the workspace at the positions of their bytes.
     const uint32_t groups = (raw + 15) / 16;
     if (t < S) {
         const uint32_t my_groups = t < groups ? (groups - t + S - 1) / S : 0;
@@ -412,28 +412,29 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
             } else {
                 for (uint32_t i = 0; i < n; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
             }
-            uint32_t it[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            uint32_t it[8]; // per two symbols: the width of both fields, and both fields from bit 8 on
 #pragma unroll
-            for (int i = 15; i >= 0; i--) {
-                if ((uint32_t)i < n) {
-                    const uint32_t v = (w[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-                    const uint32_t cq = cumq[v];
-                    const uint32_t first = cq & 0xFFFFu, q = cq >> 16;
-                    uint32_t nb = (uint32_t)__builtin_clz(2 * q - 1) - (31 - kTansBits); // 12 - bit length of 2q - 1
-                    nb += (X >> nb) >= 2 * q;
-                    it[i >> 1] |= ((nb << 12) | (X & ((1u << nb) - 1u))) << (16 * (i & 1));
-                    X = kTansL + state_of[(first + (X >> nb) - q) & (kTansL - 1)];
-                    bits += nb;
+            for (int j = 7; j >= 0; j--) {
+                uint32_t field = 0, width = 0;
+#pragma unroll
+                for (int i = 2 * j + 1; i >= 2 * j; i--) {
+                    if ((uint32_t)i < n) {
+                        const uint32_t v = (w[i >> 2] >> (8 * (i & 3))) & 0xFFu;
+                        const uint32_t cq = cumq[v];
+                        const uint32_t first = cq & 0xFFFFu, q = cq >> 16;
+                        uint32_t nb = (uint32_t)__builtin_clz(2 * q - 1) - (31 - kTansBits); // 12 - bit length of 2q - 1
+                        nb += (X >> nb) >= 2 * q;
+                        field = field << nb | (X & ((1u << nb) - 1u));
+                        width += nb;
+                        X = kTansL + state_of[(first + (X >> nb) - q) & (kTansL - 1)];
+                    }
                 }
+                it[j] = width | field << 8;
+                bits += width;
             }
-            uint16_t *dst = a.items + (k * a.chunk_bytes + lo);
-            if (n == 16) {
-                const u32x4 v0 = {it[0], it[1], it[2], it[3]}, v1 = {it[4], it[5], it[6], it[7]};
-                reinterpret_cast<u32x4 *>(dst)[0] = v0;
-                reinterpret_cast<u32x4 *>(dst)[1] = v1;
-            } else {
-                for (uint32_t i = 0; i < n; i++) dst[i] = (uint16_t)(it[i >> 1] >> (16 * (i & 1u)));
-            }
+            u32x4 *dst = reinterpret_cast<u32x4 *>(a.items + (k * a.chunk_bytes + lo) / 2);
+            dst[0] = u32x4{it[0], it[1], it[2], it[3]};
+            dst[1] = u32x4{it[4], it[5], it[6], it[7]};
         }
         if (my_groups) bits += kTansBits;
         a.first[k * S + t] = (uint16_t)(X - kTansL);
@@ -564,25 +565,25 @@ __global__ __launch_bounds__(256) void dc_layout_kernel(EncArgs a)
     }
 }
 
-// One sub-stream while it is written: the coder runs ahead of the position a decoder would have at
-// the current step, only as far as the next block it must hand over.
+// One sub-stream while it is written.  The coder keeps step with the decoder it writes for: the placement rule gives block
+// f its place when a decoder would ask for it, 3 to 5 blocks before its bits are coded, and the place waits in a queue
+// in LDS until the block is full.
 struct Coder {
-    uint64_t acc;       // bits not yet in the ring
-    uint32_t nbits;     // valid bits in acc
-    uint32_t words;     // words put into the ring so far
-    uint32_t next_half; // next half group to code
-    uint64_t bytes;     // its bytes, loaded ahead of use
-    u32x4 items;        // tANS: their items (field | width << 12, 16 bits each) instead
-    uint32_t n;         // how many of them exist
+    uint32_t pos;   // position in bits, from where block 0 would start
+    uint32_t asked; // blocks that have their place
+    uint32_t blk[4]; // the block at the position, as far as it is coded
+    u32x4 head;      // block 0
 };
+
+constexpr uint32_t kPlaces = 8; // places a lane's queue holds; at most 520 bits, 5 blocks, are placed beyond the position
 
 template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_emit_kernel(EncArgs a)
 {
     constexpr int WAVES = THREADS / 64;
     constexpr bool TANS = CODEC == DC_CODEC_TANS;
     constexpr uint32_t kFront = TANS ? 384 : 128; // code description at the start of a payload
-    __shared__ __attribute__((aligned(4096))) uint32_t ring[WAVES * 16 * 64]; // 16 words a lane, as in the decoder
-    __shared__ uint32_t book[256];                                            // bit-reversed code | length << 16
+    __shared__ __attribute__((aligned(16))) uint32_t places[WAVES * kPlaces * 64]; // the lanes' queues: region block numbers
+    __shared__ uint32_t book[256];                                                  // length | bit-reversed code << 16
     __shared__ uint8_t len_of[256];
     __shared__ uint32_t set_bytes[WAVES];
     __shared__ uint32_t len_count[4][kL + 1]; // [64 byte values][code length]
@@ -661,7 +662,7 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
             for (uint32_t m = 1; m < l; m++)
                 code += (len_count[0][m] + len_count[1][m] + len_count[2][m] + len_count[3][m]) << (l - m);
             for (uint32_t b = 0; b < (v >> 6); b++) code += len_count[b][l];
-            entry = (__brev(code) >> (32 - l)) | (l << 16);
+            entry = l | (__brev(code) >> (32 - l)) << 16;
         }
         book[v] = entry;
     }
@@ -671,180 +672,132 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     // ---- the sub-stream of this lane
     const uint32_t groups = (raw + 15) / 16;
     const uint32_t rounds = (groups + S - 1) / S;
-    const uint32_t my_groups = t < groups ? (groups - t + S - 1) / S : 0;
-    const uint32_t ring_lane = lds_address(ring + wave * (16 * 64) + lane);
-    uint32_t taken = 0, used = 8 * pad; // positions count from where block 0 would start
-    u32x4 head_blk = {0, 0, 0, 0};
+    const uint32_t full_rounds = raw / (16 * S); // rounds in which every lane has a whole group
+    const uint32_t places_lane = lds_address(places + wave * (kPlaces * 64) + lane);
     uint32_t next_block = region / DC_BLOCK_BYTES;
     const uint64_t set_lanes = S < 64 ? (1ull << S) - 1 : ~0ull;
+    Coder c = {8 * pad, 0, {0, 0, 0, 0}, {0, 0, 0, 0}}; // the stream starts behind the `pad` bytes that block 0 lacks
 
-    // bytes [lo, lo + n) of the chunk, n <= 8, as a 64-bit word (missing bytes zero)
-    auto half_group = [&](uint32_t h, uint32_t &n) -> uint64_t {
-        const uint32_t g = t + (h >> 1) * S;
-        const uint32_t lo = 16 * g + 8 * (h & 1);
-        n = lo < raw ? (raw - lo < 8 ? raw - lo : 8) : 0;
-        if (n == 8) return *reinterpret_cast<const uint64_t *>(src + lo);
-        uint64_t v = 0;
-        for (uint32_t i = 0; i < n; i++) v |= (uint64_t)src[lo + i] << (8 * i);
-        return v;
+    // One carrying out of the placement rule.
+    auto place = [&]() {
+        const uint32_t bound = c.pos + DC_LOOKAHEAD_BITS;
+        const bool want = c.asked < nb && kBlockBits * c.asked < bound;
+        const uint64_t m = __ballot(want && c.asked != 0) & set_lanes; // block 0 goes to the heads
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (want) {
+            *(lds_u32 *)(uintptr_t)(places_lane + 256 * (c.asked % kPlaces)) = next_block + rank;
+            c.asked++;
+        }
+        next_block += (uint32_t)__popcll(m);
+    };
+    // The block at the position is complete: block 0 is kept for the heads, any other goes to its place.
+    auto hand_over = [&]() {
+        const uint32_t f = c.pos / kBlockBits;
+        const u32x4 v = {c.blk[0], c.blk[1], c.blk[2], c.blk[3]};
+        if (f == 0) c.head = v;
+        else
+            *reinterpret_cast<u32x4 *>(out + (size_t)lds_load32(places_lane + 256 * (f % kPlaces)) * DC_BLOCK_BYTES) = v;
+    };
+    // Appends n <= 96 bits: shifted by the position inside its word, then by whole words to their place in a window of two
+    // blocks, whose first is the block at the position.
+    auto append = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t n) {
+        const uint32_t o = c.pos & 31u;
+        const uint64_t a = ((uint64_t)w1 << 32 | w0) << o, b = ((uint64_t)w2 << 32 | w1) << o, d = (uint64_t)w2 << o;
+        uint32_t v[8] = {(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(d >> 32), 0, 0, 0, 0};
+        const bool one = (c.pos & 32u) != 0, two = (c.pos & 64u) != 0;
+#pragma unroll
+        for (int i = 4; i >= 0; i--) v[i] = one ? (i ? v[i - 1] : 0u) : v[i];
+#pragma unroll
+        for (int i = 6; i >= 0; i--) v[i] = two ? (i >= 2 ? v[i - 2] : 0u) : v[i];
+#pragma unroll
+        for (int i = 0; i < 4; i++) c.blk[i] |= v[i];
+        const uint32_t end = c.pos + n;
+        if ((end ^ c.pos) >= kBlockBits) {
+            hand_over();
+#pragma unroll
+            for (int i = 0; i < 4; i++) c.blk[i] = v[4 + i];
+        }
+        c.pos = end;
     };
 
-    // tANS: the items of those bytes, 8 of 16 bits (missing ones zero)
-    const uint16_t *items = TANS ? a.items + k * a.chunk_bytes : nullptr;
-    auto half_group_items = [&](uint32_t h, uint32_t &n) -> u32x4 {
-        const uint32_t g = t + (h >> 1) * S;
-        const uint32_t lo = 16 * g + 8 * (h & 1);
-        n = lo < raw ? (raw - lo < 8 ? raw - lo : 8) : 0;
-        if (n == 8) return *reinterpret_cast<const u32x4 *>(items + lo);
-        u32x4 v = {0, 0, 0, 0};
-        for (uint32_t i = 0; i < n; i++) v[i >> 1] |= (uint32_t)items[lo + i] << (16 * (i & 1u));
-        return v;
-    };
-
-    // the coder starts behind the `pad` bytes that block 0 lacks (zeros in the ring, never stored)
-    Coder c = {0, 8 * (pad & 3u), pad >> 2, 0, 0, {0, 0, 0, 0}, 0};
-    for (uint32_t i = 0; i < (pad >> 2); i++) *(lds_u32 *)(uintptr_t)(ring_lane + (i << 8)) = 0;
-    if (TANS && my_groups) {
-        // a tANS stream opens with its first state
-        c.acc = (uint64_t)a.first[k * S + t] << c.nbits;
-        c.nbits += DC_TANS_STATE_BITS;
-        if (c.nbits >= 32) {
-            *(lds_u32 *)(uintptr_t)(ring_lane + ((c.words & 15u) << 8)) = (uint32_t)c.acc;
-            c.words++;
-            c.acc >>= 32;
-            c.nbits -= 32;
-        }
-    }
-    if (my_groups) {
-        if (TANS) c.items = half_group_items(0, c.n);
-        else c.bytes = half_group(0, c.n);
-    }
-    // codes the next half group into the ring: at most 88 bits on top of fewer than 32, so at most
-    // three words
-    auto code_half = [&]() {
-        const uint64_t bytes = c.bytes;
-        const u32x4 its = c.items;
-        const uint32_t n = c.n;
-        c.next_half++;
-        if (c.next_half < 2 * my_groups) {
-            if (TANS) c.items = half_group_items(c.next_half, c.n);
-            else c.bytes = half_group(c.next_half, c.n);
-        }
-        auto flush = [&]() {
-            if (c.nbits >= 32) {
-                *(lds_u32 *)(uintptr_t)(ring_lane + ((c.words & 15u) << 8)) = (uint32_t)c.acc;
-                c.words++;
-                c.acc >>= 32;
-                c.nbits -= 32;
-            }
-        };
+    // what a round codes of this lane's stream: the group's 16 bytes; tANS: its items, two symbols in 32 bits
+    u32x4 in[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+    uint32_t in_n = 0; // bytes of it that exist
+    const uint32_t *items = TANS ? a.items + k * (a.chunk_bytes / 2) : nullptr;
+    auto load_group = [&](uint32_t r) {
+        const uint32_t lo = 16 * (t + r * S);
+        in_n = lo < raw ? (raw - lo < 16 ? raw - lo : 16) : 0;
         if (TANS) {
-            // two items at a time: at most 22 bits on top of fewer than 32 (absent items are zero: no bits)
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const uint32_t w0 = (its[i] >> 12) & 15u, w1 = its[i] >> 28;
-                const uint32_t two = (its[i] & 0xFFFu) | ((its[i] >> 16) & 0xFFFu) << w0;
-                c.acc |= (uint64_t)two << c.nbits;
-                c.nbits += w0 + w1;
-                flush();
+            // the model kernel has left items for every byte of a group, empty ones for bytes that do not exist
+            if (in_n) {
+                in[0] = *reinterpret_cast<const u32x4 *>(items + lo / 2);
+                in[1] = *reinterpret_cast<const u32x4 *>(items + lo / 2 + 4);
             }
-        } else if (n == 8) {
-            // the table reads do not depend on each other; the bit buffer takes two codes (at most 22
-            // bits on top of fewer than 32) between checks
-            uint32_t e[8];
-#pragma unroll
-            for (int i = 0; i < 8; i++) e[i] = book[(bytes >> (8 * i)) & 0xFFu];
-#pragma unroll
-            for (int i = 0; i < 8; i += 2) {
-                const uint32_t l0 = e[i] >> 16;
-                const uint32_t two = (e[i] & 0xFFFFu) | (e[i + 1] & 0xFFFFu) << l0;
-                c.acc |= (uint64_t)two << c.nbits;
-                c.nbits += l0 + (e[i + 1] >> 16);
-                flush();
-            }
+        } else if (in_n == 16) {
+            in[0] = *reinterpret_cast<const u32x4 *>(src + lo);
         } else {
-            for (uint32_t i = 0; i < n; i++) { // the ragged end of the chunk
-                const uint32_t e = book[(bytes >> (8 * i)) & 0xFFu];
-                c.acc |= (uint64_t)(e & 0xFFFFu) << c.nbits;
-                c.nbits += e >> 16;
-                flush();
-            }
+            in[0] = u32x4{0, 0, 0, 0};
+            for (uint32_t i = 0; i < in_n; i++) in[0][i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
         }
     };
-    // bits that the items of a half group take
-    auto bits_of_items = [&](const u32x4 &its) -> uint32_t {
-        uint32_t sum = 0;
+    // Codes half a group, at most 88 bits: codes are joined to pairs (22 bits), fours (44) and eights.  In the loop below nothing
+    // depends on another lane or on how far the stream has come, so all lanes do the same work at every step.
+    auto code_half = [&](const u32x4 &bytes, const u32x4 &its, uint32_t half, uint32_t n, bool whole) {
+        uint32_t p[4], l[4]; // pairs, and their bits in the low byte
 #pragma unroll
-        for (int i = 0; i < 4; i++) sum += ((its[i] >> 12) & 15u) + (its[i] >> 28);
-        return sum;
-    };
-    // bits that the codes of a half group take
-    auto bits_of = [&](uint64_t bytes, uint32_t n) -> uint32_t {
-        uint32_t sum = 0;
-        if (n == 8) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) sum += book[(bytes >> (8 * i)) & 0xFFu] >> 16;
-        } else {
-            for (uint32_t i = 0; i < n; i++) sum += book[(bytes >> (8 * i)) & 0xFFu] >> 16;
-        }
-        return sum;
-    };
-
-    for (uint32_t h = 0; h < 2 * rounds; h++) {
-        // the half group a decoder consumes at this step (needed after the blocks of the step)
-        uint32_t step_n = 0;
-        uint64_t step_bytes = 0;
-        u32x4 step_items = {0, 0, 0, 0};
-        if ((h >> 1) < my_groups) {
-            if (TANS) step_items = half_group_items(h, step_n);
-            else step_bytes = half_group(h, step_n);
-        }
-        // All lanes code one half group ahead together while the ring has room for it (the words of
-        // block `taken` onwards are still in the ring, 16 words in all), so that the loop below, where
-        // lanes diverge, rarely has anything left to do.
-        if (c.next_half < 2 * my_groups && c.words + 3 <= 4 * taken + 16) code_half();
-        // step 0 is carried out four times (a fifth changes nothing for Huffman codes); a tANS stream has read its
-        // first state before the fifth
-        for (int pass = 0; pass < (h == 0 ? (TANS ? 5 : 4) : 1); pass++) {
-            if (TANS && h == 0 && pass == 4 && my_groups) used += DC_TANS_STATE_BITS;
-            const bool want = taken < nb && kBlockBits * taken < used + DC_LOOKAHEAD_BITS;
-            if (want) {
-                // code on until block `taken` is complete (or the stream ends, then pad with zeros)
-                while (c.words < 4 * (taken + 1)) {
-                    if (c.next_half < 2 * my_groups) {
-                        code_half();
-                    } else {
-                        *(lds_u32 *)(uintptr_t)(ring_lane + ((c.words & 15u) << 8)) = (uint32_t)c.acc;
-                        c.words++;
-                        c.acc = 0;
-                        c.nbits = 0;
-                    }
+        for (int i = 0; i < 4; i++) {
+            if (TANS) {
+                const uint32_t it = whole || 2u * i < n ? its[i] : 0u;
+                p[i] = it >> 8;
+                l[i] = it & 0xFFu;
+            } else {
+                const uint32_t w = bytes[2 * half + i / 2] >> (16 * (i & 1));
+                uint32_t e0 = book[w & 0xFFu], e1 = book[(w >> 8) & 0xFFu];
+                if (!whole) {
+                    e0 = 2u * i < n ? e0 : 0u;
+                    e1 = 2u * i + 1 < n ? e1 : 0u;
                 }
+                p[i] = (e0 >> 16) | (e1 >> 16) << (e0 & 31u);
+                l[i] = (e0 + e1) & 0xFFu;
             }
-            const bool head = taken == 0; // block 0 goes to the heads, without the bytes it lacks
-            const uint64_t m = __ballot(want && !head) & set_lanes;
-            if (want) {
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                u32x4 blk;
-#pragma unroll
-                for (int i = 0; i < 4; i++) blk[i] = lds_load32(ring_lane + (((4 * taken + i) & 15u) << 8));
-                if (!head) *reinterpret_cast<u32x4 *>(out + (size_t)(next_block + rank) * DC_BLOCK_BYTES) = blk;
-                else head_blk = blk; // written with the other heads of the set, below
-                taken++;
-            }
-            next_block += (uint32_t)__popcll(m);
         }
-        // the decoder's position after half group h
-        used += TANS ? bits_of_items(step_items) : bits_of(step_bytes, step_n);
-    }
+        const uint64_t lo = (uint64_t)p[1] << l[0] | p[0], hi = (uint64_t)p[3] << l[2] | p[2];
+        const uint32_t m = l[0] + l[1]; // at most 44
+        const uint64_t low = lo | hi << m;
+        const uint32_t high = m ? (uint32_t)(hi >> (64 - m)) : 0u;
+        append((uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]);
+    };
 
-    // ---- the heads of the set: put together in the wave's ring, which is free now (the lanes of a wave
+    load_group(0);
+    // step 0 is carried out five times; a tANS stream opens with its first state, which a decoder reads before the fifth
+    for (int pass = 0; pass < 4; pass++) place();
+    if (TANS && in_n) append(a.first[k * S + t], 0, 0, DC_TANS_STATE_BITS);
+    for (uint32_t r = 0; r < rounds; r++) {
+        const u32x4 now[2] = {in[0], in[1]};
+        const uint32_t n = in_n;
+        if (r + 1 < rounds) load_group(r + 1);
+        if (r < full_rounds) {
+            place();
+            code_half(now[0], now[0], 0, 8, true);
+            place();
+            code_half(now[0], now[1], 1, 8, true);
+        } else {
+            place();
+            code_half(now[0], now[0], 0, n, false);
+            place();
+            code_half(now[0], now[1], 1, n > 8 ? n - 8 : 0, false);
+        }
+    }
+    // the last block, unless its last bit was the stream's (the zero bits that fill the last byte are not coded)
+    if (c.pos % kBlockBits) hand_over();
+
+    // ---- the heads of the set: put together where the wave's queues were (the lanes of a wave
     // leave the loop together), then written with whole 16-byte stores, the padding of the area included
-    uint8_t *stage = reinterpret_cast<uint8_t *>(ring + wave * (16 * 64));
+    uint8_t *stage = reinterpret_cast<uint8_t *>(places + wave * (kPlaces * 64));
     if (lane == 0)
         for (uint32_t p = heads_total; p < heads_padded; p++) stage[p] = 0;
     for (uint32_t i = pad; i < DC_BLOCK_BYTES && nb; i++)
-        stage[heads_incl - hb + i - pad] = (uint8_t)((i < 8 ? (i < 4 ? head_blk[0] : head_blk[1]) : (i < 12 ? head_blk[2] : head_blk[3])) >> (8 * (i & 3u)));
+        stage[heads_incl - hb + i - pad] = (uint8_t)((i < 8 ? (i < 4 ? c.head[0] : c.head[1]) : (i < 12 ? c.head[2] : c.head[3])) >> (8 * (i & 3u)));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -927,7 +880,7 @@ int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const d
         uint8_t *more = ws + align256(nc * 256) + align256(nc * a.S * 4) + align256(nc * 4);
         a.freq = reinterpret_cast<uint16_t *>(more);
         a.first = reinterpret_cast<uint16_t *>(more + align256(nc * 512));
-        a.items = reinterpret_cast<uint16_t *>(more + align256(nc * 512) + align256(nc * a.S * 2));
+        a.items = reinterpret_cast<uint32_t *>(more + align256(nc * 512) + align256(nc * a.S * 2));
     }
     a.blob = blob_dev;
     a.blob_cap = blob_cap;
