@@ -569,10 +569,9 @@ __global__ __launch_bounds__(256) void dc_layout_kernel(EncArgs a)
 // f its place when a decoder would ask for it, 3 to 5 blocks before its bits are coded, and the place waits in a queue
 // in LDS until the block is full.
 struct Coder {
-    uint32_t pos;   // position in bits, from where block 0 would start
-    uint32_t asked; // blocks that have their place
+    uint32_t pos;    // position in bits, from where block 0 would start
+    uint32_t asked;  // 128 * (blocks that have their place)
     uint32_t blk[4]; // the block at the position, as far as it is coded
-    u32x4 head;      // block 0
 };
 
 constexpr uint32_t kPlaces = 8; // places a lane's queue holds; at most 520 bits, 5 blocks, are placed beyond the position
@@ -583,6 +582,7 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     constexpr bool TANS = CODEC == DC_CODEC_TANS;
     constexpr uint32_t kFront = TANS ? 384 : 128; // code description at the start of a payload
     __shared__ __attribute__((aligned(16))) uint32_t places[WAVES * kPlaces * 64]; // the lanes' queues: region block numbers
+    __shared__ __attribute__((aligned(16))) u32x4 heads[WAVES * 64];               // every lane's block 0
     __shared__ uint32_t book[256];                                                  // length | bit-reversed code << 16
     __shared__ uint8_t len_of[256];
     __shared__ uint32_t set_bytes[WAVES];
@@ -599,8 +599,16 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
 
     if (ent.raw_bytes_flags & DC_CHUNK_RAW) {
         const uint32_t n16 = raw / 16;
-        for (uint32_t i = t; i < n16; i += THREADS)
-            *reinterpret_cast<u32x4 *>(out + 16 * (size_t)i) = *reinterpret_cast<const u32x4 *>(src + 16 * (size_t)i);
+        for (uint32_t base = t; base < n16; base += 4 * THREADS) { // four loads in flight per thread
+            u32x4 v[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++)
+                if (base + j * THREADS < n16) v[j] = load16_stream(src + 16 * (size_t)(base + j * THREADS));
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++)
+                if (base + j * THREADS < n16)
+                    __builtin_nontemporal_store(v[j], reinterpret_cast<u32x4 *>(out + 16 * (size_t)(base + j * THREADS)));
+        }
         if (t < 16 && n16 * 16 < raw) out[n16 * 16 + t] = n16 * 16 + t < raw ? src[n16 * 16 + t] : 0;
         return;
     }
@@ -675,28 +683,31 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     const uint32_t full_rounds = raw / (16 * S); // rounds in which every lane has a whole group
     const uint32_t places_lane = lds_address(places + wave * (kPlaces * 64) + lane);
     uint32_t next_block = region / DC_BLOCK_BYTES;
-    const uint64_t set_lanes = S < 64 ? (1ull << S) - 1 : ~0ull;
-    Coder c = {8 * pad, 0, {0, 0, 0, 0}, {0, 0, 0, 0}}; // the stream starts behind the `pad` bytes that block 0 lacks
+    const uint32_t end_blocks = kBlockBits * nb;
+    // the stream starts behind the `pad` bytes that block 0 lacks; block 0 is among the heads and takes no place
+    Coder c = {8 * pad, nb ? kBlockBits : 0, {0, 0, 0, 0}};
 
     // One carrying out of the placement rule.
     auto place = [&]() {
         const uint32_t bound = c.pos + DC_LOOKAHEAD_BITS;
-        const bool want = c.asked < nb && kBlockBits * c.asked < bound;
-        const uint64_t m = __ballot(want && c.asked != 0) & set_lanes; // block 0 goes to the heads
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        const bool want = c.asked < (bound < end_blocks ? bound : end_blocks);
+        const uint64_t m = __ballot(want);
         if (want) {
-            *(lds_u32 *)(uintptr_t)(places_lane + 256 * (c.asked % kPlaces)) = next_block + rank;
-            c.asked++;
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            *(lds_u32 *)(uintptr_t)(places_lane + ((c.asked << 1) & 256 * (kPlaces - 1))) = next_block + rank;
+            c.asked += kBlockBits;
         }
         next_block += (uint32_t)__popcll(m);
     };
     // The block at the position is complete: block 0 is kept for the heads, any other goes to its place.
     auto hand_over = [&]() {
-        const uint32_t f = c.pos / kBlockBits;
         const u32x4 v = {c.blk[0], c.blk[1], c.blk[2], c.blk[3]};
-        if (f == 0) c.head = v;
-        else
-            *reinterpret_cast<u32x4 *>(out + (size_t)lds_load32(places_lane + 256 * (f % kPlaces)) * DC_BLOCK_BYTES) = v;
+        if (c.pos < kBlockBits) {
+            heads[t] = v;
+        } else {
+            const uint32_t at = lds_load32(places_lane + ((c.pos << 1) & 256 * (kPlaces - 1)));
+            *reinterpret_cast<u32x4 *>(out + at * DC_BLOCK_BYTES) = v;
+        }
     };
     // Appends n <= 96 bits: shifted by the position inside its word, then by whole words to their place in a window of two
     // blocks, whose first is the block at the position.
@@ -722,11 +733,10 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
 
     // what a round codes of this lane's stream: the group's 16 bytes; tANS: its items, two symbols in 32 bits
     u32x4 in[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-    uint32_t in_n = 0; // bytes of it that exist
     const uint32_t *items = TANS ? a.items + k * (a.chunk_bytes / 2) : nullptr;
-    auto load_group = [&](uint32_t r) {
+    auto load_group = [&](uint32_t r) -> uint32_t { // returns the bytes of it that exist
         const uint32_t lo = 16 * (t + r * S);
-        in_n = lo < raw ? (raw - lo < 16 ? raw - lo : 16) : 0;
+        const uint32_t in_n = lo < raw ? (raw - lo < 16 ? raw - lo : 16) : 0;
         if (TANS) {
             // the model kernel has left items for every byte of a group, empty ones for bytes that do not exist
             if (in_n) {
@@ -738,6 +748,16 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
         } else {
             in[0] = u32x4{0, 0, 0, 0};
             for (uint32_t i = 0; i < in_n; i++) in[0][i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
+        }
+        return in_n;
+    };
+    auto load_whole_group = [&](uint32_t r) {
+        const uint32_t lo = 16 * (t + r * S);
+        if (TANS) {
+            in[0] = *reinterpret_cast<const u32x4 *>(items + lo / 2);
+            in[1] = *reinterpret_cast<const u32x4 *>(items + lo / 2 + 4);
+        } else {
+            in[0] = *reinterpret_cast<const u32x4 *>(src + lo);
         }
     };
     // Codes half a group, at most 88 bits: codes are joined to pairs (22 bits), fours (44) and eights.  In the loop below nothing
@@ -768,25 +788,25 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
         append((uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]);
     };
 
-    load_group(0);
-    // step 0 is carried out five times; a tANS stream opens with its first state, which a decoder reads before the fifth
-    for (int pass = 0; pass < 4; pass++) place();
-    if (TANS && in_n) append(a.first[k * S + t], 0, 0, DC_TANS_STATE_BITS);
-    for (uint32_t r = 0; r < rounds; r++) {
+    // step 0 is carried out five times, the first of which takes block 0; a tANS stream opens with its first state, which a
+    // decoder reads before the fifth
+    for (int pass = 1; pass < 4; pass++) place();
+    if (TANS && t < groups) append(a.first[k * S + t], 0, 0, DC_TANS_STATE_BITS);
+    if (full_rounds) load_whole_group(0);
+    for (uint32_t r = 0; r < full_rounds; r++) {
         const u32x4 now[2] = {in[0], in[1]};
-        const uint32_t n = in_n;
-        if (r + 1 < rounds) load_group(r + 1);
-        if (r < full_rounds) {
-            place();
-            code_half(now[0], now[0], 0, 8, true);
-            place();
-            code_half(now[0], now[1], 1, 8, true);
-        } else {
-            place();
-            code_half(now[0], now[0], 0, n, false);
-            place();
-            code_half(now[0], now[1], 1, n > 8 ? n - 8 : 0, false);
-        }
+        load_whole_group(r + 1 < full_rounds ? r + 1 : r);
+        place();
+        code_half(now[0], now[0], 0, 8, true);
+        place();
+        code_half(now[0], now[1], 1, 8, true);
+    }
+    if (rounds > full_rounds) { // the chunk's last groups: some lanes have none, one may have a part of one
+        const uint32_t n = load_group(full_rounds);
+        place();
+        code_half(in[0], in[0], 0, n, false);
+        place();
+        code_half(in[0], in[1], 1, n > 8 ? n - 8 : 0, false);
     }
     // the last block, unless its last bit was the stream's (the zero bits that fill the last byte are not coded)
     if (c.pos % kBlockBits) hand_over();
@@ -796,8 +816,9 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     uint8_t *stage = reinterpret_cast<uint8_t *>(places + wave * (kPlaces * 64));
     if (lane == 0)
         for (uint32_t p = heads_total; p < heads_padded; p++) stage[p] = 0;
+    const u32x4 head = nb ? heads[t] : u32x4{0, 0, 0, 0};
     for (uint32_t i = pad; i < DC_BLOCK_BYTES && nb; i++)
-        stage[heads_incl - hb + i - pad] = (uint8_t)((i < 8 ? (i < 4 ? c.head[0] : c.head[1]) : (i < 12 ? c.head[2] : c.head[3])) >> (8 * (i & 3u)));
+        stage[heads_incl - hb + i - pad] = (uint8_t)((i < 8 ? (i < 4 ? head[0] : head[1]) : (i < 12 ? head[2] : head[3])) >> (8 * (i & 3u)));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
