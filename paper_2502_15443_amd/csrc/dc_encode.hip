@@ -449,11 +449,12 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     }
 }
 
-// Gain of Huffman coding a chunk (raw size less Huffman payload size) as an unsigned key in the same order.
-__device__ __forceinline__ uint32_t gain_key(const EncArgs &a, uint64_t k)
+// Gain of coding a chunk (raw size less coded payload size) as an unsigned key in the same order.
+__device__ __forceinline__ uint32_t gain_key(uint32_t raw, uint32_t coded)
 {
-    return (uint32_t)((int64_t)chunk_len(a, k) - (int64_t)a.comp[k] + (int64_t)0x80000000ll);
+    return raw - coded + 0x80000000u; // both are below 2^24
 }
+__device__ __forceinline__ uint32_t gain_key(const EncArgs &a, uint64_t k) { return gain_key(chunk_len(a, k), a.comp[k]); }
 
 // Which chunks stay raw.  DC_POLICY_RAW_FRACTION: the n_raw chunks of lowest gain, lower index first
 // among equal gains, i.e. the chunks with key < threshold and the first `equal_raw` chunks with
@@ -463,78 +464,130 @@ struct RawRule {
     uint32_t equal_raw;
 };
 
-__device__ __forceinline__ bool stays_raw(const EncArgs &a, const RawRule &r, uint64_t k, uint32_t &equal_seen)
+constexpr uint32_t kLayoutThreads = 1024;
+constexpr uint32_t kLayoutTile = 4 * kLayoutThreads; // chunks a pass of the layout kernel looks at
+
+// Sum of v over the threads before this one, and over all of them (`total`).  waves: 16 words of LDS, free again after the
+// next barrier that the caller issues.
+__device__ __forceinline__ uint32_t threads_prefix_sum(uint32_t v, uint32_t *waves, uint32_t &total)
 {
-    if (a.policy == DC_POLICY_AUTO) return gain_key(a, k) <= 0x80000000u;
-    if (a.policy == DC_POLICY_BLOCK_LAST) return (k % a.block_chunks) != a.block_chunks - 1;
-    if (a.policy == DC_POLICY_RAW_FRACTION) {
-        const uint32_t key = gain_key(a, k);
-        if (key != r.threshold) return key < r.threshold;
-        return equal_seen++ < r.equal_raw;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t incl = lanes_prefix_sum<false>(v);
+    if (lane == 63) waves[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kLayoutThreads / 64; w++) {
+        const uint32_t c = waves[w];
+        before += w < wave ? c : 0u;
+        total += c;
     }
-    return false;
+    return before + incl - v;
 }
 
-// One workgroup; thread t looks after the chunks [t * per, (t + 1) * per).
-__global__ __launch_bounds__(256) void dc_layout_kernel(EncArgs a)
+// One workgroup, because offsets are sums over all chunks before.  Bound by latency: it works through the payload sizes
+// in tiles of 4096 chunks, four consecutive ones a thread, so that a tile costs one trip to memory and two barriers (a
+// thread with a run of chunks of its own, read one by one, took 13.7 us for 3088 chunks; this takes 5).  Sizes are summed in units
+// of 16 bytes: a tile's fit 32 bits.
+__global__ __launch_bounds__(kLayoutThreads) void dc_layout_kernel(EncArgs a)
 {
-    __shared__ uint64_t part[256];
     __shared__ uint32_t digit_count[256];
-    __shared__ uint32_t equal_part[256];
+    __shared__ uint32_t waves[2][kLayoutThreads / 64];
     __shared__ uint32_t sel_prefix, sel_rank;
     const uint32_t t = threadIdx.x;
-    const uint64_t per = (a.n_chunks + 255) / 256;
-    const uint64_t k0 = t * per < a.n_chunks ? t * per : a.n_chunks, k1 = k0 + per < a.n_chunks ? k0 + per : a.n_chunks;
+    const bool by_gain = a.policy == DC_POLICY_RAW_FRACTION && a.n_raw > 0;
 
     RawRule rule = {0, 0};
-    uint32_t equal_before = 0; // chunks before k0 whose key is the threshold
-    if (a.policy == DC_POLICY_RAW_FRACTION && a.n_raw > 0) {
+    if (by_gain) {
         // Radix select, most significant byte first: the key of rank n_raw - 1 in ascending order.
         if (t == 0) {
             sel_prefix = 0;
             sel_rank = (uint32_t)(a.n_raw - 1);
         }
         for (int shift = 24; shift >= 0; shift -= 8) {
-            digit_count[t] = 0;
+            if (t < 256) digit_count[t] = 0;
             __syncthreads();
             const uint32_t prefix = sel_prefix;
-            for (uint64_t k = k0; k < k1; k++) {
+            for (uint64_t k = t; k < a.n_chunks; k += kLayoutThreads) {
                 const uint32_t key = gain_key(a, k);
                 if (shift == 24 || ((key ^ prefix) >> (shift + 8)) == 0) atomicAdd(&digit_count[(key >> shift) & 0xFFu], 1u);
             }
             __syncthreads();
-            if (t == 0) {
-                uint32_t rank = sel_rank, d = 0;
-                while (d < 255 && rank >= digit_count[d]) rank -= digit_count[d++]; // the rank lies among the counted keys
-                sel_prefix = prefix | (d << shift);
-                sel_rank = rank;
+            if (t < 64) {
+                // the digit in which the rank lies: four digits a lane, counts of the lanes before
+                uint32_t c[4], sum = 0;
+#pragma unroll
+                for (int i = 0; i < 4; i++) sum += c[i] = digit_count[4 * t + i];
+                uint32_t before = lanes_prefix_sum<false>(sum) - sum;
+                const uint32_t rank = sel_rank;
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (uint32_t i = 0; i < 4; i++) {
+                    if (rank >= before && rank - before < c[i]) {
+                        sel_prefix = prefix | (4 * t + i) << shift;
+                        sel_rank = rank - before;
+                    }
+                    before += c[i];
+                }
             }
             __syncthreads();
         }
         rule.threshold = sel_prefix;
         rule.equal_raw = sel_rank + 1;
-        uint32_t mine = 0;
-        for (uint64_t k = k0; k < k1; k++) mine += gain_key(a, k) == rule.threshold;
-        equal_part[t] = mine;
-        __syncthreads();
-        for (uint32_t i = 0; i < t; i++) equal_before += equal_part[i];
     }
 
-    uint64_t sum = 0;
-    uint32_t equal_seen = equal_before;
-    for (uint64_t k = k0; k < k1; k++) {
-        const uint32_t raw = chunk_len(a, k);
-        sum += stays_raw(a, rule, k, equal_seen) ? (raw + 15u) & ~15u : a.comp[k];
-    }
-    part[t] = sum;
-    __syncthreads();
-    if (t == 0) {
-        uint64_t run = 0;
-        for (int i = 0; i < 256; i++) {
-            const uint64_t s = part[i];
-            part[i] = run;
-            run += s;
+    uint64_t run = 0;       // bytes of the payloads of the tiles before
+    uint32_t run_equal = 0; // chunks of exactly the threshold in them
+    for (uint64_t tile = 0; tile < a.n_chunks; tile += kLayoutTile) {
+        const uint64_t k0 = tile + 4 * t;
+        uint32_t coded[4] = {0, 0, 0, 0};
+        if (k0 + 4 <= a.n_chunks) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(a.comp + k0);
+#pragma unroll
+            for (int i = 0; i < 4; i++) coded[i] = v[i];
+        } else {
+            for (uint32_t i = 0; i < 4; i++)
+                if (k0 + i < a.n_chunks) coded[i] = a.comp[k0 + i];
         }
+        uint32_t raw[4], key[4], equal = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            raw[i] = k0 + i < a.n_chunks ? chunk_len(a, k0 + i) : 0u;
+            key[i] = gain_key(raw[i], coded[i]);
+            equal += by_gain && raw[i] && key[i] == rule.threshold;
+        }
+        uint32_t equal_total = 0;
+        if (by_gain) equal = run_equal + threads_prefix_sum(equal, waves[0], equal_total);
+        uint32_t size[4], sum = 0; // in units of 16 bytes
+        bool is_raw[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            bool keep = false;
+            if (a.policy == DC_POLICY_AUTO) keep = key[i] <= 0x80000000u;
+            else if (a.policy == DC_POLICY_BLOCK_LAST) keep = (uint32_t)(k0 + i) % a.block_chunks != a.block_chunks - 1; // n_chunks < 2^31
+            else if (by_gain) keep = key[i] != rule.threshold ? key[i] < rule.threshold : equal++ < rule.equal_raw;
+            is_raw[i] = keep;
+            size[i] = raw[i] ? (keep ? (raw[i] + 15u) / 16 : coded[i] / 16) : 0u;
+            sum += size[i];
+        }
+        uint32_t total;
+        uint64_t off = run + 16ull * threads_prefix_sum(sum, waves[1], total);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++) {
+            if (!raw[i]) continue;
+            dc_chunk e;
+            e.off = off;
+            e.comp_bytes = 16 * size[i];
+            e.raw_bytes_flags = raw[i] | (is_raw[i] ? DC_CHUNK_RAW : 0u);
+            a.table[k0 + i] = e;
+            off += e.comp_bytes;
+        }
+        run += 16ull * total;
+        run_equal += equal_total;
+        __syncthreads();
+    }
+    if (t == 0) {
         a.result[0] = run + DC_BLOB_TAIL_BYTES;
         a.result[1] = run + DC_BLOB_TAIL_BYTES > a.blob_cap ? (uint64_t)(int64_t)DC_E_CAP : 0;
         if (run + DC_BLOB_TAIL_BYTES <= a.blob_cap) {
@@ -548,20 +601,6 @@ __global__ __launch_bounds__(256) void dc_layout_kernel(EncArgs a)
             trailer[2] = a.chunk_bytes;
             trailer[3] = a.S | a.codec << 16;
         }
-    }
-    __syncthreads();
-    uint64_t off = part[t];
-    equal_seen = equal_before;
-    for (uint64_t k = k0; k < k1; k++) {
-        const uint32_t raw = chunk_len(a, k);
-        const bool is_raw = stays_raw(a, rule, k, equal_seen);
-        const uint32_t size = is_raw ? (raw + 15u) & ~15u : a.comp[k];
-        dc_chunk e;
-        e.off = off;
-        e.comp_bytes = size;
-        e.raw_bytes_flags = raw | (is_raw ? DC_CHUNK_RAW : 0u);
-        a.table[k] = e;
-        off += size;
     }
 }
 
@@ -910,7 +949,7 @@ int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (a.codec == DC_CODEC_TANS) hipLaunchKernelGGL(dc_tans_model_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dc_codes_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(dc_layout_kernel, dim3(1), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(dc_layout_kernel, dim3(1), dim3(kLayoutThreads), 0, stream, a);
     switch (a.S) {
     case 32:
     case 64: launch_emit<64>(a, stream); break;
