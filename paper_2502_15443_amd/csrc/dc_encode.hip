@@ -241,35 +241,77 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
 constexpr uint32_t kTansBits = DC_TANS_STATE_BITS;
 constexpr uint32_t kTansL = 1u << kTansBits;
 
-// A candidate of the normalisation rule: value v with count c and the divisor d its ratio c/d is taken with
-// (d = 0: no candidate).
-struct Cand {
-    uint32_t c, d, v;
-};
-// larger ratio first, the lower value among equal ratios (c * d fits 32 bits: c <= 2^20, d <= 2^11)
-__device__ __forceinline__ bool larger(const Cand &x, const Cand &y)
+// Smallest (or largest) of the lanes' values, for all lanes.  `none` is what a lane without a source counts as.
+template <bool LARGEST> __device__ __forceinline__ double lanes_extreme(double v, double none)
 {
-    if (x.d == 0 || y.d == 0) return x.d != 0 && y.d == 0;
-    const uint32_t l = x.c * y.d, r = y.c * x.d;
-    return l > r || (l == r && x.v < y.v);
-}
-__device__ __forceinline__ bool smaller(const Cand &x, const Cand &y)
-{
-    if (x.d == 0 || y.d == 0) return x.d != 0 && y.d == 0;
-    const uint32_t l = x.c * y.d, r = y.c * x.d;
-    return l < r || (l == r && x.v < y.v);
-}
-template <bool LARGEST> __device__ __forceinline__ Cand wave_best(Cand best)
-{
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        Cand o;
-        o.c = (uint32_t)__shfl_xor((int)best.c, m);
-        o.d = (uint32_t)__shfl_xor((int)best.d, m);
-        o.v = (uint32_t)__shfl_xor((int)best.v, m);
-        if (LARGEST ? larger(o, best) : smaller(o, best)) best = o;
+    const uint64_t fill = __builtin_bit_cast(uint64_t, none);
+#define DC_EXTREME_STEP(CTRL, MASK)                                                                                        \
+    {                                                                                                                      \
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);                                                                \
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)fill, (int)(uint32_t)u, CTRL, MASK, 0xF, false); \
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(fill >> 32), (int)(uint32_t)(u >> 32), CTRL, MASK, 0xF, false); \
+        const double o = __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);                                              \
+        v = LARGEST ? (o > v ? o : v) : (o < v ? o : v);                                                                   \
     }
-    return best;
+    DC_EXTREME_STEP(0x111, 0xF)
+    DC_EXTREME_STEP(0x112, 0xF)
+    DC_EXTREME_STEP(0x114, 0xF)
+    DC_EXTREME_STEP(0x118, 0xF)
+    DC_EXTREME_STEP(0x142, 0xA)
+    DC_EXTREME_STEP(0x143, 0xC)
+#undef DC_EXTREME_STEP
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// The second half of the normalisation rule by one wavefront; lane l holds counts and frequencies of the values l, l + 64,
+// l + 128, l + 192.  GROW: the value with the largest count / q gains one, `steps` times; else the value with q > 1 and
+// the smallest count / (q - 1) loses one; the lower value among equals.  The ratios are compared as 64-bit floating
+// point quotients: counts are at most 2^20 and divisors at most 2^11, so different ratios differ by more than 2^-42 of
+// themselves and their quotients in the same direction, and equal ratios have equal quotients.  A step is one
+// reduction over the lanes and one division, 0.15 us; cross products of (count, divisor, value) triples through
+// shuffles took 1.4 us.
+template <bool GROW> __device__ __forceinline__ void settle_frequencies(const uint32_t c[4], uint32_t q[4], uint32_t steps, uint32_t lane)
+{
+    const double none = GROW ? -1.0 : __builtin_huge_val();
+    auto ratio = [&](uint32_t count, uint32_t freq) -> double {
+        const bool candidate = GROW ? count != 0 : freq >= 2;
+        return candidate ? (double)count / (double)(GROW ? freq : freq - 1) : none;
+    };
+    double key[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) key[i] = ratio(c[i], q[i]);
+    for (; steps > 0; steps--) {
+        double mine = key[0];
+#pragma unroll
+        for (int i = 1; i < 4; i++) mine = GROW ? (key[i] > mine ? key[i] : mine) : (key[i] < mine ? key[i] : mine);
+        const double best = lanes_extreme<GROW>(mine, none);
+        // the lowest value among those with the best ratio
+        uint32_t which = 4, from = 0;
+#pragma unroll
+        for (int i = 3; i >= 0; i--) {
+            const uint64_t m = __ballot(key[i] == best);
+            if (m) {
+                which = i;
+                from = (uint32_t)__builtin_ctzll(m);
+            }
+        }
+        if (lane == from) {
+            uint32_t count = 0, freq = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++)
+                if (which == i) {
+                    q[i] += GROW ? 1u : ~0u;
+                    count = c[i];
+                    freq = q[i];
+                }
+            const double next = ratio(count, freq);
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++) key[i] = which == i ? next : key[i];
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
@@ -278,11 +320,12 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     __shared__ uint32_t hist[256];
     __shared__ uint32_t nq[256];       // normalised frequencies
     __shared__ uint32_t cumq[256];     // first place | frequency << 16
+    __shared__ uint2 step_of[256];     // what a symbol does to X (see below)
     __shared__ uint32_t wave_sum[4];
     __shared__ uint32_t sbits[256];
     __shared__ uint32_t area_bytes[4];
     uint16_t *marks = reinterpret_cast<uint16_t *>(arena);
-    uint16_t *state_of = reinterpret_cast<uint16_t *>(arena + 1024); // state of value v numbered q + i at cum[v] + i
+    uint16_t *state_of = reinterpret_cast<uint16_t *>(arena + 1024); // 2048 + the state of value v numbered q + i at cum[v] + i
 
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint64_t k = blockIdx.x;
@@ -307,37 +350,15 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     }
     __syncthreads();
     if (wave == 0) {
-        int32_t diff = (int32_t)kTansL - (int32_t)(wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]);
+        const int32_t diff = (int32_t)kTansL - (int32_t)(wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]);
         uint32_t c[4], q[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             c[i] = hist[lane + 64 * i];
             q[i] = nq[lane + 64 * i];
         }
-        for (; diff > 0; diff--) {
-            Cand best = {0, 0, 0};
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const Cand x = {c[i], c[i] ? q[i] : 0u, lane + 64u * i};
-                if (larger(x, best)) best = x;
-            }
-            best = wave_best<true>(best);
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                if (best.v == lane + 64u * i) q[i]++;
-        }
-        for (; diff < 0; diff++) {
-            Cand best = {0, 0, 0};
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const Cand x = {c[i], q[i] >= 2 ? q[i] - 1 : 0u, lane + 64u * i};
-                if (smaller(x, best)) best = x;
-            }
-            best = wave_best<false>(best);
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                if (best.v == lane + 64u * i) q[i]--;
-        }
+        if (diff > 0) settle_frequencies<true>(c, q, (uint32_t)diff, lane);
+        else if (diff < 0) settle_frequencies<false>(c, q, (uint32_t)-diff, lane);
 #pragma unroll
         for (int i = 0; i < 4; i++) nq[lane + 64 * i] = q[i];
     }
@@ -354,6 +375,10 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         for (uint32_t w = 0; w < wave; w++) cum += wave_sum[w];
         cumq[t] = cum | qv << 16;
         a.freq[k * 256 + t] = (uint16_t)qv;
+        // A symbol's field has nb bits, nb the smallest n with (X >> n) < 2q: X lies in [2048, 4096), so that is
+        // n0 = 12 - (bits of 2q - 1), or one more from X = 2q << n0 on: nb = (X + ((n0 + 1) << 16) - (2q << n0)) >> 16.
+        const uint32_t n0 = (uint32_t)__builtin_clz((2 * qv - 1) | 1u) - (31 - kTansBits);
+        step_of[t] = make_uint2(((n0 + 1) << 16) - (2 * qv << n0), 2 * (cum - qv));
         if (qv) {
             marks[cum] = (uint16_t)(t + 1);
             // also at the first place of every later wave of the pass below that the value reaches into
@@ -390,7 +415,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
                 const uint32_t n = (q + M - 1 - ((off - (1u << b)) & (M - 1))) >> (b + 1);
                 rank += ((p >> b) & 1u) ? n : 0u;
             }
-            state_of[(first + rank) & (kTansL - 1)] = (uint16_t)(__brev(p) >> (32 - kTansBits));
+            state_of[(first + rank) & (kTansL - 1)] = (uint16_t)(kTansL + (__brev(p) >> (32 - kTansBits)));
         }
     }
     __syncthreads();
@@ -398,35 +423,45 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     // ---- every sub-stream coded from its last symbol to its first: X = 2048; per symbol the smallest n with
     // (X >> n) < 2q, the field X mod 2^n, then X = 2048 + the state of the value numbered X >> n.  The items
     // (two symbols each: width | fields << 8) land in the workspace at the positions of their bytes.
+    // This is one serial chain per lane, few wavefronts to a SIMD: everything that does not depend on X (the bytes of the
+    // next group, what the 16 values do to X) is loaded before the chain needs it, and a link of the chain is four
+    // operations and one look-up of the next state (40 us for 688 chunks of 64 KiB when the field's width was worked out
+    // from the frequency inside the chain, 18 now).
     const uint32_t groups = (raw + 15) / 16;
     if (t < S) {
         const uint32_t my_groups = t < groups ? (groups - t + S - 1) / S : 0;
+        const uint32_t states = lds_address(state_of);
         uint32_t X = kTansL, bits = 0;
-        for (uint32_t r = my_groups; r-- > 0;) {
+        uint32_t w[4] = {0, 0, 0, 0};
+        auto load_group = [&](uint32_t r) {
             const uint32_t lo = 16 * (t + r * S);
-            const uint32_t n = raw - lo < 16 ? raw - lo : 16;
-            uint32_t w[4] = {0, 0, 0, 0};
-            if (n == 16) {
+            if (raw - lo >= 16) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(src + lo);
                 w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
             } else {
-                for (uint32_t i = 0; i < n; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
+                w[0] = w[1] = w[2] = w[3] = 0;
+                for (uint32_t i = 0; lo + i < raw; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
             }
-            uint32_t it[8]; // per two symbols: the width of both fields, and both fields from bit 8 on
+        };
+        if (my_groups) load_group(my_groups - 1);
+        for (uint32_t r = my_groups; r-- > 0;) {
+            const uint32_t lo = 16 * (t + r * S);
+            const uint32_t n = raw - lo < 16 ? raw - lo : 16;
+            uint2 step[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) step[i] = step_of[(w[i >> 2] >> (8 * (i & 3))) & 0xFFu];
+            if (r > 0) load_group(r - 1);
+            uint32_t it[8];
 #pragma unroll
             for (int j = 7; j >= 0; j--) {
                 uint32_t field = 0, width = 0;
 #pragma unroll
                 for (int i = 2 * j + 1; i >= 2 * j; i--) {
                     if ((uint32_t)i < n) {
-                        const uint32_t v = (w[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-                        const uint32_t cq = cumq[v];
-                        const uint32_t first = cq & 0xFFFFu, q = cq >> 16;
-                        uint32_t nb = (uint32_t)__builtin_clz(2 * q - 1) - (31 - kTansBits); // 12 - bit length of 2q - 1
-                        nb += (X >> nb) >= 2 * q;
+                        const uint32_t nb = (X + step[i].x) >> 16;
                         field = field << nb | (X & ((1u << nb) - 1u));
                         width += nb;
-                        X = kTansL + state_of[(first + (X >> nb) - q) & (kTansL - 1)];
+                        X = lds_load16(states + step[i].y + 2 * (X >> nb));
                     }
                 }
                 it[j] = width | field << 8;
