@@ -242,16 +242,12 @@ constexpr uint32_t kTansBits = DC_TANS_STATE_BITS;
 constexpr uint32_t kTansL = 1u << kTansBits;
 
 // Smallest (or largest) of the lanes' values, for all lanes.  `none` is what a lane without a source counts as.
-template <bool LARGEST> __device__ __forceinline__ double lanes_extreme(double v, double none)
+template <bool LARGEST> __device__ __forceinline__ float lanes_extreme(float v, float none)
 {
-    const uint64_t fill = __builtin_bit_cast(uint64_t, none);
-#define DC_EXTREME_STEP(CTRL, MASK)                                                                                        \
-    {                                                                                                                      \
-        const uint64_t u = __builtin_bit_cast(uint64_t, v);                                                                \
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)fill, (int)(uint32_t)u, CTRL, MASK, 0xF, false); \
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(fill >> 32), (int)(uint32_t)(u >> 32), CTRL, MASK, 0xF, false); \
-        const double o = __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);                                              \
-        v = LARGEST ? (o > v ? o : v) : (o < v ? o : v);                                                                   \
+#define DC_EXTREME_STEP(CTRL, MASK)                                                                                      \
+    {                                                                                                                    \
+        const float o = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(none), (int)__float_as_uint(v), CTRL, MASK, 0xF, false)); \
+        v = LARGEST ? __builtin_fmaxf(o, v) : __builtin_fminf(o, v);                                                     \
     }
     DC_EXTREME_STEP(0x111, 0xF)
     DC_EXTREME_STEP(0x112, 0xF)
@@ -260,57 +256,65 @@ template <bool LARGEST> __device__ __forceinline__ double lanes_extreme(double v
     DC_EXTREME_STEP(0x142, 0xA)
     DC_EXTREME_STEP(0x143, 0xC)
 #undef DC_EXTREME_STEP
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
 }
 
 // The second half of the normalisation rule by one wavefront; lane l holds counts and frequencies of the values l, l + 64,
 // l + 128, l + 192.  GROW: the value with the largest count / q gains one, `steps` times; else the value with q > 1 and
-// the smallest count / (q - 1) loses one; the lower value among equals.  The ratios are compared as 64-bit floating
-// point quotients: counts are at most 2^20 and divisors at most 2^11, so different ratios differ by more than 2^-42 of
-// themselves and their quotients in the same direction, and equal ratios have equal quotients.  A step is one
-// reduction over the lanes and one division, 0.15 us; cross products of (count, divisor, value) triples through
-// shuffles took 1.4 us.
+// the smallest count / (q - 1) loses one; the lower value among equals.  A step is a serial link, so it is kept short: the
+// ratios are held as 32-bit quotients, which are within 2^-22 of the ratio (counts and divisors are exact, the
+// reciprocal is within one unit of the last place and the product within half of one); the value sought has a quotient
+// within 2^-20 of the best one, and where several have, their exact cross products (below 2^31) decide.
+// (Cross products of (count, divisor, value) triples through shuffles: 1.4 us a step.)
 template <bool GROW> __device__ __forceinline__ void settle_frequencies(const uint32_t c[4], uint32_t q[4], uint32_t steps, uint32_t lane)
 {
-    const double none = GROW ? -1.0 : __builtin_huge_val();
-    auto ratio = [&](uint32_t count, uint32_t freq) -> double {
+    const float none = GROW ? -1.0f : __builtin_huge_valf();
+    auto divisor = [](uint32_t freq) -> uint32_t { return GROW ? freq : freq - 1; };
+    auto ratio = [&](uint32_t count, uint32_t freq) -> float {
         const bool candidate = GROW ? count != 0 : freq >= 2;
-        return candidate ? (double)count / (double)(GROW ? freq : freq - 1) : none;
+        return candidate ? (float)count * __builtin_amdgcn_rcpf((float)divisor(freq)) : none;
     };
-    double key[4];
+    float key[4];
 #pragma unroll
     for (int i = 0; i < 4; i++) key[i] = ratio(c[i], q[i]);
     for (; steps > 0; steps--) {
-        double mine = key[0];
+        float mine = key[0];
 #pragma unroll
-        for (int i = 1; i < 4; i++) mine = GROW ? (key[i] > mine ? key[i] : mine) : (key[i] < mine ? key[i] : mine);
-        const double best = lanes_extreme<GROW>(mine, none);
-        // the lowest value among those with the best ratio
-        uint32_t which = 4, from = 0;
+        for (int i = 1; i < 4; i++) mine = GROW ? __builtin_fmaxf(key[i], mine) : __builtin_fminf(key[i], mine);
+        const float best = lanes_extreme<GROW>(mine, none);
+        const float near = best * (GROW ? 1.0f - 0x1p-20f : 1.0f + 0x1p-20f);
+        uint64_t m[4];
+        uint32_t many = 0;
 #pragma unroll
-        for (int i = 3; i >= 0; i--) {
-            const uint64_t m = __ballot(key[i] == best);
-            if (m) {
-                which = i;
-                from = (uint32_t)__builtin_ctzll(m);
-            }
+        for (int i = 0; i < 4; i++) {
+            m[i] = __ballot(GROW ? key[i] >= near : key[i] <= near);
+            many += (uint32_t)__popcll(m[i]);
         }
-        if (lane == from) {
-            uint32_t count = 0, freq = 0;
+        uint32_t value = m[0] ? (uint32_t)__builtin_ctzll(m[0]) : m[1] ? 64u + (uint32_t)__builtin_ctzll(m[1])
+                       : m[2] ? 128u + (uint32_t)__builtin_ctzll(m[2]) : 192u + (uint32_t)__builtin_ctzll(m[3] | 1ull << 63);
+        if (many != 1) {
+            // in ascending order of the values, so that only a strictly better ratio takes over
+            uint32_t best_c = 0, best_d = 0;
 #pragma unroll
             for (uint32_t i = 0; i < 4; i++)
-                if (which == i) {
-                    q[i] += GROW ? 1u : ~0u;
-                    count = c[i];
-                    freq = q[i];
+                for (uint64_t left = m[i]; left; left &= left - 1) {
+                    const uint32_t from = (uint32_t)__builtin_ctzll(left);
+                    const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)c[i], from);
+                    const uint32_t d = divisor((uint32_t)__builtin_amdgcn_readlane((int)q[i], from));
+                    const uint32_t l = count * best_d, r = best_c * d;
+                    if (best_d == 0 || (GROW ? l > r : l < r)) {
+                        best_c = count;
+                        best_d = d;
+                        value = 64 * i + from;
+                    }
                 }
-            const double next = ratio(count, freq);
-#pragma unroll
-            for (uint32_t i = 0; i < 4; i++) key[i] = which == i ? next : key[i];
         }
+#pragma unroll
+        for (uint32_t i = 0; i < 4; i++)
+            if (value == lane + 64 * i) {
+                q[i] += GROW ? 1u : ~0u;
+                key[i] = ratio(c[i], q[i]);
+            }
     }
 }
 
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     // among frequencies above one loses one; the lower value among equals)
     {
         const uint32_t cnt = hist[t];
-        const uint32_t share = (uint32_t)(((uint64_t)cnt << kTansBits) / raw);
+        const uint32_t share = (cnt << kTansBits) / raw; // cnt is at most 2^20
         const uint32_t q0 = cnt ? (share ? share : 1u) : 0u;
         nq[t] = q0;
         const uint32_t incl = lanes_prefix_sum<false>(q0);
@@ -426,7 +430,8 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     // This is one serial chain per lane, few wavefronts to a SIMD: everything that does not depend on X (the bytes of the
     // next group, what the 16 values do to X) is loaded before the chain needs it, and a link of the chain is four
     // operations and one look-up of the next state (40 us for 688 chunks of 64 KiB when the field's width was worked out
-    // from the frequency inside the chain, 18 now).
+    // from the frequency inside the chain, 22 now, of which the
+    // 1.4 KiB a wavefront and round that go to and from memory are the larger part).
     const uint32_t groups = (raw + 15) / 16;
     if (t < S) {
         const uint32_t my_groups = t < groups ? (groups - t + S - 1) / S : 0;
@@ -434,19 +439,11 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         uint32_t X = kTansL, bits = 0;
         uint32_t w[4] = {0, 0, 0, 0};
         auto load_group = [&](uint32_t r) {
-            const uint32_t lo = 16 * (t + r * S);
-            if (raw - lo >= 16) {
-                const u32x4 v = *reinterpret_cast<const u32x4 *>(src + lo);
-                w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
-            } else {
-                w[0] = w[1] = w[2] = w[3] = 0;
-                for (uint32_t i = 0; lo + i < raw; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
-            }
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(src + 16 * (t + r * S));
+            w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
         };
-        if (my_groups) load_group(my_groups - 1);
-        for (uint32_t r = my_groups; r-- > 0;) {
-            const uint32_t lo = 16 * (t + r * S);
-            const uint32_t n = raw - lo < 16 ? raw - lo : 16;
+        // codes a group, the bytes from the n-th on absent; its bytes are in w, those of group r - 1 are loaded meanwhile
+        auto code_group = [&](uint32_t r, uint32_t n, bool whole) {
             uint2 step[16];
 #pragma unroll
             for (int i = 0; i < 16; i++) step[i] = step_of[(w[i >> 2] >> (8 * (i & 3))) & 0xFFu];
@@ -457,7 +454,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
                 uint32_t field = 0, width = 0;
 #pragma unroll
                 for (int i = 2 * j + 1; i >= 2 * j; i--) {
-                    if ((uint32_t)i < n) {
+                    if (whole || (uint32_t)i < n) {
                         const uint32_t nb = (X + step[i].x) >> 16;
                         field = field << nb | (X & ((1u << nb) - 1u));
                         width += nb;
@@ -467,10 +464,19 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
                 it[j] = width | field << 8;
                 bits += width;
             }
-            u32x4 *dst = reinterpret_cast<u32x4 *>(a.items + (k * a.chunk_bytes + lo) / 2);
+            u32x4 *dst = reinterpret_cast<u32x4 *>(a.items + (k * a.chunk_bytes + 16 * (t + r * S)) / 2);
             dst[0] = u32x4{it[0], it[1], it[2], it[3]};
             dst[1] = u32x4{it[4], it[5], it[6], it[7]};
+        };
+        uint32_t r = my_groups;
+        if (r) {
+            const uint32_t lo = 16 * (t + (r - 1) * S);
+            const uint32_t n = raw - lo < 16 ? raw - lo : 16; // only a stream's last group may lack bytes
+            w[0] = w[1] = w[2] = w[3] = 0;
+            for (uint32_t i = 0; i < n; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
+            code_group(--r, n, false);
         }
+        while (r > 0) code_group(--r, 16, true);
         if (my_groups) bits += kTansBits;
         a.first[k * S + t] = (uint16_t)(X - kTansL);
         a.bits[k * S + t] = bits;
