@@ -362,15 +362,14 @@ __device__ __forceinline__ uint32_t pack4(uint32_t e0, uint32_t e1, uint32_t e2,
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
-// Half a group: 8 symbols, at most 88 bits, out of the four words in r.  The words are shifted down once by the position
+// Half a group: the table entries of 8 symbols, at most 88 bits, out of the four words in r.  The words are shifted down once by the position
 // inside its word (96 bits are left, the lead among them) and then by the bits every pair of symbols has used, so that every pair starts at
 // bit 0 of w0: no lane waits for another's refill, and nothing is conditional.  A lane past its stream's last symbol
 // decodes on over what the ring holds (it has no blocks left to ask for, so its position no longer matters) and its
 // symbols are dropped where they would be stored.
 template <int CODEC>
-__device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_lane, uint32_t out[2])
+__device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_lane, uint32_t e[8])
 {
-    uint32_t e[8];
     const uint32_t o = s.pos >> 3; // shifts read the low 5 bits
     uint32_t w0 = __builtin_amdgcn_alignbit(s.r[1], s.r[0], o);
     uint32_t w1 = __builtin_amdgcn_alignbit(s.r[2], s.r[1], o);
@@ -388,18 +387,21 @@ __device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_l
     const uint32_t before = s.pos;
     s.pos += ((u0 + u1 + u2 + u3) & 0xFFu) << 3;
     read_window<CODEC == DC_CODEC_TANS>(s, before, ring_lane);
-    out[0] = pack4(e[0], e[1], e[2], e[3]);
-    out[1] = pack4(e[4], e[5], e[6], e[7]);
 }
 
 // One whole group of 16 symbols with the two steps of the placement rule that precede its halves.
 template <bool UNIFORM, int CODEC = DC_CODEC_HUFFMAN>
 __device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t out[4])
 {
+    uint32_t e[8];
     stream_step<UNIFORM, 0, CODEC>(s, rg, ring_lane);
-    decode8<CODEC>(s, tbl, ring_lane, out);
+    decode8<CODEC>(s, tbl, ring_lane, e);
+    out[0] = pack4(e[0], e[1], e[2], e[3]);
+    out[1] = pack4(e[4], e[5], e[6], e[7]);
     stream_step<UNIFORM, 1, CODEC>(s, rg, ring_lane);
-    decode8<CODEC>(s, tbl, ring_lane, out + 2);
+    decode8<CODEC>(s, tbl, ring_lane, e);
+    out[2] = pack4(e[0], e[1], e[2], e[3]);
+    out[3] = pack4(e[4], e[5], e[6], e[7]);
 }
 
 __device__ __forceinline__ uint32_t bf16x2(float a, float b)
@@ -414,8 +416,10 @@ __device__ __forceinline__ uint32_t bf16x2(float a, float b)
 // acc + a.lo * b.lo + a.hi * b.hi for two pairs of bf16 values
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc)
 {
-    asm("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(acc) : "v"(a), "v"(b));
-    return acc;
+    // The builtin, not inline assembly: the result of a dot product may be read by another instruction three wait states
+    // later at the earliest, and the compiler only keeps that distance for instructions it knows.
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
 }
 
 // int8 value number N of a word as fp32: one v_cvt_f32_i32 whose operand selects the byte and sign-extends it
@@ -942,33 +946,42 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             acc = 0.0f;
             cur_row = 0xFFFFFFFFu;
         };
-        for (uint32_t r = 0; r < rounds; r++) {
-            const uint32_t start = r * round_bytes + ct * 16;
-            const bool whole = raw >= start + 16;
-            uint32_t w[4] = {0, 0, 0, 0};
-            if (huff) {
-                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
-            } else if (whole) {
-                const u32x4 v = load16_stream(payload8 + start);
-                w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
-            }
+        // An int8 value is a bf16 value exactly: two of them packed, times two values of x as they lie in memory, in one
+        // instruction (products exact in fp32, summed in fp32).  The values come straight out of byte 1 of their table
+        // entries, without being packed to bytes first, and x is asked for before the group is decoded.
+        auto one_round = [&](uint32_t r, bool whole) {
+            const uint4 *xp = reinterpret_cast<const uint4 *>(mat.x_bf16 + col); // col + 16 <= cols, group or not
+            const uint4 xa = xp[0], xb = xp[1];
+            const uint32_t xs[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
             if (__any(whole && row != cur_row && cur_row != 0xFFFFFFFFu)) flush();
-            if (whole) {
-                cur_row = row;
-                const uint4 *xp = reinterpret_cast<const uint4 *>(mat.x_bf16 + col);
-                const uint4 xa = xp[0], xb = xp[1];
-                const uint32_t xs[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
+            cur_row = whole ? row : cur_row;
+            if (huff) {
+                uint32_t e[8];
+                auto products = [&](uint32_t half) {
+                    if (whole)
+#pragma unroll
+                        for (int i = 0; i < 4; i++)
+                            acc = dot2_bf16(bf16x2(byte_f32<1>(e[2 * i]), byte_f32<1>(e[2 * i + 1])), xs[4 * half + i], acc);
+                };
+                stream_step<UNI, 0, CODEC>(st, rg, ring_lane);
+                decode8<CODEC>(st, tbl_addr, ring_lane, e);
+                products(0);
+                stream_step<UNI, 1, CODEC>(st, rg, ring_lane);
+                decode8<CODEC>(st, tbl_addr, ring_lane, e);
+                products(1);
+            } else if (whole) {
+                const u32x4 w = load16_stream(payload8 + r * round_bytes + ct * 16);
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    // an int8 value is a bf16 value exactly: two of them packed, times two values of x as they lie in
-                    // memory, in one instruction (products exact in fp32, summed in fp32)
                     acc = dot2_bf16(bf16x2(byte_f32<0>(w[i]), byte_f32<1>(w[i])), xs[2 * i], acc);
                     acc = dot2_bf16(bf16x2(byte_f32<2>(w[i]), byte_f32<3>(w[i])), xs[2 * i + 1], acc);
                 }
             }
             col += round_bytes;
             while (col >= cols) { col -= cols; row++; }
-        }
+        };
+        for (uint32_t r = 0; r < full_rounds; r++) one_round(r, true);
+        if (rem) one_round(full_rounds, raw >= full_rounds * round_bytes + ct * 16 + 16);
         flush();
         if (MODE == kModeGemv) {
             float total = mine;
@@ -993,24 +1006,22 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         int32_t *y_sum = reinterpret_cast<int32_t *>(mat.y_accum);
         uint32_t cur_row = 0xFFFFFFFFu;
         int32_t acc = 0;
-        for (uint32_t r = 0; r < rounds; r++) {
-            const uint32_t start = r * round_bytes + ct * 16;
-            const bool whole = raw >= start + 16;
-            uint32_t w[4] = {0, 0, 0, 0};
-            if (huff) {
-                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
-            } else if (whole) {
-                const u32x4 v = load16_stream(payload8 + start);
-                w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
-            }
+        auto one_round = [&](uint32_t r, bool whole) {
+            const uint4 x = *reinterpret_cast<const uint4 *>(mat.x_i8 + col); // asked for before the group is decoded
             if (__any(whole && row != cur_row && cur_row != 0xFFFFFFFFu)) {
                 lanes_add_by_key<CPW == 2, int32_t>(y_sum, cur_row < mat.rows ? cur_row : 0xFFFFFFFFu, acc);
                 acc = 0;
                 cur_row = 0xFFFFFFFFu;
             }
+            cur_row = whole ? row : cur_row;
+            uint32_t w[4] = {0, 0, 0, 0};
+            if (huff) {
+                decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            } else if (whole) {
+                const u32x4 v = load16_stream(payload8 + r * round_bytes + ct * 16);
+                w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
+            }
             if (whole) {
-                cur_row = row;
-                const uint4 x = *reinterpret_cast<const uint4 *>(mat.x_i8 + col);
                 acc = __builtin_amdgcn_sdot4((int)w[0], (int)x.x, acc, false);
                 acc = __builtin_amdgcn_sdot4((int)w[1], (int)x.y, acc, false);
                 acc = __builtin_amdgcn_sdot4((int)w[2], (int)x.z, acc, false);
@@ -1018,7 +1029,9 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             }
             col += round_bytes;
             while (col >= cols) { col -= cols; row++; }
-        }
+        };
+        for (uint32_t r = 0; r < full_rounds; r++) one_round(r, true);
+        if (rem) one_round(full_rounds, raw >= full_rounds * round_bytes + ct * 16 + 16);
         lanes_add_by_key<CPW == 2, int32_t>(y_sum, cur_row < mat.rows ? cur_row : 0xFFFFFFFFu, acc);
     }
 }
