@@ -424,9 +424,10 @@ int dc_decompress_dequant_bf16(const uint8_t *blob_dev, uint64_t blob_bytes, con
  *                                    work on the stream is done
  * Two launches: the decode kernel leaves in the workspace one partial sum per chunk and row the chunk
  * touches, added up inside the chunk in a fixed order, and a second kernel adds a row's partial sums in
- * chunk order and scales them.  No atomic operation is involved, so a call returns the same bits every
- * time it runs on the same input.  That holds while a chunk touches at most min(n_streams, 64) rows
- * (chunk_bytes / cols rows if cols divides chunk_bytes, else ceil(chunk_bytes / cols) + 1); for
+ * chunk order and scales them.  One launch, with the same bits, if cols divides chunk_bytes (no row reaches
+ * into a second chunk) and no result lies over an input.  No atomic operation is involved, so a call returns
+ * the same bits every time it runs on the same input.  That holds while a chunk touches at most
+ * min(n_streams, 64) rows (chunk_bytes / cols rows if cols divides chunk_bytes, else ceil(chunk_bytes / cols) + 1); for
  * flatter matrices the call falls back to three launches that add with fp32 atomics on y_f32_dev (the
  * workspace is then not used and may be NULL), and results are reproducible to rounding only.
  * Errors: DC_E_ARG, DC_E_CAP (workspace too small), DC_E_HIP.
@@ -460,7 +461,7 @@ int dc_decompress_gemv_layer(const uint8_t *blob_dev, uint64_t blob_bytes, const
  * so the result has one right value whatever the order of the additions.  x_i8_dev: cols int8 values,
  * 16-byte aligned; x_scale: their scale (dc_quantize_vector makes both).  y_accum_dev: rows fp32 results
  * (it holds the integer sums while the call runs); y_bf16_dev: the same rounded to bf16, may be NULL.
- * Three launches on hip_stream; nothing decoded is written to memory.  Errors as dc_decompress_gemv.
+ * Three launches on hip_stream, or one where dc_decompress_gemv takes one; nothing decoded is written to memory.  Errors as dc_decompress_gemv.
  * The _layer form takes x_i8_dev and x_scale from the matrix descriptors.
  */
 int dc_decompress_gemv_w8a8(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *table_dev,

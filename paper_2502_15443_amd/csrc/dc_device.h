@@ -79,6 +79,10 @@ __device__ __forceinline__ float lanes_sum(float v)
 #undef DC_SUM_STEP
     return v;
 }
+__device__ __forceinline__ int32_t lanes_sum(int32_t v)
+{
+    return __builtin_bit_cast(int32_t, lanes_prefix_sum<false>(__builtin_bit_cast(uint32_t, v)));
+}
 
 } // namespace dcdev
 

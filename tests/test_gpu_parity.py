@@ -438,6 +438,56 @@ def test_gemv_w8a8_bit_exact(S, rows, cols, C, f):
             assert abs(int(oq.gemv_w8a8_acc(q, xq)[2])) > 2 ** 24  # beyond the integers fp32 holds exactly
 
 
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.HUFFMAN), (128, oc.TANS), (256, oc.HUFFMAN)])
+@pytest.mark.parametrize("rows,cols,C,f", [(7, 4096, 4096, 0.0),     # a row a chunk
+                                           (37, 1024, 16384, 0.5),   # sixteen, the last chunk has five, some chunks raw
+                                           (70, 512, 16384, 0.3),    # thirty-two, a lane each at 32 sub-streams
+                                           (130, 256, 16384, 0.5),   # sixty-four: more than 32 sub-streams' lanes
+                                           (3, 16384, 65536, 0.0)])  # one chunk, not full
+def test_rows_finished_by_the_decode_launch(S, codec, rows, cols, C, f):
+    """Chunks that hold whole rows: the decode launch writes the results.  Against the exact int8 result, and against the
+    bits of the two-launch product, which is what runs when a result lies over an input (it must still be right then)."""
+    print(f"case rows S={S} codec={codec} {rows}x{cols} C={C} f={f}", flush=True)
+    seed = synth.matrix_seed(8, 2)
+    q, scale = oracle_matrix(rows, cols, seed, False)
+    c = oc.compress(q, C, S, oc.RAW_FRACTION, f, codec=codec)
+    table = c.table.copy()
+    blob_d, scale_d, p = dev(c.blob), torch.from_numpy(scale).cuda(), dc.Params(C, S, codec=codec)
+    x = synth.gen_activation_bf16(cols, seed)
+    xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
+
+    def product(int8, in_place):
+        room = torch.full((max(cols, 2 * rows) + 64,), 0x5A5A, dtype=torch.int16, device="cuda")
+        xs = torch.from_numpy(xq).cuda() if int8 else torch.from_numpy(x.view(np.int16)).cuda()
+        if in_place:
+            room[:xs.numel() * xs.element_size() // 2] = xs.view(torch.int16)
+            xs = room
+        y32 = torch.full((rows + 3,), 7.0, dtype=torch.float32, device="cuda")
+        args = (blob_d, c.blob.size, dev(table), c.n_chunks, p, scale_d, rows, cols, xs)
+        if int8:
+            dc.decompress_gemv_w8a8(*args, float(sx), y32, room, stream())
+        else:
+            dc.decompress_gemv(*args, y32, room, *gemv_workspace(c.n_chunks), stream())
+        torch.cuda.synchronize()
+        y = y32.cpu().numpy()
+        assert (y[rows:] == 7.0).all()
+        assert np.array_equal(room[:rows].cpu().numpy().view(np.uint16), oq.bf16_round(y[:rows]))
+        return y[:rows]
+
+    y8 = product(True, False)
+    assert np.array_equal(y8.view(np.uint32), oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
+    assert np.array_equal(product(True, True).view(np.uint32), y8.view(np.uint32))
+    y = product(False, False)
+    gemv_check(y, oq.gemv_ref(q, scale, x))
+    if C // cols <= min(S, 64):  # else the sums are added by atomics
+        assert np.array_equal(product(False, True).view(np.uint32), y.view(np.uint32))
+    # a chunk that is not decoded leaves its rows the results of empty sums, as the three launches do
+    table["comp_bytes"][c.n_chunks - 1] = 1 << 30
+    first = (c.n_chunks - 1) * C // cols
+    y8_cut = product(True, False)
+    assert (y8_cut[first:] == 0.0).all() and np.array_equal(y8_cut[:first].view(np.uint32), y8[:first].view(np.uint32))
+
+
 def test_gemv_w8a8_whole_layer_call_and_argument_checks():
     C, S = 16384, 256
     shapes = [(96, 1024), (40, 2752), (33, 5120)]
