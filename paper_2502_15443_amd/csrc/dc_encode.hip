@@ -67,6 +67,20 @@ __device__ __forceinline__ uint32_t chunk_len(const EncArgs &a, uint64_t k)
     return left < a.chunk_bytes ? (uint32_t)left : a.chunk_bytes;
 }
 
+// step(16 bytes) for the groups t, t + 256, ... below n16, four loads in flight (one load at a time left a chunk alone on its
+// compute unit waiting for memory sixteen times over: 8 us of the 28 us such a chunk of 64 KiB took in the statistics).
+template <typename Step> __device__ __forceinline__ void each_group(const uint8_t *src, uint32_t t, uint32_t n16, Step step)
+{
+    const u32x4 *p = reinterpret_cast<const u32x4 *>(src);
+    uint32_t i = t;
+    for (; i + 768 < n16; i += 1024) {
+        const u32x4 v[4] = {p[i], p[i + 256], p[i + 512], p[i + 768]};
+#pragma unroll
+        for (int j = 0; j < 4; j++) step(v[j]);
+    }
+    for (; i < n16; i += 256) step(p[i]);
+}
+
 // Byte histogram of a chunk by 256 threads.  arena: 4096 words of LDS.  Column c = t mod 32 holds, for every
 // pair of byte values (2p, 2p+1), two 16-bit counts in the word arena[32 p + c] (one column per LDS bank, so the
 // lanes of one update never meet in a bank); a column sees at most raw / 32 <= 32768 bytes, so the low count
@@ -79,13 +93,12 @@ __device__ __forceinline__ void chunk_histogram(const uint8_t *src, uint32_t raw
     uint32_t *column = arena + (t & 31u);
     auto count = [&](uint32_t b) { atomicAdd(column + ((b >> 1) << 5), 1u << ((b & 1u) << 4)); };
     const uint32_t n16 = raw / 16;
-    for (uint32_t i = t; i < n16; i += 256) {
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(src + 16 * (size_t)i);
+    each_group(src, t, n16, [&](const u32x4 &v) {
 #pragma unroll
         for (int w = 0; w < 4; w++)
 #pragma unroll
             for (int b = 0; b < 4; b++) count((v[w] >> (8 * b)) & 0xFFu);
-    }
+    });
     for (uint32_t i = n16 * 16 + t; i < raw; i += 256) count(src[i]);
     __syncthreads();
     {
@@ -97,7 +110,26 @@ __device__ __forceinline__ void chunk_histogram(const uint8_t *src, uint32_t raw
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
+// Bitonic sort of the wave's 64 keys, ascending.  Partners 1, 2 and 8 lanes apart come through the data-parallel primitives.
+__device__ __forceinline__ uint32_t wave_sorted(uint32_t k, uint32_t lane)
+{
+#pragma unroll
+    for (uint32_t size = 2; size <= 64; size <<= 1) {
+#pragma unroll
+        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
+            uint32_t o;
+            if (stride == 1) o = (uint32_t)__builtin_amdgcn_mov_dpp((int)k, 0xB1, 0xF, 0xF, true);       // quad_perm 1 0 3 2
+            else if (stride == 2) o = (uint32_t)__builtin_amdgcn_mov_dpp((int)k, 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
+            else if (stride == 8) o = (uint32_t)__builtin_amdgcn_mov_dpp((int)k, 0x128, 0xF, 0xF, true); // rotation by 8 of 16
+            else o = (uint32_t)__shfl_xor((int)k, (int)stride);
+            const bool smaller = ((lane & size) == 0) == ((lane & stride) == 0); // this lane keeps the smaller key
+            k = smaller ? (k < o ? k : o) : (k < o ? o : k);
+        }
+    }
+    return k;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void dc_codes_kernel(EncArgs a)
 {
     // 16 KiB used twice: first the histogram columns, then the tables of the package-merge.
     __shared__ uint32_t arena[4112];
@@ -107,9 +139,9 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
     __shared__ uint8_t len_of[256];
     __shared__ uint32_t sbits[256];
     __shared__ uint32_t area_bytes[4]; // per stream set: whole blocks and short first blocks
-    uint32_t(*level)[512] = reinterpret_cast<uint32_t(*)[512]>(arena);              // weights of the items of the previous / current level
-    uint32_t *pack = arena + 1024;                                                    // [256] packages made of the previous level
-    uint16_t(*leaves_before)[514] = reinterpret_cast<uint16_t(*)[514]>(arena + 1280); // [kL][514]
+    uint32_t *unsorted = arena;                                                       // [256] the waves' sorted keys
+    uint32_t(*pack)[256] = reinterpret_cast<uint32_t(*)[256]>(arena + 256);           // packages made of a level, two levels in turn
+    uint16_t(*leaves_before)[514] = reinterpret_cast<uint16_t(*)[514]>(arena + 768);  // [kL][514]
 
     const uint32_t t = threadIdx.x;
     const uint64_t k = blockIdx.x;
@@ -122,22 +154,24 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
     chunk_histogram(src, raw, arena, hist);
 
     const uint32_t cnt = hist[t];
-    key[t] = cnt ? (cnt << 8 | t) : 0xFFFFFFFFu;
     const uint32_t n = (uint32_t)__syncthreads_count(cnt != 0);
-    // bitonic sort, ascending: leaves in order of (count, byte value)
-    for (uint32_t size = 2; size <= 256; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            __syncthreads();
-            const uint32_t partner = t ^ stride;
-            if (partner > t) {
-                const bool up = (t & size) == 0;
-                const uint32_t x = key[t], y = key[partner];
-                if ((x > y) == up) {
-                    key[t] = y;
-                    key[partner] = x;
-                }
-            }
+    // leaves in order of (count, byte value): sorted in the waves first, then every key finds its place among the other
+    // three waves' keys
+    {
+        const uint32_t lane = t & 63u, wave = t >> 6;
+        const uint32_t k1 = wave_sorted(cnt ? (cnt << 8 | t) : (0xFF000000u | t), lane); // counts are below 2^24 - 2^16
+        unsorted[t] = k1;
+        __syncthreads();
+        uint32_t place = lane;
+#pragma unroll
+        for (uint32_t o = 1; o < 4; o++) {
+            const uint32_t *other = unsorted + 64 * ((wave + o) & 3u);
+            uint32_t below = 0;
+#pragma unroll
+            for (uint32_t step = 32; step > 0; step >>= 1) below += other[below + step - 1] < k1 ? step : 0u;
+            place += below + (other[below] < k1 ? 1u : 0u);
         }
+        key[place] = k1;
     }
     __syncthreads();
 
@@ -147,38 +181,49 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
         // Package-merge: level 0 is the sorted leaves; level j is the leaves merged with the pairs of
         // level j-1, a leaf before a package of equal weight.  leaves_before[j][m] = leaves among the
         // first m items of level j.
-        const uint32_t lw = t < n ? key[t] >> 8 : 0;
-        if (t < n) level[0][t] = lw;
+        // Thread t owns items 2t and 2t + 1 of a level, the pair that is package t of the next: it searches for the number a
+        // of leaves among the 2t items before them, so a level costs one search and one barrier.  From level to
+        // level items get lighter and a falls, by about half as much each time, so the search begins that far below the
+        // last a and is mostly over after a few steps.  (Two searches of nine steps and two barriers a level, the items written
+        // out: 9.3 of the 28 us of a chunk alone on its compute unit; together with the loads in flight and the sort above the
+        // call takes 157 instead of 169 us on 3088 chunks of 64 KiB, 36 instead of 43 on 1024 of 16 KiB.)
+        uint32_t size = n;
         for (uint32_t m = t; m < 514; m += 256) leaves_before[0][m] = (uint16_t)(m < n ? m : n);
-        uint32_t size_prev = n, cur = 0;
+        if (2 * t + 1 < n) pack[0][t] = (key[2 * t] >> 8) + (key[2 * t + 1] >> 8);
+        const uint32_t d = 2 * t;
+        uint32_t a_last = d < n ? d : n;
         for (int j = 1; j < kL; j++) {
             __syncthreads();
-            const uint32_t npk = size_prev / 2;
-            if (t < npk) pack[t] = level[cur][2 * t] + level[cur][2 * t + 1];
-            __syncthreads();
-            // A leaf goes after the packages lighter than it, a package after the leaves not heavier
-            // than it.  Both counts come from one 9-step search over an ascending array of at most 256
-            // entries, the two searches side by side so that their LDS reads overlap.
-            const uint32_t pw = t < npk ? pack[t] : 0;
-            uint32_t packs_below = 0, leaves_upto = 0;
-#pragma unroll
-            for (uint32_t step = 256; step > 0; step >>= 1) {
-                const uint32_t ip = packs_below + step - 1, il = leaves_upto + step - 1;
-                const uint32_t yp = pack[ip < npk ? ip : 0], yl = key[il < n ? il : 0] >> 8;
-                if (ip < npk && yp < lw) packs_below += step;
-                if (il < n && yl <= pw) leaves_upto += step;
+            const uint32_t *packs = pack[(j - 1) & 1];
+            const uint32_t npk = size / 2;
+            size = n + npk;
+            uint32_t a = 0, a1 = 0, weight = 0;
+            if (d <= size) {
+                // the smallest a with leaf a heavier than package d - 1 - a
+                uint32_t lo = d > npk ? d - npk : 0, hi = a_last;
+                const uint32_t fall = j < 8 ? 256u >> j : 1u;
+                uint32_t mid = lo + fall < hi ? hi - fall : (lo + hi) / 2;
+                while (lo < hi) {
+                    if (key[mid] >> 8 <= packs[d - 1 - mid]) lo = mid + 1;
+                    else hi = mid;
+                    mid = (lo + hi) / 2;
+                }
+                a = a1 = lo;
+                uint32_t b = d - a;
+                // items d and d + 1
+                const uint32_t l0 = key[a < 255 ? a : 255] >> 8, l1 = key[a < 254 ? a + 1 : 255] >> 8;
+                const uint32_t p0 = packs[b < 255 ? b : 255], p1 = packs[b < 254 ? b + 1 : 255];
+                const bool leaf0 = a < n && (b >= npk || l0 <= p0);
+                a1 += leaf0;
+                b += !leaf0;
+                const uint32_t l = leaf0 ? l1 : l0, p = leaf0 ? p0 : p1;
+                const bool leaf1 = a1 < n && (b >= npk || l <= p);
+                weight = (leaf0 ? l0 : p0) + (leaf1 ? l : p);
+                a_last = a;
+                leaves_before[j][d] = (uint16_t)a;
+                leaves_before[j][d + 1] = (uint16_t)(d + 1 <= size ? a1 : n);
             }
-            if (t < n) {
-                level[cur ^ 1][t + packs_below] = lw;
-                leaves_before[j][t + packs_below] = (uint16_t)t;
-            }
-            if (t < npk) {
-                level[cur ^ 1][t + leaves_upto] = pw;
-                leaves_before[j][t + leaves_upto] = (uint16_t)leaves_upto;
-            }
-            if (t == 0) leaves_before[j][n + npk] = (uint16_t)n;
-            size_prev = n + npk;
-            cur ^= 1;
+            if (d + 1 < size) pack[j & 1][t] = weight;
         }
         __syncthreads();
         if (t == 0) {
@@ -207,18 +252,14 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
     // sub-stream t mod S (S divides 256)
     const uint32_t groups = (raw + 15) / 16;
     uint32_t mine = 0;
-    for (uint32_t g = t; g < groups; g += 256) {
-        const uint32_t lo = 16 * g, hi = lo + 16 < raw ? lo + 16 : raw;
-        if (hi - lo == 16) {
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(src + lo);
+    each_group(src, t, raw / 16, [&](const u32x4 &v) {
 #pragma unroll
-            for (int w = 0; w < 4; w++)
+        for (int w = 0; w < 4; w++)
 #pragma unroll
-                for (int b = 0; b < 4; b++) mine += len_of[(v[w] >> (8 * b)) & 0xFFu];
-        } else {
-            for (uint32_t p = lo; p < hi; p++) mine += len_of[src[p]];
-        }
-    }
+            for (int b = 0; b < 4; b++) mine += len_of[(v[w] >> (8 * b)) & 0xFFu];
+    });
+    if (groups > raw / 16 && t == (groups - 1) % 256) // the last group lacks bytes
+        for (uint32_t p = 16 * (groups - 1); p < raw; p++) mine += len_of[src[p]];
     if (mine) atomicAdd(&sbits[t % a.S], mine);
     __syncthreads();
     if (t < a.S) {
@@ -241,38 +282,70 @@ __global__ __launch_bounds__(256) void dc_codes_kernel(EncArgs a)
 constexpr uint32_t kTansBits = DC_TANS_STATE_BITS;
 constexpr uint32_t kTansL = 1u << kTansBits;
 
-// Smallest (or largest) of the lanes' values, for all lanes.  `none` is what a lane without a source counts as.
-template <bool LARGEST> __device__ __forceinline__ float lanes_extreme(float v, float none)
+// Smallest of the lanes' values, for all lanes.
+__device__ __forceinline__ float lanes_smallest(float v)
 {
-#define DC_EXTREME_STEP(CTRL, MASK)                                                                                      \
-    {                                                                                                                    \
-        const float o = __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(none), (int)__float_as_uint(v), CTRL, MASK, 0xF, false)); \
-        v = LARGEST ? __builtin_fmaxf(o, v) : __builtin_fminf(o, v);                                                     \
-    }
-    DC_EXTREME_STEP(0x111, 0xF)
-    DC_EXTREME_STEP(0x112, 0xF)
-    DC_EXTREME_STEP(0x114, 0xF)
-    DC_EXTREME_STEP(0x118, 0xF)
-    DC_EXTREME_STEP(0x142, 0xA)
-    DC_EXTREME_STEP(0x143, 0xC)
-#undef DC_EXTREME_STEP
+    const uint32_t none = __float_as_uint(__builtin_huge_valf()); // what a lane without a source counts as
+#define DC_SMALLEST_STEP(CTRL, MASK)                                                                                     \
+    v = __builtin_fminf(__uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)__float_as_uint(v), CTRL, MASK, 0xF, false)), v);
+    DC_SMALLEST_STEP(0x111, 0xF)
+    DC_SMALLEST_STEP(0x112, 0xF)
+    DC_SMALLEST_STEP(0x114, 0xF)
+    DC_SMALLEST_STEP(0x118, 0xF)
+    DC_SMALLEST_STEP(0x142, 0xA)
+    DC_SMALLEST_STEP(0x143, 0xC)
+#undef DC_SMALLEST_STEP
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
 }
 
 // The second half of the normalisation rule by one wavefront; lane l holds counts and frequencies of the values l, l + 64,
-// l + 128, l + 192.  GROW: the value with the largest count / q gains one, `steps` times; else the value with q > 1 and
-// the smallest count / (q - 1) loses one; the lower value among equals.  A step is a serial link, so it is kept short: the
+// l + 128, l + 192.
+
+// Too few states: `steps` times the value with the largest count / q gains one, the lower value among equals.  No value
+// gains twice: with R = raw / 2048, a value whose share is one state or more has count / q >= R before and count / (q + 1) < R
+// after, a value that got its one state for being present has count < R, and there are more of the former than steps, which
+// are the sum of their shares' fractions less what the others were given.  So the steps go to the `steps` largest ratios, found
+// through the smallest of them, bit by bit.  Ratios are below 1024 and two of them differ by 1 / (2048 * 2048) or more, so
+// that their fixed-point quotients of 22 bits stand in the same order, and only equal ones are equal.
+// (One step at a time, a reduction over the lanes each: the whole call 77 us on 688 chunks of 64 KiB and 65 on 1024 of 16 KiB
+// where it now takes 69 and 40.)
+__device__ __forceinline__ void grant_states(const uint32_t c[4], uint32_t q[4], uint32_t steps, uint32_t raw)
+{
+    uint32_t key[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint32_t d = q[i] ? q[i] : 1u, high = (c[i] << 11) / d, rest = (c[i] << 11) - high * d;
+        key[i] = (c[i] << kTansBits) >= raw ? (high << 11) + (rest << 11) / d : 0u;
+    }
+    uint32_t last = 0; // the smallest key that gains: the largest that `steps` keys are not below
+    for (uint32_t bit = 1u << 31; bit > 0; bit >>= 1) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) n += (uint32_t)__popcll(__ballot(key[i] >= (last | bit)));
+        if (n >= steps) last |= bit;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) steps -= (uint32_t)__popcll(__ballot(key[i] > last)); // what is left for keys equal to it
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const uint64_t m = __ballot(key[i] == last);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        q[i] += key[i] > last || (key[i] == last && rank < steps) ? 1u : 0u;
+        const uint32_t n = (uint32_t)__popcll(m);
+        steps -= n < steps ? n : steps;
+    }
+}
+
+// Too many states: `steps` times the value with q > 1 and the smallest count / (q - 1) loses one, the lower value among equals.
+// A value may lose several.  A step is a serial link, so it is kept short: the
 // ratios are held as 32-bit quotients, which are within 2^-22 of the ratio (counts and divisors are exact, the
 // reciprocal is within one unit of the last place and the product within half of one); the value sought has a quotient
 // within 2^-20 of the best one, and where several have, their exact cross products (below 2^31) decide.
 // (Cross products of (count, divisor, value) triples through shuffles: 1.4 us a step.)
-template <bool GROW> __device__ __forceinline__ void settle_frequencies(const uint32_t c[4], uint32_t q[4], uint32_t steps, uint32_t lane)
+__device__ __forceinline__ void take_states(const uint32_t c[4], uint32_t q[4], uint32_t steps, uint32_t lane)
 {
-    const float none = GROW ? -1.0f : __builtin_huge_valf();
-    auto divisor = [](uint32_t freq) -> uint32_t { return GROW ? freq : freq - 1; };
     auto ratio = [&](uint32_t count, uint32_t freq) -> float {
-        const bool candidate = GROW ? count != 0 : freq >= 2;
-        return candidate ? (float)count * __builtin_amdgcn_rcpf((float)divisor(freq)) : none;
+        return freq >= 2 ? (float)count * __builtin_amdgcn_rcpf((float)(freq - 1)) : __builtin_huge_valf();
     };
     float key[4];
 #pragma unroll
@@ -280,14 +353,13 @@ template <bool GROW> __device__ __forceinline__ void settle_frequencies(const ui
     for (; steps > 0; steps--) {
         float mine = key[0];
 #pragma unroll
-        for (int i = 1; i < 4; i++) mine = GROW ? __builtin_fmaxf(key[i], mine) : __builtin_fminf(key[i], mine);
-        const float best = lanes_extreme<GROW>(mine, none);
-        const float near = best * (GROW ? 1.0f - 0x1p-20f : 1.0f + 0x1p-20f);
+        for (int i = 1; i < 4; i++) mine = __builtin_fminf(key[i], mine);
+        const float near = lanes_smallest(mine) * (1.0f + 0x1p-20f);
         uint64_t m[4];
         uint32_t many = 0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            m[i] = __ballot(GROW ? key[i] >= near : key[i] <= near);
+            m[i] = __ballot(key[i] <= near);
             many += (uint32_t)__popcll(m[i]);
         }
         uint32_t value = m[0] ? (uint32_t)__builtin_ctzll(m[0]) : m[1] ? 64u + (uint32_t)__builtin_ctzll(m[1])
@@ -300,9 +372,8 @@ template <bool GROW> __device__ __forceinline__ void settle_frequencies(const ui
                 for (uint64_t left = m[i]; left; left &= left - 1) {
                     const uint32_t from = (uint32_t)__builtin_ctzll(left);
                     const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)c[i], from);
-                    const uint32_t d = divisor((uint32_t)__builtin_amdgcn_readlane((int)q[i], from));
-                    const uint32_t l = count * best_d, r = best_c * d;
-                    if (best_d == 0 || (GROW ? l > r : l < r)) {
+                    const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)q[i], from) - 1;
+                    if (best_d == 0 || count * best_d < best_c * d) {
                         best_c = count;
                         best_d = d;
                         value = 64 * i + from;
@@ -312,7 +383,7 @@ template <bool GROW> __device__ __forceinline__ void settle_frequencies(const ui
 #pragma unroll
         for (uint32_t i = 0; i < 4; i++)
             if (value == lane + 64 * i) {
-                q[i] += GROW ? 1u : ~0u;
+                q[i]--;
                 key[i] = ratio(c[i], q[i]);
             }
     }
@@ -361,8 +432,8 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
             c[i] = hist[lane + 64 * i];
             q[i] = nq[lane + 64 * i];
         }
-        if (diff > 0) settle_frequencies<true>(c, q, (uint32_t)diff, lane);
-        else if (diff < 0) settle_frequencies<false>(c, q, (uint32_t)-diff, lane);
+        if (diff > 0) grant_states(c, q, (uint32_t)diff, raw);
+        else if (diff < 0) take_states(c, q, (uint32_t)-diff, lane);
 #pragma unroll
         for (int i = 0; i < 4; i++) nq[lane + 64 * i] = q[i];
     }

@@ -69,6 +69,22 @@ def test_device_compress_degenerate_and_limit_cases(S):
     check_equal_to_oracle(data, C, S, oc.BLOCK_LAST, block=3)
 
 
+@pytest.mark.parametrize("codec", [oc.HUFFMAN, oc.TANS])
+@pytest.mark.parametrize("n", [16, 255 * 16, 1023 * 16 + 5, 1024 * 16, 1025 * 16, 2048 * 16 + 1, 65536])
+def test_device_statistics_at_the_edges_of_the_loads_and_of_the_rules(codec, n):
+    """Chunks around the 1024 groups that are loaded four at a time, with counts that the rules find hard: all equal (ties
+    everywhere), powers of two (codes at the length limit), few values and many rare ones (frequencies given and taken back)."""
+    print(f"case dev statistics codec={codec} n={n}", flush=True)
+    r = np.random.default_rng(n)
+    flat = np.arange(n, dtype=np.uint32).astype(np.uint8)
+    powers = np.minimum(r.geometric(0.5, n), 40).astype(np.uint8)
+    rare = np.where(r.random(n) < 0.9, 5, r.integers(0, 256, n)).astype(np.uint8)
+    three = r.integers(0, 3, n).astype(np.uint8)
+    pairs = (np.minimum(r.geometric(0.02, n), 127) * 2 + r.integers(0, 2, n)).astype(np.uint8)
+    for data in (flat, powers, rare, three, pairs):
+        check_equal_to_oracle(data, 65536, 256, codec=codec)
+
+
 def test_device_compress_config2_matrix_and_round_trip():
     """gate_proj of the Llama-7B-shaped layer in the benchmark's parameters: same blob as the library's host
     compressor (itself checked against the oracle), accepted by the validator, decoded back on the GPU."""
