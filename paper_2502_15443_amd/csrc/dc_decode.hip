@@ -627,13 +627,22 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     constexpr bool UNI = CPW == 1; // all lanes of the wave belong to one stream set
 
     // ---- products of whole rows: the rows of the chunk, and what lane r of the chunk's first wave does with the sum of
-    // the r-th.  A chunk that is not decoded leaves the results of empty sums.
+    // the r-th.
     auto finish_rows = [&](auto sum) {
         const uint32_t row = (uint32_t)(dst_pos / mat.cols) + cl;
         if (k < a.n_chunks && wave == 0 && cl < a.chunk_bytes / mat.cols && row < mat.rows)
             store_row(mat, row, scaled_sum(mat, row, decltype(sum)(0) + sum));
     };
+    // ---- ordered product: the same for the sums that the chunk leaves in the workspace.  One for every row that the chunk's
+    // place in the matrix touches, whatever its table entry says, because the finish kernel adds them all up.
+    auto leave_partial_sums = [&](float sum) {
+        const uint64_t end = dst_pos + a.chunk_bytes < dst_cap ? dst_pos + a.chunk_bytes : dst_cap;
+        if (k < a.n_chunks && wave == 0 && cl <= (uint32_t)((end - 1) / mat.cols) - (uint32_t)(dst_pos / mat.cols))
+            a.partial[k * kPartialSlots + cl] = sum;
+    };
+    // A chunk that is not decoded leaves empty sums, or their results.
     auto finish_empty = [&]() {
+        if (MODE == kModeGemv || MODE == kModeGemvRows) leave_partial_sums(0.0f);
         if (MODE == kModeGemvRows) finish_rows(0.0f);
         if (MODE == kModeGemvW8A8Rows) finish_rows((int32_t)0);
     };
@@ -1070,9 +1079,8 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         flush();
         if (MODE != kModeGemvAtomic) {
             const float total = over_waves(mine);
+            leave_partial_sums(total);
             if (MODE == kModeGemvRows) finish_rows(total);
-            const uint32_t last_row = (uint32_t)((dst_pos + raw - 1) / cols);
-            if (wave == 0 && cl <= last_row - first_row) a.partial[k * kPartialSlots + cl] = total;
         }
     }
 

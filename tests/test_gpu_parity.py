@@ -488,6 +488,42 @@ def test_rows_finished_by_the_decode_launch(S, codec, rows, cols, C, f):
     assert (y8_cut[first:] == 0.0).all() and np.array_equal(y8_cut[:first].view(np.uint32), y8[:first].view(np.uint32))
 
 
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.TANS), (256, oc.HUFFMAN)])
+@pytest.mark.parametrize("rows,cols,C", [(50, 5120, 65536),   # two launches, rows reach into a second chunk
+                                         (16, 13824, 4096),   # two launches, rows of several chunks
+                                         (96, 512, 16384)])   # one launch
+def test_gemv_of_a_chunk_that_is_not_decoded(S, codec, rows, cols, C):
+    """A chunk whose table entry is impossible, or says fewer bytes than the chunk's place in the matrix holds, adds nothing
+    for the bytes that are not decoded; in particular nothing that the workspace held before the call (here NaN)."""
+    print(f"case gemv undecoded S={S} codec={codec} {rows}x{cols} C={C}", flush=True)
+    seed = synth.matrix_seed(5, 2)
+    q, scale = oracle_matrix(rows, cols, seed, False)
+    c = oc.compress(q, C, S, codec=codec)
+    x = synth.gen_activation_bf16(cols, seed)
+    blob_d, scale_d, x_d = dev(c.blob), torch.from_numpy(scale).cuda(), torch.from_numpy(x.view(np.int16)).cuda()
+    for j in {0, c.n_chunks // 2, c.n_chunks - 1}:
+        size = int(c.table["raw_bytes_flags"][j])
+        for decoded in (0, size // 32 * 16):
+            table = c.table.copy()
+            if decoded:
+                table["raw_bytes_flags"][j] = decoded
+            else:
+                table["comp_bytes"][j] = 1 << 30
+            left = q.reshape(-1).copy()
+            left[j * C + decoded:j * C + size] = 0
+            y = torch.full((rows,), 7.0, dtype=torch.float32, device="cuda")
+            dc.decompress_gemv(blob_d, c.blob.size, dev(table), c.n_chunks, dc.Params(C, S, codec=codec), scale_d, rows, cols,
+                               x_d, y, None, *gemv_workspace(c.n_chunks), stream())
+            torch.cuda.synchronize()
+            y_ref = oq.gemv_ref(left.reshape(rows, cols), scale, x)
+            got = y.cpu().numpy()
+            assert np.isfinite(got).all(), (j, decoded)
+            assert (got[y_ref == 0.0] == 0.0).all()
+            # fp32 sums of at most 13824 products against 64 bits: 2^-24 a step at most, of the sum of the magnitudes
+            size_of = np.abs(left.reshape(rows, cols).astype(np.float64)) @ np.abs(oq.bf16_to_f64(x)) * scale
+            assert (np.abs(got - y_ref) <= cols * 2.0 ** -24 * size_of).all()
+
+
 def test_gemv_w8a8_whole_layer_call_and_argument_checks():
     C, S = 16384, 256
     shapes = [(96, 1024), (40, 2752), (33, 5120)]
