@@ -962,8 +962,11 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     // the last block, unless its last bit was the stream's (the zero bits that fill the last byte are not coded)
     if (c.pos % kBlockBits) hand_over();
 
-    // ---- the heads of the set: put together where the wave's queues were (the lanes of a wave
-    // leave the loop together), then written with whole 16-byte stores, the padding of the area included
+    // ---- the heads of the set: put together where the wave's queues were, once all of its lanes have read the last of
+    // their queues, then written with whole 16-byte stores, the padding of the area included
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     uint8_t *stage = reinterpret_cast<uint8_t *>(places + wave * (kPlaces * 64));
     if (lane == 0)
         for (uint32_t p = heads_total; p < heads_padded; p++) stage[p] = 0;

@@ -1,0 +1,58 @@
+"""The kernels of the device compressor compiled for the CPU, lane by lane (tests/lanes/hip/hip_runtime.h): the lanes of a
+workgroup run one at a time between the places where the source makes them meet, in three orders, with LDS, workspace and
+results holding arbitrary bytes at the start.  The blob must be the oracle's in every order: then nothing is read before it is
+written, and no access is right only because the lanes of a wave happen to keep in step."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle.codec as oc
+from tests.helpers import lopsided_bytes, weightlike_bytes
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CLANG = "/opt/rocm/llvm/bin/clang++"
+ORDERS = {"ascending": 0, "descending": 1, "shuffled": 2}
+
+
+@pytest.fixture(scope="module")
+def encode(tmp_path_factory):
+    d = tmp_path_factory.mktemp("lanes")
+    exe, src, out = str(d / "encode"), str(d / "source"), str(d / "result")
+    # no position-independent code: LDS variables have addresses of 32 bits, as on the device
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-no-pie", "-fno-pie", "-w", "-I", os.path.join(HERE, "lanes"),
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_15443_amd", "csrc"),
+                    os.path.join(HERE, "lanes", "encode.cpp"), "-o", exe], check=True)
+
+    def run(order, seed, data, C, S, policy=oc.ALL_HUFF, f=0.0, block=0, codec=oc.HUFFMAN):
+        data.tofile(src)
+        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], seed, C, S, policy, f, block, codec)] + [src, out],
+                              capture_output=True, text=True, timeout=100)
+        assert done.returncode == 0, (done.returncode, done.stderr)
+        b = open(out, "rb").read()
+        used, status, nc = (int(v) for v in np.frombuffer(b[:24], np.uint64))
+        return used, status, np.frombuffer(b[24:24 + 16 * nc], oc.CHUNK_DTYPE), np.frombuffer(b[24 + 16 * nc:], np.uint8)
+
+    return run
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.HUFFMAN), (128, oc.HUFFMAN), (256, oc.HUFFMAN),
+                                     (64, oc.TANS), (128, oc.TANS), (256, oc.TANS)])
+def test_compressor_does_not_depend_on_the_order_of_the_lanes(encode, order, S, codec):
+    r = np.random.default_rng(S)
+    C = 16384
+    tail = r.permutation(256)[np.minimum(r.geometric(0.03, C), 255)].astype(np.uint8)
+    cases = [(weightlike_bytes(3 * C + 777, S), {}), (lopsided_bytes(C, S, 7), {}),
+             (np.concatenate([np.zeros(C, np.uint8), r.integers(0, 256, C, dtype=np.uint8), tail, weightlike_bytes(C, 3)]),
+              dict(policy=oc.RAW_FRACTION, f=0.3)),
+             (np.concatenate([r.integers(0, 256, C, dtype=np.uint8), tail[:1234]]), dict(policy=oc.AUTO)),
+             (np.array([7], np.uint8), {})]
+    for i, (data, options) in enumerate(cases):
+        want = oc.compress(data, C, S, options.get("policy", oc.ALL_HUFF), options.get("f", 0.0), codec=codec)
+        used, status, table, blob = encode(order, 11 * i + S, data, C, S, codec=codec, **options)
+        assert status == 0 and used == want.blob.size, i
+        assert np.array_equal(table, want.table), i
+        assert np.array_equal(blob, want.blob), i
