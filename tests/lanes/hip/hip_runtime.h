@@ -16,6 +16,7 @@
 
 #include <setjmp.h>
 #include <ucontext.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <functional>
@@ -67,13 +68,13 @@ inline std::vector<Wave> wave;
 inline uint32_t now = 0, threads = 0; // the lane that runs; lanes of the workgroup
 inline uint32_t counted = 0;          // __syncthreads_count
 inline jmp_buf scheduler;
-inline ucontext_t scheduler_context;
 inline std::function<void()> body;
+inline std::mt19937_64 strays;
 
 inline void fail(const char *what)
 {
     fprintf(stderr, "%s\n", what);
-    exit(3);
+    _exit(3);
 }
 inline void wait(Meet kind, const char *op)
 {
@@ -94,8 +95,8 @@ inline uint32_t meet(uint64_t v, const char *op)
 inline bool came(uint32_t half, uint32_t l) { return wave[now / 64].there[half] >> l & 1u; }
 inline uint64_t from(uint32_t half, uint32_t l)
 {
-    if (!came(half, l)) fail("a lane that has returned is read");
-    return wave[now / 64].value[half][l];
+    // the register of a lane that has returned holds anything
+    return came(half, l) ? wave[now / 64].value[half][l] : strays();
 }
 inline void run_lane()
 {
@@ -251,7 +252,6 @@ inline int __shfl(int v, int l, int width = 64)
 inline int __shfl_xor(int v, int mask) { return (int)lanes::from(lanes::meet((uint32_t)v, "shuffle"), (lanes::now ^ (uint32_t)mask) & 63u); }
 inline int __builtin_amdgcn_readlane(int v, uint32_t l)
 {
-    // LDS and registers of a lane that has returned hold nothing: the value must come from a lane that is here
     return (int)lanes::from(lanes::meet((uint32_t)v, "readlane"), l & 63u);
 }
 inline int __builtin_amdgcn_readfirstlane(int v)

@@ -1,0 +1,60 @@
+"""The decode kernels compiled for the CPU, lane by lane, as in test_encode_lanes.py: bytes, bf16 values and both products must
+be the oracle's whatever the order of the lanes between the places where the source makes them meet, and whatever LDS and the
+workspace held."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle.codec as oc
+import oracle.quant as oq
+import synth
+from tests.helpers import oracle_matrix
+from tests.test_encode_lanes import CLANG, HERE, ORDERS, ROOT
+
+BYTES, BF16, PRODUCT, PRODUCT_INT8 = range(4)
+
+
+@pytest.fixture(scope="module")
+def decode(tmp_path_factory):
+    d = tmp_path_factory.mktemp("lanes")
+    exe, src, out = str(d / "decode"), str(d / "source"), str(d / "result")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-no-pie", "-fno-pie", "-w", "-I", os.path.join(HERE, "lanes"),
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_15443_amd", "csrc"),
+                    os.path.join(HERE, "lanes", "decode.cpp"), "-o", exe], check=True)
+
+    def run(order, c, C, S, codec, mode, rows, cols, *more):
+        parts = [np.array([c.n_chunks, c.blob.size], np.uint64), c.table, c.blob, *more]
+        with open(src, "wb") as f:
+            f.write(b"".join(np.ascontiguousarray(a).tobytes() for a in parts))
+        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], rows + mode, C, S, codec, mode, rows, cols)] + [src, out],
+                              capture_output=True, text=True, timeout=100)
+        assert done.returncode == 0, (done.returncode, done.stderr)
+        return np.fromfile(out, np.uint8)
+
+    return run
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.HUFFMAN), (128, oc.HUFFMAN), (256, oc.HUFFMAN),
+                                     (64, oc.TANS), (128, oc.TANS), (256, oc.TANS)])
+@pytest.mark.parametrize("rows,cols,C,f", [(8, 4096, 16384, 0.0),   # whole rows
+                                           (3, 4096, 4096, 0.0),    # an odd number of chunks
+                                           (5, 2064, 4096, 0.4)])   # rows over chunks, a short last chunk, raw ones
+def test_decoder_does_not_depend_on_the_order_of_the_lanes(decode, order, S, codec, rows, cols, C, f):
+    if S == 32 and f:
+        f, rows, cols = 0.0, 4, 2048  # two chunks to a wavefront that differ in length or kind part its lanes: not modelled
+    q, scale = oracle_matrix(rows, cols, synth.matrix_seed(9, S), False)
+    c = oc.compress(q, C, S, oc.RAW_FRACTION, f, codec=codec)
+    x = synth.gen_activation_bf16(cols, 3)
+    xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
+    run = lambda mode, *more: decode(order, c, C, S, codec, mode, rows, cols, *more)
+    assert np.array_equal(run(BYTES), q.view(np.uint8).ravel())
+    assert np.array_equal(run(BF16, scale).view(np.uint16).reshape(rows, cols), oq.dequant_bf16(q, scale))
+    y8 = run(PRODUCT_INT8, scale, np.float32(sx), xq).view(np.uint32)
+    assert np.array_equal(y8, oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
+    # fp32 sums of `cols` products against 64 bits: 2^-24 a step at most, of the sum of the magnitudes
+    size = np.abs(q.astype(np.float64)) @ np.abs(oq.bf16_to_f64(x)) * scale
+    y = run(PRODUCT, scale, x).view(np.float32)
+    assert (np.abs(y - oq.gemv_ref(q, scale, x)) <= cols * 2.0 ** -24 * size).all()
