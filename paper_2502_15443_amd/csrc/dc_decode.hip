@@ -1520,9 +1520,9 @@ uint64_t rows_touched_by_a_chunk(uint32_t chunk_bytes, uint32_t cols)
     return (chunk_bytes + cols - 1) / cols + 1;
 }
 
-// Whether no result of the products lies over something that a decoding workgroup reads: then a workgroup may write results
-// while others still read.
-bool results_apart(const DecodeArgs &a)
+// Whether no result of the products lies over something that a decoding workgroup reads or the workspace, which one writes:
+// then a workgroup may write results while others are still at work.
+bool results_apart(const DecodeArgs &a, const void *workspace, uint64_t workspace_bytes)
 {
     struct Range { uintptr_t at; uint64_t n; };
     auto apart = [](Range x, Range y) { return x.at + x.n <= y.at || y.at + y.n <= x.at; };
@@ -1530,7 +1530,9 @@ bool results_apart(const DecodeArgs &a)
     for (uint32_t i = 0; i < a.n_mats; i++) {
         const MatrixArgs &out = a.mats[i];
         for (const Range &r : {range(out.y_accum, 4ull * out.rows), range(out.y_bf16, 2ull * out.rows)}) {
-            if (!apart(r, range(a.blob, a.blob_bytes)) || !apart(r, range(a.table, a.n_chunks * sizeof(dc_chunk)))) return false;
+            if (!apart(r, range(a.blob, a.blob_bytes)) || !apart(r, range(a.table, a.n_chunks * sizeof(dc_chunk))) ||
+                !apart(r, range(workspace, workspace_bytes)))
+                return false;
             for (uint32_t j = 0; j < a.n_mats; j++) {
                 const MatrixArgs &in = a.mats[j];
                 if (!apart(r, range(in.row_scale, 4ull * in.rows)) || !apart(r, range(in.x_bf16, 2ull * in.cols)) ||
@@ -1558,8 +1560,9 @@ int gemv_layer(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
     bool ordered = MODE == kModeGemv;
     // One launch instead of two or three (4 MiB at 256 sub-streams: 21.6 -> 20.0 us, int8 27.0 -> 19.3) if no row reaches
     // into a second chunk, the chunk's rows have a lane each, and results may be written
-    // while other chunks are decoded (a caller may put y in the place of x).
-    bool whole_rows = results_apart(a);
+    // while other chunks are decoded (a caller may put y in the place of x).  The chunks leave their partial sums in the
+    // workspace on this route too: what a call leaves there does not depend on where its results lie.
+    bool whole_rows = results_apart(a, workspace_dev, n_chunks * kPartialSlots * sizeof(float));
     for (uint32_t i = 0; i < n_mats; i++) {
         rb.mats[i] = a.mats[i];
         rb.first_block[i + 1] = rb.first_block[i] + (a.mats[i].rows + 255) / 256;

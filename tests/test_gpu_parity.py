@@ -524,6 +524,30 @@ def test_gemv_of_a_chunk_that_is_not_decoded(S, codec, rows, cols, C):
             assert (np.abs(got - y_ref) <= cols * 2.0 ** -24 * size_of).all()
 
 
+@pytest.mark.parametrize("S", [32, 256])
+def test_gemv_results_over_the_workspace(S):
+    """One chunk of whole rows, its results where the workspace begins: the results are what is left there, as in the product
+    of two launches, in which the thread that reads a partial sum is the one that writes its row."""
+    rows, cols, C = 12, 1024, 16384
+    print(f"case gemv over workspace S={S}", flush=True)
+    seed = synth.matrix_seed(5, 3)
+    q, scale = oracle_matrix(rows, cols, seed, False)
+    c = oc.compress(q, C, S)
+    x = synth.gen_activation_bf16(cols, seed)
+    blob_d, table_d, scale_d = dev(c.blob), dev(c.table), torch.from_numpy(scale).cuda()
+    x_d = torch.from_numpy(x.view(np.int16)).cuda()
+    got = []
+    for over in (False, True):
+        ws, ws_bytes = gemv_workspace(c.n_chunks)
+        y = ws.view(torch.float32)[:rows] if over else torch.full((rows,), 7.0, dtype=torch.float32, device="cuda")
+        dc.decompress_gemv(blob_d, c.blob.size, table_d, c.n_chunks, dc.Params(C, S), scale_d, rows, cols, x_d, y, None, ws,
+                           ws_bytes, stream())
+        torch.cuda.synchronize()
+        got.append(y.cpu().numpy().view(np.uint32))
+    gemv_check(got[0].view(np.float32), oq.gemv_ref(q, scale, x))
+    assert np.array_equal(got[0], got[1])
+
+
 def test_gemv_w8a8_whole_layer_call_and_argument_checks():
     C, S = 16384, 256
     shapes = [(96, 1024), (40, 2752), (33, 5120)]
