@@ -64,6 +64,16 @@ def lopsided_bytes(n: int, S: int, seed: int) -> np.ndarray:
     return out
 
 
+def stalling_bytes(n: int, S: int, seed: int) -> np.ndarray:
+    """Bytes whose tANS streams move fast and stand still in turn: runs of one value that takes no field bits from most states,
+    between short bursts of rare values, so that positions come to rest anywhere in a word for many half groups."""
+    r = np.random.default_rng(seed)
+    rounds = (n + 16 * S - 1) // (16 * S)
+    rare = r.integers(1, 40, size=(rounds, S, 16), dtype=np.uint8)
+    burst = r.random((rounds, S, 1)) < 0.25
+    return np.where(burst & (r.random((rounds, S, 16)) < 0.9), rare, 0).astype(np.uint8).reshape(-1)[:n]
+
+
 def empty_buffer_before_three_codes(data: np.ndarray, S: int):
     """Walk of a decoder that keeps a 64-bit buffer per sub-stream, refills it by 32 bits whenever at most 32
     bits are valid, and decodes each half group of 8 symbols as 3 + 2 + 3 codes: the places (lane, group,

@@ -9,7 +9,7 @@ from __future__ import annotations
 import heapq
 import itertools
 import math
-from typing import Dict, List, Sequence
+from typing import Dict, List, Optional, Sequence
 
 
 def entropy_bits(cnt: Sequence[int]) -> float:
@@ -107,7 +107,35 @@ def tans_state_table(q: Sequence[int]):
     return table
 
 
-def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False, flight: int = 0) -> bytes:
+class Ring:
+    """What the lane of one sub-stream holds in a decoder with a ring of 16 words and 4 words in registers, by the number of
+    the word in the stream (word 4 b + i is word i of block b): a block taken at a step goes into the ring two steps later;
+    the registers get the four words from the position on when a half group is done, before the next step.  With tANS the
+    word at the position is only read when the position has moved to another word.  Huffman positions are kept one bit
+    early, so that a window begins one bit before the code."""
+
+    def __init__(self, tans):
+        self.tans, self.words, self.registers, self.at = tans, [None] * 16, [None] * 4, None
+        self.kept = 0  # half groups that used bits of a word whose place in the ring a later block had taken
+
+    def push(self, block):
+        for i in range(4):
+            self.words[(4 * block + i) % 16] = 4 * block + i
+
+    def read(self, bit, again):
+        at = (bit - (0 if self.tans else 1)) >> 5
+        keep = self.tans and again and at == self.at
+        self.registers = [self.registers[0] if keep and k == 0 else self.words[(at + k) % 16] for k in range(4)]
+        self.at = at
+
+    def use(self, first, end):
+        for w in range(first >> 5, ((end - 1) >> 5) + 1 if end > first else first >> 5):
+            assert self.registers[w - self.at] == w, ("a word is not there", w, self.registers)
+            self.kept += self.words[w % 16] != w
+
+
+def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False, flight: int = 0, need: int = 215,
+                     rings: Optional[List[Ring]] = None) -> bytes:
     """Decode one Huffman (or, with `tans`, tANS) payload by walking bits, from the written format alone.
 
     header: 128 bytes of 4-bit code lengths (value v in nibble v&1 of byte v>>1), then S little-endian
@@ -130,9 +158,12 @@ def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False,
 
     flight > 0 checks what a decoder may rely on that gets a block `flight` steps after the step that took it
     (the blocks of the first four runs are there when decoding starts): at the start of every half group a
-    stream has 215 bits beyond its position among the blocks that have arrived, or all of its blocks have.
-    (215 = the 88 bits half a group can use, the 96 a decoder may hold in registers beyond them, 31 of rounding
-    to whole words.)
+    stream has `need` bits beyond its position among the blocks that have arrived, or all of its blocks have.
+    (The default is for a decoder that refills as it goes: the 88 bits half a group can use, 96 held in registers
+    beyond them, 31 of rounding to whole words.)
+
+    rings (S of them) check the decode kernel's own arrangement, see Ring: every word that holds bits of a half group's
+    symbols is in its register.
     """
     front = 384 if tans else 128
     book: Dict[tuple, int] = {}
@@ -181,6 +212,8 @@ def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False,
                 j = w * W + i
                 if len(data[i]) < 16 * nb[j] and 8 * len(data[i]) - bit[i] < 392:
                     taken_at[i].append(now)
+                    if rings and now < 0:
+                        rings[j].push(len(data[i]) // 16)
                     if len(data[i]) > 0:
                         data[i] += payload[pos:pos + 16]
                         pos += 16
@@ -198,28 +231,42 @@ def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False,
             return v
 
         state = [0] * W
+        if rings:
+            assert flight > 0, "blocks of the first four runs must be known by the time they were taken"
         for h in range(2 * rounds):
+            if rings and h:
+                for i in range(W):
+                    rings[w * W + i].read(bit[i], True)
+                    for b, t in enumerate(taken_at[i]):
+                        if t == h - 2 and t >= 0:
+                            rings[w * W + i].push(b)
             step()
             if h == 0:
                 step()
                 step()
                 step()
+                for i in range(W if rings else 0):
+                    rings[w * W + i].read(bit[i], False)
                 if tans:
                     for i in range(W):
                         if w * W + i < groups:
                             state[i] = take(i, 11)
+                            if rings:
+                                rings[w * W + i].use(bit[i] - 11, bit[i])
+                                rings[w * W + i].read(bit[i], True)
                 now = 0
                 step()
             if flight:
                 for i in range(W):
                     arrived = sum(1 for t in taken_at[i] if t <= h - flight)
-                    assert arrived == nb[w * W + i] or bit[i] + 215 <= 128 * arrived, (w * W + i, h, bit[i], arrived)
+                    assert arrived == nb[w * W + i] or bit[i] + need <= 128 * arrived, (w * W + i, h, bit[i], arrived)
             now = h + 1
             for i in range(W):
                 g = w * W + i + (h // 2) * S
                 if g >= groups:
                     continue
                 lo = 16 * g + 8 * (h % 2)
+                began = bit[i]
                 for p in range(lo, min(lo + 8, raw_bytes)):
                     if tans:
                         out[p], k = table[state[i]]
@@ -235,6 +282,8 @@ def parse_and_decode(payload: bytes, raw_bytes: int, S: int, tans: bool = False,
                             out[p] = book[(l, c)]
                             break
                         assert l < 15, "no code matched"
+                if rings:
+                    rings[w * W + i].use(began, bit[i])
         assert not any(state), "a tANS stream does not end in state 0"
         for i in range(W):
             assert len(data[i]) == 16 * nb[w * W + i], "blocks left unplaced"

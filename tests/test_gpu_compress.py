@@ -139,6 +139,47 @@ def test_device_compress_raw_fraction_is_the_oracles_selection(f):
     check_equal_to_oracle(data, C, S, oc.RAW_FRACTION, f=f)
 
 
+@pytest.mark.parametrize("f", [0.2, 0.5, 0.9])
+def test_device_compress_raw_fraction_with_equal_gains_over_many_tiles(f):
+    """More chunks than the layout kernel looks at in one pass (4096): chunks of equal gain lie on both sides of the passes'
+    edges, and which of them stay raw depends on how many came before."""
+    C, S, n_chunks = 256, 32, 9000
+    print(f"case dev compress raw fraction over tiles f={f}", flush=True)
+    r = np.random.default_rng(23)
+    kinds = np.stack([np.zeros(C, np.uint8), r.integers(0, 256, C, dtype=np.uint8), np.tile(np.array([1, 2, 3, 4], np.uint8), C // 4)])
+    data = kinds[r.integers(0, 3, n_chunks)].reshape(-1)
+    check_equal_to_oracle(np.concatenate([data, data[:77]]), C, S, oc.RAW_FRACTION, f=f)
+
+
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.HUFFMAN), (128, oc.HUFFMAN), (256, oc.HUFFMAN), (64, oc.TANS),
+                                     (128, oc.TANS), (256, oc.TANS)])
+@pytest.mark.parametrize("C", [8192, 16384])
+def test_device_blob_of_many_small_chunks_equals_the_oracles_at_every_run(S, codec, C):
+    """2050 chunks of one shape, many of them on every compute unit at once, compressed several times into buffers that held
+    something else before: the oracle's bytes every time."""
+    print(f"case dev compress many chunks S={S} codec={codec} C={C}", flush=True)
+    q, _ = oracle_matrix(2050, C, synth.matrix_seed(3, 1), False)
+    c = oc.compress(q, C, S, oc.AUTO, threads=8, codec=codec)
+    p = dc.Params(C, S, dc.POLICY_AUTO, codec=codec)
+    st = torch.cuda.current_stream().cuda_stream
+    src = torch.from_numpy(q).cuda().view(torch.uint8).reshape(-1)
+    want_blob, want_table = torch.from_numpy(c.blob).cuda(), torch.from_numpy(c.table.view(np.uint8).reshape(-1)).cuda()
+    cap, nc = dc.compress_bound(q.size, p)
+    ws_bytes = dc.compress_chunks_dev_workspace(q.size, p)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    blob, table = torch.empty(cap, dtype=torch.uint8, device="cuda"), torch.empty(16 * nc, dtype=torch.uint8, device="cuda")
+    res = torch.zeros(2, dtype=torch.int64, device="cuda")
+    for fill in (0x00, 0xFF, 0xA5, 0x5A):
+        for t in (ws, blob, table):
+            t.fill_(fill)
+        dc.compress_chunks_dev(src, q.size, p, blob, cap, table, nc, ws, ws_bytes, res, st)
+        torch.cuda.synchronize()
+        assert res.tolist() == [c.blob.size, 0]
+        assert torch.equal(table, want_table), fill
+        wrong = torch.nonzero(blob[:c.blob.size] != want_blob).flatten()
+        assert not len(wrong), (fill, len(wrong), int(np.searchsorted(c.table["off"], int(wrong[0]), side="right")) - 1)
+
+
 @pytest.mark.parametrize("S", [32, 256])
 def test_largest_chunk_size_both_ways(S):
     """1 MiB chunks (the largest the format allows): device compression equals the oracle's, device decode

@@ -548,6 +548,88 @@ def test_gemv_results_over_the_workspace(S):
     assert np.array_equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.TANS), (256, oc.HUFFMAN)])
+@pytest.mark.parametrize("over", ["nothing", "row scales", "another matrix's x", "the table", "bf16 over x"])
+def test_layer_call_of_matrices_of_whole_rows(S, codec, over):
+    """Three matrices whose chunks hold whole rows in one call, with results apart from everything that is read (one launch),
+    or over row scales, another matrix's activations or the chunk table: the same bits, and (S >= 64, a chunk to a workgroup)
+    those of three calls with one matrix each.  With int8 activations the fp32 results of the call over three launches are zeroed first, so there only bf16 results may lie
+    over an input."""
+    C, shapes = 16384, [(32, 512), (37, 1024), (30, 256)]
+    print(f"case whole rows layer S={S} codec={codec} over={over}", flush=True)
+    p = dc.Params(C, S, codec=codec)
+    qs, scales, tables, blobs, off = [], [], [], [], 0
+    for i, (rows, cols) in enumerate(shapes):
+        q, scale = oracle_matrix(rows, cols, synth.matrix_seed(7, i), False)
+        if S == 32 and C // cols > 32:  # a lane a row: not more than 32 rows to a chunk
+            q, scale, shapes[i] = q[:, :cols].reshape(rows // 2, 2 * cols), scale[:rows // 2], (rows // 2, 2 * cols)
+        c = oc.compress(q, C, S, codec=codec)
+        t = c.table.copy()
+        t["off"] += off
+        off += c.blob.size
+        qs.append(q), scales.append(scale), tables.append(t), blobs.append(c.blob)
+    blob_d = dev(np.concatenate(blobs))
+    for int8 in (False, True):
+        if int8 and over not in ("nothing", "bf16 over x"):
+            continue
+        xs = [synth.gen_activation_bf16(cols, i) for i, (_, cols) in enumerate(shapes)]
+        xq = [oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32)) for x in xs]
+
+        def inputs():
+            x_d = [torch.from_numpy(v[0]).cuda() if int8 else torch.from_numpy(x.view(np.int16)).cuda() for v, x in zip(xq, xs)]
+            return x_d, [torch.from_numpy(s.copy()).cuda() for s in scales], dev(np.concatenate(tables))
+
+        def results():
+            return ([torch.full((r,), 7.0, dtype=torch.float32, device="cuda") for r, _ in shapes],
+                    [torch.zeros(r, dtype=torch.int16, device="cuda") for r, _ in shapes])
+
+        def call(which, x_d, s_d, table_d, y32, y16):
+            k, mats = 0, []
+            first = sum(len(t) for t in tables[:which[0]])
+            for i in which:
+                r, cols = shapes[i]
+                x = dict(x_i8_dev=x_d[i], x_scale=float(xq[i][1])) if int8 else dict(x_bf16_dev=x_d[i])
+                mats.append(dc.Matrix(k, r, cols, s_d[i], y_accum_dev=y32[i], y_bf16_dev=y16[i], **x))
+                k += len(tables[i])
+            args = (blob_d, blob_d.numel(), table_d[16 * first:], k, p, mats)
+            if int8:
+                dc.decompress_gemv_w8a8_layer(*args, stream())
+            else:
+                dc.decompress_gemv_layer(*args, *gemv_workspace(k), stream())
+            torch.cuda.synchronize()
+
+        want32, want16 = results()
+        call([0, 1, 2], *inputs(), want32, want16)
+        for i in range(3):
+            if int8:
+                y_ref = oq.gemv_w8a8(qs[i], scales[i], *xq[i])
+                assert np.array_equal(want32[i].cpu().numpy().view(np.uint32), y_ref.view(np.uint32))
+            else:
+                gemv_check(want32[i].cpu().numpy(), oq.gemv_ref(qs[i], scales[i], xs[i]))
+            assert np.array_equal(want16[i].cpu().numpy().view(np.uint16), oq.bf16_round(want32[i].cpu().numpy()))
+        x_d, s_d, table_d = inputs()
+        y32, y16 = results()
+        if over == "row scales":
+            y32 = s_d
+        elif over == "another matrix's x":
+            y32[0] = x_d[1].view(torch.float32)[:shapes[0][0]]
+        elif over == "the table":
+            table_d = torch.cat([table_d, torch.zeros(256, dtype=torch.uint8, device="cuda")])
+            y32[0] = table_d.view(torch.float32)[:shapes[0][0]]
+        elif over == "bf16 over x":
+            y16[2] = x_d[1].view(torch.int16)[:shapes[2][0]]
+        if over == "nothing":
+            for i in range(3):
+                call([i], x_d, s_d, table_d, y32, y16)
+        else:
+            call([0, 1, 2], x_d, s_d, table_d, y32, y16)
+        for i in range(3):
+            if S == 32 and over == "nothing" and not int8:
+                continue  # other chunks share a wavefront in calls with one matrix: the sums are the same but for their order
+            assert torch.equal(y32[i].view(torch.int32), want32[i].view(torch.int32)), (int8, i)
+            assert torch.equal(y16[i], want16[i]), (int8, i)
+
+
 def test_gemv_w8a8_whole_layer_call_and_argument_checks():
     C, S = 16384, 256
     shapes = [(96, 1024), (40, 2752), (33, 5120)]

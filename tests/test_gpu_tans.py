@@ -6,7 +6,7 @@ import pytest
 
 import oracle.codec as oc
 import paper_2502_15443_amd as dc
-from tests.helpers import gemv_workspace, lopsided_bytes, weightlike_bytes
+from tests.helpers import gemv_workspace, lopsided_bytes, stalling_bytes, weightlike_bytes
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -60,6 +60,16 @@ def test_decode_degenerate_chunks(S):
     for policy in (oc.ALL_HUFF, oc.AUTO):
         c = oc.compress(data, C, S, policy, codec=oc.TANS)
         assert np.array_equal(gpu_decode(c.blob, c.table, tans(C, S), data.size), data)
+
+
+@pytest.mark.parametrize("S", [64, 128, 256])
+def test_decode_streams_that_stand_still(S):
+    """Positions that rest in the last bits of a block while the block four further on takes its place in the ring."""
+    print(f"case tans stalling S={S}", flush=True)
+    C = 65536
+    data = stalling_bytes(5 * C, S, S)
+    c = oc.compress(data, C, S, codec=oc.TANS)
+    assert np.array_equal(gpu_decode(c.blob, c.table, tans(C, S), data.size), data)
 
 
 @pytest.mark.parametrize("S", [64, 128, 256])

@@ -496,8 +496,8 @@ def test_layer_sizes_of_the_papers_speed_table():
 @pytest.mark.parametrize("codec", [oc.HUFFMAN, oc.TANS])
 @pytest.mark.parametrize("raw,S", [(65536, 64), (40000, 128), (65536, 256), (5000, 64)])
 def test_the_rule_covers_two_steps_of_flight_for_a_block(raw, S, codec):
-    """What a decoder may rely on that receives a block two steps after the step that took it (the device
-    kernel does): the independent decoder checks, at every half group of every stream, that 215 bits beyond
+    """What a decoder may rely on that receives a block two steps after the step that took it and refills as it
+    goes: the independent decoder checks, at every half group of every stream, that 215 bits beyond
     the position lie in blocks taken at least two steps before (88 bits the half group can use, 96 a decoder
     holds in registers beyond them, 31 of rounding to words), or that the stream's blocks are all there.
     Streams of the longest codes are the hard case; with three steps of flight the same check fails on them,
@@ -513,3 +513,29 @@ def test_the_rule_covers_two_steps_of_flight_for_a_block(raw, S, codec):
         payload = oc.encode_chunk(lopsided_bytes(raw, S, raw + S), S, codec=codec).tobytes()
         with pytest.raises(AssertionError):
             pyref.parse_and_decode(payload, raw, S, tans=tans, flight=3)
+
+
+@pytest.mark.parametrize("codec", [oc.HUFFMAN, oc.TANS])
+@pytest.mark.parametrize("raw,S", [(65536, 64), (40000, 128), (65536, 256), (16384, 32)])
+def test_the_rule_suits_the_decode_kernels_ring(raw, S, codec):
+    """What the decode kernel relies on.  It reads the words of a half group before the step that precedes it, when the blocks
+    taken three steps earlier or before are in the ring: 88 bits beyond the position, all that half a group can use, lie in
+    those, or the stream's blocks are all there (a step more fails with tANS, two with the codes of these inputs).  And its ring of 16 words in which block b + 4 takes
+    the place of block b two steps after it was taken: every word with bits of the half group is in its register, also where
+    a tANS position rests in the last bits of a block whose place has been taken (a register has held that word since)."""
+    from tests.helpers import lopsided_bytes, stalling_bytes, weightlike_bytes
+    tans = codec == oc.TANS
+    if tans and S == 32:
+        pytest.skip("the tANS payload needs at least 64 sub-streams")
+    kept = 0
+    for data in (lopsided_bytes(raw, S, raw + S), weightlike_bytes(raw, 5), stalling_bytes(raw, S, S),
+                 np.random.default_rng(raw).integers(0, 256, raw, dtype=np.uint8)):
+        payload = oc.encode_chunk(data, S, codec=codec).tobytes()
+        rings = [pyref.Ring(tans) for _ in range(S)]
+        assert pyref.parse_and_decode(payload, raw, S, tans=tans, flight=3, need=88, rings=rings) == data.tobytes()
+        kept += sum(r.kept for r in rings)
+    assert bool(kept) == tans  # 24 Huffman codes take the position out of the block
+    if raw >= 40000:
+        payload = oc.encode_chunk(lopsided_bytes(raw, S, raw + S), S, codec=codec).tobytes()
+        with pytest.raises(AssertionError):
+            pyref.parse_and_decode(payload, raw, S, tans=tans, flight=4 if tans else 5, need=88)
