@@ -397,7 +397,6 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     __shared__ uint32_t cumq[256];     // first place | frequency << 16
     __shared__ uint2 step_of[256];     // what a symbol does to X (see below)
     __shared__ uint32_t wave_sum[4];
-    __shared__ uint32_t sbits[256];
     __shared__ uint32_t area_bytes[4];
     uint16_t *marks = reinterpret_cast<uint16_t *>(arena);
     uint16_t *state_of = reinterpret_cast<uint16_t *>(arena + 1024); // 2048 + the state of value v numbered q + i at cum[v] + i
@@ -408,7 +407,6 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     const uint8_t *src = a.src + k * a.chunk_bytes;
     const uint32_t S = a.S;
 
-    sbits[t] = 0;
     if (t < 4) area_bytes[t] = 0;
     chunk_histogram(src, raw, arena, hist);
 
