@@ -49,7 +49,7 @@
  *                        coded payload when it changes: DC_LOOKAHEAD_BITS and the five times of step 0
  *                        (how far ahead of its position a stream's blocks are placed: the kernel
  *                        keeps a block in flight for two steps), steps of half a group of 8 symbols
- *                        (the kernel's unit between two refills of its ring), DC_BLOCK_BYTES (one
+ *                        (what the kernel decodes between two reads of its ring), DC_BLOCK_BYTES (one
  *                        128-bit load) and stream sets of 64 (one wavefront).  Earlier formats
  *                        (look-ahead 320, sub-streams padded to whole blocks, no trailer) had none
  *                        of this written into the blob; a blob without the trailer of this format

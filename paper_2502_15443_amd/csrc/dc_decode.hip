@@ -7,18 +7,19 @@
 // Work decomposition: a lane owns one sub-stream, a wavefront owns one stream set (64 sub-streams
 // whose 16-byte blocks are stored interleaved in the order the wavefront asks for them), a workgroup
 // owns one chunk (S/64 wavefronts; with S = 32 one wavefront owns two chunks, lanes 0-31 / 32-63).
-// Per chunk the LDS holds the decode table (2048 x u16: symbol << 8 | length - 1, indexed by the next
+// Per chunk the LDS holds the decode table (2048 x u16: symbol << 8 | length, indexed by the next
 // 11 stream bits).  Per wavefront the LDS holds a ring of 16 stream words per lane.  Before every
 // half group of 8 symbols the lanes that are short of look-ahead each take the next block of the
 // wavefront's region (consecutive lanes, consecutive blocks: one coalesced load, and the region is
 // read front to back exactly once); the block goes into the ring two steps later (the look-ahead of
-// DC_LOOKAHEAD_BITS bits in the format allows for it), so the per-symbol loop does not wait on memory.  A lane packs 16 decoded bytes and writes them with one 128-bit
-// store; the lanes of a chunk write S*16 contiguous bytes per round.
+// DC_LOOKAHEAD_BITS bits in the format allows for it), so the per-symbol loop does not wait on memory.  The four
+// words that hold a half group come out of the ring together and are only shifted from there on (decode8).  A lane
+// packs 16 decoded bytes and writes them with one 128-bit store; the lanes of a chunk write S*16 contiguous bytes per round.
 //
 // The container's second coder (tANS, 2048 states; Section 4.2 of the paper settles on ANS) runs through the
 // same kernel with another table and another symbol step: the table holds one 32-bit entry per state
 // (build_tans_table), the lane carries the state, and a symbol costs one table read and the state's field
-// of stream bits (tans_symbols).  Rings, block placement, refills, stores and the fused epilogues are shared.
+// of stream bits (two_symbols).  Rings, block placement, the words in registers, stores and the fused epilogues are shared.
 #include <hip/hip_runtime.h>
 
 #include "dc.h"
@@ -911,7 +912,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             col_b += round_bytes;
             while (col_b >= cols) { col_b -= cols; row_b++; }
         };
-        // the 16 values of a round, traded between the lanes, scaled and stored (CHECK: groups may be absent)
+        // the 16 values of a round, traded between the lanes, scaled and stored (has_a, has_b: whether the two groups exist)
         auto convert_and_store = [&](const uint32_t w[4], float s_a, float s_b, uint32_t r, bool has_a, bool has_b) {
             // rows of 16 lanes: the odd rows of the first operand change places with the even rows of the second
             const auto x02 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);

@@ -1007,7 +1007,7 @@ extern "C" int dc_compress_chunks_dev_workspace(uint64_t raw_bytes, const dc_par
     if (params->format != DC_FORMAT_ID) return DC_E_FORMAT;
     const uint64_t nc = (raw_bytes + params->chunk_bytes - 1) / params->chunk_bytes;
     *workspace_bytes = align256(nc * 256) + align256(nc * params->n_streams * 4) + align256(nc * 4);
-    // tANS: the frequencies, the first states and one 16-bit item per byte besides
+    // tANS: the frequencies, the first states and one 32-bit item per two bytes besides
     if (params->codec == DC_CODEC_TANS)
         *workspace_bytes += align256(nc * 512) + align256(nc * params->n_streams * 2) + align256(nc * params->chunk_bytes * 2);
     return DC_OK;

@@ -75,7 +75,7 @@ def stalling_bytes(n: int, S: int, seed: int) -> np.ndarray:
 
 
 def empty_buffer_before_three_codes(data: np.ndarray, S: int):
-    """Walk of a decoder that keeps a 64-bit buffer per sub-stream, refills it by 32 bits whenever at most 32
+    """Walk of a decoder (not the present kernel) that keeps a 64-bit buffer per sub-stream, refills it by 32 bits whenever at most 32
     bits are valid, and decodes each half group of 8 symbols as 3 + 2 + 3 codes: the places (lane, group,
     half, first symbol of the batch) where a batch of three 11-bit codes (33 bits) begins on a buffer that the
     batch before it emptied completely, so that one refill leaves 32 bits.  Code lengths from the oracle."""

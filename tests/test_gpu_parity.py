@@ -93,10 +93,11 @@ def test_decode_block_last_policy():
 
 @pytest.mark.parametrize("S", [32, 64])
 def test_three_longest_codes_on_a_buffer_that_was_just_emptied(S):
-    """Three 11-bit codes need 33 bits, one refill of an empty bit buffer gives 32: the decoder must take a
-    second word there.  The input is built so that this happens (checked by a walk over the code lengths);
-    every decode mode must still give the oracle's result.  Found by a random sweep: one such case in
-    about ten thousand chunks of weight-like data."""
+    """Three 11-bit codes need 33 bits, one refill of an empty bit buffer gives 32: a decoder that refills a buffer must take a
+    second word there.  The kernel did so once and got this wrong (a random sweep found it: one such case in about ten thousand
+    chunks of weight-like data); it reads the four words of a half group at once now and has no buffer to empty.  The input,
+    built so that the case occurs (checked by a walk over the code lengths), stays for what it holds besides: one stream of
+    the longest codes among streams of the shortest.  Every decode mode must give the oracle's result."""
     from tests.helpers import emptied_buffer_bytes, empty_buffer_before_three_codes
     data = emptied_buffer_bytes(S)
     assert empty_buffer_before_three_codes(data, S)
