@@ -637,9 +637,9 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     // ---- ordered product: the same for the sums that the chunk leaves in the workspace.  One for every row that the chunk's
     // place in the matrix touches, whatever its table entry says, because the finish kernel adds them all up.
     auto leave_partial_sums = [&](float sum) {
-        const uint64_t last_row = (dst_pos + a.chunk_bytes - 1) / mat.cols; // or the matrix's last, if that comes first
-        const uint32_t row = (uint32_t)(dst_pos / mat.cols) + cl;
-        if (k < a.n_chunks && wave == 0 && row <= last_row && row < mat.rows) a.partial[k * kPartialSlots + cl] = sum;
+        const uint64_t end = dst_pos + a.chunk_bytes < dst_cap ? dst_pos + a.chunk_bytes : dst_cap;
+        if (k < a.n_chunks && wave == 0 && cl <= (uint32_t)((end - 1) / mat.cols) - (uint32_t)(dst_pos / mat.cols))
+            a.partial[k * kPartialSlots + cl] = sum;
     };
     // A chunk that is not decoded leaves empty sums, or their results.
     auto finish_empty = [&]() {
