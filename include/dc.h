@@ -425,7 +425,8 @@ int dc_decompress_dequant_bf16(const uint8_t *blob_dev, uint64_t blob_bytes, con
  * Two launches: the decode kernel leaves in the workspace one partial sum per chunk and row the chunk
  * touches, added up inside the chunk in a fixed order, and a second kernel adds a row's partial sums in
  * chunk order and scales them.  One launch, with the same bits, if cols divides chunk_bytes (no row reaches
- * into a second chunk) and no result lies over an input.  No atomic operation is involved, so a call returns
+ * into a second chunk) and no result lies over an input or the workspace.  A chunk that is not decoded adds
+ * nothing to its rows.  No atomic operation is involved, so a call returns
  * the same bits every time it runs on the same input.  That holds while a chunk touches at most
  * min(n_streams, 64) rows (chunk_bytes / cols rows if cols divides chunk_bytes, else ceil(chunk_bytes / cols) + 1); for
  * flatter matrices the call falls back to three launches that add with fp32 atomics on y_f32_dev (the
