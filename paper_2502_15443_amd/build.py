@@ -44,7 +44,7 @@ def loop_mix(asm_text: str) -> dict:
     "cycles_per_instruction": c, "lookups": symbols a turn}}."""
     out = {}
     for mode, label in ((0, "int8"), (1, "bf16"), (2, "gemv")):
-        m = re.search(r"^(_ZN\S*dc_decode_kernelILi256ELi%dELi0ELb0E\S*):" % mode, asm_text, re.M)
+        m = re.search(r"^(_ZN\S*dc_decode_kernelILi256ELi%dELi0ELb0ELb0E\S*):" % mode, asm_text, re.M)
         if not m:
             continue
         body = asm_text[m.start():asm_text.index(".Lfunc_end", m.start())].split("\n")

@@ -13,7 +13,8 @@
 // wavefront's region (consecutive lanes, consecutive blocks: one coalesced load, and the region is
 // read front to back exactly once); the block goes into the ring two steps later (the look-ahead of
 // DC_LOOKAHEAD_BITS bits in the format allows for it), so the per-symbol loop does not wait on memory.  The four
-// words that hold a half group come out of the ring together and are only shifted from there on (decode8).  A lane
+// words that hold a half group come out of the ring together and are only shifted from there on (decode8; where a launch has
+// about one wavefront to a SIMD, step_and_decode8_few, which arranges the same work around the chain of look-ups).  A lane
 // packs 16 decoded bytes and writes them with one 128-bit store; the lanes of a chunk write S*16 contiguous bytes per round.
 //
 // The container's second coder (tANS, 2048 states; Section 4.2 of the paper settles on ANS) runs through the
@@ -159,12 +160,25 @@ template <bool HALVES, typename T> __device__ __forceinline__ void lanes_add_run
 // stand, and bits 10-11 of a block count the slot of the block's first word.
 // Huffman positions are kept one bit early (kLead): a window that begins there is "the next 11 bits, times 2" under a
 // mask, which is the byte offset of the table entry, so a look-up needs no shift of its own.
+// FEW: launches of few wavefronts (step_and_decode8_few).  A wave's 4 KiB of ring are followed by 4 KiB that hold the ring's first
+// four words again, so that words behind one another in the stream can be read without a wrap, and four words for blocks that are
+// nobody's.  With four waves to a chunk the LDS is busy enough for the second copy to cost more than it saves (4096 x 4096 at
+// 256 sub-streams 14.3 instead of 13.7 us; at 32, 64 and 128 it saves 3 %).
+template <int S, bool FEW> struct Ring {
+    static constexpr int kStride = FEW ? 2048 : kRingWords * 64; // words of LDS a wave
+    static constexpr bool kAgain = FEW && S < 256;
+    static constexpr uint32_t kAgainAt = 4096, kNowhereAt = 5120; // bytes from the ring's start
+};
+
 template <int CODEC> struct Lead { static constexpr uint32_t kBits = CODEC == DC_CODEC_TANS ? 0 : 1; };
 struct Stream {
     uint32_t pos;     // 8 * (position in bits - kLead)
     uint32_t asked;   // 1024 * (blocks asked for so far, f of the placement rule)
     uint32_t end;     // 1024 * (blocks of the stream)
-    uint32_t r[4];    // the words at the position and behind it: all a half group can need
+    uint32_t r[4];    // the words at the position and behind it: all a half group can need (FEW: three, shifted to begin at it)
+    uint32_t next;    // FEW: the table entry of the symbol at the position
+    uint32_t nowhere; // FEW: the ring place of a block that is not the stream's
+    uint32_t again[2]; // FEW: where blk[p] goes a second time
     uint32_t x4;      // tANS: 4 * state = byte offset of the state's table entry
     u32x4 blk[2];     // a block travels for two steps: asked for at step h, put into the ring at step h + 2
     uint32_t slot[2]; // where in the ring blk[p] goes
@@ -249,6 +263,19 @@ __device__ __forceinline__ void stream_step(Stream &s, Region &rg, uint32_t ring
     if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
 }
 
+// The table entry of the symbol that follows the first `by` bits of w (Huffman).
+__device__ __forceinline__ uint32_t look_up(uint32_t w, uint32_t by, uint32_t tbl)
+{
+    return lds_load16(tbl + ((w >> (by & 31u)) & (2 * kTableEntries - 2)));
+}
+
+// N words, and word N behind them, shifted down by `by` < 32 bits.
+template <int N> __device__ __forceinline__ void shift_down(uint32_t *w, uint32_t by)
+{
+#pragma unroll
+    for (int i = 0; i < N; i++) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], by);
+}
+
 // Start of a sub-stream.  Block 0 of a stream is short: its first pad = 16 - hb bytes do not exist and
 // its hb bytes lie among the heads, which follow the whole blocks of the set in lane order.  The lane
 // loads the 20 bytes from the 4-byte boundary at or before the place where block 0 would start and
@@ -315,18 +342,31 @@ __device__ __forceinline__ void stream_fetch(Stream &s, Region &rg, uint32_t fie
 
 // Second half: block 0 shifted into place and the further blocks go into the ring, and the first words are read.
 // A tANS stream reads its first state, its first 11 bits, and the words after them.
-template <int CODEC> __device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, uint32_t ring_lane)
+template <int CODEC, int S, bool FEW>
+__device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, uint32_t ring_lane, uint32_t tbl)
 {
+    using R = Ring<S, FEW>;
     if (f.has_head) {
         const u32x4 b0 = {__builtin_amdgcn_alignbyte(f.v[1], f.v[0], f.shift), __builtin_amdgcn_alignbyte(f.v[2], f.v[1], f.shift),
                           __builtin_amdgcn_alignbyte(f.v[3], f.v[2], f.shift), __builtin_amdgcn_alignbyte(f.v4, f.v[3], f.shift)};
         push_block(ring_lane, b0);
+        if (R::kAgain) push_block(ring_lane + R::kAgainAt, b0);
     }
 #pragma unroll
     for (int t = 0; t < 3; t++)
         if (f.got[t]) push_block(ring_lane + ((t + 1) << 10), f.b[t]);
     s.pos = 64u * f.pad - 8u * Lead<CODEC>::kBits; // the stream begins `pad` bytes into block 0
     read_window<false>(s, 0, ring_lane);
+    if (FEW) {
+        s.nowhere = ring_lane + R::kNowhereAt;
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            s.slot[p] = s.again[p] = s.nowhere;
+            s.blk[p] = u32x4{0, 0, 0, 0};
+        }
+        shift_down<3>(s.r, s.pos >> 3);
+        s.next = look_up(s.r[0], 0, tbl);
+    }
     s.x4 = 0;
     if (CODEC == DC_CODEC_TANS) {
         const uint32_t before = s.pos;
@@ -393,19 +433,132 @@ __device__ __forceinline__ void decode8(Stream &s, uint32_t tbl, uint32_t ring_l
     read_window<CODEC == DC_CODEC_TANS>(s, before, ring_lane);
 }
 
-// One whole group of 16 symbols with the two steps of the placement rule that precede its halves.
-template <bool UNIFORM, int CODEC = DC_CODEC_HUFFMAN>
-__device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t out[4])
+// Work of the caller that half a group's look-ups can hide: early() while the second entry is on its way, late(0) and late(1)
+// while the fifth and sixth are.
+struct Nothing {
+    __device__ __forceinline__ void early() const {}
+    __device__ __forceinline__ void late(int) const {}
+};
+template <typename F> struct Early {
+    F early;
+    __device__ __forceinline__ void late(int) const {}
+};
+template <typename F> struct Late {
+    F late;
+    __device__ __forceinline__ void early() const {}
+};
+template <typename F> __device__ __forceinline__ Early<F> early(F f) { return {f}; }
+template <typename F> __device__ __forceinline__ Late<F> late(F f) { return {f}; }
+
+// FEW: a step of the placement rule and half a group for launches that have one or two wavefronts to a SIMD (Huffman).  Such a wave has
+// nothing but its own instructions to fill the time that a look-up takes, 27 ns of the 33 that a link of the chain (read, shift, mask)
+// takes by itself; with the step, then the half group, then the next words one after the other a link took 43 ns.  So the order
+// is fixed here: the next look-up is asked for as soon as an entry has come, and everything that does not decide it stands behind
+// it.  The words of the next half group are read when 6 of the 8 symbols are known, and its first look-up ends this one; a
+// block goes into the ring without a branch, to a place of its own if the lane asked for none, so that all of it is one
+// block of code.  77 instead of 94 us for 256 chunks of 64 KiB at 32 sub-streams, 39 instead of 47 at 64.
+// Reading at the 7th symbol and not at the 9th leaves what stream_step says of the ring as it is: no step lies between, so what has been
+// put into the ring is the same, the bits needed end where they did, and the position is still 22 codes beyond the one at which
+// the youngest block in the ring was asked for, 22 bits at least, the lead among them, and so past block b - 4.
+template <bool UNIFORM, int P, bool AGAIN, typename Meanwhile>
+__device__ __forceinline__ void step_and_decode8_few(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t e[8], Meanwhile meanwhile)
 {
-    uint32_t e[8];
-    stream_step<UNIFORM, 0, CODEC>(s, rg, ring_lane);
-    decode8<CODEC>(s, tbl, ring_lane, e);
-    out[0] = pack4(e[0], e[1], e[2], e[3]);
-    out[1] = pack4(e[4], e[5], e[6], e[7]);
-    stream_step<UNIFORM, 1, CODEC>(s, rg, ring_lane);
-    decode8<CODEC>(s, tbl, ring_lane, e);
-    out[2] = pack4(e[0], e[1], e[2], e[3]);
-    out[3] = pack4(e[4], e[5], e[6], e[7]);
+    uint32_t w[4] = {s.r[0], s.r[1], s.r[2], 0};
+    e[0] = s.next;
+    keep_order();
+    e[1] = look_up(w[0], e[0], tbl);
+    keep_order();
+    shift_down<3>(w, e[0]);
+    push_block(s.slot[P], s.blk[P]);
+    if (AGAIN) push_block(s.again[P], s.blk[P]);
+    keep_order();
+    meanwhile.early();
+    keep_order();
+    e[2] = look_up(w[0], e[1], tbl);
+    keep_order();
+    shift_down<3>(w, e[1]);
+    const uint32_t bound = s.pos + 8u * (DC_LOOKAHEAD_BITS + Lead<DC_CODEC_HUFFMAN>::kBits);
+    const bool want = s.asked < (bound < s.end ? bound : s.end);
+    const uint64_t m = UNIFORM ? __ballot(want) : __ballot(want) & rg.lanes;
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    keep_order();
+    e[3] = look_up(w[0], e[2], tbl);
+    keep_order();
+    shift_down<2>(w, e[2]); // from here on two words hold what may still be needed, one after the sixth symbol
+    s.blk[P] = *reinterpret_cast<const u32x4 *>(rg.payload8 + (rg.next_block + rank) * kBlockBytes);
+    s.slot[P] = want ? (s.asked & 0xC00u) | ring_lane : s.nowhere;
+    if (AGAIN) s.again[P] = s.slot[P] == ring_lane ? ring_lane + Ring<64, true>::kAgainAt : s.nowhere;
+    s.asked += want ? 1024u : 0u;
+    rg.next_block += (uint32_t)__popcll(m);
+    if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
+    keep_order();
+    e[4] = look_up(w[0], e[3], tbl);
+    keep_order();
+    shift_down<2>(w, e[3]);
+    meanwhile.late(0);
+    keep_order();
+    e[5] = look_up(w[0], e[4], tbl);
+    keep_order();
+    w[2] = 0;
+    shift_down<2>(w, e[4]);
+    meanwhile.late(1);
+    keep_order();
+    e[6] = look_up(w[0], e[5], tbl);
+    keep_order();
+    shift_down<1>(w, e[5]);
+    s.pos += ((e[0] + e[1] + e[2] + e[3] + e[4] + e[5]) & 0xFFu) << 3;
+    uint32_t v[5]; // from 31 bits before the position to 129 behind it; two symbols and half a group may need 110, and the lead
+    const uint32_t at = (s.pos & 0xF00u) | ring_lane;
+#pragma unroll
+    for (uint32_t k = 0; k < 5; k++) v[k] = lds_load32(AGAIN ? at + 256u * k : ((s.pos + 256u * k) & 0xF00u) | ring_lane);
+    keep_order();
+    e[7] = look_up(w[0], e[6], tbl);
+    keep_order();
+    shift_down<4>(v, s.pos >> 3);
+    v[4] = 0;
+    shift_down<4>(v, e[6]);
+    keep_order();
+    s.next = look_up(v[0], e[7], tbl);
+    keep_order();
+    shift_down<3>(v, e[7]);
+#pragma unroll
+    for (int i = 0; i < 3; i++) s.r[i] = v[i];
+    s.pos += ((e[6] + e[7]) & 0xFFu) << 3;
+}
+
+// A step of the placement rule and the half group behind it.
+template <int S, int P, int CODEC, bool FEW, typename Meanwhile = Nothing>
+__device__ __forceinline__ void step_and_decode8(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t e[8],
+                                                 Meanwhile meanwhile = Meanwhile())
+{
+    constexpr bool UNIFORM = S >= 64;
+    if constexpr (FEW) {
+        step_and_decode8_few<UNIFORM, P, Ring<S, FEW>::kAgain>(s, rg, tbl, ring_lane, e, meanwhile);
+    } else {
+        stream_step<UNIFORM, P, CODEC>(s, rg, ring_lane);
+        decode8<CODEC>(s, tbl, ring_lane, e);
+    }
+}
+
+// One whole group of 16 symbols with the two steps of the placement rule that precede its halves.
+template <int S, int CODEC, bool FEW, typename Meanwhile = Nothing>
+__device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t out[4],
+                                         Meanwhile meanwhile = Meanwhile())
+{
+    uint32_t e[8], f[8];
+    step_and_decode8<S, 0, CODEC, FEW>(s, rg, tbl, ring_lane, e, meanwhile);
+    if constexpr (FEW) {
+        step_and_decode8<S, 1, CODEC, FEW>(s, rg, tbl, ring_lane, f, late([&](int i) {
+            out[i] = pack4(e[4 * i], e[4 * i + 1], e[4 * i + 2], e[4 * i + 3]);
+            in_register<false>(out[i]);
+        }));
+    } else {
+        out[0] = pack4(e[0], e[1], e[2], e[3]);
+        out[1] = pack4(e[4], e[5], e[6], e[7]);
+        step_and_decode8<S, 1, CODEC, FEW>(s, rg, tbl, ring_lane, f);
+    }
+    out[2] = pack4(f[0], f[1], f[2], f[3]);
+    out[3] = pack4(f[4], f[5], f[6], f[7]);
 }
 
 __device__ __forceinline__ uint32_t bf16x2(float a, float b)
@@ -550,7 +703,7 @@ __device__ __forceinline__ void store_row(const MatrixArgs &m, uint32_t row, flo
     if (m.y_bf16) m.y_bf16[row] = (uint16_t)(bf16x2(y, 0.0f) & 0xFFFFu);
 }
 
-template <int S, int MODE, int CODEC, bool TRACE = false>
+template <int S, int MODE, int CODEC, bool FEW = false, bool TRACE = false>
 __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(DecodeArgs a)
 {
     using G = Geometry<S>;
@@ -573,6 +726,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     constexpr int TPC = G::kThreadsPerChunk;
     constexpr int SPL = G::kSymbolsPerLane;
     static_assert(CODEC == DC_CODEC_HUFFMAN || S >= 64, "tANS: the workgroup's threads are the chunk's");
+    static_assert(CODEC == DC_CODEC_HUFFMAN || !FEW, "tANS keeps the word its position lies in (see stream_step)");
     constexpr uint32_t kFront = CODEC == DC_CODEC_TANS ? 384 : 128; // code description at the start of a payload
     constexpr uint32_t kHeader = (kFront + 2 * S + 4 * (S / Geometry<S>::kLanesPerChunk) + 15) / 16 * 16;
 
@@ -580,10 +734,11 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     // the tables are built, before any ring is used, the front part holds the slot markers (one
     // u16 per table slot in code order, 4 KiB a chunk) and the start of the table part holds the
     // first codes of the lengths and the per-wave length counts.
-    constexpr int kFrontWords = (WAVES > CPW ? WAVES : CPW) * kRingWords * 64;
+    constexpr int kRingStride = Ring<S, FEW>::kStride;
+    constexpr int kFrontWords = FEW ? WAVES * kRingStride : (WAVES > CPW ? WAVES : CPW) * kRingStride;
     // (tANS: 2048 entries of 32 bits, then 256 words of (first place, frequency) and a word per wave)
     constexpr int kTableWords = CODEC == DC_CODEC_TANS ? kTableEntries + 256 + 16 : CPW * kTableEntries / 2;
-    __shared__ __attribute__((aligned(4096))) uint32_t lds_all[kFrontWords + kTableWords];
+    __shared__ __attribute__((aligned(4 * kRingStride))) uint32_t lds_all[kFrontWords + kTableWords];
     uint16_t(*lds_table)[kTableEntries] = reinterpret_cast<uint16_t(*)[kTableEntries]>(lds_all + kFrontWords);
     uint32_t(*lds_first)[16] = reinterpret_cast<uint32_t(*)[16]>(lds_all + kFrontWords); // [wave * CPW + sub][length]
     uint32_t(*lds_counts)[4] = reinterpret_cast<uint32_t(*)[4]>(lds_all + kFrontWords + 16 * WAVES * CPW); // [wave]
@@ -624,7 +779,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
 
     uint16_t *tbl = lds_table[sub];
     const uint32_t tbl_addr = lds_address(tbl);
-    const uint32_t ring_lane = lds_address(lds_all + wave * (kRingWords * 64) + lane);
+    const uint32_t ring_lane = lds_address(lds_all + wave * kRingStride + lane);
     constexpr bool UNI = CPW == 1; // all lanes of the wave belong to one stream set
 
     // ---- products of whole rows: the rows of the chunk, and what lane r of the chunk's first wave does with the sum of
@@ -853,7 +1008,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     }
 
     // ---- sub-stream set-up, second half: the ring is free now
-    if (huff) stream_start<CODEC>(st, sf, ring_lane);
+    if (huff) stream_start<CODEC, S, FEW>(st, sf, ring_lane, tbl_addr);
 
     const uint32_t round_bytes = 16 * S;
     const uint32_t full_rounds = raw / round_bytes;
@@ -863,7 +1018,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         uint8_t *d8 = static_cast<uint8_t *>(a.dst) + dst_pos + ct * 16;
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
             store16_stream(d8 + (size_t)r * round_bytes, w[0], w[1], w[2], w[3]);
         }
         if (rem) {
@@ -872,7 +1027,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             const uint32_t n = rem > start ? (rem - start < 16 ? rem - start : 16) : 0;
             uint8_t *d = d8 + (size_t)full_rounds * round_bytes;
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
             if (n == 16) {
                 store16_stream(d, w[0], w[1], w[2], w[3]);
             } else if (n) {
@@ -886,7 +1041,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     }
 
     // ---- fused consumers walk the matrix: group position -> (row, column)
-    const uint32_t cols = mat.cols;
+    const uint32_t cols = mat.cols, mat_rows = mat.rows;
     const uint32_t rounds = full_rounds + (rem ? 1 : 0);
     uint64_t pos = dst_pos + ct * 16;
     uint32_t row = (uint32_t)(pos / cols);
@@ -959,7 +1114,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         float s_a = scale_of(row_a), s_b = scale_of(row_b);
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, r, true, true);
             next_round();
             s_a = scale_of(row_a);
@@ -968,7 +1123,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         if (rem) {
             const uint32_t base = full_rounds * round_bytes;
             uint32_t w[4] = {0, 0, 0, 0};
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, full_rounds, raw >= base + ct_a * 16 + 16, raw >= base + ct_b * 16 + 16);
         }
         return;
@@ -995,12 +1150,12 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         using T = decltype(mine);
         T total = mine;
         if (WAVES > 1) {
-            lds_all[wave * (kRingWords * 64) + lane] = __builtin_bit_cast(uint32_t, mine);
+            lds_all[wave * kRingStride + lane] = __builtin_bit_cast(uint32_t, mine);
             __syncthreads();
             if (wave == 0) {
                 total = T(0);
 #pragma unroll
-                for (int v = 0; v < WAVES; v++) total += __builtin_bit_cast(T, lds_all[v * (kRingWords * 64) + lane]);
+                for (int v = 0; v < WAVES; v++) total += __builtin_bit_cast(T, lds_all[v * kRingStride + lane]);
             }
         }
         return total;
@@ -1015,11 +1170,15 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         // added in wave order through LDS and the chunk leaves one sum per row in the workspace.  Every
         // addition then has a fixed place in a fixed order, so the result is the same bits at every run.
         const uint32_t first_row = (uint32_t)(dst_pos / cols);
+        const uint16_t *x = mat.x_bf16;
+        in_register<UNI>(mat_rows);
+        in_register<UNI>(cols);
+        in_register<UNI>(x);
         float mine = 0.0f; // this wave's sum for row first_row + cl
         uint32_t cur_row = 0xFFFFFFFFu;
         float acc = 0.0f;
         auto flush = [&]() {
-            const uint32_t key = cur_row < mat.rows ? cur_row : 0xFFFFFFFFu;
+            const uint32_t key = cur_row < mat_rows ? cur_row : 0xFFFFFFFFu;
             if (MODE == kModeGemvAtomic) lanes_add_by_key<CPW == 2, float>(mat.y_accum, key, acc);
             else lanes_add_runs_to_slots<CPW == 2, float>(mine, key, (cur_row - first_row) % LPC + sub * LPC, acc);
             acc = 0.0f;
@@ -1042,26 +1201,36 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         };
         struct Sixteen { uint32_t x[8]; };
         auto load_x = [&]() -> Sixteen {
-            const uint4 *xp = reinterpret_cast<const uint4 *>(mat.x_bf16 + col); // col + 16 <= cols, group or not
+            const uint4 *xp = reinterpret_cast<const uint4 *>(x + col); // col + 16 <= cols, group or not
             const uint4 xa = xp[0], xb = xp[1];
             return {{xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w}};
         };
         auto coded_round = [&](bool whole) {
-            const Sixteen xs = load_x();
-            enter_row(whole);
+            Sixteen xs;
             uint32_t e[8];
-            auto products = [&](uint32_t half) {
+            auto products = [&](const uint32_t e[8], uint32_t half, int from, int to) {
                 if (whole)
 #pragma unroll
-                    for (int i = 0; i < 4; i++)
+                    for (int i = from; i < to; i++)
                         acc = dot2_bf16(bf16x2(byte_f32<1>(e[2 * i]), byte_f32<1>(e[2 * i + 1])), xs.x[4 * half + i], acc);
+                if (FEW) in_register<false>(acc);
             };
-            stream_step<UNI, 0, CODEC>(st, rg, ring_lane);
-            decode8<CODEC>(st, tbl_addr, ring_lane, e);
-            products(0);
-            stream_step<UNI, 1, CODEC>(st, rg, ring_lane);
-            decode8<CODEC>(st, tbl_addr, ring_lane, e);
-            products(1);
+            auto begin = [&]() {
+                xs = load_x();
+                enter_row(whole);
+            };
+            if constexpr (FEW) {
+                uint32_t f[8];
+                step_and_decode8<S, 0, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e, early(begin));
+                step_and_decode8<S, 1, CODEC, FEW>(st, rg, tbl_addr, ring_lane, f, late([&](int i) { products(e, 0, 2 * i, 2 * i + 2); }));
+                products(f, 1, 0, 4);
+            } else {
+                begin();
+                step_and_decode8<S, 0, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e);
+                products(e, 0, 0, 4);
+                step_and_decode8<S, 1, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e);
+                products(e, 1, 0, 4);
+            }
         };
         auto raw_round = [&](bool whole, const u32x4 &w) {
             const Sixteen xs = load_x();
@@ -1092,11 +1261,15 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         // The same walk with int8 activations (Eq. 4 of the paper): four v_dot4 per group, exact int32
         // sums, integer atomics (or the lanes' slots, see above), so the result does not depend on the order of the additions.
         const uint32_t first_row = (uint32_t)(dst_pos / cols);
+        const int8_t *x = mat.x_i8;
+        in_register<UNI>(mat_rows);
+        in_register<UNI>(cols);
+        in_register<UNI>(x);
         int32_t mine = 0;
         uint32_t cur_row = 0xFFFFFFFFu;
         int32_t acc = 0;
         auto flush = [&]() {
-            const uint32_t key = cur_row < mat.rows ? cur_row : 0xFFFFFFFFu;
+            const uint32_t key = cur_row < mat_rows ? cur_row : 0xFFFFFFFFu;
             if (MODE == kModeGemvW8A8) lanes_add_by_key<CPW == 2, int32_t>(reinterpret_cast<int32_t *>(mat.y_accum), key, acc);
             else lanes_add_runs_to_slots<CPW == 2, int32_t>(mine, key, (cur_row - first_row) % LPC + sub * LPC, acc);
             acc = 0;
@@ -1110,7 +1283,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
                 acc = __builtin_amdgcn_sdot4((int)w[3], (int)x.w, acc, false);
             }
         };
-        auto load_x = [&]() { return *reinterpret_cast<const uint4 *>(mat.x_i8 + col); };
+        auto load_x = [&]() { return *reinterpret_cast<const uint4 *>(x + col); };
         auto enter_row = [&](bool whole) {
             if (__any(whole && row != cur_row && cur_row != 0xFFFFFFFFu)) flush();
             cur_row = whole ? row : cur_row;
@@ -1118,17 +1291,25 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             while (col >= cols) { col -= cols; row++; }
         };
         auto coded_round = [&](bool whole) {
-            const uint4 x = load_x(); // asked for before the group is decoded
-            enter_row(whole);
+            uint4 xs;
             uint32_t w[4];
-            decode16<UNI, CODEC>(st, rg, tbl_addr, ring_lane, w);
-            add_products(whole, w, x);
+            auto begin = [&]() {
+                xs = load_x(); // asked for before the group is decoded
+                enter_row(whole);
+            };
+            if constexpr (FEW) {
+                decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w, early(begin));
+            } else {
+                begin();
+                decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+            }
+            add_products(whole, w, xs);
         };
         auto raw_round = [&](bool whole, const u32x4 &v) {
-            const uint4 x = load_x();
+            const uint4 xs = load_x();
             enter_row(whole);
             const uint32_t w[4] = {v[0], v[1], v[2], v[3]};
-            add_products(whole, w, x);
+            add_products(whole, w, xs);
         };
         const bool last_whole = raw >= full_rounds * round_bytes + ct * 16 + 16;
         if (huff) {
@@ -1371,7 +1552,13 @@ template <int S, int MODE> void launch_one(const DecodeArgs &a, hipStream_t stre
 {
     using G = Geometry<S>;
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
-    hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);
+    // Up to one wavefront a SIMD (1024 of them) a launch is as long as a lane's chain of look-ups, and FEW is 10 to 19 % shorter; at
+    // two it still is by 1 to 3 % from 64 sub-streams on and longer by 2 % at 32; at three, where the wavefronts hide each
+    // other's look-ups and the LDS is what they wait for, it is longer by 7 to 17 %.
+    if (grid * (uint64_t)G::kWaves <= (S < 64 ? 1024 : 2048))
+        hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
+    else
+        hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);
 }
 
 // tANS payloads: S >= 64, one chunk per workgroup
@@ -1448,7 +1635,7 @@ extern "C" int dc_decompress_chunks_traced(const uint8_t *blob_dev, uint64_t blo
     a.dst = dst_dev;
     a.dst_cap = dst_cap;
     a.trace = trace_dev;
-    hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, true>), dim3((uint32_t)n_chunks), dim3(256), 0,
+    hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, false, true>), dim3((uint32_t)n_chunks), dim3(256), 0,
                        static_cast<hipStream_t>(hip_stream), a);
     return launch_status();
 }

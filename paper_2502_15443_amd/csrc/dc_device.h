@@ -31,6 +31,24 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
 __device__ __forceinline__ uint32_t lds_load32(uint32_t addr) { return *(const lds_u32 *)(uintptr_t)addr; }
 __device__ __forceinline__ uint32_t lds_load16(uint32_t addr) { return *(const lds_u16 *)(uintptr_t)addr; }
 
+// The compiler moves no instruction across this place.
+__device__ __forceinline__ void keep_order()
+{
+#ifdef __AMDGCN__
+    __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// The value is in its register from here on (SAME: it is the same in all lanes, a scalar register): it is not worked out later, and
+// a loop behind this place does not wait for the load that it came from.
+template <bool SAME, typename T> __device__ __forceinline__ void in_register(const T &v)
+{
+#ifdef __AMDGCN__
+    if constexpr (SAME) asm volatile("" ::"s"(v));
+    else asm volatile("" ::"v"(v));
+#endif
+}
+
 // Value of another lane through the data-parallel primitives; lanes without a source (and rows that
 // the row mask leaves out) read 0.  0x110 + n: n lanes to the right inside a row of 16; 0x142 / 0x143:
 // lane 15 of a row to the next row / lane 31 to rows 2 and 3; 0x138: one lane to the right over

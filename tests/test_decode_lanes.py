@@ -58,3 +58,14 @@ def test_decoder_does_not_depend_on_the_order_of_the_lanes(decode, order, S, cod
     size = np.abs(q.astype(np.float64)) @ np.abs(oq.bf16_to_f64(x)) * scale
     y = run(PRODUCT, scale, x).view(np.float32)
     assert (np.abs(y - oq.gemv_ref(q, scale, x)) <= cols * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("S", [32, 64, 128, 256])
+def test_decoder_of_many_wavefronts(decode, S):
+    # just beyond the line up to which a launch has few wavefronts
+    C, cols = 512, 64
+    chunks = {32: 2050, 64: 2049, 128: 1025, 256: 513}[S]
+    q, _ = oracle_matrix(chunks * C // cols, cols, synth.matrix_seed(10, S), False)
+    c = oc.compress(q, C, S)
+    assert c.n_chunks == chunks
+    assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape), q.view(np.uint8).ravel())

@@ -691,3 +691,37 @@ def test_config1_full_size_bit_exact_and_ratio():
     assert q.size / (blob.size + table.nbytes) == c.ratio
     out = gpu_decode(blob, table, p, q.size)
     assert np.array_equal(out, q.view(np.uint8).ravel())
+
+
+@pytest.mark.parametrize("S", [32, 64, 128, 256])
+@pytest.mark.parametrize("more", [0, 1])
+def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, more):
+    # 1024 wavefronts at 32 sub-streams (two chunks each), 2048 otherwise, and one workgroup more; some chunks raw, the last one short
+    chunks = {32: 2048, 64: 2048, 128: 1024, 256: 512}[S] + more * (2 if S == 32 else 1)
+    C, cols = 4096, 2048
+    rows = 2 * chunks - 1
+    data = weightlike_bytes(rows * cols, 7 + S)
+    c = oc.compress(data, C, S, oc.RAW_FRACTION, 0.1, threads=8)
+    assert c.n_chunks == chunks
+    p = dc.Params(C, S)
+    blob, table, st = dev(c.blob), dev(c.table), torch.cuda.current_stream().cuda_stream
+    q = data.view(np.int8).reshape(rows, cols)
+    scale = (np.random.default_rng(S).random(rows) + 0.5).astype(np.float32) * np.float32(0.01)
+    scale_d = torch.from_numpy(scale).cuda()
+    dst = torch.full((rows * cols + 64,), 0x5A, dtype=torch.uint8, device="cuda")
+    dc.decompress_chunks(blob, c.blob.size, table, chunks, p, dst, rows * cols, st)
+    out = dst.cpu().numpy()
+    assert np.array_equal(out[:rows * cols], data) and (out[rows * cols:] == 0x5A).all()
+    wide = torch.zeros(rows * cols, dtype=torch.int16, device="cuda")
+    dc.decompress_dequant_bf16(blob, c.blob.size, table, chunks, p, scale_d, rows, cols, wide, rows * cols, st)
+    assert np.array_equal(wide.cpu().numpy().view(np.uint16).reshape(rows, cols), oq.dequant_bf16(q, scale))
+    x = synth.gen_activation_bf16(cols, S)
+    y = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    dc.decompress_gemv(blob, c.blob.size, table, chunks, p, scale_d, rows, cols, torch.from_numpy(x.view(np.int16)).cuda(), y, None,
+                       *gemv_workspace(chunks), st)
+    # fp32 sums of `cols` products: 2^-24 a step at most, of the sum of the magnitudes
+    size = np.abs(q.astype(np.float64)) @ np.abs(oq.bf16_to_f64(x)) * scale
+    assert (np.abs(y.cpu().numpy() - oq.gemv_ref(q, scale, x)) <= cols * 2.0 ** -24 * size).all()
+    xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
+    dc.decompress_gemv_w8a8(blob, c.blob.size, table, chunks, p, scale_d, rows, cols, torch.from_numpy(xq).cuda(), float(sx), y, None, st)
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
