@@ -39,6 +39,14 @@ __device__ __forceinline__ void keep_order()
 #endif
 }
 
+// The value is taken as a new one: what follows from it is worked out here, not ahead of a loop and kept.
+__device__ __forceinline__ void anew(uint32_t &v)
+{
+#ifdef __AMDGCN__
+    asm volatile("" : "+v"(v));
+#endif
+}
+
 // The value is in its register from here on (SAME: it is the same in all lanes, a scalar register): it is not worked out later, and
 // a loop behind this place does not wait for the load that it came from.
 template <bool SAME, typename T> __device__ __forceinline__ void in_register(const T &v)

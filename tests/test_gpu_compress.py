@@ -301,3 +301,15 @@ def test_device_compress_of_more_than_4_gib(codec):
     dc.decompress_chunks(blob_d, used, table_d, nc, p, dst, n, st)
     torch.cuda.synchronize()
     assert torch.equal(dst, src)
+
+
+@pytest.mark.parametrize("codec", [oc.HUFFMAN, oc.TANS])
+@pytest.mark.parametrize("n", [262143, 262144, 262144 + 17, 3 * 262144 + 5, 1 << 20])
+def test_device_histogram_of_chunks_counted_in_parts(codec, n):
+    """A chunk's bytes are counted in parts of 256 KiB, values that differ in the upper bit in one word: a part of one value fills a
+    field as far as it can be filled, with the upper bit clear, set, and both in turn."""
+    print(f"case dev histogram codec={codec} n={n}", flush=True)
+    r = np.random.default_rng(n)
+    for data in (np.full(n, 0x7F, np.uint8), np.full(n, 0xFF, np.uint8), np.tile(np.array([0x85, 0x05], np.uint8), n // 2 + 1)[:n],
+                 r.integers(0, 256, n, dtype=np.uint8)):
+        check_equal_to_oracle(data, 1 << 20, 256, codec=codec)
