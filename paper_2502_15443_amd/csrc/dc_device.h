@@ -21,6 +21,35 @@ __device__ __forceinline__ u32x4 load16_stream(const void *p)
     return __builtin_nontemporal_load(static_cast<const u32x4 *>(p));
 }
 
+// `bytes` bytes from an address on (both the same in all lanes) into which 16-byte stores go by offset; a lane that gives kNowhere
+// stores nothing, though the instruction is issued.
+class StoreWindow {
+public:
+    static constexpr uint32_t kNowhere = 0x80000000u; // beyond any window
+    __device__ __forceinline__ StoreWindow(uint8_t *base, uint32_t bytes)
+#ifdef __AMDGCN__
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000)) {} // untyped 32-bit data, no swizzle
+#else
+        : base(base), bytes(bytes) {}
+#endif
+    __device__ __forceinline__ void store16(uint32_t offset, const u32x4 &v) const
+    {
+#ifdef __AMDGCN__
+        __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)offset, 0, 0);
+#else
+        if (offset != kNowhere && offset + 16 <= bytes) *reinterpret_cast<u32x4 *>(base + offset) = v;
+#endif
+    }
+
+private:
+#ifdef __AMDGCN__
+    __amdgpu_buffer_rsrc_t rsrc;
+#else
+    uint8_t *base;
+    uint32_t bytes;
+#endif
+};
+
 // LDS accessed through 32-bit byte addresses, so that address arithmetic stays in one VALU operation.
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;

@@ -754,22 +754,28 @@ __global__ __launch_bounds__(kLayoutThreads) void dc_layout_kernel(EncArgs a)
 
 // One sub-stream while it is written.  The coder keeps step with the decoder it writes for: the placement rule gives block
 // f its place when a decoder would ask for it, 3 to 5 blocks before its bits are coded, and the place waits in a queue
-// in LDS until the block is full.
+// in LDS until the block is full.  The words of the block at the position and the next lie in LDS too.  Positions and block counts are
+// kept times 8: bits 8-10 of a position are then the slot of its word as they stand.
 struct Coder {
-    uint32_t pos;    // position in bits, from where block 0 would start
-    uint32_t asked;  // 128 * (blocks that have their place)
-    uint32_t blk[4]; // the block at the position, as far as it is coded
+    uint32_t pos;   // 8 * (position in bits, from where block 0 would start)
+    uint32_t asked; // 1024 * (blocks that have their place)
 };
 
 constexpr uint32_t kPlaces = 8; // places a lane's queue holds; at most 520 bits, 5 blocks, are placed beyond the position
+constexpr uint32_t kWords = 8;  // words of a lane: two blocks
 
+// Bound by the issue of vector instructions where the chip is full (four workgroups a compute unit instead of eight cost 7 %), by the trips
+// to LDS and memory of a round where it is not.  So a round is free of branches, its reads stand together ahead of what needs
+// them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying over its words took 24
+// of the 90 vector operations of half a group, against 14 of 66 and six LDS accesses more.  3088 chunks of 64 KiB 77 -> 72 us, 45 MB in
+// chunks of 256 KiB with the statistics 98 -> 83, 256 chunks of 64 KiB at 32 sub-streams with them 129 -> 107.
 template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_emit_kernel(EncArgs a)
 {
     constexpr int WAVES = THREADS / 64;
     constexpr bool TANS = CODEC == DC_CODEC_TANS;
     constexpr uint32_t kFront = TANS ? 384 : 128; // code description at the start of a payload
-    __shared__ __attribute__((aligned(16))) uint32_t places[WAVES * kPlaces * 64]; // the lanes' queues: region block numbers
-    __shared__ __attribute__((aligned(16))) u32x4 heads[WAVES * 64];               // every lane's block 0
+    __shared__ __attribute__((aligned(2048))) uint32_t places[WAVES * kPlaces * 64]; // the lanes' queues: payload offsets
+    __shared__ __attribute__((aligned(2048))) uint32_t words[WAVES * kWords * 64];   // the lanes' words
     __shared__ uint32_t book[256];                                                  // length | bit-reversed code << 16
     __shared__ uint8_t len_of[256];
     __shared__ uint32_t set_bytes[WAVES];
@@ -869,52 +875,65 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     const uint32_t rounds = (groups + S - 1) / S;
     const uint32_t full_rounds = raw / (16 * S); // rounds in which every lane has a whole group
     const uint32_t places_lane = lds_address(places + wave * (kPlaces * 64) + lane);
-    uint32_t next_block = region / DC_BLOCK_BYTES;
-    const uint32_t end_blocks = kBlockBits * nb;
+    const uint32_t words_lane = lds_address(words + wave * (kWords * 64) + lane);
+    uint32_t next_place = region;
+    const uint32_t end_blocks = 8 * kBlockBits * nb;
     // the stream starts behind the `pad` bytes that block 0 lacks; block 0 is among the heads and takes no place
-    Coder c = {8 * pad, nb ? kBlockBits : 0, {0, 0, 0, 0}};
+    Coder c = {64 * pad, nb ? 8 * kBlockBits : 0};
+    *(lds_u32 *)(uintptr_t)places_lane = StoreWindow::kNowhere;
+#pragma unroll
+    for (int i = 0; i < 4; i++) *(lds_u32 *)(uintptr_t)(words_lane + 256 * i) = 0; // nothing before the stream's first bit
+    u32x4 head = {0, 0, 0, 0};
 
-    // One carrying out of the placement rule.
+    // One carrying out of the placement rule.  Every lane writes; one that asks for no block writes where its next place will go
+    // (the queue is longer than what is ever placed, so nothing that is still needed lies there).
     auto place = [&]() {
-        const uint32_t bound = c.pos + DC_LOOKAHEAD_BITS;
+        const uint32_t bound = c.pos + 8 * DC_LOOKAHEAD_BITS;
         const bool want = c.asked < (bound < end_blocks ? bound : end_blocks);
         const uint64_t m = __ballot(want);
-        if (want) {
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            *(lds_u32 *)(uintptr_t)(places_lane + ((c.asked << 1) & 256 * (kPlaces - 1))) = next_block + rank;
-            c.asked += kBlockBits;
-        }
-        next_block += (uint32_t)__popcll(m);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        *(lds_u32 *)(uintptr_t)(((c.asked >> 2) & 256 * (kPlaces - 1)) | places_lane) = next_place + rank * DC_BLOCK_BYTES;
+        c.asked += want ? 8 * kBlockBits : 0u;
+        next_place += (uint32_t)__popcll(m) * DC_BLOCK_BYTES;
     };
-    // The block at the position is complete: block 0 is kept for the heads, any other goes to its place.
-    auto hand_over = [&]() {
-        const u32x4 v = {c.blk[0], c.blk[1], c.blk[2], c.blk[3]};
-        if (c.pos < kBlockBits) {
-            heads[t] = v;
-        } else {
-            const uint32_t at = lds_load32(places_lane + ((c.pos << 1) & 256 * (kPlaces - 1)));
-            *reinterpret_cast<u32x4 *>(out + at * DC_BLOCK_BYTES) = v;
+    // What the last half group has completed: block 0 is kept for the heads, any other goes to its place.  The store is issued
+    // in any case, for a lane without a complete block outside the window: with a store on some paths only, the wait for the
+    // next round's bytes was one for all stores as well.
+    const StoreWindow window(out, ent.comp_bytes);
+    struct Done {
+        uint32_t words; // where the block's words lie
+        uint32_t place;
+        uint64_t first; // the lanes whose block 0 it is
+    } done = {words_lane, StoreWindow::kNowhere, 0};
+    // What LDS holds for the next half group: the word that the last bit coded lies in, and the place of the block at the position.
+    struct Held {
+        uint32_t word, place;
+    };
+    auto slot_of_word = [&](uint32_t k) { return (lds_u32 *)(uintptr_t)(((c.pos - 8 + 256 * k) & 256 * (kWords - 1)) | words_lane); };
+    auto held = [&]() -> Held { return {*slot_of_word(0), lds_load32(((c.pos >> 2) & 256 * (kPlaces - 1)) | places_lane)}; };
+    auto completed = [&](bool complete, uint32_t place) { // the block at the position
+        done.words = (c.pos & 0x400u) | words_lane;
+        done.place = complete ? place : StoreWindow::kNowhere;
+        done.first = __ballot(complete && c.pos < 8 * kBlockBits);
+    };
+    auto hand_over = [&](const u32x4 &v) {
+        window.store16(done.place, v);
+        if (done.first) {
+            keep_order(); // a branch that is hardly ever taken, not four selections
+            if (done.first >> lane & 1u) head = v;
         }
     };
-    // Appends n <= 96 bits: shifted by the position inside its word, then by whole words to their place in a window of two
-    // blocks, whose first is the block at the position.
-    auto append = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t n) {
-        const uint32_t o = c.pos & 31u;
-        const uint64_t a = ((uint64_t)w1 << 32 | w0) << o, b = ((uint64_t)w2 << 32 | w1) << o, d = (uint64_t)w2 << o;
-        uint32_t v[8] = {(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(d >> 32), 0, 0, 0, 0};
-        const bool one = (c.pos & 32u) != 0, two = (c.pos & 64u) != 0;
-#pragma unroll
-        for (int i = 4; i >= 0; i--) v[i] = one ? (i ? v[i - 1] : 0u) : v[i];
-#pragma unroll
-        for (int i = 6; i >= 0; i--) v[i] = two ? (i >= 2 ? v[i - 2] : 0u) : v[i];
-#pragma unroll
-        for (int i = 0; i < 4; i++) c.blk[i] |= v[i];
-        const uint32_t end = c.pos + n;
-        if ((end ^ c.pos) >= kBlockBits) {
-            hand_over();
-#pragma unroll
-            for (int i = 0; i < 4; i++) c.blk[i] = v[4 + i];
-        }
+    auto done_words = [&]() { return u32x4{lds_load32(done.words), lds_load32(done.words + 256), lds_load32(done.words + 512), lds_load32(done.words + 768)}; };
+    // Appends n <= 96 bits, n in the low byte of `bits`.  What the word that the last bit lies in holds is shifted up to its end and goes
+    // before the new bits, which then only shift down into their words; a full word is shifted by nothing and written once more.
+    auto append = [&](const Held &h, uint32_t w0, uint32_t w1, uint32_t w2, uint32_t bits) {
+        const uint32_t up = 0u - (c.pos >> 3); // shifts read the low 5 bits
+        *slot_of_word(0) = __builtin_amdgcn_alignbit(w0, h.word << (up & 31u), up);
+        *slot_of_word(1) = __builtin_amdgcn_alignbit(w1, w0, up);
+        *slot_of_word(2) = __builtin_amdgcn_alignbit(w2, w1, up);
+        *slot_of_word(3) = w2 >> (up & 31u);
+        const uint32_t end = c.pos + ((bits & 0xFFu) << 3);
+        completed((end ^ c.pos) >= 8 * kBlockBits, h.place);
         c.pos = end;
     };
 
@@ -950,13 +969,18 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     // Codes half a group, at most 88 bits: codes are joined to pairs (22 bits), fours (44) and eights.  In the loop below nothing
     // depends on another lane or on how far the stream has come, so all lanes do the same work at every step.
     auto code_half = [&](const u32x4 &bytes, const u32x4 &its, uint32_t half, uint32_t n, bool whole) {
-        uint32_t p[4], l[4]; // pairs, and their bits in the low byte
+        // what depends on the position is read from LDS ahead of the codes
+        const u32x4 last = done_words();
+        const Held h = held();
+        keep_order();
+        place();
+        uint32_t p[4], l[4]; // pairs, and their bits in the low byte (shifts read no more than that)
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             if (TANS) {
                 const uint32_t it = whole || 2u * i < n ? its[i] : 0u;
                 p[i] = it >> 8;
-                l[i] = it & 0xFFu;
+                l[i] = it;
             } else {
                 const uint32_t w = bytes[2 * half + i / 2] >> (16 * (i & 1));
                 uint32_t e0 = book[w & 0xFFu], e1 = book[(w >> 8) & 0xFFu];
@@ -965,55 +989,69 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
                     e1 = 2u * i + 1 < n ? e1 : 0u;
                 }
                 p[i] = (e0 >> 16) | (e1 >> 16) << (e0 & 31u);
-                l[i] = (e0 + e1) & 0xFFu;
+                l[i] = e0 + e1;
             }
         }
-        const uint64_t lo = (uint64_t)p[1] << l[0] | p[0], hi = (uint64_t)p[3] << l[2] | p[2];
+        hand_over(last);
+        const uint64_t lo = (uint64_t)p[1] << (l[0] & 63u) | p[0], hi = (uint64_t)p[3] << (l[2] & 63u) | p[2];
         const uint32_t m = l[0] + l[1]; // at most 44
-        const uint64_t low = lo | hi << m;
-        const uint32_t high = m ? (uint32_t)(hi >> (64 - m)) : 0u;
-        append((uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]);
+        const uint64_t low = lo | hi << (m & 63u);
+        // four Huffman codes have 4 bits or more
+        const uint32_t high = (whole && !TANS) || (m & 0xFFu) ? (uint32_t)(hi >> ((64 - m) & 63u)) : 0u;
+        append(h, (uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]);
     };
 
     // step 0 is carried out five times, the first of which takes block 0; a tANS stream opens with its first state, which a
     // decoder reads before the fifth
     for (int pass = 1; pass < 4; pass++) place();
-    if (TANS && t < groups) append(a.first[k * S + t], 0, 0, DC_TANS_STATE_BITS);
+    if (TANS) append(held(), t < groups ? a.first[k * S + t] : 0u, 0, 0, t < groups ? DC_TANS_STATE_BITS : 0u);
     if (full_rounds) load_whole_group(0);
+    in_register<false>(in[0]); // so that the wait in the loop is for the turn before and not for the first one's
+    if (TANS) in_register<false>(in[1]);
     for (uint32_t r = 0; r < full_rounds; r++) {
         const u32x4 now[2] = {in[0], in[1]};
         load_whole_group(r + 1 < full_rounds ? r + 1 : r);
-        place();
         code_half(now[0], now[0], 0, 8, true);
-        place();
+        keep_order(); // the second half's addresses are not worked out ahead: registers for eight wavefronts a SIMD
         code_half(now[0], now[1], 1, 8, true);
     }
     if (rounds > full_rounds) { // the chunk's last groups: some lanes have none, one may have a part of one
         const uint32_t n = load_group(full_rounds);
-        place();
         code_half(in[0], in[0], 0, n, false);
-        place();
         code_half(in[0], in[1], 1, n > 8 ? n - 8 : 0, false);
     }
+    hand_over(done_words());
     // the last block, unless its last bit was the stream's (the zero bits that fill the last byte are not coded)
-    if (c.pos % kBlockBits) hand_over();
+    completed(c.pos % (8 * kBlockBits) != 0, held().place);
+    hand_over(done_words());
 
     // ---- the heads of the set: put together where the wave's queues were, once all of its lanes have read the last of
-    // their queues, then written with whole 16-byte stores, the padding of the area included
+    // their queues, then written with whole 16-byte stores, the padding of the area included.  A lane's block 0 goes, its first
+    // `pad` bytes zero, to the place where those bytes would begin: shifted to words, five of them, and added to the
+    // cleared area (16 bytes before it for the first lane's).  Byte by byte it took 170 of the wave's 2900 vector operations.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    uint8_t *stage = reinterpret_cast<uint8_t *>(places + wave * (kPlaces * 64));
-    if (lane == 0)
-        for (uint32_t p = heads_total; p < heads_padded; p++) stage[p] = 0;
-    const u32x4 head = nb ? heads[t] : u32x4{0, 0, 0, 0};
-    for (uint32_t i = pad; i < DC_BLOCK_BYTES && nb; i++)
-        stage[heads_incl - hb + i - pad] = (uint8_t)((i < 8 ? (i < 4 ? head[0] : head[1]) : (i < 12 ? head[2] : head[3])) >> (8 * (i & 3u)));
+    const uint32_t stage = lds_address(places + wave * (kPlaces * 64));
+    typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+    *(lds_u32x4 *)(uintptr_t)(stage + 16 * lane) = u32x4{0, 0, 0, 0};
+    if (lane < 2) *(lds_u32x4 *)(uintptr_t)(stage + 16 * (set_width(S) + lane)) = u32x4{0, 0, 0, 0};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    {
+        const uint32_t at = 16 + heads_incl - hb - pad, up = 8 * (at & 3u);
+        const uint32_t h[6] = {0, head[0], head[1], head[2], head[3], 0};
+#pragma unroll
+        for (uint32_t i = 0; i < 5; i++)
+            atomicAdd((uint32_t *)(lds_u32 *)(uintptr_t)(stage + (at & ~3u) + 4 * i),
+                     (uint32_t)((((uint64_t)h[i + 1] << 32 | h[i]) << up) >> 32));
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     for (uint32_t o = DC_BLOCK_BYTES * lane; o < heads_padded; o += DC_BLOCK_BYTES * 64)
-        *reinterpret_cast<u32x4 *>(out + heads_at + o) = *reinterpret_cast<const u32x4 *>(stage + o);
+        *reinterpret_cast<u32x4 *>(out + heads_at + o) = *(lds_u32x4 *)(uintptr_t)(stage + 16 + o);
 }
 
 template <int THREADS> void launch_emit(const EncArgs &a, hipStream_t stream)
