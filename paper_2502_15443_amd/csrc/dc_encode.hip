@@ -1,9 +1,11 @@
 // Device side of libdc_mi355x: chunk compression on the GPU (the compression stage of Section 3.1 of
-// the paper; Section 4.2 also reports compression speed).  Three launches:
+// the paper; Section 4.2 also reports compression speed).  Three launches, two where chunks are raw or coded
+// each by itself:
 //   dc_codes_kernel   one workgroup per chunk: byte histogram, length-limited code lengths by
 //                     package-merge (same ordering rules as the host compressor, so the lengths are
 //                     identical), bits of every sub-stream, size of the Huffman payload;
-//   dc_layout_kernel  one workgroup: which chunks stay raw, payload offsets (prefix sum), chunk table;
+//   dc_layout_kernel  one workgroup: which chunks stay raw, payload offsets (prefix sum), chunk table (up to
+//                     8192 chunks that are raw or coded each by itself, the next kernel does this on the side: own_place);
 //   dc_emit_kernel    one workgroup per chunk: header, canonical codes, and the sub-streams written as
 //                     16-byte blocks in the order of the format's placement rule.
 // For the container's second coder (tANS) dc_tans_model_kernel takes the place of dc_codes_kernel: byte
@@ -35,6 +37,7 @@ struct EncArgs {
     uint32_t block_chunks;
     uint64_t n_raw; // DC_POLICY_RAW_FRACTION: chunks that stay raw
     uint32_t codec;
+    bool placed; // the layout kernel has run; else the coder finds the chunks' places
     // workspace
     uint8_t *lens;  // [n_chunks][256] code lengths (Huffman)
     uint32_t *bits; // [n_chunks][S] bits of every sub-stream
@@ -604,6 +607,30 @@ __device__ __forceinline__ uint32_t gain_key(uint32_t raw, uint32_t coded)
 }
 __device__ __forceinline__ uint32_t gain_key(const EncArgs &a, uint64_t k) { return gain_key(chunk_len(a, k), a.comp[k]); }
 
+// Whether chunk k stays raw under the policies that look at the chunk alone.
+__device__ __forceinline__ bool stays_raw(const EncArgs &a, uint32_t k, uint32_t raw, uint32_t coded)
+{
+    if (a.policy == DC_POLICY_AUTO) return coded >= raw;
+    return a.policy == DC_POLICY_BLOCK_LAST && k % a.block_chunks != a.block_chunks - 1;
+}
+// What follows the payloads (`bytes` of them), and the result words.
+__device__ __forceinline__ void close_blob(const EncArgs &a, uint64_t bytes)
+{
+    const bool fits = bytes + DC_BLOB_TAIL_BYTES <= a.blob_cap;
+    a.result[0] = bytes + DC_BLOB_TAIL_BYTES;
+    a.result[1] = fits ? 0 : (uint64_t)(int64_t)DC_E_CAP;
+    if (!fits) return;
+    // the closing bytes: zeros, then the trailer (magic number, format id and look-ahead, chunk size,
+    // sub-streams and coder); the blob is 16-byte aligned and so is `bytes`
+    uint32_t *closing = reinterpret_cast<uint32_t *>(a.blob + bytes);
+    for (int i = 0; i < (DC_BLOB_TAIL_BYTES - DC_TRAILER_BYTES) / 4; i++) closing[i] = 0;
+    uint32_t *trailer = closing + (DC_BLOB_TAIL_BYTES - DC_TRAILER_BYTES) / 4;
+    trailer[0] = DC_TRAILER_MAGIC;
+    trailer[1] = DC_FORMAT_ID | (uint32_t)DC_LOOKAHEAD_BITS << 16;
+    trailer[2] = a.chunk_bytes;
+    trailer[3] = a.S | a.codec << 16;
+}
+
 // Which chunks stay raw.  DC_POLICY_RAW_FRACTION: the n_raw chunks of lowest gain, lower index first
 // among equal gains, i.e. the chunks with key < threshold and the first `equal_raw` chunks with
 // key == threshold.
@@ -711,10 +738,8 @@ __global__ __launch_bounds__(kLayoutThreads) void dc_layout_kernel(EncArgs a)
         bool is_raw[4];
 #pragma unroll
         for (uint32_t i = 0; i < 4; i++) {
-            bool keep = false;
-            if (a.policy == DC_POLICY_AUTO) keep = key[i] <= 0x80000000u;
-            else if (a.policy == DC_POLICY_BLOCK_LAST) keep = (uint32_t)(k0 + i) % a.block_chunks != a.block_chunks - 1; // n_chunks < 2^31
-            else if (by_gain) keep = key[i] != rule.threshold ? key[i] < rule.threshold : equal++ < rule.equal_raw;
+            bool keep = stays_raw(a, (uint32_t)(k0 + i), raw[i], coded[i]); // n_chunks < 2^31
+            if (by_gain) keep = key[i] != rule.threshold ? key[i] < rule.threshold : equal++ < rule.equal_raw;
             is_raw[i] = keep;
             size[i] = raw[i] ? (keep ? (raw[i] + 15u) / 16 : coded[i] / 16) : 0u;
             sum += size[i];
@@ -735,21 +760,63 @@ __global__ __launch_bounds__(kLayoutThreads) void dc_layout_kernel(EncArgs a)
         run_equal += equal_total;
         __syncthreads();
     }
-    if (t == 0) {
-        a.result[0] = run + DC_BLOB_TAIL_BYTES;
-        a.result[1] = run + DC_BLOB_TAIL_BYTES > a.blob_cap ? (uint64_t)(int64_t)DC_E_CAP : 0;
-        if (run + DC_BLOB_TAIL_BYTES <= a.blob_cap) {
-            // the closing bytes: zeros, then the trailer (magic number, format id and look-ahead, chunk size,
-            // sub-streams and coder); the blob is 16-byte aligned and so is `run`
-            uint32_t *closing = reinterpret_cast<uint32_t *>(a.blob + run);
-            for (int i = 0; i < (DC_BLOB_TAIL_BYTES - DC_TRAILER_BYTES) / 4; i++) closing[i] = 0;
-            uint32_t *trailer = closing + (DC_BLOB_TAIL_BYTES - DC_TRAILER_BYTES) / 4;
-            trailer[0] = DC_TRAILER_MAGIC;
-            trailer[1] = DC_FORMAT_ID | (uint32_t)DC_LOOKAHEAD_BITS << 16;
-            trailer[2] = a.chunk_bytes;
-            trailer[3] = a.S | a.codec << 16;
+    if (t == 0) close_blob(a, run);
+}
+
+// The layout without a launch of its own, where every chunk is raw or coded by itself: chunk k's workgroup adds up the sizes of the
+// chunks before it (they come out of the L2), writes the chunk's table entry, and the last one closes the blob.  The launch takes 5 us and
+// leaves a gap; the sums take more the more chunks there are.  With the launch and without: a 1023 x 1021
+// matrix in chunks of 16 KiB 22.8 and 20.0 us, 3088 chunks of 64 KiB 144.6 and 140.1, 8192 of 16 KiB 150.7 and 145.9, of 4 KiB at 64
+// sub-streams (a quarter of the threads) 105.9 and 103.7; 12 352 at 256 227.6 and 225.5, where it ends to pay.  sums: a word for every wave.
+constexpr uint64_t kOwnLayoutChunks = 8192;
+template <int THREADS> __device__ __forceinline__ dc_chunk own_place(const EncArgs &a, uint32_t k, uint32_t *sums)
+{
+    const uint32_t t = threadIdx.x;
+    uint32_t sum = 0; // in units of 16 bytes; all chunks before this one are whole
+    if (a.policy == DC_POLICY_BLOCK_LAST) {
+        // the last of every block_chunks chunks is coded
+        const uint32_t blocks = k / a.block_chunks;
+        if (t == 0) sum = (k - blocks) * (a.chunk_bytes / 16);
+        for (uint32_t b = t; b < blocks; b += THREADS) sum += a.comp[(b + 1) * a.block_chunks - 1] / 16;
+    } else {
+        const uint32_t most = a.policy == DC_POLICY_AUTO ? a.chunk_bytes : 0xFFFFFFFFu; // what a chunk takes at most
+        auto add = [&](uint32_t v) { sum += (v < most ? v : most) / 16; };
+        uint32_t j = 4 * t;
+        for (; j + 4 * THREADS + 4 <= k; j += 8 * THREADS) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(a.comp + j), w = *reinterpret_cast<const u32x4 *>(a.comp + j + 4 * THREADS);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                add(v[i]);
+                add(w[i]);
+            }
+        }
+        for (; j < k; j += 4 * THREADS) // (the sizes' array is padded to 256 bytes)
+        {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(a.comp + j);
+#pragma unroll
+            for (uint32_t i = 0; i < 4; i++)
+                if (j + i < k) add(v[i]);
         }
     }
+    sum = (uint32_t)__builtin_amdgcn_readlane((int)lanes_prefix_sum<false>(sum), 63);
+    if (THREADS > 64) {
+        if ((t & 63u) == 0) sums[t >> 6] = sum;
+        __syncthreads();
+        sum = 0;
+#pragma unroll
+        for (int w = 0; w < THREADS / 64; w++) sum += sums[w];
+    }
+    const uint32_t raw = chunk_len(a, k), coded = a.comp[k];
+    const bool keep = stays_raw(a, k, raw, coded);
+    dc_chunk e;
+    e.off = 16ull * sum;
+    e.comp_bytes = keep ? (raw + 15u) & ~15u : coded;
+    e.raw_bytes_flags = raw | (keep ? DC_CHUNK_RAW : 0u);
+    if (t == 0) {
+        a.table[k] = e;
+        if (k + 1 == a.n_chunks) close_blob(a, e.off + e.comp_bytes);
+    }
+    return e;
 }
 
 // One sub-stream while it is written.  The coder keeps step with the decoder it writes for: the placement rule gives block
@@ -778,13 +845,13 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     __shared__ __attribute__((aligned(2048))) uint32_t words[WAVES * kWords * 64];   // the lanes' words
     __shared__ uint32_t book[256];                                                  // length | bit-reversed code << 16
     __shared__ uint8_t len_of[256];
-    __shared__ uint32_t set_bytes[WAVES];
+    __shared__ uint32_t set_bytes[WAVES], place_sums[WAVES];
     __shared__ uint32_t len_count[4][kL + 1]; // [64 byte values][code length]
 
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint64_t k = blockIdx.x;
     const uint32_t S = a.S;
-    const dc_chunk ent = a.table[k];
+    const dc_chunk ent = a.placed ? a.table[k] : own_place<THREADS>(a, (uint32_t)k, place_sums);
     const uint32_t raw = ent.raw_bytes_flags & ~DC_CHUNK_RAW;
     if (ent.off + ent.comp_bytes + DC_BLOB_TAIL_BYTES > a.blob_cap) return; // the caller's blob is too small
     const uint8_t *src = a.src + k * a.chunk_bytes;
@@ -1138,7 +1205,8 @@ int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (a.codec == DC_CODEC_TANS) hipLaunchKernelGGL(dc_tans_model_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dc_codes_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(dc_layout_kernel, dim3(1), dim3(kLayoutThreads), 0, stream, a);
+    a.placed = nc > kOwnLayoutChunks || a.n_raw > 0;
+    if (a.placed) hipLaunchKernelGGL(dc_layout_kernel, dim3(1), dim3(kLayoutThreads), 0, stream, a);
     switch (a.S) {
     case 32:
     case 64: launch_emit<64>(a, stream); break;

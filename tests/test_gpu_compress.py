@@ -313,3 +313,19 @@ def test_device_histogram_of_chunks_counted_in_parts(codec, n):
     for data in (np.full(n, 0x7F, np.uint8), np.full(n, 0xFF, np.uint8), np.tile(np.array([0x85, 0x05], np.uint8), n // 2 + 1)[:n],
                  r.integers(0, 256, n, dtype=np.uint8)):
         check_equal_to_oracle(data, 1 << 20, 256, codec=codec)
+
+
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (128, oc.TANS), (256, oc.HUFFMAN)])
+@pytest.mark.parametrize("policy,block", [(oc.ALL_HUFF, 0), (oc.AUTO, 0), (oc.BLOCK_LAST, 1), (oc.BLOCK_LAST, 3), (oc.BLOCK_LAST, 9000)])
+@pytest.mark.parametrize("chunks", [1, 5, 1023, 2047, 2052, 8192, 8193])
+def test_device_layout_with_and_without_a_launch_of_its_own(S, codec, policy, block, chunks):
+    """Up to 8192 chunks the workgroups of the coder find their places by themselves: numbers of chunks around the turns of the
+    sums (four sizes a thread, two turns at a time) and on both sides of the line; some chunks do not shrink, the last one is short."""
+    print(f"case dev layout S={S} codec={codec} policy={policy} block={block} chunks={chunks}", flush=True)
+    C = 512
+    r = np.random.default_rng(chunks)
+    data = weightlike_bytes(chunks * C - 5, chunks + S)
+    for k in r.integers(0, chunks, max(1, chunks // 4)):
+        part = data[k * C:(k + 1) * C]
+        part[:] = r.integers(0, 256, part.size, dtype=np.uint8) if k % 2 else 3
+    check_equal_to_oracle(data, C, S, policy, block, codec=codec)
