@@ -10,7 +10,7 @@
 //                     16-byte blocks in the order of the format's placement rule.
 // For the container's second coder (tANS) dc_tans_model_kernel takes the place of dc_codes_kernel: byte
 // histogram, frequencies normalised to 2048 by the format's rule, the states of every value, and every
-// sub-stream coded backwards once, which leaves one 32-bit item (fields and width) per two bytes in the
+// sub-stream coded backwards once, which leaves one 96-bit item (fields and width) per eight bytes in the
 // workspace; dc_emit_kernel then writes those items forwards where it would write codes.
 // The stored format is in include/dc.h.
 #include <hip/hip_runtime.h>
@@ -44,7 +44,7 @@ struct EncArgs {
     uint32_t *comp; // [n_chunks] bytes of the coded payload
     uint16_t *freq;  // tANS: [n_chunks][256] normalised frequencies
     uint16_t *first; // tANS: [n_chunks][S] first state of every sub-stream
-    uint32_t *items; // tANS: [n_chunks * chunk_bytes / 2] per two bytes: width of both fields | both fields << 8
+    uint8_t *items;  // tANS: [n_chunks][2 * chunk_bytes], see HalfItem
     // results
     uint8_t *blob;
     uint64_t blob_cap;
@@ -68,6 +68,36 @@ __device__ __forceinline__ uint32_t chunk_len(const EncArgs &a, uint64_t k)
     const uint64_t lo = k * a.chunk_bytes;
     const uint64_t left = a.raw_bytes - lo;
     return left < a.chunk_bytes ? (uint32_t)left : a.chunk_bytes;
+}
+
+// Pairs of codes (at most 22 bits each, their widths in the low bytes of l) joined to the at most 88 bits of half a group.
+// some: the first two pairs may have no bits at all.
+struct HalfGroup {
+    uint32_t w0, w1, w2;
+    uint32_t bits; // in the low byte
+};
+__device__ __forceinline__ HalfGroup joined(const uint32_t p[4], const uint32_t l[4], bool some)
+{
+    const uint64_t lo = (uint64_t)p[1] << (l[0] & 63u) | p[0], hi = (uint64_t)p[3] << (l[2] & 63u) | p[2];
+    const uint32_t m = l[0] + l[1]; // at most 44
+    const uint64_t low = lo | hi << (m & 63u);
+    const uint32_t high = !some || (m & 0xFFu) ? (uint32_t)(hi >> ((64 - m) & 63u)) : 0u;
+    return {(uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]};
+}
+
+// What the tANS model kernel leaves for the coder: half a group in three words, its width above the 24 bits that the third
+// needs.  A chunk's items lie by rounds of its sub-streams' groups, as the coder reads them: four words of every
+// group, then the other two (24 bytes a group of the 32 it has in the workspace).  With an item of 32 bits for every two bytes the
+// two kernels moved 180 MB of items for 45 MB of bytes; now 135, and the coder does not join them (the call 72.5 -> 68.2 us, of 202 MB
+// 321 -> 266).
+struct ItemPlace {
+    uint64_t first, rest; // bytes from the start of the items
+};
+__device__ __forceinline__ ItemPlace item_place(uint64_t k, uint32_t chunk_bytes, uint32_t groups, uint32_t S, uint32_t r, uint32_t t)
+{
+    const uint32_t in_round = groups - r * S < S ? groups - r * S : S;
+    const uint64_t round = k * 2 * chunk_bytes + 24 * r * S;
+    return {round + 16 * t, round + 16 * in_round + 8 * t};
 }
 
 // step(16 bytes) for the groups t, t + 256, ... below n16, four loads in flight (one load at a time left a chunk alone on its
@@ -436,7 +466,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     __shared__ uint32_t hist[256];
     __shared__ uint32_t nq[256];       // normalised frequencies
     __shared__ uint32_t cumq[256];     // first place | frequency << 16
-    __shared__ uint2 step_of[256];     // what a symbol does to X (see below)
+    __shared__ uint32_t step_of[256];  // what a symbol does to X (see below)
     __shared__ uint32_t wave_sum[4];
     __shared__ uint32_t area_bytes[4];
     uint16_t *marks = reinterpret_cast<uint16_t *>(arena);
@@ -492,7 +522,9 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         // A symbol's field has nb bits, nb the smallest n with (X >> n) < 2q: X lies in [2048, 4096), so that is
         // n0 = 12 - (bits of 2q - 1), or one more from X = 2q << n0 on: nb = (X + ((n0 + 1) << 16) - (2q << n0)) >> 16.
         const uint32_t n0 = (uint32_t)__builtin_clz((2 * qv - 1) | 1u) - (31 - kTansBits);
-        step_of[t] = make_uint2(((n0 + 1) << 16) - (2 * qv << n0), 2 * (cum - qv));
+        // That addend takes 20 bits (n0 is 11 at most), the place of the value's states less q the 12 above them, signed: one word, because
+        // the look-ups of this table and of the states, at random, keep the LDS busy through the whole chain.
+        step_of[t] = (((n0 + 1) << 16) - (2 * qv << n0)) | (cum - qv) << 20;
         if (qv) {
             marks[cum] = (uint16_t)(t + 1);
             // also at the first place of every later wave of the pass below that the value reaches into
@@ -554,29 +586,31 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         };
         // codes a group, the bytes from the n-th on absent; its bytes are in w, those of group r - 1 are loaded meanwhile
         auto code_group = [&](uint32_t r, uint32_t n, bool whole) {
-            uint2 step[16];
+            uint32_t step[16];
 #pragma unroll
             for (int i = 0; i < 16; i++) step[i] = step_of[(w[i >> 2] >> (8 * (i & 3))) & 0xFFu];
             if (r > 0) load_group(r - 1);
-            uint32_t it[8];
+            uint32_t p[8], l[8];
 #pragma unroll
             for (int j = 7; j >= 0; j--) {
                 uint32_t field = 0, width = 0;
 #pragma unroll
                 for (int i = 2 * j + 1; i >= 2 * j; i--) {
                     if (whole || (uint32_t)i < n) {
-                        const uint32_t nb = (X + step[i].x) >> 16;
+                        const uint32_t nb = (X + (step[i] & 0xFFFFFu)) >> 16;
                         field = field << nb | (X & ((1u << nb) - 1u));
                         width += nb;
-                        X = lds_load16(states + step[i].y + 2 * (X >> nb));
+                        X = lds_load16(states + 2 * (uint32_t)((int32_t)step[i] >> 20) + 2 * (X >> nb));
                     }
                 }
-                it[j] = width | field << 8;
-                bits += width;
+                p[j] = field;
+                l[j] = width;
             }
-            u32x4 *dst = reinterpret_cast<u32x4 *>(a.items + (k * a.chunk_bytes + 16 * (t + r * S)) / 2);
-            dst[0] = u32x4{it[0], it[1], it[2], it[3]};
-            dst[1] = u32x4{it[4], it[5], it[6], it[7]};
+            const HalfGroup h0 = joined(p, l, true), h1 = joined(p + 4, l + 4, true);
+            bits += h0.bits + h1.bits;
+            const ItemPlace at = item_place(k, a.chunk_bytes, groups, S, r, t);
+            *reinterpret_cast<u32x4 *>(a.items + at.first) = u32x4{h0.w0, h0.w1, h0.w2 | h0.bits << 24, h1.w0};
+            *reinterpret_cast<uint2 *>(a.items + at.rest) = make_uint2(h1.w1, h1.w2 | h1.bits << 24);
         };
         uint32_t r = my_groups;
         if (r) {
@@ -1004,52 +1038,52 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
         c.pos = end;
     };
 
-    // what a round codes of this lane's stream: the group's 16 bytes; tANS: its items, two symbols in 32 bits
-    u32x4 in[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-    const uint32_t *items = TANS ? a.items + k * (a.chunk_bytes / 2) : nullptr;
+    // what a round codes of this lane's stream: the group's 16 bytes; tANS: its items
+    u32x4 in = {0, 0, 0, 0};
+    uint2 in_rest = {0, 0};
+    auto load_items = [&](uint32_t r) {
+        const ItemPlace at = item_place(k, a.chunk_bytes, groups, S, r, t);
+        in = *reinterpret_cast<const u32x4 *>(a.items + at.first);
+        in_rest = *reinterpret_cast<const uint2 *>(a.items + at.rest);
+    };
     auto load_group = [&](uint32_t r) -> uint32_t { // returns the bytes of it that exist
         const uint32_t lo = 16 * (t + r * S);
         const uint32_t in_n = lo < raw ? (raw - lo < 16 ? raw - lo : 16) : 0;
         if (TANS) {
             // the model kernel has left items for every byte of a group, empty ones for bytes that do not exist
-            if (in_n) {
-                in[0] = *reinterpret_cast<const u32x4 *>(items + lo / 2);
-                in[1] = *reinterpret_cast<const u32x4 *>(items + lo / 2 + 4);
-            }
+            if (in_n) load_items(r);
+            else in = u32x4{0, 0, 0, 0}, in_rest = make_uint2(0, 0);
         } else if (in_n == 16) {
-            in[0] = *reinterpret_cast<const u32x4 *>(src + lo);
+            in = *reinterpret_cast<const u32x4 *>(src + lo);
         } else {
-            in[0] = u32x4{0, 0, 0, 0};
-            for (uint32_t i = 0; i < in_n; i++) in[0][i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
+            in = u32x4{0, 0, 0, 0};
+            for (uint32_t i = 0; i < in_n; i++) in[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
         }
         return in_n;
     };
     auto load_whole_group = [&](uint32_t r) {
-        const uint32_t lo = 16 * (t + r * S);
-        if (TANS) {
-            in[0] = *reinterpret_cast<const u32x4 *>(items + lo / 2);
-            in[1] = *reinterpret_cast<const u32x4 *>(items + lo / 2 + 4);
-        } else {
-            in[0] = *reinterpret_cast<const u32x4 *>(src + lo);
-        }
+        if (TANS) load_items(r);
+        else in = *reinterpret_cast<const u32x4 *>(src + 16 * (t + r * S));
     };
     // Codes half a group, at most 88 bits: codes are joined to pairs (22 bits), fours (44) and eights.  In the loop below nothing
     // depends on another lane or on how far the stream has come, so all lanes do the same work at every step.
-    auto code_half = [&](const u32x4 &bytes, const u32x4 &its, uint32_t half, uint32_t n, bool whole) {
+    auto code_half = [&](const u32x4 &now, const uint2 &rest, uint32_t half, uint32_t n, bool whole) {
         // what depends on the position is read from LDS ahead of the codes
         const u32x4 last = done_words();
         const Held h = held();
         keep_order();
         place();
-        uint32_t p[4], l[4]; // pairs, and their bits in the low byte (shifts read no more than that)
+        HalfGroup g;
+        if (TANS) {
+            hand_over(last);
+            g = half ? HalfGroup{now[3], rest.x, rest.y, 0} : HalfGroup{now[0], now[1], now[2], 0};
+            g.bits = g.w2 >> 24;
+            g.w2 &= 0xFFFFFFu;
+        } else {
+            uint32_t p[4], l[4]; // pairs, and their bits in the low byte (shifts read no more than that)
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            if (TANS) {
-                const uint32_t it = whole || 2u * i < n ? its[i] : 0u;
-                p[i] = it >> 8;
-                l[i] = it;
-            } else {
-                const uint32_t w = bytes[2 * half + i / 2] >> (16 * (i & 1));
+            for (int i = 0; i < 4; i++) {
+                const uint32_t w = now[2 * half + i / 2] >> (16 * (i & 1));
                 uint32_t e0 = book[w & 0xFFu], e1 = book[(w >> 8) & 0xFFu];
                 if (!whole) {
                     e0 = 2u * i < n ? e0 : 0u;
@@ -1058,14 +1092,10 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
                 p[i] = (e0 >> 16) | (e1 >> 16) << (e0 & 31u);
                 l[i] = e0 + e1;
             }
+            hand_over(last);
+            g = joined(p, l, !whole);
         }
-        hand_over(last);
-        const uint64_t lo = (uint64_t)p[1] << (l[0] & 63u) | p[0], hi = (uint64_t)p[3] << (l[2] & 63u) | p[2];
-        const uint32_t m = l[0] + l[1]; // at most 44
-        const uint64_t low = lo | hi << (m & 63u);
-        // four Huffman codes have 4 bits or more
-        const uint32_t high = (whole && !TANS) || (m & 0xFFu) ? (uint32_t)(hi >> ((64 - m) & 63u)) : 0u;
-        append(h, (uint32_t)low, (uint32_t)(low >> 32), high, m + l[2] + l[3]);
+        append(h, g.w0, g.w1, g.w2, g.bits);
     };
 
     // step 0 is carried out five times, the first of which takes block 0; a tANS stream opens with its first state, which a
@@ -1073,19 +1103,20 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     for (int pass = 1; pass < 4; pass++) place();
     if (TANS) append(held(), t < groups ? a.first[k * S + t] : 0u, 0, 0, t < groups ? DC_TANS_STATE_BITS : 0u);
     if (full_rounds) load_whole_group(0);
-    in_register<false>(in[0]); // so that the wait in the loop is for the turn before and not for the first one's
-    if (TANS) in_register<false>(in[1]);
+    in_register<false>(in); // so that the wait in the loop is for the turn before and not for the first one's
+    if (TANS) in_register<false>(in_rest.x);
     for (uint32_t r = 0; r < full_rounds; r++) {
-        const u32x4 now[2] = {in[0], in[1]};
+        const u32x4 now = in;
+        const uint2 rest = in_rest;
         load_whole_group(r + 1 < full_rounds ? r + 1 : r);
-        code_half(now[0], now[0], 0, 8, true);
+        code_half(now, rest, 0, 8, true);
         keep_order(); // the second half's addresses are not worked out ahead: registers for eight wavefronts a SIMD
-        code_half(now[0], now[1], 1, 8, true);
+        code_half(now, rest, 1, 8, true);
     }
     if (rounds > full_rounds) { // the chunk's last groups: some lanes have none, one may have a part of one
         const uint32_t n = load_group(full_rounds);
-        code_half(in[0], in[0], 0, n, false);
-        code_half(in[0], in[1], 1, n > 8 ? n - 8 : 0, false);
+        code_half(in, in_rest, 0, n, false);
+        code_half(in, in_rest, 1, n > 8 ? n - 8 : 0, false);
     }
     hand_over(done_words());
     // the last block, unless its last bit was the stream's (the zero bits that fill the last byte are not coded)
@@ -1196,7 +1227,7 @@ int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const d
         uint8_t *more = ws + align256(nc * 256) + align256(nc * a.S * 4) + align256(nc * 4);
         a.freq = reinterpret_cast<uint16_t *>(more);
         a.first = reinterpret_cast<uint16_t *>(more + align256(nc * 512));
-        a.items = reinterpret_cast<uint32_t *>(more + align256(nc * 512) + align256(nc * a.S * 2));
+        a.items = more + align256(nc * 512) + align256(nc * a.S * 2);
     }
     a.blob = blob_dev;
     a.blob_cap = blob_cap;
