@@ -878,13 +878,21 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     __shared__ __attribute__((aligned(2048))) uint32_t places[WAVES * kPlaces * 64]; // the lanes' queues: payload offsets
     __shared__ __attribute__((aligned(2048))) uint32_t words[WAVES * kWords * 64];   // the lanes' words
     __shared__ uint32_t book[256];                                                  // length | bit-reversed code << 16
-    __shared__ uint8_t len_of[256];
     __shared__ uint32_t set_bytes[WAVES], place_sums[WAVES];
     __shared__ uint32_t len_count[4][kL + 1]; // [64 byte values][code length]
 
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint64_t k = blockIdx.x;
     const uint32_t S = a.S;
+    // Asked for ahead of the chunk's place: the code lengths of the byte values t, t + THREADS, ... and the bits of the lane's
+    // stream.  (Trips to memory one after the other and codes numbered in loops over the lengths were 10 of the 34 us of a workgroup's life.)
+    constexpr int kValues = 256 / THREADS;
+    uint32_t len[kValues];
+    if (!TANS)
+#pragma unroll
+        for (int i = 0; i < kValues; i++) len[i] = a.lens[k * 256 + t + i * THREADS];
+    const bool has_stream = t < S;
+    const uint32_t stream_bits = has_stream ? a.bits[k * S + t] : 0;
     const dc_chunk ent = a.placed ? a.table[k] : own_place<THREADS>(a, (uint32_t)k, place_sums);
     const uint32_t raw = ent.raw_bytes_flags & ~DC_CHUNK_RAW;
     if (ent.off + ent.comp_bytes + DC_BLOB_TAIL_BYTES > a.blob_cap) return; // the caller's blob is too small
@@ -917,12 +925,15 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
             out[3 * i + 2] = (uint8_t)(two >> 16);
         }
     } else {
-        for (uint32_t v = t; v < 256; v += THREADS) len_of[v] = a.lens[k * 256 + v];
-        __syncthreads();
-        for (uint32_t i = t; i < 128; i += THREADS) out[i] = (uint8_t)(len_of[2 * i] | (len_of[2 * i + 1] << 4));
+#pragma unroll
+        for (int i = 0; i < kValues; i++) { // eight lengths to a word, put together by the lanes that hold them
+            uint32_t x = len[i] << (4 * (t & 7u));
+            x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true); // quad_perm 1 0 3 2
+            x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true); // quad_perm 2 3 0 1
+            x |= (uint32_t)__shfl_xor((int)x, 4);
+            if ((t & 7u) == 0) *reinterpret_cast<uint32_t *>(out + (t + i * THREADS) / 2) = x;
+        }
     }
-    const bool has_stream = t < S;
-    const uint32_t stream_bits = has_stream ? a.bits[k * S + t] : 0;
     const uint32_t nb = blocks_of(stream_bits), hb = head_bytes_of(stream_bits);
     const uint32_t pad = nb ? DC_BLOCK_BYTES - hb : 0; // bytes that block 0 of the stream lacks at its front
     if (has_stream) reinterpret_cast<uint16_t *>(out + kFront)[t] = (uint16_t)(nb | (hb ? (hb - 1) << 12 : 0));
@@ -931,6 +942,21 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     const uint32_t heads_incl = lanes_prefix_sum<false>(hb);
     const uint32_t whole_total = (uint32_t)__builtin_amdgcn_readlane((int)whole_incl, 63);
     const uint32_t heads_total = (uint32_t)__builtin_amdgcn_readlane((int)heads_incl, 63);
+    uint32_t rank[kValues];
+    if (!TANS)
+#pragma unroll
+        for (int i = 0; i < kValues; i++) {
+            uint32_t count = 0;
+            rank[i] = 0;
+#pragma unroll
+            for (uint32_t l = 1; l <= (uint32_t)kL; l++) {
+                const uint64_t m = __ballot(len[i] == l);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                rank[i] = len[i] == l ? below : rank[i];
+                count = lane == l ? (uint32_t)__popcll(m) : count;
+            }
+            if (lane <= (uint32_t)kL) len_count[wave + i * WAVES][lane] = count;
+        }
     if (lane == 63) set_bytes[wave] = (DC_BLOCK_BYTES * whole_total + heads_total + 15u) & ~15u;
     __syncthreads();
     const uint32_t hdr = header_bytes(S, CODEC);
@@ -942,31 +968,26 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
     const uint32_t heads_padded = set_bytes[wave] - DC_BLOCK_BYTES * whole_total; // ... take this many bytes
     for (uint32_t i = kFront + 2 * S + 4 * n_sets + t; i < hdr; i += THREADS) out[i] = 0;
 
-    // ---- canonical codes: numbered in order of (length, byte value).  A wave looks at 64 consecutive
-    // byte values at a time: rank = values of the same length before this one within the 64.
-    for (uint32_t v = t; v < 256 && !TANS; v += THREADS) {
-        const uint32_t l = len_of[v];
-        uint32_t rank = 0;
-        for (uint32_t l2 = 1; l2 <= (uint32_t)kL; l2++) {
-            const uint64_t m = __ballot(l == l2);
-            if (l == l2) rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (lane == 0) len_count[v >> 6][l2] = (uint32_t)__popcll(m);
+    // ---- canonical codes: numbered in order of (length, byte value).  Before the barrier a wave has ranked its values among those of
+    // equal length in the same 64; behind it lane l has the counts of length l, and every shorter code of length m stands
+    // for 2^(l - m) codes of length l that come first: a prefix sum over the lanes, aligned to the longest code.
+    if (!TANS) {
+        uint32_t count[4], total = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+            count[b] = lane <= (uint32_t)kL ? len_count[b][lane] : 0u;
+            total += count[b];
         }
-        book[v] = rank;
-    }
-    __syncthreads();
-    for (uint32_t v = t; v < 256 && !TANS; v += THREADS) {
-        const uint32_t l = len_of[v];
-        uint32_t entry = 0;
-        if (l) {
-            // every shorter code of length m stands for 2^(l - m) codes of length l that come first
-            uint32_t code = book[v];
-            for (uint32_t m = 1; m < l; m++)
-                code += (len_count[0][m] + len_count[1][m] + len_count[2][m] + len_count[3][m]) << (l - m);
-            for (uint32_t b = 0; b < (v >> 6); b++) code += len_count[b][l];
-            entry = l | (__brev(code) >> (32 - l)) << 16;
+        const uint32_t longest = lane <= (uint32_t)kL ? kL - lane : 0u; // how far a code of this length is aligned up
+        const uint32_t first = (lanes_prefix_sum<false>(total << longest) - (total << longest)) >> longest;
+#pragma unroll
+        for (int i = 0; i < kValues; i++) {
+            uint32_t base = first;
+#pragma unroll
+            for (int b = 0; b < 3; b++) base += (uint32_t)b < wave + i * WAVES ? count[b] : 0u;
+            const uint32_t code = rank[i] + (uint32_t)__shfl((int)base, (int)len[i]);
+            book[t + i * THREADS] = len[i] ? len[i] | (__brev(code) >> ((32 - len[i]) & 31u)) << 16 : 0u;
         }
-        book[v] = entry;
     }
     __syncthreads();
     if (!has_stream) return;
