@@ -520,11 +520,12 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         cumq[t] = cum | qv << 16;
         a.freq[k * 256 + t] = (uint16_t)qv;
         // A symbol's field has nb bits, nb the smallest n with (X >> n) < 2q: X lies in [2048, 4096), so that is
-        // n0 = 12 - (bits of 2q - 1), or one more from X = 2q << n0 on: nb = (X + ((n0 + 1) << 16) - (2q << n0)) >> 16.
+        // n0 = 12 - (bits of 2q - 1), or one more from X = 2q << n0 on, which lies in (2048, 4096] too:
+        // nb = (X + ((n0 + 1) << 12) - (2q << n0)) >> 12.  That addend takes 16 bits (n0 is 11 at most), and so does the place of the value's
+        // states less q, in bytes and signed: one word, because the look-ups of this table and of the states, at random, keep the LDS
+        // busy through the whole chain.
         const uint32_t n0 = (uint32_t)__builtin_clz((2 * qv - 1) | 1u) - (31 - kTansBits);
-        // That addend takes 20 bits (n0 is 11 at most), the place of the value's states less q the 12 above them, signed: one word, because
-        // the look-ups of this table and of the states, at random, keep the LDS busy through the whole chain.
-        step_of[t] = (((n0 + 1) << 16) - (2 * qv << n0)) | (cum - qv) << 20;
+        step_of[t] = ((((n0 + 1) << 12) - (2 * qv << n0)) & 0xFFFFu) | 2 * (cum - qv) << 16;
         if (qv) {
             marks[cum] = (uint16_t)(t + 1);
             // also at the first place of every later wave of the pass below that the value reaches into
@@ -597,10 +598,10 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
 #pragma unroll
                 for (int i = 2 * j + 1; i >= 2 * j; i--) {
                     if (whole || (uint32_t)i < n) {
-                        const uint32_t nb = (X + (step[i] & 0xFFFFFu)) >> 16;
-                        field = field << nb | (X & ((1u << nb) - 1u));
+                        const uint32_t nb = (X + (step[i] & 0xFFFFu)) >> 12;
+                        field = field << nb | __builtin_amdgcn_ubfe(X, 0u, nb);
                         width += nb;
-                        X = lds_load16(states + 2 * (uint32_t)((int32_t)step[i] >> 20) + 2 * (X >> nb));
+                        X = lds_load16(states + (uint32_t)((int32_t)step[i] >> 16) + 2 * (X >> nb));
                     }
                 }
                 p[j] = field;
