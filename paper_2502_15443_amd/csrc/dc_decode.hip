@@ -78,8 +78,9 @@ struct DecodeArgs {
     uint64_t dst_cap;
     // kModeGemv: kPartialSlots sums per chunk (slot r: the chunk's share of the r-th row it touches)
     float *partial;
-    // fused modes: the matrices, in table order
+    // fused modes: the matrices, in table order, and the first chunks of the second to the last (beyond them, no chunk's number)
     uint32_t n_mats;
+    uint32_t next_first[DC_MAX_MATRICES - 1];
     MatrixArgs mats[DC_MAX_MATRICES];
 };
 
@@ -692,11 +693,8 @@ __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32
 
 // A row's result from its sum.  y_i = scale_i * sum; W8A8: y_i = (float(sum) * scale_i) * x_scale, each step rounded
 // once, in this order.
-__device__ __forceinline__ float scaled_sum(const MatrixArgs &m, uint32_t row, float sum) { return m.row_scale[row] * sum; }
-__device__ __forceinline__ float scaled_sum(const MatrixArgs &m, uint32_t row, int32_t sum)
-{
-    return ((float)sum * m.row_scale[row]) * m.x_scale;
-}
+__device__ __forceinline__ float scaled_sum(const MatrixArgs &m, float scale, float sum) { return scale * sum; }
+__device__ __forceinline__ float scaled_sum(const MatrixArgs &m, float scale, int32_t sum) { return ((float)sum * scale) * m.x_scale; }
 __device__ __forceinline__ void store_row(const MatrixArgs &m, uint32_t row, float y)
 {
     m.y_accum[row] = y;
@@ -763,9 +761,9 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     const bool is_raw = (ent.raw_bytes_flags & DC_CHUNK_RAW) != 0;
     // fused modes: the matrix the chunk belongs to, and the chunk's number inside it
     uint32_t mi = 0;
-    if (MODE != kModeI8)
-        for (uint32_t i = 1; i < a.n_mats; i++)
-            if (k >= a.mats[i].first_chunk) mi = i;
+    if (MODE != kModeI8) // (one load and no loop: a loop over the descriptors was a trip to memory for each of them)
+#pragma unroll
+        for (uint32_t i = 0; i < DC_MAX_MATRICES - 1; i++) mi += (uint32_t)k >= a.next_first[i] ? 1u : 0u;
     const MatrixArgs &mat = a.mats[mi];
     const uint64_t dst_cap = MODE == kModeI8 ? a.dst_cap : (uint64_t)mat.rows * mat.cols;
     // first decoded byte of the chunk (in the buffer, or in its matrix)
@@ -783,11 +781,14 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     constexpr bool UNI = CPW == 1; // all lanes of the wave belong to one stream set
 
     // ---- products of whole rows: the rows of the chunk, and what lane r of the chunk's first wave does with the sum of
-    // the r-th.
+    // the r-th.  Its scale is asked for now: at the end the trip to memory would be one that nothing hides.
+    constexpr bool kRows = MODE == kModeGemvRows || MODE == kModeGemvW8A8Rows;
+    const uint32_t own_row = kRows ? (uint32_t)(dst_pos / mat.cols) + cl : 0u;
+    const bool has_row = kRows && k < a.n_chunks && wave == 0 && cl < a.chunk_bytes / mat.cols && own_row < mat.rows;
+    float own_scale = 0.0f;
+    if (has_row) own_scale = mat.row_scale[own_row];
     auto finish_rows = [&](auto sum) {
-        const uint32_t row = (uint32_t)(dst_pos / mat.cols) + cl;
-        if (k < a.n_chunks && wave == 0 && cl < a.chunk_bytes / mat.cols && row < mat.rows)
-            store_row(mat, row, scaled_sum(mat, row, decltype(sum)(0) + sum));
+        if (has_row) store_row(mat, own_row, scaled_sum(mat, own_scale, decltype(sum)(0) + sum));
     };
     // ---- ordered product: the same for the sums that the chunk leaves in the workspace.  One for every row that the chunk's
     // place in the matrix touches, whatever its table entry says, because the finish kernel adds them all up.
@@ -1325,32 +1326,35 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
 
 // Blocks of 256 rows of the matrices of a fused GEMV call, matrix after matrix.
 struct RowBlocks {
-    uint32_t n_mats;
     uint32_t chunk_bytes;
     const float *partial; // the ordered product: kPartialSlots sums per chunk
-    uint32_t first_block[DC_MAX_MATRICES + 1];
+    uint32_t first_block[DC_MAX_MATRICES]; // no block's number beyond the last matrix
     MatrixArgs mats[DC_MAX_MATRICES];
 };
+__device__ __forceinline__ uint32_t matrix_of_block(const RowBlocks &rb, uint32_t block)
+{
+    uint32_t mi = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < DC_MAX_MATRICES; i++) mi += block >= rb.first_block[i] ? 1u : 0u;
+    return mi;
+}
 
 __global__ __launch_bounds__(256) void dc_gemv_zero_kernel(RowBlocks rb)
 {
-    uint32_t mi = 0;
-    for (uint32_t i = 1; i < rb.n_mats; i++)
-        if (blockIdx.x >= rb.first_block[i]) mi = i;
+    const uint32_t mi = matrix_of_block(rb, blockIdx.x);
     const uint32_t i = (blockIdx.x - rb.first_block[mi]) * 256 + threadIdx.x;
     if (i < rb.mats[mi].rows) rb.mats[mi].y_accum[i] = 0.0f;
 }
 
 template <bool W8A8> __global__ __launch_bounds__(256) void dc_gemv_finish_kernel(RowBlocks rb)
 {
-    uint32_t mi = 0;
-    for (uint32_t i = 1; i < rb.n_mats; i++)
-        if (blockIdx.x >= rb.first_block[i]) mi = i;
+    const uint32_t mi = matrix_of_block(rb, blockIdx.x);
     const MatrixArgs &m = rb.mats[mi];
     const uint32_t i = (blockIdx.x - rb.first_block[mi]) * 256 + threadIdx.x;
     if (i < m.rows) {
-        if (W8A8) store_row(m, i, scaled_sum(m, i, reinterpret_cast<const int32_t *>(m.y_accum)[i]));
-        else store_row(m, i, scaled_sum(m, i, m.y_accum[i]));
+        const float scale = m.row_scale[i];
+        if (W8A8) store_row(m, i, scaled_sum(m, scale, reinterpret_cast<const int32_t *>(m.y_accum)[i]));
+        else store_row(m, i, scaled_sum(m, scale, m.y_accum[i]));
     }
 }
 
@@ -1359,20 +1363,21 @@ template <bool W8A8> __global__ __launch_bounds__(256) void dc_gemv_finish_kerne
 // row it touches, row (c*C) div cols + r, in slot r.
 __global__ __launch_bounds__(256) void dc_gemv_ordered_finish_kernel(RowBlocks rb)
 {
-    uint32_t mi = 0;
-    for (uint32_t i = 1; i < rb.n_mats; i++)
-        if (blockIdx.x >= rb.first_block[i]) mi = i;
+    const uint32_t mi = matrix_of_block(rb, blockIdx.x);
     const MatrixArgs &m = rb.mats[mi];
     const uint32_t i = (blockIdx.x - rb.first_block[mi]) * 256 + threadIdx.x;
     if (i < m.rows) {
+        const float scale = m.row_scale[i]; // on its way while the sums are found
         const uint64_t C = rb.chunk_bytes;
         const uint64_t begin = (uint64_t)i * m.cols, last = begin + m.cols - 1;
-        float sum = 0.0f;
-        for (uint64_t c = begin / C; c <= last / C; c++) {
-            const uint64_t first_row = c * C / m.cols;
-            sum += rb.partial[(m.first_chunk + c) * kPartialSlots + (i - first_row)];
-        }
-        store_row(m, i, scaled_sum(m, i, sum));
+        const uint64_t c0 = begin / C, c1 = last / C;
+        const float *p = rb.partial + (m.first_chunk + c0) * kPartialSlots;
+        // chunks after the first begin inside the row: it is the first that they touch.  Two sums are asked for at once.
+        const float next = c1 > c0 ? p[kPartialSlots] : 0.0f;
+        float sum = p[i - (uint32_t)(c0 * C / m.cols)];
+        if (c1 > c0) sum += next;
+        for (uint64_t c = c0 + 2; c <= c1; c++) sum += p[(c - c0) * kPartialSlots];
+        store_row(m, i, scaled_sum(m, scale, sum));
     }
 }
 
@@ -1396,6 +1401,7 @@ __global__ __launch_bounds__(256) void dc_gemv_i8_kernel(const uint8_t *__restri
         const uint32_t row = row0 + r < rows ? row0 + r : rows - 1; // rows past the end repeat the last one
         qr[r] = q + (size_t)row * cols;
     }
+    const float scale = row_scale[row0 + (threadIdx.x & 3u) < rows ? row0 + (threadIdx.x & 3u) : row0]; // for the end, where nothing would hide its trip
     float acc[kGemvRows] = {0.0f, 0.0f, 0.0f, 0.0f};
     struct Turn { u32x4 w[kGemvRows]; uint4 xa, xb; };
     auto load = [&](uint32_t c) -> Turn {
@@ -1438,6 +1444,7 @@ __global__ __launch_bounds__(256) void dc_gemv_i8_kernel(const uint8_t *__restri
         }
         add(now);
     }
+    in_register<false>(scale);
 #pragma unroll
     for (int r = 0; r < kGemvRows; r++) acc[r] = lanes_sum(acc[r]);
     if (lane == 63) {
@@ -1448,7 +1455,7 @@ __global__ __launch_bounds__(256) void dc_gemv_i8_kernel(const uint8_t *__restri
     if (threadIdx.x < kGemvRows && row0 + threadIdx.x < rows) {
         const uint32_t r = threadIdx.x;
         const float total = part[0][r] + part[1][r] + part[2][r] + part[3][r];
-        const float y = row_scale[row0 + r] * total;
+        const float y = scale * total;
         y_f32[row0 + r] = y;
         if (y_bf16) y_bf16[row0 + r] = (uint16_t)(bf16x2(y, 0.0f) & 0xFFFFu);
     }
@@ -1470,6 +1477,7 @@ __global__ __launch_bounds__(256) void dc_gemv_w8a8_kernel(const uint8_t *__rest
         const uint32_t row = row0 + r < rows ? row0 + r : rows - 1; // rows past the end repeat the last one
         qr[r] = q + (size_t)row * cols;
     }
+    const float scale = row_scale[row0 + (threadIdx.x & 3u) < rows ? row0 + (threadIdx.x & 3u) : row0]; // for the end, where nothing would hide its trip
     int32_t acc[kGemvRows] = {0, 0, 0, 0};
     struct Turn { u32x4 w[kGemvRows]; uint4 x; };
     auto load = [&](uint32_t c) -> Turn {
@@ -1496,6 +1504,7 @@ __global__ __launch_bounds__(256) void dc_gemv_w8a8_kernel(const uint8_t *__rest
         }
         add(now);
     }
+    in_register<false>(scale);
 #pragma unroll
     for (int r = 0; r < kGemvRows; r++)
         acc[r] = __builtin_bit_cast(int32_t, lanes_prefix_sum<false>(__builtin_bit_cast(uint32_t, acc[r]))); // total in lane 63
@@ -1507,7 +1516,7 @@ __global__ __launch_bounds__(256) void dc_gemv_w8a8_kernel(const uint8_t *__rest
     if (threadIdx.x < kGemvRows && row0 + threadIdx.x < rows) {
         const uint32_t r = threadIdx.x;
         const int32_t total = part[0][r] + part[1][r] + part[2][r] + part[3][r];
-        const float y = ((float)total * row_scale[row0 + r]) * x_scale;
+        const float y = ((float)total * scale) * x_scale;
         y_f32[row0 + r] = y;
         if (y_bf16) y_bf16[row0 + r] = (uint16_t)(bf16x2(y, 0.0f) & 0xFFFFu);
     }
@@ -1654,6 +1663,7 @@ int fused_args(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
     a = DecodeArgs{};
     common_args(a, blob_dev, blob_bytes, table_dev, n_chunks, params);
     a.n_mats = n_mats;
+    for (uint32_t &first : a.next_first) first = 0xFFFFFFFFu;
     uint64_t next_chunk = 0;
     for (uint32_t i = 0; i < n_mats; i++) {
         const dc_matrix &m = mats[i];
@@ -1671,6 +1681,7 @@ int fused_args(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
         // the matrices follow each other in the table, each starting at a chunk of its own
         if (m.first_chunk != next_chunk) return DC_E_ARG;
         next_chunk += (total + params->chunk_bytes - 1) / params->chunk_bytes;
+        if (i) a.next_first[i - 1] = (uint32_t)m.first_chunk; // below 2^31, or the launch is refused
         MatrixArgs &k = a.mats[i];
         k.first_chunk = m.first_chunk;
         k.rows = m.rows;
@@ -1743,7 +1754,8 @@ int gemv_layer(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
     int rc = fused_args(blob_dev, blob_bytes, table_dev, n_chunks, params, mats_host, n_mats, MODE, a);
     if (rc != DC_OK) return rc;
     RowBlocks rb = {};
-    rb.n_mats = n_mats;
+    uint32_t row_blocks = 0;
+    for (uint32_t &first : rb.first_block) first = 0xFFFFFFFFu;
     rb.chunk_bytes = params->chunk_bytes;
     bool ordered = MODE == kModeGemv;
     // One launch instead of two or three (4 MiB at 256 sub-streams: 21.6 -> 20.0 us, int8 27.0 -> 19.3) if no row reaches
@@ -1753,7 +1765,8 @@ int gemv_layer(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
     bool whole_rows = results_apart(a, workspace_dev, n_chunks * kPartialSlots * sizeof(float));
     for (uint32_t i = 0; i < n_mats; i++) {
         rb.mats[i] = a.mats[i];
-        rb.first_block[i + 1] = rb.first_block[i] + (a.mats[i].rows + 255) / 256;
+        rb.first_block[i] = row_blocks;
+        row_blocks += (a.mats[i].rows + 255) / 256;
         // the ordered product keeps a row's sum in the lane of the row's number inside the chunk
         if (rows_touched_by_a_chunk(params->chunk_bytes, a.mats[i].cols) > (params->n_streams < 64 ? params->n_streams : 64))
             ordered = whole_rows = false;
@@ -1769,14 +1782,14 @@ int gemv_layer(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *tab
         rb.partial = a.partial;
         rc = launch_decode<kModeGemv>(a, params->n_streams, stream, params->codec);
         if (rc != DC_OK) return rc;
-        hipLaunchKernelGGL(dc_gemv_ordered_finish_kernel, dim3(rb.first_block[n_mats]), dim3(256), 0, stream, rb);
+        hipLaunchKernelGGL(dc_gemv_ordered_finish_kernel, dim3(row_blocks), dim3(256), 0, stream, rb);
         return launch_status();
     }
     if (MODE == kModeGemvW8A8 && whole_rows) return launch_decode<kModeGemvW8A8Rows>(a, params->n_streams, stream, params->codec);
-    hipLaunchKernelGGL(dc_gemv_zero_kernel, dim3(rb.first_block[n_mats]), dim3(256), 0, stream, rb);
+    hipLaunchKernelGGL(dc_gemv_zero_kernel, dim3(row_blocks), dim3(256), 0, stream, rb);
     rc = launch_decode<MODE == kModeGemv ? kModeGemvAtomic : MODE>(a, params->n_streams, stream, params->codec);
     if (rc != DC_OK) return rc;
-    hipLaunchKernelGGL(dc_gemv_finish_kernel<MODE == kModeGemvW8A8>, dim3(rb.first_block[n_mats]), dim3(256), 0, stream, rb);
+    hipLaunchKernelGGL(dc_gemv_finish_kernel<MODE == kModeGemvW8A8>, dim3(row_blocks), dim3(256), 0, stream, rb);
     return launch_status();
 }
 
