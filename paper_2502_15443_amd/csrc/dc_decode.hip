@@ -23,6 +23,8 @@
 // of stream bits (two_symbols).  Rings, block placement, the words in registers, stores and the fused epilogues are shared.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dc.h"
 #include "dc_device.h"
 
@@ -1145,6 +1147,32 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         if (rem) step(last_whole, last_whole ? load16_stream(p + r * round_bytes) : u32x4{0, 0, 0, 0});
     };
 
+    // The coded rounds of a chunk of whole rows that are whole numbers of rounds: all lanes move to the next row at once, so that a
+    // round needs no look at the lanes' rows, and a row's end no sorting of them.  The additions are the general walk's, in its
+    // order.  4096 columns: 1024 chunks at 64 sub-streams 51.6 -> 47.1 us, int8 48.2 -> 45.9; at 256 28.6 -> 27.2 and 26.5 -> 25.1, 4096
+    // chunks 81.4 -> 79.3.
+    const bool rows_of_rounds = (kRows || MODE == kModeGemv) && UNI && huff && cols % round_bytes == 0 && dst_pos % cols == 0 && raw % cols == 0;
+    auto sum_rows_of_rounds = [&](auto &mine, auto &acc, uint32_t &col, auto coded_round) {
+        using T = std::remove_reference_t<decltype(acc)>;
+        uint32_t slot = 0, left = cols / round_bytes;
+        auto end_row = [&]() {
+            const T v = __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lanes_sum(acc)), 63));
+            mine += lane == slot ? v : T(0);
+            acc = T(0);
+        };
+        for (uint32_t r = 0; r < full_rounds; r++)
+            coded_round(true, [&]() {
+                if (left == 0) {
+                    end_row();
+                    slot++;
+                    left = cols / round_bytes;
+                }
+                left--;
+                col = left ? col + round_bytes : ct * 16;
+            });
+        end_row();
+    };
+
     // Sums over the waves of the chunk, in wave order, for its first wave.  A wave's ring is its own, and the wave has read
     // the last of it: the totals go there.
     auto over_waves = [&](auto mine) {
@@ -1206,7 +1234,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             const uint4 xa = xp[0], xb = xp[1];
             return {{xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w}};
         };
-        auto coded_round = [&](bool whole) {
+        auto coded_round = [&](bool whole, auto enter) {
             Sixteen xs;
             uint32_t e[8];
             auto products = [&](const uint32_t e[8], uint32_t half, int from, int to) {
@@ -1218,7 +1246,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             };
             auto begin = [&]() {
                 xs = load_x();
-                enter_row(whole);
+                enter();
             };
             if constexpr (FEW) {
                 uint32_t f[8];
@@ -1244,13 +1272,17 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
                 }
         };
         const bool last_whole = raw >= full_rounds * round_bytes + ct * 16 + 16;
-        if (huff) {
-            for (uint32_t r = 0; r < full_rounds; r++) coded_round(true);
-            if (rem) coded_round(last_whole);
+        if (rows_of_rounds) {
+            sum_rows_of_rounds(mine, acc, col, coded_round);
         } else {
-            raw_rounds(last_whole, raw_round);
+            if (huff) {
+                for (uint32_t r = 0; r < full_rounds; r++) coded_round(true, [&]() { enter_row(true); });
+                if (rem) coded_round(last_whole, [&]() { enter_row(last_whole); });
+            } else {
+                raw_rounds(last_whole, raw_round);
+            }
+            flush();
         }
-        flush();
         if (MODE != kModeGemvAtomic) {
             const float total = over_waves(mine);
             leave_partial_sums(total);
@@ -1291,12 +1323,12 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             col += round_bytes;
             while (col >= cols) { col -= cols; row++; }
         };
-        auto coded_round = [&](bool whole) {
+        auto coded_round = [&](bool whole, auto enter) {
             uint4 xs;
             uint32_t w[4];
             auto begin = [&]() {
                 xs = load_x(); // asked for before the group is decoded
-                enter_row(whole);
+                enter();
             };
             if constexpr (FEW) {
                 decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w, early(begin));
@@ -1313,13 +1345,17 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             add_products(whole, w, xs);
         };
         const bool last_whole = raw >= full_rounds * round_bytes + ct * 16 + 16;
-        if (huff) {
-            for (uint32_t r = 0; r < full_rounds; r++) coded_round(true);
-            if (rem) coded_round(last_whole);
+        if (rows_of_rounds) {
+            sum_rows_of_rounds(mine, acc, col, coded_round);
         } else {
-            raw_rounds(last_whole, raw_round);
+            if (huff) {
+                for (uint32_t r = 0; r < full_rounds; r++) coded_round(true, [&]() { enter_row(true); });
+                if (rem) coded_round(last_whole, [&]() { enter_row(last_whole); });
+            } else {
+                raw_rounds(last_whole, raw_round);
+            }
+            flush();
         }
-        flush();
         if (MODE == kModeGemvW8A8Rows) finish_rows(over_waves(mine));
     }
 }

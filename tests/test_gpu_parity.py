@@ -725,3 +725,30 @@ def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, more):
     xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
     dc.decompress_gemv_w8a8(blob, c.blob.size, table, chunks, p, scale_d, rows, cols, torch.from_numpy(xq).cuda(), float(sx), y, None, st)
     assert np.array_equal(y.cpu().numpy().view(np.uint32), oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
+
+
+@pytest.mark.parametrize("S,codec", [(64, oc.HUFFMAN), (64, oc.TANS), (128, oc.HUFFMAN), (256, oc.HUFFMAN), (256, oc.TANS)])
+@pytest.mark.parametrize("rounds,rows_a_chunk,chunks", [(1, 3, 5), (3, 1, 4), (2, 60, 2), (1, 2, 2100)])
+def test_products_of_rows_of_whole_rounds(S, codec, rounds, rows_a_chunk, chunks):
+    # rows of one and of several rounds, one row a chunk, a short last chunk; both sides of the line for few wavefronts; raw chunks
+    cols = 16 * S * rounds
+    if cols * rows_a_chunk > 1 << 20 or (chunks > 100 and codec == oc.TANS):
+        rows_a_chunk, chunks = 4, 7
+    C, rows = cols * rows_a_chunk, rows_a_chunk * chunks - (rows_a_chunk - 1)
+    data = weightlike_bytes(rows * cols, S + rounds)
+    c = oc.compress(data, C, S, oc.RAW_FRACTION, 0.2 if chunks > 2 else 0.0, codec=codec, threads=8)
+    p = dc.Params(C, S, codec=codec)
+    blob, table = dev(c.blob), dev(c.table)
+    q = data.view(np.int8).reshape(rows, cols)
+    scale = (np.random.default_rng(S).random(rows) + 0.5).astype(np.float32) * np.float32(0.01)
+    scale_d = torch.from_numpy(scale).cuda()
+    x = synth.gen_activation_bf16(cols, S)
+    y = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    dc.decompress_gemv(blob, c.blob.size, table, c.n_chunks, p, scale_d, rows, cols, torch.from_numpy(x.view(np.int16)).cuda(), y, None,
+                       *gemv_workspace(c.n_chunks), stream())
+    # fp32 sums of `cols` products: 2^-24 a step at most, of the sum of the magnitudes
+    size = np.abs(q.astype(np.float64)) @ np.abs(oq.bf16_to_f64(x)) * scale
+    assert (np.abs(y.cpu().numpy() - oq.gemv_ref(q, scale, x)) <= cols * 2.0 ** -24 * size).all()
+    xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
+    dc.decompress_gemv_w8a8(blob, c.blob.size, table, c.n_chunks, p, scale_d, rows, cols, torch.from_numpy(xq).cuda(), float(sx), y, None, stream())
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
