@@ -1147,30 +1147,52 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         if (rem) step(last_whole, last_whole ? load16_stream(p + r * round_bytes) : u32x4{0, 0, 0, 0});
     };
 
-    // The coded rounds of a chunk of whole rows that are whole numbers of rounds: all lanes move to the next row at once, so that a
-    // round needs no look at the lanes' rows, and a row's end no sorting of them.  The additions are the general walk's, in its
-    // order.  4096 columns: 1024 chunks at 64 sub-streams 51.6 -> 47.1 us, int8 48.2 -> 45.9; at 256 28.6 -> 27.2 and 26.5 -> 25.1, 4096
-    // chunks 81.4 -> 79.3.
-    const bool rows_of_rounds = (kRows || MODE == kModeGemv) && UNI && huff && cols % round_bytes == 0 && dst_pos % cols == 0 && raw % cols == 0;
-    auto sum_rows_of_rounds = [&](auto &mine, auto &acc, uint32_t &col, auto coded_round) {
+    // The coded rounds where the 1024 bytes that a wave decodes in a round never lie in two rows: the wave moves to another row with all
+    // of its lanes, so that a round needs no look at the lanes' rows, and a row's end no sorting of them.  The additions are the
+    // general walk's, in its order.  13B layer (rows of 5 * 1024 and 13.5 * 1024) 101.5 -> 99.7 us; 4096 columns, 1024 chunks at 256 sub-streams
+    // 28.6 -> 27.2, int8 26.5 -> 25.1.  Launches of few wavefronts only take it where rows are whole rounds, which is counted with less (at 64
+    // sub-streams 51.6 -> 47.1 and 48.2 -> 45.9; 2 % of it lost with the walk for any rows).
+    constexpr uint32_t kSpan = 16 * 64;
+    const uint32_t unit = FEW ? round_bytes : kSpan;
+    const bool rows_of_spans = (kRows || MODE == kModeGemv) && UNI && huff && cols % unit == 0 && dst_pos % (FEW ? cols : kSpan) == 0 &&
+                               raw % (FEW ? cols : kSpan) == 0;
+    auto sum_rows_of_spans = [&](auto &mine, auto &acc, uint32_t &col, uint32_t first_row, bool last_whole, auto coded_round) {
         using T = std::remove_reference_t<decltype(acc)>;
-        uint32_t slot = 0, left = cols / round_bytes;
-        auto end_row = [&]() {
+        auto end_row = [&](uint32_t slot) {
             const T v = __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lanes_sum(acc)), 63));
-            mine += lane == slot ? v : T(0);
+            mine += lane == (slot & 63u) ? v : T(0);
             acc = T(0);
         };
-        for (uint32_t r = 0; r < full_rounds; r++)
-            coded_round(true, [&]() {
-                if (left == 0) {
-                    end_row();
-                    slot++;
-                    left = cols / round_bytes;
+        if constexpr (FEW) {
+            uint32_t slot = 0, left = cols / round_bytes;
+            for (uint32_t r = 0; r < full_rounds; r++)
+                coded_round(true, [&]() {
+                    if (left == 0) {
+                        end_row(slot++);
+                        left = cols / round_bytes;
+                    }
+                    left--;
+                    col = left ? col + round_bytes : ct * 16;
+                });
+            end_row(slot);
+        } else {
+            uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)col), next_row = (uint32_t)__builtin_amdgcn_readfirstlane((int)row);
+            uint32_t cur = next_row;
+            const uint32_t whole_rows = round_bytes / cols, part = round_bytes - whole_rows * cols; // a round takes the wave this far
+            auto enter = [&]() {
+                if (next_row != cur) {
+                    end_row(cur - first_row);
+                    cur = next_row;
                 }
-                left--;
-                col = left ? col + round_bytes : ct * 16;
-            });
-        end_row();
+                at += part;
+                next_row += whole_rows + (at >= cols ? 1u : 0u);
+                at -= at >= cols ? cols : 0u;
+                col = at + 16 * lane;
+            };
+            for (uint32_t r = 0; r < full_rounds; r++) coded_round(true, enter);
+            if (rem && (bool)__builtin_amdgcn_readfirstlane((int)last_whole)) coded_round(true, enter);
+            end_row(cur - first_row);
+        }
     };
 
     // Sums over the waves of the chunk, in wave order, for its first wave.  A wave's ring is its own, and the wave has read
@@ -1272,8 +1294,8 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
                 }
         };
         const bool last_whole = raw >= full_rounds * round_bytes + ct * 16 + 16;
-        if (rows_of_rounds) {
-            sum_rows_of_rounds(mine, acc, col, coded_round);
+        if (rows_of_spans) {
+            sum_rows_of_spans(mine, acc, col, first_row, last_whole, coded_round);
         } else {
             if (huff) {
                 for (uint32_t r = 0; r < full_rounds; r++) coded_round(true, [&]() { enter_row(true); });
@@ -1345,8 +1367,8 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             add_products(whole, w, xs);
         };
         const bool last_whole = raw >= full_rounds * round_bytes + ct * 16 + 16;
-        if (rows_of_rounds) {
-            sum_rows_of_rounds(mine, acc, col, coded_round);
+        if (rows_of_spans) {
+            sum_rows_of_spans(mine, acc, col, first_row, last_whole, coded_round);
         } else {
             if (huff) {
                 for (uint32_t r = 0; r < full_rounds; r++) coded_round(true, [&]() { enter_row(true); });

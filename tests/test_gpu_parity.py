@@ -728,14 +728,15 @@ def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, more):
 
 
 @pytest.mark.parametrize("S,codec", [(64, oc.HUFFMAN), (64, oc.TANS), (128, oc.HUFFMAN), (256, oc.HUFFMAN), (256, oc.TANS)])
-@pytest.mark.parametrize("rounds,rows_a_chunk,chunks", [(1, 3, 5), (3, 1, 4), (2, 60, 2), (1, 2, 2100)])
-def test_products_of_rows_of_whole_rounds(S, codec, rounds, rows_a_chunk, chunks):
-    # rows of one and of several rounds, one row a chunk, a short last chunk; both sides of the line for few wavefronts; raw chunks
-    cols = 16 * S * rounds
-    if cols * rows_a_chunk > 1 << 20 or (chunks > 100 and codec == oc.TANS):
-        rows_a_chunk, chunks = 4, 7
-    C, rows = cols * rows_a_chunk, rows_a_chunk * chunks - (rows_a_chunk - 1)
-    data = weightlike_bytes(rows * cols, S + rounds)
+@pytest.mark.parametrize("cols,C,chunks", [(4096, 12288, 5), (12288, 12288, 4), (8192, 491520, 2), (4096, 8192, 2100),  # whole rows
+                                           (5120, 4096, 2100), (5120, 65536, 600), (3072, 10240, 2100), (1024, 9216, 2100), (1024, 5120, 9)])
+def test_products_of_rows_of_whole_rounds_or_spans(S, codec, cols, C, chunks):
+    # rows of one and of several rounds, rows over chunks in spans of 1024 bytes, several rows to a round, one row a chunk, a short last
+    # chunk; both sides of the line for few wavefronts; raw chunks
+    if codec == oc.TANS and chunks > 1000:
+        chunks = 9
+    rows = (chunks * C - C // 2) // cols
+    data = weightlike_bytes(rows * cols, S + cols)
     c = oc.compress(data, C, S, oc.RAW_FRACTION, 0.2 if chunks > 2 else 0.0, codec=codec, threads=8)
     p = dc.Params(C, S, codec=codec)
     blob, table = dev(c.blob), dev(c.table)
