@@ -284,7 +284,7 @@ int dc_compress_chunks(const int8_t *src_host, uint64_t raw_bytes, const dc_para
 
 /*
  * The same compression on the GPU (Section 3.1; Section 4.2 reports compression speed as well).
- * Device to device, asynchronous on hip_stream, three launches.  The blob and table are byte for
+ * Device to device, asynchronous on hip_stream, two or three launches.  The blob and table are byte for
  * byte those of dc_compress_chunks for the same input and params.  Policies: DC_POLICY_ALL_HUFF,
  * DC_POLICY_AUTO, DC_POLICY_RAW_FRACTION, DC_POLICY_BLOCK_LAST (DC_POLICY_RAW_MASK names a mask in
  * host memory: DC_E_ARG).
@@ -377,6 +377,7 @@ int dc_decompress_chunks(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_
  *               low 32 bits (compute unit in bits 8-11, shader engine from bit 13) and its XCC_ID register in
  *               the high 32 (the XCD in bits 0-3); [3] one of DC_TRACE_*.
  * The record does not change a launch's duration measurably (74.7 us with it and without it on a layer of 3088 chunks).
+ * (Launches of up to 512 chunks, for which dc_decompress_chunks has a kernel of its own, are traced with the general one.)
  */
 #define DC_TRACE_DECODED 0u /* a coded chunk, decoded */
 #define DC_TRACE_COPIED 1u  /* a raw chunk, copied */

@@ -763,7 +763,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     const bool is_raw = (ent.raw_bytes_flags & DC_CHUNK_RAW) != 0;
     // fused modes: the matrix the chunk belongs to, and the chunk's number inside it
     uint32_t mi = 0;
-    if (MODE != kModeI8) // (one load and no loop: a loop over the descriptors was a trip to memory for each of them)
+    if (MODE != kModeI8 && a.n_mats > 1) // (one load and no loop: a loop over the descriptors was a trip to memory for each of them)
 #pragma unroll
         for (uint32_t i = 0; i < DC_MAX_MATRICES - 1; i++) mi += (uint32_t)k >= a.next_first[i] ? 1u : 0u;
     const MatrixArgs &mat = a.mats[mi];
