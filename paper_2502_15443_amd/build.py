@@ -39,7 +39,7 @@ TWO_CYCLE = {"v_and_b32", "v_or_b32", "v_xor_b32", "v_add_u32", "v_sub_u32", "v_
 
 
 def loop_mix(asm_text: str) -> dict:
-    """Vector-ALU instructions of the main loop (the innermost loop with the most table look-ups) of every decode
+    """Vector-ALU instructions of the main loop (the shortest loop with a round's 16 table look-ups) of every decode
     kernel at 256 sub-streams, Huffman, by issue class: {mode: {"valu": n, "two_cycle": a, "four_cycle": b,
     "cycles_per_instruction": c, "lookups": symbols a turn}}."""
     out = {}
@@ -55,7 +55,7 @@ def loop_mix(asm_text: str) -> dict:
             if mm and mm.group(1) in at and at[mm.group(1)] < i:
                 a, b = at[mm.group(1)], i
                 n = sum("ds_read_u16" in x for x in body[a:b])
-                if best is None or n > best[0] or (n == best[0] and b - a < best[2] - best[1]):
+                if n >= 16 and (best is None or b - a < best[2] - best[1]):
                     best = (n, a, b)
         n, a, b = best
         two = four = 0
