@@ -74,6 +74,32 @@ def loop_mix(asm_text: str) -> dict:
     return out
 
 
+def buffer_access_loops(asm_text: str) -> list:
+    """Kernels in which the compiler has put a buffer access into a loop that makes its descriptor scalar, one value a
+    turn: the source forms the descriptor from something that is the same in all lanes without the compiler seeing it."""
+    found, kernel, body = [], None, None
+    for ln in asm_text.split("\n"):
+        m = re.match(r"(_Z\w+):", ln)
+        kernel = m.group(1) if m else kernel
+        m = re.match(r"(\.LBB\w+):", ln)
+        if m:
+            body = (m.group(1), [])
+        elif body:
+            body[1].append(ln)
+            m = re.search(r"s_cbranch_execnz\s+(\.LBB\w+)", ln)
+            if m and m.group(1) == body[0] and any("v_readfirstlane" in x for x in body[1]) and \
+                    any(re.match(r"\s*buffer_(load|store|atomic)", x) for x in body[1]) and kernel not in found:
+                found.append(kernel)
+    return found
+
+
+def device_assembly(source: str) -> str:
+    """The gfx950 assembly of one source, as the build compiles it."""
+    flags = [f for f in FLAGS if f not in ("-fPIC", "-shared", "-pthread")]
+    return subprocess.run([HIPCC, *flags, "--offload-device-only", "-S", source, "-o", "-"], check=True, capture_output=True,
+                          text=True).stdout
+
+
 def stale() -> bool:
     if not os.path.exists(LIB):
         return True
@@ -103,6 +129,9 @@ def build(force: bool = True, extra=(), want_mix: bool = False) -> str:
             hit = PACKED_FP32.search(text)
             if hit:
                 raise RuntimeError(f"packed fp32 operation {hit.group(0)} in {os.path.basename(path)}")
+            looped = buffer_access_loops(text)
+            if looped:
+                raise RuntimeError(f"buffer accesses in loops over their descriptors in {', '.join(looped)}")
             if want_mix and "dc_decode_kernel" in text:
                 import json
                 print(json.dumps({"main_loop_instruction_mix": loop_mix(text)}))

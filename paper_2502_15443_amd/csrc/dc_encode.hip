@@ -867,7 +867,7 @@ constexpr uint32_t kPlaces = 8; // places a lane's queue holds; at most 520 bits
 constexpr uint32_t kWords = 8;  // words of a lane: two blocks
 
 // Bound by the issue of vector instructions where the chip is full (four workgroups a compute unit instead of eight cost 7 %), by the trips
-// to LDS and memory of a round where it is not.  So a round is free of branches, its reads stand together ahead of what needs
+// to LDS and memory of a round where it is not.  So a round is free of branches (but for two around a stream's first block), its reads stand together ahead of what needs
 // them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying over its words took 24
 // of the 90 vector operations of half a group, against 14 of 66 and six LDS accesses more.  3088 chunks of 64 KiB 77 -> 72 us, 45 MB in
 // chunks of 256 KiB with the statistics 98 -> 83, 256 chunks of 64 KiB at 32 sub-streams with them 129 -> 107.
@@ -894,7 +894,14 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
         for (int i = 0; i < kValues; i++) len[i] = a.lens[k * 256 + t + i * THREADS];
     const bool has_stream = t < S;
     const uint32_t stream_bits = has_stream ? a.bits[k * S + t] : 0;
-    const dc_chunk ent = a.placed ? a.table[k] : own_place<THREADS>(a, (uint32_t)k, place_sums);
+    dc_chunk ent = a.placed ? a.table[k] : own_place<THREADS>(a, (uint32_t)k, place_sums);
+    // The entry is the same in all lanes, which the compiler does not see: left in vector registers it makes every store through the window
+    // below a loop over the window's values (a round 169 vector and 29 scalar instructions instead of 157 and 18, 3088 chunks of 64 KiB 78.3 us
+    // instead of 74.9 in a trace, 688 with tANS 21.0 instead of 19.9).
+    auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+    ent.off = (uint64_t)uniform((uint32_t)(ent.off >> 32)) << 32 | uniform((uint32_t)ent.off);
+    ent.comp_bytes = uniform(ent.comp_bytes);
+    ent.raw_bytes_flags = uniform(ent.raw_bytes_flags);
     const uint32_t raw = ent.raw_bytes_flags & ~DC_CHUNK_RAW;
     if (ent.off + ent.comp_bytes + DC_BLOB_TAIL_BYTES > a.blob_cap) return; // the caller's blob is too small
     const uint8_t *src = a.src + k * a.chunk_bytes;

@@ -1,0 +1,38 @@
+"""What the build looks for in the device assembly."""
+import importlib.util
+import os
+
+import pytest
+
+PKG = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2502_15443_amd")
+
+
+@pytest.fixture(scope="module")
+def build():
+    spec = importlib.util.spec_from_file_location("dc_build_checks", os.path.join(PKG, "build.py"))
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    return m
+
+
+LOOPED = """_Zkernel:
+.LBB3_95:
+\tv_readfirstlane_b32 s4, v28
+\tv_cmp_eq_u64_e64 s[0:1], s[4:5], v[28:29]
+\ts_and_saveexec_b64 s[0:1], s[0:1]
+\tbuffer_store_dwordx4 v[50:53], v41, s[4:7], 0 offen
+\ts_xor_b64 exec, exec, s[0:1]
+\ts_cbranch_execnz .LBB3_95
+"""
+
+
+def test_loops_around_buffer_accesses_are_found(build):
+    assert build.buffer_access_loops(LOOPED) == ["_Zkernel"]
+    straight = LOOPED.replace("\ts_cbranch_execnz .LBB3_95\n", "\ts_endpgm\n")
+    assert build.buffer_access_loops(straight) == []
+
+
+def test_the_coders_stores_are_straight(build):
+    asm = build.device_assembly(os.path.join(PKG, "csrc", "dc_encode.hip"))
+    assert asm.count("buffer_store_dwordx4") >= 6
+    assert build.buffer_access_loops(asm) == []
