@@ -800,19 +800,28 @@ __global__ __launch_bounds__(kLayoutThreads) void dc_layout_kernel(EncArgs a)
 
 // The layout without a launch of its own, where every chunk is raw or coded by itself: chunk k's workgroup adds up the sizes of the
 // chunks before it (they come out of the L2), writes the chunk's table entry, and the last one closes the blob.  The launch takes 5 us and
-// leaves a gap; the sums take more the more chunks there are.  With the launch and without: a 1023 x 1021
-// matrix in chunks of 16 KiB 22.8 and 20.0 us, 3088 chunks of 64 KiB 144.6 and 140.1, 8192 of 16 KiB 150.7 and 145.9, of 4 KiB at 64
-// sub-streams (a quarter of the threads) 105.9 and 103.7; 12 352 at 256 227.6 and 225.5, where it ends to pay.  sums: a word for every wave.
+// leaves a gap; the sums take more the more chunks there are.  With the launch and without, replays of a graph: 64 chunks of
+// 16 KiB 24.3 and 21.6 us, 3072 of 64 KiB 152.3 and 147.1, 8192 of 16 KiB 144.9 and 140.6, of 4 KiB at 64 sub-streams (a quarter of the
+// threads) 92.6 and 90.6, with tANS 101.6 and 97.2; 12 288 of 16 KiB 212.0 and 216.8.  Blocks of one or two chunks (BLOCK_LAST) have as
+// many sizes to add: one trip to memory after the other they took 10 and 4 % longer than with the launch at 8192 chunks of 4 KiB and 64
+// sub-streams, with all asked for in batches 5 and 2 % less.  sums: a word for every wave.
 constexpr uint64_t kOwnLayoutChunks = 8192;
 template <int THREADS> __device__ __forceinline__ dc_chunk own_place(const EncArgs &a, uint32_t k, uint32_t *sums)
 {
     const uint32_t t = threadIdx.x;
     uint32_t sum = 0; // in units of 16 bytes; all chunks before this one are whole
-    if (a.policy == DC_POLICY_BLOCK_LAST) {
-        // the last of every block_chunks chunks is coded
+    if (a.policy == DC_POLICY_BLOCK_LAST && a.block_chunks > 1) { // (blocks of one chunk: all are coded)
+        // the last of every block_chunks chunks is coded; eight sizes are asked for at once
         const uint32_t blocks = k / a.block_chunks;
         if (t == 0) sum = (k - blocks) * (a.chunk_bytes / 16);
-        for (uint32_t b = t; b < blocks; b += THREADS) sum += a.comp[(b + 1) * a.block_chunks - 1] / 16;
+        for (uint32_t b = t; b < blocks; b += 8 * THREADS) {
+            uint32_t v[8];
+#pragma unroll
+            for (uint32_t i = 0; i < 8; i++) v[i] = a.comp[((b + i * THREADS < blocks ? b + i * THREADS : b) + 1) * a.block_chunks - 1];
+            keep_order();
+#pragma unroll
+            for (uint32_t i = 0; i < 8; i++) sum += b + i * THREADS < blocks ? v[i] / 16 : 0u;
+        }
     } else {
         const uint32_t most = a.policy == DC_POLICY_AUTO ? a.chunk_bytes : 0xFFFFFFFFu; // what a chunk takes at most
         auto add = [&](uint32_t v) { sum += (v < most ? v : most) / 16; };
