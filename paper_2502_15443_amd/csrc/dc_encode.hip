@@ -814,14 +814,17 @@ template <int THREADS> __device__ __forceinline__ dc_chunk own_place(const EncAr
         // the last of every block_chunks chunks is coded; eight sizes are asked for at once
         const uint32_t blocks = k / a.block_chunks;
         if (t == 0) sum = (k - blocks) * (a.chunk_bytes / 16);
-        for (uint32_t b = t; b < blocks; b += 8 * THREADS) {
+        const uint32_t *p = a.comp + (a.block_chunks - 1);
+        uint32_t b = t;
+        for (; b + 7 * THREADS < blocks; b += 8 * THREADS) {
             uint32_t v[8];
 #pragma unroll
-            for (uint32_t i = 0; i < 8; i++) v[i] = a.comp[((b + i * THREADS < blocks ? b + i * THREADS : b) + 1) * a.block_chunks - 1];
+            for (uint32_t i = 0; i < 8; i++) v[i] = p[(b + i * THREADS) * a.block_chunks];
             keep_order();
 #pragma unroll
-            for (uint32_t i = 0; i < 8; i++) sum += b + i * THREADS < blocks ? v[i] / 16 : 0u;
+            for (uint32_t i = 0; i < 8; i++) sum += v[i] / 16;
         }
+        for (; b < blocks; b += THREADS) sum += p[b * a.block_chunks] / 16;
     } else {
         const uint32_t most = a.policy == DC_POLICY_AUTO ? a.chunk_bytes : 0xFFFFFFFFu; // what a chunk takes at most
         auto add = [&](uint32_t v) { sum += (v < most ? v : most) / 16; };
