@@ -1010,7 +1010,9 @@ template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_
         }
     }
     __syncthreads();
-    if (!has_stream) return;
+    // (A set whose sub-streams hold nothing has no part in what follows: of a chunk of 512 bytes the first of 256 sub-streams' four waves codes
+    // all, and 8192 such chunks took 5 %, with tANS 11 % longer when the other three went through its rounds as well.)
+    if (!has_stream || whole_total + heads_total == 0) return;
 
     // ---- the sub-stream of this lane
     const uint32_t groups = (raw + 15) / 16;
