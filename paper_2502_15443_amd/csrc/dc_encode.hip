@@ -1279,7 +1279,14 @@ int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const d
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (a.codec == DC_CODEC_TANS) hipLaunchKernelGGL(dc_tans_model_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(dc_codes_kernel, dim3((uint32_t)nc), dim3(256), 0, stream, a);
-    a.placed = nc > kOwnLayoutChunks || a.n_raw > 0;
+    // (The layout kernel has read all sizes when it writes; a workgroup of the coder writes its entry, its payload and, the last one, the
+    // result words while others still add sizes up.)
+    auto over_workspace = [&](const void *p, uint64_t bytes) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(p), w = reinterpret_cast<uintptr_t>(workspace_dev);
+        return at < w + need && w < at + bytes;
+    };
+    a.placed = nc > kOwnLayoutChunks || a.n_raw > 0 || over_workspace(result_dev, 16) || over_workspace(blob_dev, blob_cap) ||
+               over_workspace(table_dev, nc * sizeof(dc_chunk));
     if (a.placed) hipLaunchKernelGGL(dc_layout_kernel, dim3(1), dim3(kLayoutThreads), 0, stream, a);
     switch (a.S) {
     case 32:

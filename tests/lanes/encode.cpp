@@ -1,13 +1,17 @@
 // The device compressor on the CPU, lane by lane (hip/hip_runtime.h beside this file):
-//   encode ORDER SEED chunk_bytes n_streams policy raw_fraction block_chunks codec SOURCE RESULT
+//   encode ORDER SEED chunk_bytes n_streams policy raw_fraction block_chunks codec SOURCE RESULT [OVER]
 // SOURCE holds the bytes to compress; RESULT gets the two result words, the number of chunks (u64), the table and the blob.
+// OVER: "result" or "blob" lies over the chunks' sizes, the last part of the workspace of a Huffman call.
 #include "dc_encode.hip"
+
+#include <string>
 
 int dc_launch_status() { return DC_OK; }
 
 int main(int argc, char **argv)
 {
-    if (argc != 11) return 2;
+    if (argc != 11 && argc != 12) return 2;
+    const std::string over = argc == 12 ? argv[11] : "";
     lanes::config.order = (lanes::Order)atoi(argv[1]);
     lanes::config.seed = strtoull(argv[2], nullptr, 10);
     dc_params p = {};
@@ -34,10 +38,12 @@ int main(int argc, char **argv)
         for (uint64_t i = 0; i < bytes; i++) b[i] = (uint8_t)rng();
         return b;
     };
-    uint8_t *src = buffer(n), *blob = buffer(cap), *ws = buffer(ws_bytes);
+    const uint64_t sizes = (nc * 4 + 255) / 256 * 256;
+    uint8_t *src = buffer(n), *ws = buffer(ws_bytes + cap), *blob = over == "blob" ? ws + ws_bytes - sizes : buffer(cap);
     memcpy(src, source.data(), n);
     dc_chunk *table = reinterpret_cast<dc_chunk *>(buffer(nc * sizeof(dc_chunk)));
-    uint64_t result[2] = {1, 1};
+    uint64_t words[2] = {1, 1};
+    uint64_t *result = over == "result" ? reinterpret_cast<uint64_t *>(ws + ws_bytes - sizes) : words;
     if (dc_compress_chunks_dev(reinterpret_cast<int8_t *>(src), n, &p, blob, cap, table, nc, ws, ws_bytes, result, nullptr)) return 5;
     FILE *f = fopen(argv[10], "wb");
     if (!f) return 6;

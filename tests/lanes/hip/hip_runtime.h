@@ -1,5 +1,6 @@
 // Stands in for the HIP runtime header when a device source of the library is compiled for the CPU: a launch runs the
-// kernel's workgroups one after the other, every lane as a fiber of its own that runs alone until it has to meet others.
+// kernel's workgroups one after the other, in the order the caller chooses for the lanes (first to last, last to first, shuffled),
+// every lane as a fiber of its own that runs alone until it has to meet others.
 //
 // Lanes meet where the source says so: at a barrier, a wave barrier, or an operation that reads other lanes (ballot, DPP,
 // shuffle, readlane), which waits for all lanes of the wave that have not returned.  Between two meetings every lane runs
@@ -209,7 +210,10 @@ template <typename Kernel, typename... Args> void lanes::launch(Kernel kernel, d
     std::mt19937_64 rng(config.seed);
     gridDim = grid;
     body = [&] { kernel(args...); };
-    for (uint32_t b = 0; b < grid.x; b++) {
+    std::vector<uint32_t> order(grid.x);
+    for (uint32_t b = 0; b < grid.x; b++) order[b] = config.order == kDescending ? grid.x - 1 - b : b;
+    if (config.order == kShuffled) std::shuffle(order.begin(), order.end(), rng);
+    for (uint32_t b : order) {
         blockIdx = dim3(b);
         run_block(block.x, rng);
     }

@@ -26,9 +26,9 @@ def encode(tmp_path_factory):
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_15443_amd", "csrc"),
                     os.path.join(HERE, "lanes", "encode.cpp"), "-o", exe], check=True)
 
-    def run(order, seed, data, C, S, policy=oc.ALL_HUFF, f=0.0, block=0, codec=oc.HUFFMAN):
+    def run(order, seed, data, C, S, policy=oc.ALL_HUFF, f=0.0, block=0, codec=oc.HUFFMAN, over=()):
         data.tofile(src)
-        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], seed, C, S, policy, f, block, codec)] + [src, out],
+        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], seed, C, S, policy, f, block, codec)] + [src, out, *over],
                               capture_output=True, text=True, timeout=100)
         assert done.returncode == 0, (done.returncode, done.stderr)
         b = open(out, "rb").read()
@@ -56,3 +56,16 @@ def test_compressor_does_not_depend_on_the_order_of_the_lanes(encode, order, S, 
         assert status == 0 and used == want.blob.size, i
         assert np.array_equal(table, want.table), i
         assert np.array_equal(blob, want.blob), i
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("over", ["result", "blob"])
+@pytest.mark.parametrize("policy", [oc.ALL_HUFF, oc.AUTO])
+def test_compressor_results_over_the_workspace(encode, order, over, policy):
+    # nothing is written over the chunks' sizes while a workgroup may still add them up
+    C = 8192
+    data = weightlike_bytes(5 * C + 5, 4)
+    want = oc.compress(data, C, 64, policy)
+    used, status, table, blob = encode(order, 3, data, C, 64, policy=policy, over=(over,))
+    assert status == 0 and used == want.blob.size
+    assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
