@@ -23,6 +23,7 @@
 // of stream bits (two_symbols).  Rings, block placement, the words in registers, stores and the fused epilogues are shared.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "dc.h"
@@ -1615,14 +1616,39 @@ bool decode_params_ok(const dc_params *p)
     return p->n_streams == 32 || p->n_streams == 64 || p->n_streams == 128 || p->n_streams == 256;
 }
 
+// SIMDs of the current device, four to a compute unit, looked up once per device; 0 if the runtime does not say.
+uint32_t device_simds()
+{
+    static std::atomic<uint32_t> simds_of_device[kMaxDevices];
+    int dev = -1, units = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+    uint32_t n = simds_of_device[dev].load(std::memory_order_relaxed);
+    if (n == 0 && hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && units > 0) {
+        n = 4u * (uint32_t)units;
+        simds_of_device[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Whether a launch of `waves` wavefronts takes the FEW kernels.  Up to one wavefront a SIMD it is as long as a lane's chain of look-ups, and FEW
+// is up to 19 % shorter, the more the longer the chunks (4 KiB at 256 sub-streams: as long).  The conversion to bf16 at 32
+// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that; from a half on it loses 4 to 10 % in chunks of
+// 64 KiB.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks are raw and between 2 % longer and 7 % shorter
+// where none is; short chunks, in which the set-up counts for more, lose there (4 KiB: 1 to 3 %; bf16 of 16 KiB: 1 to 3 %), and so do 32
+// sub-streams (1 to 2 %).  At three, where the wavefronts hide each other's look-ups and the LDS is what they wait for, it is longer by 7
+// to 17 %.
+bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
+{
+    const bool bf16 = mode == kModeBf16;
+    if (waves <= simds) return n_streams >= 64 || !bf16 || waves <= simds / 4;
+    return n_streams >= 64 && waves <= 2ull * simds && chunk_bytes >= (bf16 ? 32768u : 16384u);
+}
+
 template <int S, int MODE> void launch_one(const DecodeArgs &a, hipStream_t stream)
 {
     using G = Geometry<S>;
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
-    // Up to one wavefront a SIMD (1024 of them) a launch is as long as a lane's chain of look-ups, and FEW is 10 to 19 % shorter; at
-    // two it still is by 1 to 3 % from 64 sub-streams on and longer by 2 % at 32; at three, where the wavefronts hide each
-    // other's look-ups and the LDS is what they wait for, it is longer by 7 to 17 %.
-    if (grid * (uint64_t)G::kWaves <= (S < 64 ? 1024 : 2048))
+    if (few_wavefronts(MODE, S, grid * (uint64_t)G::kWaves, a.chunk_bytes, device_simds()))
         hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
     else
         hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);

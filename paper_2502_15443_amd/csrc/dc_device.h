@@ -8,6 +8,8 @@
 
 namespace dcdev {
 
+constexpr int kMaxDevices = 64; // GPUs that the library keeps something about
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // 128-bit streaming accesses for data that is touched once.

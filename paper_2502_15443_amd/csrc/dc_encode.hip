@@ -1317,7 +1317,6 @@ static __device__ __align__(256) uint8_t scratch[DC_STATIC_SCRATCH_BYTES];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_lock;
 void *g_scratch_of_device[kMaxDevices]; // address of `scratch` on every device that has asked for it
 

@@ -1,13 +1,18 @@
 // The device decoder on the CPU, lane by lane (hip/hip_runtime.h beside this file):
-//   decode ORDER SEED chunk_bytes n_streams codec MODE rows cols SOURCE RESULT
+//   decode ORDER SEED chunk_bytes n_streams codec MODE rows cols SOURCE RESULT [COMPUTE_UNITS]
+//   decode few MODE n_streams waves chunk_bytes simds
 // MODE: 0 the bytes, 1 bf16 values, 2 product, 3 product with int8 activations.  SOURCE: the numbers of chunks and of blob
 // bytes (u64), the table, the blob, row scales (fp32), activations (bf16, or int8 with their scale in fp32 before them).
-// RESULT: what the call writes.
+// RESULT: what the call writes.  COMPUTE_UNITS: of the device (256); 0: no launch is one of few wavefronts.
+// few: whether such a launch takes the kernels for few wavefronts (exit status 1: it does).
 #include "dc_decode.hip"
 
 int main(int argc, char **argv)
 {
-    if (argc != 11) return 2;
+    if (argc == 7 && !strcmp(argv[1], "few"))
+        return few_wavefronts(atoi(argv[2]), (uint32_t)atoi(argv[3]), strtoull(argv[4], nullptr, 10), (uint32_t)atoi(argv[5]), (uint32_t)atoi(argv[6]));
+    if (argc != 11 && argc != 12) return 2;
+    if (argc == 12) lanes::config.compute_units = atoi(argv[11]);
     lanes::config.order = (lanes::Order)atoi(argv[1]);
     lanes::config.seed = strtoull(argv[2], nullptr, 10);
     dc_params p = {};

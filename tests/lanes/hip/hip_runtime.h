@@ -45,7 +45,7 @@ inline uint4 make_uint4(uint32_t x, uint32_t y, uint32_t z, uint32_t w) { return
 namespace lanes {
 
 enum Order { kAscending, kDescending, kShuffled };
-struct Config { Order order = kAscending; uint64_t seed = 1; };
+struct Config { Order order = kAscending; uint64_t seed = 1; int compute_units = 256; };
 inline Config config;
 
 enum class Meet { none, wave, block };
@@ -342,6 +342,8 @@ constexpr hipError_t hipSuccess = 0;
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char *hipGetErrorString(hipError_t) { return ""; }
 inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount };
+inline hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = lanes::config.compute_units; return hipSuccess; }
 template <typename T> hipError_t hipGetSymbolAddress(void **p, T &v) { *p = (void *)&v; return hipSuccess; }
 #define HIP_SYMBOL(v) v
 

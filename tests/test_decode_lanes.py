@@ -24,15 +24,16 @@ def decode(tmp_path_factory):
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2502_15443_amd", "csrc"),
                     os.path.join(HERE, "lanes", "decode.cpp"), "-o", exe], check=True)
 
-    def run(order, c, C, S, codec, mode, rows, cols, *more):
+    def run(order, c, C, S, codec, mode, rows, cols, *more, units=256):
         parts = [np.array([c.n_chunks, c.blob.size], np.uint64), c.table, c.blob, *more]
         with open(src, "wb") as f:
             f.write(b"".join(np.ascontiguousarray(a).tobytes() for a in parts))
-        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], rows + mode, C, S, codec, mode, rows, cols)] + [src, out],
+        done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], rows + mode, C, S, codec, mode, rows, cols)] + [src, out, str(units)],
                               capture_output=True, text=True, timeout=100)
         assert done.returncode == 0, (done.returncode, done.stderr)
         return np.fromfile(out, np.uint8)
 
+    run.exe = exe
     return run
 
 
@@ -69,3 +70,14 @@ def test_decoder_of_many_wavefronts(decode, S):
     c = oc.compress(q, C, S)
     assert c.n_chunks == chunks
     assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape), q.view(np.uint8).ravel())
+
+
+@pytest.mark.parametrize("mode,S,chunk,simds,line", [
+    (BYTES, 32, 65536, 1024, 1024), (BYTES, 256, 4096, 1024, 1024), (BYTES, 256, 16384, 1024, 2048),
+    (PRODUCT, 64, 16368, 1024, 1024), (PRODUCT_INT8, 128, 65536, 1024, 2048),
+    (BF16, 32, 65536, 1024, 256), (BF16, 64, 16384, 1024, 1024), (BF16, 64, 32768, 1024, 2048),
+    (BYTES, 64, 65536, 128, 256), (BF16, 32, 4096, 128, 32), (BYTES, 64, 65536, 0, 0)])
+def test_line_for_launches_of_few_wavefronts(decode, mode, S, chunk, simds, line):
+    # in wavefronts a SIMD of the device, and by what a lane has to decode
+    few = lambda waves: bool(subprocess.run([decode.exe, "few"] + [str(v) for v in (mode, S, waves, chunk, simds)]).returncode)
+    assert not few(line + 1) and few(max(1, line // 3)) == few(max(1, line)) == (line > 0)

@@ -693,13 +693,15 @@ def test_config1_full_size_bit_exact_and_ratio():
     assert np.array_equal(out, q.view(np.uint8).ravel())
 
 
-@pytest.mark.parametrize("S", [32, 64, 128, 256])
+@pytest.mark.parametrize("S,C,chunks", [(32, 4096, 2048), (64, 4096, 1024), (128, 4096, 512), (256, 4096, 256),     # 1024 wavefronts
+                                        (64, 16384, 2048), (128, 16384, 1024), (256, 16384, 512),                    # 2048 in longer chunks
+                                        (32, 4096, 512), (64, 32768, 2048), (256, 32768, 512)])                      # the lines of bf16
 @pytest.mark.parametrize("more", [0, 1])
-def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, more):
-    # 1024 wavefronts at 32 sub-streams (two chunks each), 2048 otherwise, and one workgroup more; some chunks raw, the last one short
-    chunks = {32: 2048, 64: 2048, 128: 1024, 256: 512}[S] + more * (2 if S == 32 else 1)
-    C, cols = 4096, 2048
-    rows = 2 * chunks - 1
+def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, C, chunks, more):
+    # the largest launch of few wavefronts, and one workgroup more; some chunks raw, the last one short
+    chunks += more * (2 if S == 32 else 1)
+    cols = 2048
+    rows = chunks * C // cols - 1
     data = weightlike_bytes(rows * cols, 7 + S)
     c = oc.compress(data, C, S, oc.RAW_FRACTION, 0.1, threads=8)
     assert c.n_chunks == chunks
