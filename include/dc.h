@@ -377,7 +377,7 @@ int dc_decompress_chunks(const uint8_t *blob_dev, uint64_t blob_bytes, const dc_
  *               low 32 bits (compute unit in bits 8-11, shader engine from bit 13) and its XCC_ID register in
  *               the high 32 (the XCD in bits 0-3); [3] one of DC_TRACE_*.
  * The record does not change a launch's duration measurably (74.7 us with it and without it on a layer of 3088 chunks).
- * (Launches of up to 512 chunks, for which dc_decompress_chunks has a kernel of its own, are traced with the general one.)
+ * dc_decompress_chunks has a kernel of its own for launches of few wavefronts; a traced launch takes the one that it would take.
  */
 #define DC_TRACE_DECODED 0u /* a coded chunk, decoded */
 #define DC_TRACE_COPIED 1u  /* a raw chunk, copied */

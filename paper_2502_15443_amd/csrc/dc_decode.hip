@@ -1731,8 +1731,11 @@ extern "C" int dc_decompress_chunks_traced(const uint8_t *blob_dev, uint64_t blo
     a.dst = dst_dev;
     a.dst_cap = dst_cap;
     a.trace = trace_dev;
-    hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, false, true>), dim3((uint32_t)n_chunks), dim3(256), 0,
-                       static_cast<hipStream_t>(hip_stream), a);
+    const dim3 grid((uint32_t)n_chunks), block(Geometry<256>::kThreads);
+    if (few_wavefronts(kModeI8, 256, n_chunks * Geometry<256>::kWaves, a.chunk_bytes, device_simds()))
+        hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, true, true>), grid, block, 0, static_cast<hipStream_t>(hip_stream), a);
+    else
+        hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, false, true>), grid, block, 0, static_cast<hipStream_t>(hip_stream), a);
     return launch_status();
 }
 

@@ -1,9 +1,9 @@
 // The device decoder on the CPU, lane by lane (hip/hip_runtime.h beside this file):
 //   decode ORDER SEED chunk_bytes n_streams codec MODE rows cols SOURCE RESULT [COMPUTE_UNITS]
 //   decode few MODE n_streams waves chunk_bytes simds
-// MODE: 0 the bytes, 1 bf16 values, 2 product, 3 product with int8 activations.  SOURCE: the numbers of chunks and of blob
+// MODE: 0 the bytes, 1 bf16 values, 2 product, 3 product with int8 activations, 4 the bytes, traced.  SOURCE: the numbers of chunks and of blob
 // bytes (u64), the table, the blob, row scales (fp32), activations (bf16, or int8 with their scale in fp32 before them).
-// RESULT: what the call writes.  COMPUTE_UNITS: of the device (256); 0: no launch is one of few wavefronts.
+// RESULT: what the call writes; standard output: the kernels launched.  COMPUTE_UNITS: of the device (256); 0: no launch is one of few wavefronts.
 // few: whether such a launch takes the kernels for few wavefronts (exit status 1: it does).
 #include "dc_decode.hip"
 
@@ -42,10 +42,13 @@ int main(int argc, char **argv)
     const uint8_t *blob = part(blob_bytes);
     const uint64_t n = (uint64_t)rows * cols;
     int rc;
-    uint64_t out_bytes = mode == 0 ? n : mode == 1 ? 2 * n : 4ull * rows;
+    uint64_t out_bytes = mode == 0 || mode == 4 ? n : mode == 1 ? 2 * n : 4ull * rows;
     uint8_t *out = buffer(out_bytes);
     if (mode == 0) {
         rc = dc_decompress_chunks(blob, blob_bytes, table, nc, &p, reinterpret_cast<int8_t *>(out), n, nullptr);
+    } else if (mode == 4) {
+        rc = dc_decompress_chunks_traced(blob, blob_bytes, table, nc, &p, reinterpret_cast<int8_t *>(out), n,
+                                         reinterpret_cast<uint64_t *>(buffer(32 * nc)), nullptr);
     } else {
         const float *scale = reinterpret_cast<float *>(part(4ull * rows));
         if (mode == 1) {
@@ -66,6 +69,7 @@ int main(int argc, char **argv)
     }
     fclose(f);
     if (rc) return 5;
+    for (const char *kernel : lanes::launched) puts(kernel);
     f = fopen(argv[10], "wb");
     if (!f) return 6;
     fwrite(out, 1, out_bytes, f);

@@ -218,7 +218,9 @@ template <typename Kernel, typename... Args> void lanes::launch(Kernel kernel, d
         run_block(block.x, rng);
     }
 }
-#define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) lanes::launch(kernel, grid, block, __VA_ARGS__)
+namespace lanes { inline std::vector<const char *> launched; } // the kernels' names as the source writes them
+#define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) \
+    (lanes::launched.push_back(#kernel), lanes::launch(kernel, grid, block, __VA_ARGS__))
 
 inline void __syncthreads() { lanes::wait(lanes::Meet::block, "__syncthreads"); }
 inline int __syncthreads_count(int v)

@@ -13,7 +13,7 @@ import synth
 from tests.helpers import oracle_matrix
 from tests.test_encode_lanes import CLANG, HERE, ORDERS, ROOT
 
-BYTES, BF16, PRODUCT, PRODUCT_INT8 = range(4)
+BYTES, BF16, PRODUCT, PRODUCT_INT8, TRACED = range(5)
 
 
 @pytest.fixture(scope="module")
@@ -31,6 +31,7 @@ def decode(tmp_path_factory):
         done = subprocess.run([exe] + [str(v) for v in (ORDERS[order], rows + mode, C, S, codec, mode, rows, cols)] + [src, out, str(units)],
                               capture_output=True, text=True, timeout=100)
         assert done.returncode == 0, (done.returncode, done.stderr)
+        run.launched = done.stdout.split("\n")[:-1]
         return np.fromfile(out, np.uint8)
 
     run.exe = exe
@@ -81,3 +82,14 @@ def test_line_for_launches_of_few_wavefronts(decode, mode, S, chunk, simds, line
     # in wavefronts a SIMD of the device, and by what a lane has to decode
     few = lambda waves: bool(subprocess.run([decode.exe, "few"] + [str(v) for v in (mode, S, waves, chunk, simds)]).returncode)
     assert not few(line + 1) and few(max(1, line // 3)) == few(max(1, line)) == (line > 0)
+
+
+@pytest.mark.parametrize("units,few", [(256, "true"), (0, "false")])
+def test_a_traced_launch_is_the_launch_it_stands_for(decode, units, few):
+    C, S = 4096, 256
+    q, _ = oracle_matrix(4, 4096, synth.matrix_seed(11, S), False)
+    c = oc.compress(q, C, S)
+    for mode, kernel in ((BYTES, f"(dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, {few}>)"),
+                         (TRACED, f"(dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, {few}, true>)")):
+        assert np.array_equal(decode("shuffled", c, C, S, oc.HUFFMAN, mode, *q.shape, units=units), q.view(np.uint8).ravel())
+        assert decode.launched == [kernel.replace(", false>", ">") if mode == BYTES else kernel]

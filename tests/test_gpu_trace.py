@@ -55,6 +55,24 @@ def test_traced_launch_decodes_the_same_bytes_and_records_every_workgroup(env, p
     assert (t[:, 1].max() - t[:, 0].min()) < 100 * 5000
 
 
+@pytest.mark.parametrize("chunks", [1, 250, 300])
+def test_traced_launches_of_few_and_of_many_wavefronts(env, chunks):
+    """Chunks of 4 KiB: up to 256 of them a launch is one of few wavefronts, which has its kernel, traced or not."""
+    torch, dc = env
+    q = weightlike_bytes(chunks * 4096 - 100, chunks)
+    p = dc.Params(4096, 256)
+    blob, table = dc.compress_chunks(q, p)
+    traced = torch.full((q.size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    trace = torch.full((4 * chunks + 4,), -1, dtype=torch.int64, device="cuda")
+    dc.decompress_chunks_traced(_up(torch, blob), blob.size, _up(torch, table), chunks, p, traced, q.size, trace,
+                                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    out, t = traced.cpu().numpy(), trace.cpu().numpy()
+    assert np.array_equal(out[:q.size], q) and (out[q.size:] == 0xA5).all()
+    assert (t[3:4 * chunks:4] == dc.TRACE_DECODED).all() and (t[4 * chunks:] == -1).all()
+    assert (t[1:4 * chunks:4] >= t[0:4 * chunks:4]).all()
+
+
 def test_traced_launch_is_for_huffman_at_256_sub_streams(env):
     torch, dc = env
     q = weightlike_bytes(8 * 4096, 12)
