@@ -45,13 +45,25 @@ def decode(tmp_path_factory):
                                            (3, 4096, 4096, 0.0),    # an odd number of chunks
                                            (5, 2064, 4096, 0.4)])   # rows over chunks, a short last chunk, raw ones
 def test_decoder_does_not_depend_on_the_order_of_the_lanes(decode, order, S, codec, rows, cols, C, f):
+    check_every_mode(decode, order, S, codec, rows, cols, C, f)
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("S", [32, 64, 128, 256])
+@pytest.mark.parametrize("rows,cols,C,f", [(8, 4096, 16384, 0.0), (3, 4096, 4096, 0.0), (5, 2064, 4096, 0.4)])
+def test_general_decoder_does_not_depend_on_the_order_of_the_lanes(decode, order, S, rows, cols, C, f):
+    # the kernels that launches of more wavefronts take
+    check_every_mode(decode, order, S, oc.HUFFMAN, rows, cols, C, f, units=0)
+
+
+def check_every_mode(decode, order, S, codec, rows, cols, C, f, units=256):
     if S == 32 and f:
         f, rows, cols = 0.0, 4, 2048  # two chunks to a wavefront that differ in length or kind part its lanes: not modelled
     q, scale = oracle_matrix(rows, cols, synth.matrix_seed(9, S), False)
     c = oc.compress(q, C, S, oc.RAW_FRACTION, f, codec=codec)
     x = synth.gen_activation_bf16(cols, 3)
     xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
-    run = lambda mode, *more: decode(order, c, C, S, codec, mode, rows, cols, *more)
+    run = lambda mode, *more: decode(order, c, C, S, codec, mode, rows, cols, *more, units=units)
     assert np.array_equal(run(BYTES), q.view(np.uint8).ravel())
     assert np.array_equal(run(BF16, scale).view(np.uint16).reshape(rows, cols), oq.dequant_bf16(q, scale))
     y8 = run(PRODUCT_INT8, scale, np.float32(sx), xq).view(np.uint32)
@@ -93,3 +105,16 @@ def test_a_traced_launch_is_the_launch_it_stands_for(decode, units, few):
                          (TRACED, f"(dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, {few}, true>)")):
         assert np.array_equal(decode("shuffled", c, C, S, oc.HUFFMAN, mode, *q.shape, units=units), q.view(np.uint8).ravel())
         assert decode.launched == [kernel.replace(", false>", ">") if mode == BYTES else kernel]
+
+
+@pytest.mark.parametrize("S", [32, 64, 128, 256])
+@pytest.mark.parametrize("rows,cols,C", [(6, 4096, 12288), (3, 8192, 24576),  # whole rows: counted rounds, spans of 1024 bytes
+                                         (7, 3072, 10240), (5, 5120, 4096), (9, 1024, 9216),  # spans, where few wavefronts walk lane by lane
+                                         (4, 2064, 4096)])                     # lane by lane
+def test_products_have_the_same_bits_with_few_wavefronts_and_many(decode, S, rows, cols, C):
+    # the kernels and the walks over rows differ, the additions and their order do not
+    q, scale = oracle_matrix(rows, cols, synth.matrix_seed(12, S), False)
+    c = oc.compress(q, C, S)
+    x = synth.gen_activation_bf16(cols, 7)
+    few, many = (decode("ascending", c, C, S, oc.HUFFMAN, PRODUCT, rows, cols, scale, x, units=units) for units in (256, 0))
+    assert np.array_equal(few, many) and few.size == 4 * rows
