@@ -81,11 +81,11 @@ struct DecodeArgs {
     uint64_t dst_cap;
     // kModeGemv: kPartialSlots sums per chunk (slot r: the chunk's share of the r-th row it touches)
     float *partial;
-    // fused modes: the matrices, in table order, and the first chunks of the second to the last (beyond them, no chunk's number), which calls
-    // of one matrix do not read
+    // fused modes: the matrices, in table order, and the first chunks of the second to the last (beyond them, no chunk's number).  (Behind
+    // the matrices they are a cache line of arguments of their own: a layer of seven 100.1 instead of 99.7 us, one matrix alone 0.5 % less.)
     uint32_t n_mats;
-    MatrixArgs mats[DC_MAX_MATRICES];
     uint32_t next_first[DC_MAX_MATRICES - 1];
+    MatrixArgs mats[DC_MAX_MATRICES];
 };
 
 // Sums `val` (float or int32) over runs of consecutive lanes with equal `key` (keys do not decrease with
