@@ -44,7 +44,7 @@ struct EncArgs {
     uint32_t *comp; // [n_chunks] bytes of the coded payload
     uint16_t *freq;  // tANS: [n_chunks][256] normalised frequencies
     uint16_t *first; // tANS: [n_chunks][S] first state of every sub-stream
-    uint8_t *items;  // tANS: [n_chunks][2 * chunk_bytes], see HalfItem
+    uint8_t *items;  // tANS: [n_chunks][2 * chunk_bytes], see item_place
     // results
     uint8_t *blob;
     uint64_t blob_cap;
@@ -568,8 +568,8 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     __syncthreads();
 
     // ---- every sub-stream coded from its last symbol to its first: X = 2048; per symbol the smallest n with
-    // (X >> n) < 2q, the field X mod 2^n, then X = 2048 + the state of the value numbered X >> n.  The items
-    // (two symbols each: width | fields << 8) land in the workspace at the positions of their bytes.
+    // (X >> n) < 2q, the field X mod 2^n, then X = 2048 + the state of the value numbered X >> n.  The fields of half a group
+    // are joined as the coder wants them (joined), and land in the workspace where it reads them (item_place).
     // This is one serial chain per lane, few wavefronts to a SIMD: everything that does not depend on X (the bytes of the
     // next group, what the 16 values do to X) is loaded before the chain needs it, and a link of the chain is four
     // operations and one look-up of the next state (40 us for 688 chunks of 64 KiB when the field's width was worked out
@@ -879,8 +879,8 @@ constexpr uint32_t kPlaces = 8; // places a lane's queue holds; at most 520 bits
 constexpr uint32_t kWords = 8;  // words of a lane: two blocks
 
 // Bound by the issue of vector instructions where the chip is full (four workgroups a compute unit instead of eight cost 7 %), by the trips
-// to LDS and memory of a round where it is not.  So a round is free of branches (but for two around a stream's first block), its reads stand together ahead of what needs
-// them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying over its words took 24
+// to LDS and memory of a round where it is not.  So a round is free of branches (but for two around a stream's first block), its reads
+// stand together ahead of what needs them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying over its words took 24
 // of the 90 vector operations of half a group, against 14 of 66 and six LDS accesses more.  3088 chunks of 64 KiB 77 -> 72 us, 45 MB in
 // chunks of 256 KiB with the statistics 98 -> 83, 256 chunks of 64 KiB at 32 sub-streams with them 129 -> 107.
 template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_emit_kernel(EncArgs a)
@@ -1224,7 +1224,8 @@ extern "C" int dc_compress_chunks_dev_workspace(uint64_t raw_bytes, const dc_par
     if (params->format != DC_FORMAT_ID) return DC_E_FORMAT;
     const uint64_t nc = (raw_bytes + params->chunk_bytes - 1) / params->chunk_bytes;
     *workspace_bytes = align256(nc * 256) + align256(nc * params->n_streams * 4) + align256(nc * 4);
-    // tANS: the frequencies, the first states and one 32-bit item per two bytes besides
+    // tANS: the frequencies, the first states and the items besides.  Of the 32 bytes for every group of 16 the items take 24 (item_place); the
+    // size stays what callers have set aside, and what the fixed workspace below refuses stays refused.
     if (params->codec == DC_CODEC_TANS)
         *workspace_bytes += align256(nc * 512) + align256(nc * params->n_streams * 2) + align256(nc * params->chunk_bytes * 2);
     return DC_OK;
@@ -1232,7 +1233,7 @@ extern "C" int dc_compress_chunks_dev_workspace(uint64_t raw_bytes, const dc_par
 
 namespace {
 
-// The three launches of the compression, with the workspace (code lengths, sub-stream sizes and payload
+// The two or three launches of the compression, with the workspace (code lengths, sub-stream sizes and payload
 // sizes between them) wherever the caller of this function has it.
 int compress_chunks_on_stream(const int8_t *src_dev, uint64_t raw_bytes, const dc_params *params, uint8_t *blob_dev,
                               uint64_t blob_cap, dc_chunk *table_dev, uint64_t table_cap, void *workspace_dev,
