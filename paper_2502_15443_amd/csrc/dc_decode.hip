@@ -785,15 +785,17 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     constexpr bool UNI = CPW == 1; // all lanes of the wave belong to one stream set
 
     // ---- products of whole rows: the rows of the chunk, and what lane r of the chunk's first wave does with the sum of
-    // the r-th.  Where other waves are added up at the end its scale is asked for now: then the trip to memory would be one that nothing hides.
-    // (A wave alone: asked for now 4096 chunks of a row of 4 KiB took 12.7 us, at the end 12.2; 65 536 bytes a chunk the same.)
+    // the r-th.  Its scale is asked for now: at the end the trip to memory would be one that nothing hides.  (Not by a wave alone with its
+    // chunk, which has nothing that hides it now either: asked for at the end 4096 chunks of a row of 4 KiB at 64 sub-streams take 12.2 instead of 12.7
+    // us, longer chunks the same.  At 32 sub-streams, two chunks to a wave, the end is 2 to 3 % slower.)
     constexpr bool kRows = MODE == kModeGemvRows || MODE == kModeGemvW8A8Rows;
     const uint32_t own_row = kRows ? (uint32_t)(dst_pos / mat.cols) + cl : 0u;
     const bool has_row = kRows && k < a.n_chunks && wave == 0 && cl < a.chunk_bytes / mat.cols && own_row < mat.rows;
     float own_scale = 0.0f;
-    if (WAVES > 1 && has_row) own_scale = mat.row_scale[own_row];
+    constexpr bool kScaleNow = S != 64;
+    if (kScaleNow && has_row) own_scale = mat.row_scale[own_row];
     auto finish_rows = [&](auto sum) {
-        if (has_row) store_row(mat, own_row, scaled_sum(mat, WAVES > 1 ? own_scale : mat.row_scale[own_row], decltype(sum)(0) + sum));
+        if (has_row) store_row(mat, own_row, scaled_sum(mat, kScaleNow ? own_scale : mat.row_scale[own_row], decltype(sum)(0) + sum));
     };
     // ---- ordered product: the same for the sums that the chunk leaves in the workspace.  One for every row that the chunk's
     // place in the matrix touches, whatever its table entry says, because the finish kernel adds them all up.
