@@ -1637,15 +1637,15 @@ uint32_t device_simds()
 
 // Whether a launch of `waves` wavefronts takes the FEW kernels.  Up to one wavefront a SIMD it is as long as a lane's chain of look-ups, and FEW
 // is up to 19 % shorter, the more the longer the chunks (4 KiB at 256 sub-streams: as long).  The conversion to bf16 at 32
-// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that; from a half on it loses 4 to 10 % in chunks of
-// 64 KiB.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks are raw and between 2 % longer and 7 % shorter
+// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that, in chunks of up to 32 KiB 1 to 3 % up to a half,
+// and loses 4 to 10 % in chunks of 64 KiB from there on.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks are raw and between 2 % longer and 7 % shorter
 // where none is; short chunks, in which the set-up counts for more, lose there (4 KiB: 1 to 3 %; bf16 of 16 KiB: 1 to 3 %), and so do 32
 // sub-streams (1 to 2 %).  At three, where the wavefronts hide each other's look-ups and the LDS is what they wait for, it is longer by 7
 // to 17 %.
 bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
 {
     const bool bf16 = mode == kModeBf16;
-    if (waves <= simds) return n_streams >= 64 || !bf16 || waves <= simds / 4;
+    if (waves <= simds) return n_streams >= 64 || !bf16 || waves <= (chunk_bytes <= 32768 ? simds / 2 : simds / 4);
     return n_streams >= 64 && waves <= 2ull * simds && chunk_bytes >= (bf16 ? 32768u : 16384u);
 }
 

@@ -88,8 +88,8 @@ def test_decoder_of_many_wavefronts(decode, S):
 @pytest.mark.parametrize("mode,S,chunk,simds,line", [
     (BYTES, 32, 65536, 1024, 1024), (BYTES, 256, 4096, 1024, 1024), (BYTES, 256, 16384, 1024, 2048),
     (PRODUCT, 64, 16368, 1024, 1024), (PRODUCT_INT8, 128, 65536, 1024, 2048),
-    (BF16, 32, 65536, 1024, 256), (BF16, 64, 16384, 1024, 1024), (BF16, 64, 32768, 1024, 2048),
-    (BYTES, 64, 65536, 128, 256), (BF16, 32, 4096, 128, 32), (BYTES, 64, 65536, 0, 0)])
+    (BF16, 32, 65536, 1024, 256), (BF16, 32, 32768, 1024, 512), (BF16, 64, 16384, 1024, 1024), (BF16, 64, 32768, 1024, 2048),
+    (BYTES, 64, 65536, 128, 256), (BF16, 32, 4096, 128, 64), (BYTES, 64, 65536, 0, 0)])
 def test_line_for_launches_of_few_wavefronts(decode, mode, S, chunk, simds, line):
     # in wavefronts a SIMD of the device, and by what a lane has to decode
     few = lambda waves: bool(subprocess.run([decode.exe, "few"] + [str(v) for v in (mode, S, waves, chunk, simds)]).returncode)
