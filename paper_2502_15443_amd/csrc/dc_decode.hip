@@ -1621,27 +1621,31 @@ bool decode_params_ok(const dc_params *p)
     return p->n_streams == 32 || p->n_streams == 64 || p->n_streams == 128 || p->n_streams == 256;
 }
 
-// SIMDs of the current device, four to a compute unit, looked up once per device; 0 if the runtime does not say.
+// SIMDs of the current device, four to a compute unit, looked up once per device; 0 if the runtime does not say, which is no error of the call.
 uint32_t device_simds()
 {
     static std::atomic<uint32_t> simds_of_device[kMaxDevices];
     int dev = -1, units = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-    uint32_t n = simds_of_device[dev].load(std::memory_order_relaxed);
-    if (n == 0 && hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && units > 0) {
-        n = 4u * (uint32_t)units;
-        simds_of_device[dev].store(n, std::memory_order_relaxed);
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
+        uint32_t n = simds_of_device[dev].load(std::memory_order_relaxed);
+        if (n) return n;
+        if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && units > 0) {
+            n = 4u * (uint32_t)units;
+            simds_of_device[dev].store(n, std::memory_order_relaxed);
+            return n;
+        }
     }
-    return n;
+    (void)hipGetLastError(); // not to be taken for the launch's
+    return 0;
 }
 
-// Whether a launch of `waves` wavefronts takes the FEW kernels.  Up to one wavefront a SIMD it is as long as a lane's chain of look-ups, and FEW
-// is up to 19 % shorter, the more the longer the chunks (4 KiB at 256 sub-streams: as long).  The conversion to bf16 at 32
-// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that, in chunks of up to 32 KiB 1 to 3 % up to a half,
-// and loses 4 to 10 % in chunks of 64 KiB from there on.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks are raw and between 2 % longer and 7 % shorter
-// where none is; short chunks, in which the set-up counts for more, lose there (4 KiB: 1 to 3 %; bf16 of 16 KiB: 1 to 3 %), and so do 32
-// sub-streams (1 to 2 %).  At three, where the wavefronts hide each other's look-ups and the LDS is what they wait for, it is longer by 7
-// to 17 %.
+// Whether a launch of `waves` wavefronts takes the FEW kernels.  Up to one wavefront a SIMD it is as long as a lane's chain of look-ups, and
+// FEW is up to 19 % shorter, the more the longer the chunks (4 KiB at 256 sub-streams: as long).  The conversion to bf16 at 32
+// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that, in chunks of up to 32 KiB 1 to 3 % up to a
+// half, and loses 4 to 10 % in chunks of 64 KiB from there on.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks
+// are raw and between 2 % longer and 7 % shorter where none is; short chunks, in which the set-up counts for more, lose there (4 KiB:
+// 1 to 3 %; bf16 of 16 KiB: 1 to 3 %), and so do 32 sub-streams (1 to 2 %).  At three, where the wavefronts hide each other's look-ups and
+// the LDS is what they wait for, it is longer by 7 to 17 %.
 bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
 {
     const bool bf16 = mode == kModeBf16;

@@ -880,9 +880,9 @@ constexpr uint32_t kWords = 8;  // words of a lane: two blocks
 
 // Bound by the issue of vector instructions where the chip is full (four workgroups a compute unit instead of eight cost 7 %), by the trips
 // to LDS and memory of a round where it is not.  So a round is free of branches (but for two around a stream's first block), its reads
-// stand together ahead of what needs them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying over its words took 24
-// of the 90 vector operations of half a group, against 14 of 66 and six LDS accesses more.  3088 chunks of 64 KiB 77 -> 72 us, 45 MB in
-// chunks of 256 KiB with the statistics 98 -> 83, 256 chunks of 64 KiB at 32 sub-streams with them 129 -> 107.
+// stand together ahead of what needs them, and the block at the position lies in LDS: kept in registers, selecting, merging and carrying
+// over its words took 24 of the 90 vector operations of half a group, against 14 of 66 and six LDS accesses more.  3088 chunks of 64 KiB
+// 77 -> 72 us, 45 MB in chunks of 256 KiB with the statistics 98 -> 83, 256 chunks of 64 KiB at 32 sub-streams with them 129 -> 107.
 template <int THREADS, int CODEC> __global__ __launch_bounds__(THREADS) void dc_emit_kernel(EncArgs a)
 {
     constexpr int WAVES = THREADS / 64;
