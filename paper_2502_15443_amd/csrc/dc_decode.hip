@@ -695,6 +695,137 @@ __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32
     return true;
 }
 
+// The decode table of a chunk, by its TPC threads (WAVES waves; HALVES: each half of a wave for a chunk of its own), of which this one is number ct.
+// nib: the code lengths of its values ct * SPL + s, four bits each.  Slot p of the table in code order (p = the next 11 stream bits, first bit
+// most significant) belongs to the code that covers p; codes in canonical order cover consecutive runs of 2^(11-length) slots.
+// (1) A value's rank among those of its length comes from a ballot for each length (four or eight values a lane: from counters of the lengths, three to
+// a register, summed over the lanes), the counts of the waves before from LDS.  Lane l has the counts of length l, and the first
+// slots of the lengths are a prefix sum over the lanes.  (2) Every value marks the first slot of its run.  A mark
+// is the run's first slot above the table entry, so that the mark that covers a slot is the largest up to it: every thread takes
+// 2048/threads consecutive slots, extends the marks forward over them, and writes the entries to the table at the
+// bit-reversed slot numbers (the stream is read least significant bit first).
+// (With the counters at 256 sub-streams too, the first codes added up by one lane, and marks without their slot, which a comparison and a
+// selection each carry forward, it took 370 instructions there, 215 now: a chunk alone on its compute unit 0.8 instead of 1.2 us.)
+// marks: 2048 words of the rings, SHARED: and of the place of the tables; counts: 16 words a wave at the place of the table (several waves).
+template <int TPC, int WAVES, bool HALVES, bool SHARED>
+__device__ __forceinline__ void build_code_table(uint32_t nib, uint32_t ct, uint32_t wave, uint32_t *marks, uint32_t (*counts)[16], uint16_t *table)
+{
+    constexpr int SPL = 256 / TPC;
+    constexpr uint32_t EPT = kTableEntries / TPC; // slots a thread fills
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t l = HALVES ? lane & 31u : lane; // the length that this lane has the counts of
+#pragma unroll
+    for (uint32_t i = 0; i < EPT / 4; i++) reinterpret_cast<u32x4 *>(marks)[ct + i * TPC] = u32x4{0, 0, 0, 0};
+    uint32_t len[SPL], rank[SPL], all = 0, waves_before = 0;
+#pragma unroll
+    for (int s = 0; s < SPL; s++) {
+        len[s] = (nib >> (4 * s)) & 15u;
+        if (len[s] > DC_MAX_CODE_LEN) len[s] = 0;
+        rank[s] = 0;
+    }
+    if constexpr (SPL <= 2) {
+#pragma unroll
+        for (uint32_t n = 1; n <= DC_MAX_CODE_LEN; n++) {
+            uint32_t total = 0, before = 0; // of this length: in the wave, with the lanes before
+            uint64_t m[SPL];
+#pragma unroll
+            for (int s = 0; s < SPL; s++) {
+                m[s] = __ballot(len[s] == n);
+                before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[s] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[s], before));
+                total += (uint32_t)__popcll(m[s]);
+            }
+            rank[0] = len[0] == n ? before : rank[0];
+            if (SPL == 2) rank[SPL - 1] = len[SPL - 1] == n ? before + (len[0] == n ? 1u : 0u) : rank[SPL - 1];
+            all = with_lane(all, n, total);
+        }
+        if (lane < 16) counts[wave][lane] = all;
+        __syncthreads();
+        all = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) {
+            const uint32_t c = counts[0][16 * w + lane]; // (of no use from lane 16 on)
+            waves_before += (uint32_t)w < wave ? c : 0u;
+            all += c;
+        }
+    } else {
+        // ten bits a length: length n in register (n-1)/3
+        uint32_t before[4] = {0, 0, 0, 0}, total = 0;
+#pragma unroll
+        for (int s = 0; s < SPL; s++)
+#pragma unroll
+            for (uint32_t r = 0; r < 4; r++)
+                if (len[s] != 0 && (len[s] - 1) / 3 == r) before[r] += 1u << (10 * ((len[s] - 1) % 3));
+#pragma unroll
+        for (uint32_t r = 0; r < 4; r++) {
+            const uint32_t incl = lanes_prefix_sum<HALVES>(before[r]);
+            before[r] = incl - before[r];
+            const uint32_t t = (uint32_t)__shfl((int)incl, TPC - 1, TPC);
+            total = (l - 1) / 3 == r ? t : total;
+        }
+        all = (total >> (10 * ((l - 1) % 3))) & 1023u;
+#pragma unroll
+        for (int s = 0; s < SPL; s++) {
+            const uint32_t r = (len[s] - 1) / 3, sh = 10 * ((len[s] - 1) % 3);
+            const uint32_t packed = r == 0 ? before[0] : r == 1 ? before[1] : r == 2 ? before[2] : before[3];
+            rank[s] = (packed >> sh) & 1023u;
+#pragma unroll
+            for (uint32_t q = 0; q < 4; q++)
+                if (r == q && len[s] != 0) before[q] += 1u << sh;
+        }
+        __syncthreads(); // the marks are clear
+    }
+    const uint32_t up = l <= DC_MAX_CODE_LEN ? kPeekBits - l : 0u;
+    uint32_t first = l != 0 && l <= DC_MAX_CODE_LEN ? all << up : 0u; // slots of this length, then of those up to it
+    const uint32_t own = first;
+    first += dpp_or_zero<0x111, 0xF>(first);
+    first += dpp_or_zero<0x112, 0xF>(first);
+    first += dpp_or_zero<0x114, 0xF>(first);
+    first += dpp_or_zero<0x118, 0xF>(first);
+    first += (waves_before << up) - own; // the first slot of this wave's first value of the length
+    // Thread ct's slots lie from word EPT * ct on, by fours in an order in which the lanes of a read spread over the banks.
+    constexpr uint32_t FOURS = EPT / 4;
+    auto place = [&](uint32_t p) { return p ^ ((p >> 6) & (FOURS - 1)) << 2; };
+#pragma unroll
+    for (int s = 0; s < SPL; s++) {
+        const uint32_t run = (uint32_t)kTableEntries >> len[s];
+        const uint32_t start = (uint32_t)__shfl((int)first, (int)len[s], HALVES ? 32 : 64) + (rank[s] << (kPeekBits - len[s]));
+        if (len[s] != 0 && start < (uint32_t)kTableEntries) {
+            const uint32_t mark = start << 16 | (ct * SPL + s) << 8 | len[s]; // never 0: the length is not
+            marks[place(start)] = mark;
+            // also at the first slot of every later wave that the run reaches into, so that no wave needs a mark from another wave's slots
+            if (WAVES > 1) {
+                constexpr uint32_t SHARE = kTableEntries / WAVES;
+                const uint32_t end = start + run < (uint32_t)kTableEntries ? start + run : kTableEntries;
+#pragma unroll 1
+                for (uint32_t p = (start | (SHARE - 1)) + 1; p < end; p += SHARE) marks[place(p)] = mark;
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t w[EPT], tail = 0; // the last mark among this thread's slots
+    const uint32_t turned = place(EPT * ct) - EPT * ct; // 4 times what the number of a four is combined with
+#pragma unroll
+    for (uint32_t i = 0; i < FOURS; i++) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(marks + EPT * ct + (turned ^ (4 * i)));
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            w[4 * i + j] = v[j];
+            tail = v[j] > tail ? v[j] : tail;
+        }
+    }
+    uint32_t cur = lanes_largest_below<HALVES>(tail);
+    if (SHARED) __syncthreads(); // the marks have been read
+    // slot EPT*ct + j in code order = slot bitrev(j) << (11-e) | bitrev(ct) in stream order, EPT = 2^e
+    constexpr int E = EPT == 64 ? 6 : EPT == 32 ? 5 : EPT == 16 ? 4 : 3;
+    const uint32_t out = lds_address(table) + 2 * (__brev(ct) >> (32 - (kPeekBits - E)));
+#pragma unroll
+    for (uint32_t i = 0; i < EPT; i++) {
+        cur = w[i] > cur ? w[i] : cur;
+        *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev(i) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)cur;
+    }
+    __syncthreads();
+}
+
 // A row's result from its sum.  y_i = scale_i * sum; W8A8: y_i = (float(sum) * scale_i) * x_scale, each step rounded
 // once, in this order.
 __device__ __forceinline__ float scaled_sum(const MatrixArgs &m, float scale, float sum) { return scale * sum; }
@@ -733,17 +864,15 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     constexpr uint32_t kHeader = (kFront + 2 * S + 4 * (S / Geometry<S>::kLanesPerChunk) + 15) / 16 * 16;
 
     // One block of LDS: the rings (4 KiB a wave, 4 KiB aligned) and then the decode tables.  While
-    // the tables are built, before any ring is used, the front part holds the slot markers (one
-    // u16 per table slot in code order, 4 KiB a chunk) and the start of the table part holds the
-    // first codes of the lengths and the per-wave length counts.
+    // the tables are built, before any ring is used, the front part holds the slot markers (8 KiB a chunk; where the rings are
+    // smaller, they reach into the tables) and the start of the table part holds the waves' counts of the lengths.
     constexpr int kRingStride = Ring<S, FEW>::kStride;
     constexpr int kFrontWords = FEW ? WAVES * kRingStride : (WAVES > CPW ? WAVES : CPW) * kRingStride;
     // (tANS: 2048 entries of 32 bits, then 256 words of (first place, frequency) and a word per wave)
     constexpr int kTableWords = CODEC == DC_CODEC_TANS ? kTableEntries + 256 + 16 : CPW * kTableEntries / 2;
     __shared__ __attribute__((aligned(4 * kRingStride))) uint32_t lds_all[kFrontWords + kTableWords];
     uint16_t(*lds_table)[kTableEntries] = reinterpret_cast<uint16_t(*)[kTableEntries]>(lds_all + kFrontWords);
-    uint32_t(*lds_first)[16] = reinterpret_cast<uint32_t(*)[16]>(lds_all + kFrontWords); // [wave * CPW + sub][length]
-    uint32_t(*lds_counts)[4] = reinterpret_cast<uint32_t(*)[4]>(lds_all + kFrontWords + 16 * WAVES * CPW); // [wave]
+    uint32_t(*lds_counts)[16] = reinterpret_cast<uint32_t(*)[16]>(lds_all + kFrontWords); // [wave][length]
 
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
@@ -753,14 +882,15 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     const uint64_t k = (uint64_t)blockIdx.x * CPW + sub;
 
     // ---- the blob's trailer: a blob of another format, or of other parameters, is left undecoded
-    const uint32_t *closing = reinterpret_cast<const uint32_t *>(a.blob + a.blob_bytes - DC_TRAILER_BYTES);
-    const bool readable = closing[0] == a.trailer[0] && closing[1] == a.trailer[1] && closing[2] == a.trailer[2] &&
-                          closing[3] == a.trailer[3];
+    const u32x4 closing = *reinterpret_cast<const u32x4 *>(a.blob + a.blob_bytes - DC_TRAILER_BYTES);
     // ---- chunk table entry, checked so that nothing below can leave the blob or the destination
-    // (asked for together with the trailer, not once that has been found right: a trip to memory less for every workgroup)
-    dc_chunk ent = {0, 0, 0};
-    if (k < a.n_chunks) ent = a.table[k];
-    bool active = readable && k < a.n_chunks;
+    // (asked for together with the trailer, and every word of that at once: compared word by word, with a branch behind each, they were four
+    // trips one after the other and the entry a fifth)
+    const dc_chunk ent = a.table[k < a.n_chunks ? k : a.n_chunks - 1];
+    if (G::kChunksPerWave == 1) in_registers(closing, ent.off, ent.comp_bytes, ent.raw_bytes_flags);
+    auto two = [](uint32_t low, uint32_t high) { return (uint64_t)high << 32 | low; };
+    bool active = two(closing[0], closing[1]) == two(a.trailer[0], a.trailer[1]) && two(closing[2], closing[3]) == two(a.trailer[2], a.trailer[3]) &&
+                  k < a.n_chunks;
     const uint32_t raw = ent.raw_bytes_flags & ~DC_CHUNK_RAW;
     const bool is_raw = (ent.raw_bytes_flags & DC_CHUNK_RAW) != 0;
     // fused modes: the matrix the chunk belongs to, and the chunk's number inside it
@@ -896,123 +1026,11 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         }
     }
 
-    // ---- decode table.  Slot p of the table in code order (p = the next 11 stream bits, first bit
-    // most significant) belongs to the code that covers p; codes in canonical order cover
-    // consecutive runs of 2^(11-length) slots.  (1) The threads of the chunk rank the 256 code
-    // lengths (packed per-length counters, prefix sum over lanes and waves) and every symbol marks
-    // the first slot of its run with its table entry.  (2) Every thread takes 2048/threads
-    // consecutive slots, extends the marks forward over them, and writes the entries to the table
-    // at the bit-reversed slot numbers (the stream is read least significant bit first).
     if (build_table) {
-        constexpr int EPT = kTableEntries / TPC; // slots a thread fills
-        uint16_t *marks = reinterpret_cast<uint16_t *>(lds_all) + sub * kTableEntries;
-        {
-            uint4 *z = reinterpret_cast<uint4 *>(marks);
-            for (uint32_t i = ct; i < kTableEntries * 2 / 16; i += TPC) z[i] = make_uint4(0, 0, 0, 0);
-        }
-        // this thread's SPL code lengths, values v = ct*SPL + s (asked for above, with the rest of the header)
-        const uint32_t nib = SPL == 1 ? (nib_word >> (4 * (ct & 1))) & 15u : nib_word;
-        // counts per length, packed three 10-bit fields a register: length l in reg (l-1)/3
-        uint32_t mine[4] = {0, 0, 0, 0};
-        uint32_t len_of[SPL];
-#pragma unroll
-        for (int s = 0; s < SPL; s++) {
-            uint32_t l = (nib >> (4 * s)) & 15u;
-            if (l > DC_MAX_CODE_LEN) l = 0;
-            len_of[s] = l;
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (l != 0 && (l - 1) / 3 == (uint32_t)r) mine[r] += 1u << (10 * ((l - 1) % 3));
-        }
-        uint32_t before[4], total[4];
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const uint32_t incl = lanes_prefix_sum<CPW == 2>(mine[r]);
-            before[r] = incl - mine[r];
-            if (WAVES > 1) {
-                if (lane == 63) lds_counts[wave][r] = incl;
-            } else if (CPW == 1) {
-                total[r] = __builtin_amdgcn_readlane(incl, 63);
-            } else {
-                total[r] = __shfl(incl, LPC - 1, LPC);
-            }
-        }
-        __syncthreads();
-        if (WAVES > 1) {
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                total[r] = 0;
-#pragma unroll
-                for (int w = 0; w < WAVES; w++) {
-                    const uint32_t c = lds_counts[w][r];
-                    if ((uint32_t)w < wave) before[r] += c;
-                    total[r] += c;
-                }
-            }
-        }
-        // left-aligned (11-bit) first code of every length, once per wave and chunk
-        uint32_t *first_of = lds_first[wave * CPW + sub];
-        if (cl == 0) {
-            uint32_t first = 0;
-#pragma unroll
-            for (int l = 1; l <= DC_MAX_CODE_LEN; l++) {
-                first_of[l] = first;
-                const uint32_t c = (total[(l - 1) / 3] >> (10 * ((l - 1) % 3))) & 1023u;
-                first += c << (kPeekBits - l);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int s = 0; s < SPL; s++) {
-            const uint32_t l = len_of[s];
-            if (l != 0) {
-                const uint32_t r = (l - 1) / 3, sh = 10 * ((l - 1) % 3);
-                const uint32_t packed = r == 0 ? before[0] : r == 1 ? before[1] : r == 2 ? before[2] : before[3];
-                const uint32_t rank = (packed >> sh) & 1023u;
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    if (r == (uint32_t)q) before[q] += 1u << sh;
-                const uint32_t run = 1u << (kPeekBits - l);
-                const uint32_t start = first_of[l] + rank * run;
-                const uint16_t entry = (uint16_t)(l | ((ct * SPL + s) << 8)); // never 0: 0 means "no mark"
-                // also at the first slot of every later wave that the run reaches into, so that no
-                // wave needs a mark from another wave's slots
-                for (uint32_t p = start; p < start + run && p < (uint32_t)kTableEntries; p += kTableEntries / WAVES)
-                    marks[p] = entry;
-            }
-        }
-        __syncthreads();
-        uint32_t w[EPT / 2];
-        {
-            const uint4 *m4 = reinterpret_cast<const uint4 *>(marks + EPT * ct);
-#pragma unroll
-            for (int i = 0; i < EPT / 8; i++) {
-                const uint4 v = m4[i];
-                w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
-            }
-        }
-        uint32_t tail = 0; // last mark among this thread's slots
-#pragma unroll
-        for (int i = 0; i < EPT / 2; i++) {
-            const uint32_t lo = w[i] & 0xFFFFu, hi = w[i] >> 16;
-            tail = lo ? lo : tail;
-            tail = hi ? hi : tail;
-        }
-        uint32_t cur = lanes_last_nonzero_below<CPW == 2>(tail);
-        // slot EPT*ct + j in code order = slot bitrev(j) << (11-e) | bitrev(ct) in stream order, EPT = 2^e
-        constexpr int E = EPT == 64 ? 6 : EPT == 32 ? 5 : EPT == 16 ? 4 : 3;
-        const uint32_t out = lds_address(lds_table[sub]) + 2 * (__brev(ct) >> (32 - (kPeekBits - E)));
-#pragma unroll
-        for (int i = 0; i < EPT / 2; i++) {
-            const uint32_t lo = w[i] & 0xFFFFu, hi = w[i] >> 16;
-            cur = lo ? lo : cur;
-            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)cur;
-            cur = hi ? hi : cur;
-            *(lds_u16 *)(uintptr_t)(out + 2 * ((__brev((uint32_t)(2 * i + 1)) >> (32 - E)) << (kPeekBits - E))) = (uint16_t)cur;
-        }
-        __syncthreads();
+        uint32_t *marks = lds_all + sub * kTableEntries;
+        constexpr bool SHARED = kFrontWords < CPW * kTableEntries;
+        static_assert(!SHARED || (WAVES == 1 && kFrontWords + kTableWords >= CPW * kTableEntries), "room for the marks");
+        build_code_table<TPC, WAVES, CPW == 2, SHARED>(SPL == 1 ? (nib_word >> (4 * (ct & 1))) & 15u : nib_word, ct, wave, marks, lds_counts, tbl);
     }
 
     // ---- sub-stream set-up, second half: the ring is free now

@@ -78,6 +78,14 @@ __device__ __forceinline__ void anew(uint32_t &v)
 #endif
 }
 
+// All of these, the same in all lanes, are in their registers from here on: none is asked for once another has come.
+__device__ __forceinline__ void in_registers(const u32x4 &a, uint64_t b, uint32_t c, uint32_t d)
+{
+#ifdef __AMDGCN__
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d));
+#endif
+}
+
 // The value is in its register from here on (SAME: it is the same in all lanes, a scalar register): it is not worked out later, and
 // a loop behind this place does not wait for the load that it came from.
 template <bool SAME, typename T> __device__ __forceinline__ void in_register(const T &v)
@@ -95,6 +103,19 @@ template <bool SAME, typename T> __device__ __forceinline__ void in_register(con
 template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+
+// v with the value of one lane (the same number in all lanes) replaced by w (the same in all lanes).
+#ifdef __AMDGCN__
+extern "C" __device__ uint32_t dc_llvm_writelane(uint32_t w, uint32_t lane, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
+#endif
+__device__ __forceinline__ uint32_t with_lane(uint32_t v, uint32_t lane, uint32_t w)
+{
+#ifdef __AMDGCN__
+    return dc_llvm_writelane(w, lane, v);
+#else
+    return (threadIdx.x & 63u) == lane ? w : v;
+#endif
 }
 
 // Inclusive prefix sum over the 64 lanes (HALVES: over each half of 32 lanes on its own).
@@ -120,6 +141,21 @@ template <bool HALVES> __device__ __forceinline__ uint32_t lanes_last_nonzero_be
     t = dpp_or_zero<0x118, 0xF>(v); v = v ? v : t;
     t = dpp_or_zero<0x142, 0xA>(v); v = v ? v : t;
     if (!HALVES) { t = dpp_or_zero<0x143, 0xC>(v); v = v ? v : t; }
+    return v;
+}
+
+// For every lane the largest value among the lanes below it (0 if none).
+template <bool HALVES> __device__ __forceinline__ uint32_t lanes_largest_below(uint32_t v)
+{
+    auto with = [&](uint32_t t) { v = t > v ? t : v; };
+    v = dpp_or_zero<0x138, 0xF>(v);
+    if (HALVES) v = threadIdx.x & 31u ? v : 0u;
+    with(dpp_or_zero<0x111, 0xF>(v));
+    with(dpp_or_zero<0x112, 0xF>(v));
+    with(dpp_or_zero<0x114, 0xF>(v));
+    with(dpp_or_zero<0x118, 0xF>(v));
+    with(dpp_or_zero<0x142, 0xA>(v));
+    if (!HALVES) with(dpp_or_zero<0x143, 0xC>(v));
     return v;
 }
 
