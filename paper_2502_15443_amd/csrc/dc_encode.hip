@@ -194,19 +194,54 @@ __device__ __forceinline__ uint32_t wave_sorted(uint32_t k, uint32_t lane)
     return k;
 }
 
+// How many of a chunk's leaves (ascending: count << 8 | value) weigh no more than a package.  Weights are put into
+// buckets by their exponent and the seven bits behind the first one; for every bucket the number of leaves in the buckets before it is kept.  The
+// leaves of the package's own bucket, two as a rule, are looked at together, kAtOnce of them, once halving has left no more; up to a
+// weight of 255 all of them count, because there a bucket is one weight.
+struct LeafRanks {
+    static constexpr uint32_t kBits = 7, kLast = (20 << kBits) + 1; // a bucket heavier than any leaf (a chunk has 2^20 bytes at most)
+    static constexpr uint32_t kEntries = 256 * 12;                  // kLast + 2 at least; as many for every thread
+    static constexpr uint32_t kAtOnce = 4;                          // leaves behind the last that may be looked at
+    uint16_t *lighter;
+    const uint32_t *leaves;
+    static __device__ __forceinline__ uint32_t bucket(uint32_t weight) // weight: 1 to 2^24
+    {
+        const uint32_t b = (__float_as_uint((float)weight) >> (23 - kBits)) - (127u << kBits);
+        return b < kLast ? b : kLast;
+    }
+    __device__ __forceinline__ uint32_t not_heavier(uint32_t weight) const
+    {
+        const uint32_t b = bucket(weight), most = weight << 8 | 0xFFu;
+        uint32_t lo = lighter[b], hi = lighter[b + 1];
+        lo = weight < 2u << kBits ? hi : lo;
+        while (hi - lo > kAtOnce) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (leaves[mid] <= most) lo = mid + 1;
+            else hi = mid;
+        }
+        uint32_t more = 0; // (behind the bucket's last leaf all are heavier)
+#pragma unroll
+        for (uint32_t i = 0; i < kAtOnce; i++) more += leaves[lo + i] <= most ? 1u : 0u;
+        return lo + more;
+    }
+};
+
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void dc_codes_kernel(EncArgs a)
 {
     // 16 KiB used twice: first the histogram columns, then the tables of the package-merge.
-    __shared__ __attribute__((aligned(64))) uint32_t arena[4112];
+    __shared__ __attribute__((aligned(64))) uint32_t arena[4096];
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t key[256];    // count << 8 | byte value, ascending after the sort; absent values last
+    __shared__ uint32_t key[256 + LeafRanks::kAtOnce]; // count << 8 | byte value, ascending after the sort; absent values last
     __shared__ uint32_t bought_leaves[kL];
     __shared__ uint8_t len_of[256];
     __shared__ uint32_t sbits[256];
     __shared__ uint32_t area_bytes[4]; // per stream set: whole blocks and short first blocks
-    uint32_t *unsorted = arena;                                                       // [256] the waves' sorted keys
-    uint32_t(*pack)[256] = reinterpret_cast<uint32_t(*)[256]>(arena + 256);           // packages made of a level, two levels in turn
-    uint16_t(*leaves_before)[514] = reinterpret_cast<uint16_t(*)[514]>(arena + 768);  // [kL][514]
+    uint32_t *unsorted = arena;                                                          // [256] the waves' sorted keys
+    uint32_t(*in_waves)[4][4] = reinterpret_cast<uint32_t(*)[4][4]>(arena);              // [two in turn][limit][wave], see wave_limits
+    uint32_t *lighter = arena + 256;                                                     // LeafRanks
+    uint32_t(*items)[512] = reinterpret_cast<uint32_t(*)[512]>(arena + 1792);            // packages where they lie among a level's items, two levels in turn
+    uint16_t(*leaves_before)[256] = reinterpret_cast<uint16_t(*)[256]>(arena + 2816);    // [kL - 1][256], of level 1 and up
+    static_assert(LeafRanks::kEntries / 2 == 1536 && 2816 + (kL - 1) * 128 <= 4096, "one behind the other");
 
     const uint32_t t = threadIdx.x;
     const uint64_t k = blockIdx.x;
@@ -218,6 +253,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
     if (t < 4) area_bytes[t] = 0;
     chunk_histogram(src, raw, arena, hist);
 
+    for (uint32_t i = t; i < (LeafRanks::kEntries / 2 + 1024) / 4; i += 256) reinterpret_cast<u32x4 *>(lighter)[i] = u32x4{0, 0, 0, 0};
+    if (t < LeafRanks::kAtOnce) key[256 + t] = ~0u;
     const uint32_t cnt = hist[t];
     const uint32_t n = (uint32_t)__syncthreads_count(cnt != 0);
     // leaves in order of (count, byte value): sorted in the waves first, then every key finds its place among the other
@@ -245,50 +282,77 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
     } else if (n >= 2) {
         // Package-merge: level 0 is the sorted leaves; level j is the leaves merged with the pairs of
         // level j-1, a leaf before a package of equal weight.  leaves_before[j][m] = leaves among the
-        // first m items of level j.
-        // Thread t owns items 2t and 2t + 1 of a level, the pair that is package t of the next: it searches for the number a
-        // of leaves among the 2t items before them, so a level costs one search and one barrier.  From level to
-        // level items get lighter and a falls, by about half as much each time, so the search begins that far below the
-        // last a and is mostly over after a few steps.  (Two searches of nine steps and two barriers a level, the items written
-        // out: 9.3 of the 28 us of a chunk alone on its compute unit; together with the loads in flight and the sort above the
-        // call takes 157 instead of 169 us on 3088 chunks of 64 KiB, 36 instead of 43 on 1024 of 16 KiB.)
-        uint32_t size = n;
-        for (uint32_t m = t; m < 514; m += 256) leaves_before[0][m] = (uint16_t)(m < n ? m : n);
-        if (2 * t + 1 < n) pack[0][t] = (key[2 * t] >> 8) + (key[2 * t + 1] >> 8);
-        const uint32_t d = 2 * t;
-        uint32_t a_last = d < n ? d : n;
-        for (int j = 1; j < kL; j++) {
-            __syncthreads();
-            const uint32_t *packs = pack[(j - 1) & 1];
-            const uint32_t npk = size / 2;
-            size = n + npk;
-            uint32_t a = 0, a1 = 0, weight = 0;
-            if (d <= size) {
-                // the smallest a with leaf a heavier than package d - 1 - a
-                uint32_t lo = d > npk ? d - npk : 0, hi = a_last;
-                const uint32_t fall = j < 8 ? 256u >> j : 1u;
-                uint32_t mid = lo + fall < hi ? hi - fall : (lo + hi) / 2;
-                while (lo < hi) {
-                    if (key[mid] >> 8 <= packs[d - 1 - mid]) lo = mid + 1;
-                    else hi = mid;
-                    mid = (lo + hi) / 2;
-                }
-                a = a1 = lo;
-                uint32_t b = d - a;
-                // items d and d + 1
-                const uint32_t l0 = key[a < 255 ? a : 255] >> 8, l1 = key[a < 254 ? a + 1 : 255] >> 8;
-                const uint32_t p0 = packs[b < 255 ? b : 255], p1 = packs[b < 254 ? b + 1 : 255];
-                const bool leaf0 = a < n && (b >= npk || l0 <= p0);
-                a1 += leaf0;
-                b += !leaf0;
-                const uint32_t l = leaf0 ? l1 : l0, p = leaf0 ? p0 : p1;
-                const bool leaf1 = a1 < n && (b >= npk || l <= p);
-                weight = (leaf0 ? l0 : p0) + (leaf1 ? l : p);
-                a_last = a;
-                leaves_before[j][d] = (uint16_t)a;
-                leaves_before[j][d + 1] = (uint16_t)(d + 1 <= size ? a1 : n);
+        // first 2m items of level j (no other numbers are asked for).
+        // Thread t makes package t of every level.  The leaves are the same at all levels, so how many of them come before a package is
+        // looked up (LeafRanks); the package goes to its place among the items, what is left empty there are the leaves in their
+        // order, and a thread finds its next package's two items by counting packages: one barrier a level and four
+        // trips to LDS one after the other, where a search for the number of leaves before every second item took some ten.  A chunk alone on
+        // its compute unit spends 5.2 us here instead of 6.5, together with seven others 7.0 instead of 8.4; the call 31.8 instead of 32.9 us on 256
+        // chunks of 64 KiB, 18.1 instead of 18.9 on 64 of 16 KiB, 146.2 instead of 148.1 on 3088 of 64 KiB.
+        const uint32_t lane = t & 63u, wave = t >> 6;
+        // How many threads' values are below each of three limits, 1 to 3 times `limit`, wave by wave.
+        auto wave_limits = [&](uint32_t (*to)[4], uint32_t v, uint32_t limit) {
+            uint32_t count = 0;
+#pragma unroll
+            for (uint32_t w = 1; w < 4; w++) count = with_lane(count, w, (uint32_t)__popcll(__ballot(v < w * limit)));
+            if (lane < 4) to[lane][wave] = count;
+        };
+        auto below_own = [&](uint32_t (*from)[4]) { // those below this wave's limit
+            const u32x4 c = *reinterpret_cast<const u32x4 *>(from[wave]);
+            return c[0] + c[1] + c[2] + c[3];
+        };
+        const LeafRanks ranks = {reinterpret_cast<uint16_t *>(lighter), key};
+        {
+            const uint32_t own = LeafRanks::bucket(key[t] >> 8), next = t + 1 < n ? LeafRanks::bucket(key[t + 1 < 255 ? t + 1 : 255] >> 8) : ~0u;
+            if (t < n && own != next) ranks.lighter[own + 1] = (uint16_t)(t + 1); // the last leaf of its bucket
+            wave_limits(in_waves[0], t < n ? own + 1 : ~0u, LeafRanks::kEntries / 4);
+        }
+        __syncthreads();
+        {
+            // every bucket without a mark takes the one before it
+            constexpr int PER = LeafRanks::kEntries / 256 / 2;
+            uint32_t *mine = lighter + PER * t, w[PER], tail = 0;
+#pragma unroll
+            for (int i = 0; i < PER; i++) {
+                w[i] = mine[i];
+                tail = w[i] & 0xFFFFu ? w[i] & 0xFFFFu : tail;
+                tail = w[i] >> 16 ? w[i] >> 16 : tail;
             }
-            if (d + 1 < size) pack[j & 1][t] = weight;
+            uint32_t cur = lanes_last_nonzero_below<false>(tail);
+            cur = cur ? cur : below_own(in_waves[0]);
+#pragma unroll
+            for (int i = 0; i < PER; i++) {
+                const uint32_t lo = w[i] & 0xFFFFu ? w[i] & 0xFFFFu : cur;
+                cur = w[i] >> 16 ? w[i] >> 16 : lo;
+                mine[i] = lo | cur << 16;
+            }
+        }
+        uint32_t size = n;
+        uint32_t weight = (key[2 * t < 255 ? 2 * t : 255] >> 8) + (key[2 * t < 254 ? 2 * t + 1 : 255] >> 8);
+        __syncthreads();
+#pragma unroll 1
+        for (int j = 1; j < kL; j++) {
+            const uint32_t packages = size / 2;
+            size = n + packages;
+            uint32_t *level = items[j & 1];
+            uint32_t place = ~0u;
+            if (t < packages) {
+                place = t + ranks.not_heavier(weight);
+                level[place] = weight;
+            }
+            wave_limits(in_waves[j & 1], place, 128);
+            __syncthreads();
+            uint2 *pair = reinterpret_cast<uint2 *>(level) + t;
+            const uint2 v = *pair;
+            const uint32_t before = below_own(in_waves[j & 1]);
+            *pair = make_uint2(0, 0); // for the level after next
+            const uint64_t m0 = __ballot(v.x != 0), m1 = __ballot(v.y != 0);
+            uint32_t packs = __builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m0, before));
+            packs = __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1, packs));
+            const uint32_t a0 = 2 * t - packs, a1 = a0 + (v.x ? 0u : 1u); // the leaves that may be items 2t and 2t + 1
+            leaves_before[j - 1][t] = (uint16_t)a0;
+            const uint32_t l0 = key[a0 < 255 ? a0 : 255] >> 8, l1 = key[a1 < 255 ? a1 : 255] >> 8;
+            weight = (v.x ? v.x : l0) + (v.y ? v.y : l1);
         }
         __syncthreads();
         if (t == 0) {
@@ -296,7 +360,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
             for (int j = kL - 1; j >= 0; j--) {
                 uint32_t nl = 0;
                 if (bought > 0) {
-                    nl = leaves_before[j][bought];
+                    nl = j ? leaves_before[j - 1][bought / 2] : bought;
                     bought = 2 * (bought - nl);
                 }
                 bought_leaves[j] = nl;

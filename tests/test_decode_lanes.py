@@ -118,3 +118,21 @@ def test_products_have_the_same_bits_with_few_wavefronts_and_many(decode, S, row
     x = synth.gen_activation_bf16(cols, 7)
     few, many = (decode("ascending", c, C, S, oc.HUFFMAN, PRODUCT, rows, cols, scale, x, units=units) for units in (256, 0))
     assert np.array_equal(few, many) and few.size == 4 * rows
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("S,codec", [(32, oc.HUFFMAN), (64, oc.HUFFMAN), (128, oc.HUFFMAN), (256, oc.HUFFMAN),
+                                     (64, oc.TANS), (128, oc.TANS), (256, oc.TANS)])
+@pytest.mark.parametrize("probabilities", [
+    [1.0], [0.5, 0.5], [0.95, 0.05], [2.0 ** -min(i + 1, 14) for i in range(15)],  # runs over several waves' slots; lengths 1 to 11
+    [1 / 256] * 256, [0.002] * 200 + [0.6 / 56] * 56, [0.7] + [0.3 / 255] * 255])  # all lengths equal; two lengths; many states and one
+def test_tables_of_extreme_codes(decode, order, S, codec, probabilities):
+    r = np.random.default_rng(len(probabilities))
+    values = r.permutation(256)[:len(probabilities)].astype(np.uint8)
+    C, n = 8192, 8192 + 4096  # the second chunk is shorter
+    q = values[r.choice(len(values), n, p=np.array(probabilities) / sum(probabilities))]
+    if S == 32:
+        q = np.concatenate([q, q[:4096]])  # two chunks of a wave alike
+    c = oc.compress(q, C, S, codec=codec)
+    got = decode(order, c, C, S, codec, BYTES, q.size // 64, 64)
+    assert np.array_equal(got, q)

@@ -69,3 +69,30 @@ def test_compressor_results_over_the_workspace(encode, order, over, policy):
     used, status, table, blob = encode(order, 3, data, C, 64, policy=policy, over=(over,))
     assert status == 0 and used == want.blob.size
     assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
+
+
+def bytes_with_counts(counts, seed):
+    """A shuffled string with these counts of the values 0, 1, ..."""
+    data = np.repeat(np.arange(len(counts), dtype=np.uint8), counts)
+    return np.random.default_rng(seed).permutation(data)
+
+
+FIBONACCI = [1, 1, 2, 3, 5, 8, 13, 21, 34, 55, 89, 144, 233, 377, 610, 987, 1597, 2584, 4181, 6765]
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("counts", [
+    [1, 1], [3, 1], [1] * 256, [2] * 255, FIBONACCI,  # ties at every level; the length limit
+    [255] * 2 + [256] * 2 + [257] * 2 + [510, 511, 512, 513],  # where a bucket of weights begins to hold several
+    [256 + i // 9 for i in range(256)],  # many leaves in a bucket, packages between them
+    [1] * 200 + [300 + 2 * i for i in range(56)],
+    [2 ** 20 - 255] + [1] * 255])  # the heaviest leaf there is
+def test_code_lengths_of_constructed_counts(encode, order, counts):
+    # packages are counted among leaves of nearly and exactly their weight
+    data = bytes_with_counts(counts, len(counts))
+    C = (data.size + 15) // 16 * 16
+    S = 256 if C < 1 << 20 else 32
+    want = oc.compress(data, C, S)
+    used, status, table, blob = encode(order, 5, data, C, S)
+    assert status == 0 and used == want.blob.size
+    assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
