@@ -667,16 +667,18 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         const uint32_t states = lds_address(state_of);
         uint32_t X = kTansL, bits = 0;
         uint32_t w[4] = {0, 0, 0, 0};
+        uint32_t step[16];
+        auto step_at = [&](const uint32_t b[4], int i) { return step_of[(b[i >> 2] >> (8 * (i & 3))) & 0xFFu]; };
         auto load_group = [&](uint32_t r) {
             const u32x4 v = *reinterpret_cast<const u32x4 *>(src + 16 * (t + r * S));
             w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
         };
-        // codes a group, the bytes from the n-th on absent; its bytes are in w, those of group r - 1 are loaded meanwhile
+        // Codes a group, the bytes from the n-th on absent.  What its bytes do to X is in `step`, the bytes of group r - 1 are in w; those of group
+        // r - 2 are loaded, and what those of r - 1 do is looked up, while the chain waits for its states (looked up ahead of the chain, sixteen at a
+        // time: 688 chunks of 64 KiB 66.6 instead of 65.8 us, 45 MB in chunks of 256 KiB 112.9 instead of 109.7, at 128 sub-streams 76.0 instead of 75.1).
         auto code_group = [&](uint32_t r, uint32_t n, bool whole) {
-            uint32_t step[16];
-#pragma unroll
-            for (int i = 0; i < 16; i++) step[i] = step_of[(w[i >> 2] >> (8 * (i & 3))) & 0xFFu];
-            if (r > 0) load_group(r - 1);
+            const uint32_t before[4] = {w[0], w[1], w[2], w[3]};
+            if (r > 1) load_group(r - 2);
             uint32_t p[8], l[8];
 #pragma unroll
             for (int j = 7; j >= 0; j--) {
@@ -689,6 +691,7 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
                         width += nb;
                         X = lds_load16(states + (uint32_t)((int32_t)step[i] >> 16) + 2 * (X >> nb));
                     }
+                    step[i] = step_at(before, i);
                 }
                 p[j] = field;
                 l[j] = width;
@@ -705,6 +708,9 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
             const uint32_t n = raw - lo < 16 ? raw - lo : 16; // only a stream's last group may lack bytes
             w[0] = w[1] = w[2] = w[3] = 0;
             for (uint32_t i = 0; i < n; i++) w[i >> 2] |= (uint32_t)src[lo + i] << (8 * (i & 3u));
+#pragma unroll
+            for (int i = 0; i < 16; i++) step[i] = step_at(w, i);
+            if (r > 1) load_group(r - 2);
             code_group(--r, n, false);
         }
         while (r > 0) code_group(--r, 16, true);
