@@ -167,11 +167,12 @@ template <bool HALVES, typename T> __device__ __forceinline__ void lanes_add_run
 // mask, which is the byte offset of the table entry, so a look-up needs no shift of its own.
 // FEW: launches of few wavefronts (step_and_decode8_few).  A wave's 4 KiB of ring are followed by 4 KiB that hold the ring's first
 // four words again, so that words behind one another in the stream can be read without a wrap, and four words for blocks that are
-// nobody's.  With four waves to a chunk the LDS is busy enough for the second copy to cost more than it saves (4096 x 4096 at
-// 256 sub-streams 14.3 instead of 13.7 us; at 32, 64 and 128 it saves 3 %).
-template <int S, bool FEW> struct Ring {
-    static constexpr int kStride = FEW ? 2048 : kRingWords * 64; // words of LDS a wave
-    static constexpr bool kAgain = FEW && S < 256;
+// nobody's.  Where the LDS is busier the second copy costs more than it saves: with four waves to a chunk (4096 x 4096 at
+// 256 sub-streams 14.3 instead of 13.7 us), and from some three waves to a compute unit on (few_again); at 32, 64 and 128 it saves 3 % below.
+constexpr int kMany = 0, kFew = 1, kFewAgain = 2; // the order of a decoder's work: one of the latter two for FEW, kFewAgain with the second copy
+template <int ORDER> struct Ring {
+    static constexpr int kStride = ORDER != kMany ? 2048 : kRingWords * 64; // words of LDS a wave
+    static constexpr bool kAgain = ORDER == kFewAgain;
     static constexpr uint32_t kAgainAt = 4096, kNowhereAt = 5120; // bytes from the ring's start
 };
 
@@ -347,10 +348,10 @@ __device__ __forceinline__ void stream_fetch(Stream &s, Region &rg, uint32_t fie
 
 // Second half: block 0 shifted into place and the further blocks go into the ring, and the first words are read.
 // A tANS stream reads its first state, its first 11 bits, and the words after them.
-template <int CODEC, int S, bool FEW>
+template <int CODEC, int S, int ORDER>
 __device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, uint32_t ring_lane, uint32_t tbl)
 {
-    using R = Ring<S, FEW>;
+    using R = Ring<ORDER>;
     if (f.has_head) {
         const u32x4 b0 = {__builtin_amdgcn_alignbyte(f.v[1], f.v[0], f.shift), __builtin_amdgcn_alignbyte(f.v[2], f.v[1], f.shift),
                           __builtin_amdgcn_alignbyte(f.v[3], f.v[2], f.shift), __builtin_amdgcn_alignbyte(f.v4, f.v[3], f.shift)};
@@ -362,7 +363,7 @@ __device__ __forceinline__ void stream_start(Stream &s, const StreamFetch &f, ui
         if (f.got[t]) push_block(ring_lane + ((t + 1) << 10), f.b[t]);
     s.pos = 64u * f.pad - 8u * Lead<CODEC>::kBits; // the stream begins `pad` bytes into block 0
     read_window<false>(s, 0, ring_lane);
-    if (FEW) {
+    if (ORDER != kMany) {
         s.nowhere = ring_lane + R::kNowhereAt;
 #pragma unroll
         for (int p = 0; p < 2; p++) {
@@ -492,7 +493,7 @@ __device__ __forceinline__ void step_and_decode8_few(Stream &s, Region &rg, uint
     shift_down<2>(w, e[2]); // from here on two words hold what may still be needed, one after the sixth symbol
     s.blk[P] = *reinterpret_cast<const u32x4 *>(rg.payload8 + (rg.next_block + rank) * kBlockBytes);
     s.slot[P] = want ? (s.asked & 0xC00u) | ring_lane : s.nowhere;
-    if (AGAIN) s.again[P] = s.slot[P] == ring_lane ? ring_lane + Ring<64, true>::kAgainAt : s.nowhere;
+    if (AGAIN) s.again[P] = s.slot[P] == ring_lane ? ring_lane + Ring<kFewAgain>::kAgainAt : s.nowhere;
     s.asked += want ? 1024u : 0u;
     rg.next_block += (uint32_t)__popcll(m);
     if (UNIFORM) rg.next_block = __builtin_amdgcn_readfirstlane(rg.next_block);
@@ -532,13 +533,13 @@ __device__ __forceinline__ void step_and_decode8_few(Stream &s, Region &rg, uint
 }
 
 // A step of the placement rule and the half group behind it.
-template <int S, int P, int CODEC, bool FEW, typename Meanwhile = Nothing>
+template <int S, int P, int CODEC, int ORDER, typename Meanwhile = Nothing>
 __device__ __forceinline__ void step_and_decode8(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t e[8],
                                                  Meanwhile meanwhile = Meanwhile())
 {
     constexpr bool UNIFORM = S >= 64;
-    if constexpr (FEW) {
-        step_and_decode8_few<UNIFORM, P, Ring<S, FEW>::kAgain>(s, rg, tbl, ring_lane, e, meanwhile);
+    if constexpr (ORDER != kMany) {
+        step_and_decode8_few<UNIFORM, P, Ring<ORDER>::kAgain>(s, rg, tbl, ring_lane, e, meanwhile);
     } else {
         stream_step<UNIFORM, P, CODEC>(s, rg, ring_lane);
         decode8<CODEC>(s, tbl, ring_lane, e);
@@ -546,21 +547,21 @@ __device__ __forceinline__ void step_and_decode8(Stream &s, Region &rg, uint32_t
 }
 
 // One whole group of 16 symbols with the two steps of the placement rule that precede its halves.
-template <int S, int CODEC, bool FEW, typename Meanwhile = Nothing>
+template <int S, int CODEC, int ORDER, typename Meanwhile = Nothing>
 __device__ __forceinline__ void decode16(Stream &s, Region &rg, uint32_t tbl, uint32_t ring_lane, uint32_t out[4],
                                          Meanwhile meanwhile = Meanwhile())
 {
     uint32_t e[8], f[8];
-    step_and_decode8<S, 0, CODEC, FEW>(s, rg, tbl, ring_lane, e, meanwhile);
-    if constexpr (FEW) {
-        step_and_decode8<S, 1, CODEC, FEW>(s, rg, tbl, ring_lane, f, late([&](int i) {
+    step_and_decode8<S, 0, CODEC, ORDER>(s, rg, tbl, ring_lane, e, meanwhile);
+    if constexpr (ORDER != kMany) {
+        step_and_decode8<S, 1, CODEC, ORDER>(s, rg, tbl, ring_lane, f, late([&](int i) {
             out[i] = pack4(e[4 * i], e[4 * i + 1], e[4 * i + 2], e[4 * i + 3]);
             in_register<false>(out[i]);
         }));
     } else {
         out[0] = pack4(e[0], e[1], e[2], e[3]);
         out[1] = pack4(e[4], e[5], e[6], e[7]);
-        step_and_decode8<S, 1, CODEC, FEW>(s, rg, tbl, ring_lane, f);
+        step_and_decode8<S, 1, CODEC, ORDER>(s, rg, tbl, ring_lane, f);
     }
     out[2] = pack4(f[0], f[1], f[2], f[3]);
     out[3] = pack4(f[4], f[5], f[6], f[7]);
@@ -855,7 +856,7 @@ __device__ __forceinline__ void store_row(const MatrixArgs &m, uint32_t row, flo
     if (m.y_bf16) m.y_bf16[row] = (uint16_t)(bf16x2(y, 0.0f) & 0xFFFFu);
 }
 
-template <int S, int MODE, int CODEC, bool FEW = false, bool TRACE = false>
+template <int S, int MODE, int CODEC, bool FEW = false, bool TRACE = false, bool AGAIN = FEW && S < 256>
 __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(DecodeArgs a)
 {
     using G = Geometry<S>;
@@ -885,7 +886,9 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     // One block of LDS: the rings (4 KiB a wave, 4 KiB aligned) and then the decode tables.  While
     // the tables are built, before any ring is used, the front part holds the slot markers (8 KiB a chunk; where the rings are
     // smaller, they reach into the tables) and the start of the table part holds the waves' counts of the lengths.
-    constexpr int kRingStride = Ring<S, FEW>::kStride;
+    constexpr int ORDER = AGAIN ? kFewAgain : FEW ? kFew : kMany;
+    static_assert(FEW || !AGAIN, "a second copy of what only FEW reads");
+    constexpr int kRingStride = Ring<ORDER>::kStride;
     constexpr int kFrontWords = FEW ? WAVES * kRingStride : (WAVES > CPW ? WAVES : CPW) * kRingStride;
     // (tANS: 2048 entries of 32 bits, then 256 words of (first place, frequency) and a word per wave)
     constexpr int kTableWords = CODEC == DC_CODEC_TANS ? kTableEntries + 256 + 16 : CPW * kTableEntries / 2;
@@ -1053,7 +1056,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     }
 
     // ---- sub-stream set-up, second half: the ring is free now
-    if (huff) stream_start<CODEC, S, FEW>(st, sf, ring_lane, tbl_addr);
+    if (huff) stream_start<CODEC, S, ORDER>(st, sf, ring_lane, tbl_addr);
 
     const uint32_t round_bytes = 16 * S;
     const uint32_t full_rounds = raw / round_bytes;
@@ -1063,7 +1066,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         uint8_t *d8 = static_cast<uint8_t *>(a.dst) + dst_pos + ct * 16;
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w);
             store16_stream(d8 + (size_t)r * round_bytes, w[0], w[1], w[2], w[3]);
         }
         if (rem) {
@@ -1072,7 +1075,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             const uint32_t n = rem > start ? (rem - start < 16 ? rem - start : 16) : 0;
             uint8_t *d = d8 + (size_t)full_rounds * round_bytes;
             uint32_t w[4];
-            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w);
             if (n == 16) {
                 store16_stream(d, w[0], w[1], w[2], w[3]);
             } else if (n) {
@@ -1159,7 +1162,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         float s_a = scale_of(row_a), s_b = scale_of(row_b);
         for (uint32_t r = 0; r < full_rounds; r++) {
             uint32_t w[4];
-            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, r, true, true);
             next_round();
             s_a = scale_of(row_a);
@@ -1168,7 +1171,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
         if (rem) {
             const uint32_t base = full_rounds * round_bytes;
             uint32_t w[4] = {0, 0, 0, 0};
-            decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+            decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w);
             convert_and_store(w, s_a, s_b, full_rounds, raw >= base + ct_a * 16 + 16, raw >= base + ct_b * 16 + 16);
         }
         return;
@@ -1315,14 +1318,14 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
             };
             if constexpr (FEW) {
                 uint32_t f[8];
-                step_and_decode8<S, 0, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e, early(begin));
-                step_and_decode8<S, 1, CODEC, FEW>(st, rg, tbl_addr, ring_lane, f, late([&](int i) { products(e, 0, 2 * i, 2 * i + 2); }));
+                step_and_decode8<S, 0, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, e, early(begin));
+                step_and_decode8<S, 1, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, f, late([&](int i) { products(e, 0, 2 * i, 2 * i + 2); }));
                 products(f, 1, 0, 4);
             } else {
                 begin();
-                step_and_decode8<S, 0, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e);
+                step_and_decode8<S, 0, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, e);
                 products(e, 0, 0, 4);
-                step_and_decode8<S, 1, CODEC, FEW>(st, rg, tbl_addr, ring_lane, e);
+                step_and_decode8<S, 1, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, e);
                 products(e, 1, 0, 4);
             }
         };
@@ -1396,10 +1399,10 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
                 enter();
             };
             if constexpr (FEW) {
-                decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w, early(begin));
+                decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w, early(begin));
             } else {
                 begin();
-                decode16<S, CODEC, FEW>(st, rg, tbl_addr, ring_lane, w);
+                decode16<S, CODEC, ORDER>(st, rg, tbl_addr, ring_lane, w);
             }
             add_products(whole, w, xs);
         };
@@ -1690,11 +1693,25 @@ bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk
     return n_streams >= 64 && waves <= 2ull * simds && chunk_bytes >= (bf16 ? 32768u : 16384u);
 }
 
+// Whether such a launch at 64 or 128 sub-streams keeps the ring's first words a second time.  What it saves is address arithmetic in the chain's shadow,
+// what it costs is a store of 16 bytes a lane and half group: up to two waves a compute unit (64 KiB chunks, 64 sub-streams) it is 2 to
+// 3 % shorter, products and conversions up to 2 % either way; with three to eight waves 1 to 3 % longer (int8 product of 1024 chunks 46.5 instead of
+// 45.3 us, conversion of 768 57.7 instead of 55.9, decode at 128 of 1000 28.4 instead of 27.6).  The bytes alone, which wait for
+// nothing else, gain from it a little longer.
+bool few_again(int mode, uint64_t waves, uint32_t simds) { return mode == kModeI8 ? waves <= simds * 5ull / 8 : waves < simds / 2; }
+
 template <int S, int MODE> void launch_one(const DecodeArgs &a, hipStream_t stream)
 {
     using G = Geometry<S>;
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
-    if (few_wavefronts(MODE, S, grid * (uint64_t)G::kWaves, a.chunk_bytes, device_simds()))
+    const uint64_t waves = grid * (uint64_t)G::kWaves;
+    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, device_simds());
+    if constexpr (S == 64 || S == 128)
+        if (few && !few_again(MODE, waves, device_simds())) {
+            hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true, false, false>), dim3(grid), dim3(G::kThreads), 0, stream, a);
+            return;
+        }
+    if (few)
         hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
     else
         hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);

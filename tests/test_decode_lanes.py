@@ -136,3 +136,21 @@ def test_tables_of_extreme_codes(decode, order, S, codec, probabilities):
     c = oc.compress(q, C, S, codec=codec)
     got = decode(order, c, C, S, codec, BYTES, q.size // 64, 64)
     assert np.array_equal(got, q)
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("S,units", [(64, 1), (128, 2)])
+@pytest.mark.parametrize("rows,cols,C,f", [(4, 4096, 4096, 0.0), (5, 2064, 4096, 0.4)])
+def test_few_wavefronts_that_keep_no_second_copy(decode, order, S, units, rows, cols, C, f):
+    check_every_mode(decode, order, S, oc.HUFFMAN, rows, cols, C, f, units=units)
+    assert any("true, false, false" in kernel for kernel in decode.launched)
+
+
+@pytest.mark.parametrize("S,chunks,units,again", [(64, 5, 2, True), (64, 6, 2, False), (64, 8, 2, False), (128, 2, 2, True), (128, 3, 2, False),
+                                                  (32, 8, 1, True), (256, 1, 1, True)])  # the latter two have one kernel each
+def test_line_for_the_second_copy(decode, S, chunks, units, again):
+    C = 4096
+    q, _ = oracle_matrix(chunks, C, synth.matrix_seed(13, S), False)
+    c = oc.compress(q, C, S)
+    assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape, units=units), q.view(np.uint8).ravel())
+    assert ["true>" in kernel for kernel in decode.launched] == [again]
