@@ -68,7 +68,8 @@ struct MatrixArgs {
     float x_scale;          // kModeGemvW8A8
 };
 
-struct DecodeArgs {
+// What every decode takes.  Alone the arguments of kModeI8 (104 bytes, not the fused modes' 1.4 KB, which every launch copies).
+struct BytesArgs {
     const uint8_t *blob;
     uint64_t blob_bytes;
     const dc_chunk *table;
@@ -79,6 +80,8 @@ struct DecodeArgs {
     // kModeI8: all chunks decode into one buffer of dst_cap bytes
     void *dst;
     uint64_t dst_cap;
+};
+struct DecodeArgs : BytesArgs {
     // kModeGemv: kPartialSlots sums per chunk (slot r: the chunk's share of the r-th row it touches)
     float *partial;
     // fused modes: the matrices, in table order, and the first chunks of the second to the last (beyond them, no chunk's number).  (Behind
@@ -87,6 +90,7 @@ struct DecodeArgs {
     uint32_t next_first[DC_MAX_MATRICES - 1];
     MatrixArgs mats[DC_MAX_MATRICES];
 };
+template <int MODE> using ArgsOf = std::conditional_t<MODE == kModeI8, BytesArgs, DecodeArgs>;
 
 // Sums `val` (float or int32) over runs of consecutive lanes with equal `key` (keys do not decrease with
 // the lane; key 0xFFFFFFFF = lane takes no part) and adds each run's sum to y[key] with one atomic,
@@ -857,7 +861,7 @@ __device__ __forceinline__ void store_row(const MatrixArgs &m, uint32_t row, flo
 }
 
 template <int S, int MODE, int CODEC, bool FEW = false, bool TRACE = false, bool AGAIN = FEW && S < 256>
-__global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(DecodeArgs a)
+__global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(ArgsOf<MODE> a)
 {
     using G = Geometry<S>;
     // traced launches: when the workgroup began and ended (ticks of the constant 100 MHz clock), where it ran (the
@@ -916,11 +920,18 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     const uint32_t raw = ent.raw_bytes_flags & ~DC_CHUNK_RAW;
     const bool is_raw = (ent.raw_bytes_flags & DC_CHUNK_RAW) != 0;
     // fused modes: the matrix the chunk belongs to, and the chunk's number inside it
-    uint32_t mi = 0;
-    if (MODE != kModeI8 && a.n_mats > 1) // (one load and no loop: a loop over the descriptors was a trip to memory for each of them)
+    const MatrixArgs none = {};
+    const MatrixArgs &mat = [&]() -> const MatrixArgs & {
+        if constexpr (MODE == kModeI8) {
+            return none; // nothing below asks for it
+        } else {
+            uint32_t mi = 0;
+            if (a.n_mats > 1) // (one load and no loop: a loop over the descriptors was a trip to memory for each of them)
 #pragma unroll
-        for (uint32_t i = 0; i < DC_MAX_MATRICES - 1; i++) mi += (uint32_t)k >= a.next_first[i] ? 1u : 0u;
-    const MatrixArgs &mat = a.mats[mi];
+                for (uint32_t i = 0; i < DC_MAX_MATRICES - 1; i++) mi += (uint32_t)k >= a.next_first[i] ? 1u : 0u;
+            return a.mats[mi];
+        }
+    }();
     const uint64_t dst_cap = MODE == kModeI8 ? a.dst_cap : (uint64_t)mat.rows * mat.cols;
     // first decoded byte of the chunk (in the buffer, or in its matrix)
     const uint64_t dst_pos = (MODE == kModeI8 ? k : k - mat.first_chunk) * (uint64_t)a.chunk_bytes;
@@ -952,9 +963,11 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(Decode
     // ---- ordered product: the same for the sums that the chunk leaves in the workspace.  One for every row that the chunk's
     // place in the matrix touches, whatever its table entry says, because the finish kernel adds them all up.
     auto leave_partial_sums = [&](float sum) {
-        const uint64_t end = dst_pos + a.chunk_bytes < dst_cap ? dst_pos + a.chunk_bytes : dst_cap;
-        if (k < a.n_chunks && wave == 0 && cl <= (uint32_t)((end - 1) / mat.cols) - (uint32_t)(dst_pos / mat.cols))
-            a.partial[k * kPartialSlots + cl] = sum;
+        if constexpr (MODE != kModeI8) {
+            const uint64_t end = dst_pos + a.chunk_bytes < dst_cap ? dst_pos + a.chunk_bytes : dst_cap;
+            if (k < a.n_chunks && wave == 0 && cl <= (uint32_t)((end - 1) / mat.cols) - (uint32_t)(dst_pos / mat.cols))
+                a.partial[k * kPartialSlots + cl] = sum;
+        }
     };
     // A chunk that is not decoded leaves empty sums, or their results.
     auto finish_empty = [&]() {
@@ -1638,7 +1651,7 @@ thread_local hipError_t g_last_hip_error = hipSuccess;
 int launch_status() { return dc_launch_status(); }
 
 // Kernel arguments every decode launch shares; the trailer is what a blob of these parameters ends with.
-void common_args(DecodeArgs &a, const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *table_dev, uint64_t n_chunks,
+void common_args(BytesArgs &a, const uint8_t *blob_dev, uint64_t blob_bytes, const dc_chunk *table_dev, uint64_t n_chunks,
                  const dc_params *p)
 {
     a.blob = blob_dev;
@@ -1700,14 +1713,15 @@ bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk
 // nothing else, gain from it a little longer.
 bool few_again(int mode, uint64_t waves, uint32_t simds) { return mode == kModeI8 ? waves <= simds * 5ull / 8 : waves < simds / 2; }
 
-template <int S, int MODE> void launch_one(const DecodeArgs &a, hipStream_t stream)
+template <int S, int MODE> void launch_one(const ArgsOf<MODE> &a, hipStream_t stream)
 {
     using G = Geometry<S>;
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
     const uint64_t waves = grid * (uint64_t)G::kWaves;
-    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, device_simds());
+    const uint32_t simds = device_simds();
+    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, simds);
     if constexpr (S == 64 || S == 128)
-        if (few && !few_again(MODE, waves, device_simds())) {
+        if (few && !few_again(MODE, waves, simds)) {
             hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true, false, false>), dim3(grid), dim3(G::kThreads), 0, stream, a);
             return;
         }
@@ -1718,7 +1732,7 @@ template <int S, int MODE> void launch_one(const DecodeArgs &a, hipStream_t stre
 }
 
 // tANS payloads: S >= 64, one chunk per workgroup
-template <int MODE> int launch_tans(const DecodeArgs &a, uint32_t S, hipStream_t stream)
+template <int MODE> int launch_tans(const ArgsOf<MODE> &a, uint32_t S, hipStream_t stream)
 {
     if (a.n_chunks > 0x7FFFFFFFull) return DC_E_ARG;
     const uint32_t grid = (uint32_t)a.n_chunks;
@@ -1731,7 +1745,7 @@ template <int MODE> int launch_tans(const DecodeArgs &a, uint32_t S, hipStream_t
     return launch_status();
 }
 
-template <int MODE> int launch_decode(const DecodeArgs &a, uint32_t S, hipStream_t stream, uint32_t codec = DC_CODEC_HUFFMAN)
+template <int MODE> int launch_decode(const ArgsOf<MODE> &a, uint32_t S, hipStream_t stream, uint32_t codec = DC_CODEC_HUFFMAN)
 {
     if (codec == DC_CODEC_TANS) return launch_tans<MODE>(a, S, stream);
     if (a.n_chunks > 0x7FFFFFFFull) return DC_E_ARG;
@@ -1766,7 +1780,7 @@ extern "C" int dc_decompress_chunks(const uint8_t *blob_dev, uint64_t blob_bytes
     if (params->format != DC_FORMAT_ID) return DC_E_FORMAT;
     if (!aligned16(blob_dev) || !aligned16(dst_dev) || (reinterpret_cast<uintptr_t>(table_dev) & 7u)) return DC_E_ARG;
     if (dst_cap < (n_chunks - 1) * (uint64_t)params->chunk_bytes + 1) return DC_E_CAP;
-    DecodeArgs a = {};
+    BytesArgs a = {};
     common_args(a, blob_dev, blob_bytes, table_dev, n_chunks, params);
     a.dst = dst_dev;
     a.dst_cap = dst_cap;
@@ -1786,7 +1800,7 @@ extern "C" int dc_decompress_chunks_traced(const uint8_t *blob_dev, uint64_t blo
         (reinterpret_cast<uintptr_t>(trace_dev) & 7u))
         return DC_E_ARG;
     if (dst_cap < (n_chunks - 1) * (uint64_t)params->chunk_bytes + 1) return DC_E_CAP;
-    DecodeArgs a = {};
+    BytesArgs a = {};
     common_args(a, blob_dev, blob_bytes, table_dev, n_chunks, params);
     a.dst = dst_dev;
     a.dst_cap = dst_cap;
