@@ -172,7 +172,8 @@ template <bool HALVES, typename T> __device__ __forceinline__ void lanes_add_run
 // FEW: launches of few wavefronts (step_and_decode8_few).  A wave's 4 KiB of ring are followed by 4 KiB that hold the ring's first
 // four words again, so that words behind one another in the stream can be read without a wrap, and four words for blocks that are
 // nobody's.  Where the LDS is busier the second copy costs more than it saves: with four waves to a chunk (4096 x 4096 at
-// 256 sub-streams 14.3 instead of 13.7 us), and from some three waves to a compute unit on (few_again); at 32, 64 and 128 it saves 3 % below.
+// 256 sub-streams 14.3 instead of 13.7 us), from some three waves to a compute unit on, and in the conversion at 32 sub-streams (few_again);
+// at 32, 64 and 128 it saves 3 % below.
 constexpr int kMany = 0, kFew = 1, kFewAgain = 2; // the order of a decoder's work: one of the latter two for FEW, kFewAgain with the second copy
 template <int ORDER> struct Ring {
     static constexpr int kStride = ORDER != kMany ? 2048 : kRingWords * 64; // words of LDS a wave
@@ -1697,7 +1698,7 @@ uint32_t device_simds()
 // sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that, in chunks of up to 32 KiB 1 to 3 % up to a
 // half, and loses 4 to 10 % in chunks of 64 KiB from there on.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks
 // are raw and between 2 % longer and 7 % shorter where none is; short chunks, in which the set-up counts for more, lose there (4 KiB:
-// 1 to 3 %; bf16 of 16 KiB: 1 to 3 %), and so do 32 sub-streams (1 to 2 %).  At three, where the wavefronts hide each other's look-ups and
+// 1 to 3 %; bf16 of 16 KiB: 1 to 3 %).  (At 32 sub-streams few_at_32 goes beyond all this.)  At three, where the wavefronts hide each other's look-ups and
 // the LDS is what they wait for, it is longer by 7 to 17 %.
 bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
 {
@@ -1706,12 +1707,30 @@ bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk
     return n_streams >= 64 && waves <= 2ull * simds && chunk_bytes >= (bf16 ? 32768u : 16384u);
 }
 
-// Whether such a launch at 64 or 128 sub-streams keeps the ring's first words a second time.  What it saves is address arithmetic in the chain's shadow,
-// what it costs is a store of 16 bytes a lane and half group: up to two waves a compute unit (64 KiB chunks, 64 sub-streams) it is 2 to
-// 3 % shorter, products and conversions up to 2 % either way; with three to eight waves 1 to 3 % longer (int8 product of 1024 chunks 46.5 instead of
-// 45.3 us, conversion of 768 57.7 instead of 55.9, decode at 128 of 1000 28.4 instead of 27.6).  The bytes alone, which wait for
-// nothing else, gain from it a little longer.
-bool few_again(int mode, uint64_t waves, uint32_t simds) { return mode == kModeI8 ? waves <= simds * 5ull / 8 : waves < simds / 2; }
+// Launches at 32 sub-streams beyond that line (microseconds before / now).  The conversion, without the second copy of the ring's first words, is up to 13 %
+// shorter up to one wavefront a SIMD (2048 chunks of 64 KiB 120.1 / 105.4, 768 119.5 / 108.0, 1536 of 16 KiB 35.6 / 31.7, of 4 KiB
+// 13.9 / 12.9; half of the chunks raw: up to 3 %), and from there on up to 8 % longer in chunks of up to 32 KiB.  Products and bytes take
+// up to 7 % less up to two wavefronts a SIMD (products of 3072 chunks of 64 KiB 131.9 / 122.2, int8 119.3 / 115.4; bytes of 2560 of
+// 32 KiB 56.7 / 54.7; half raw: 2 % less to 1 % more); chunks of 4 KiB gain nothing.  Beyond two a SIMD products would gain up to 10 %
+// where all chunks are coded and lose up to 4 % where half are raw, which the host does not know.
+bool few_at_32(int mode, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
+{
+    if (mode == kModeBf16) return waves <= simds;
+    return waves <= 2ull * simds && chunk_bytes >= 16384;
+}
+
+// Whether a launch of few wavefronts keeps the ring's first words a second time.  At 32 sub-streams the conversion never does (with it
+// up to 27 % longer, most where a compute unit has four waves), the products always (without it 1 to 5 % longer up to one wave a SIMD, as
+// long from there on), the bytes up to one wave a SIMD (without it 1 % shorter to 7 % longer there, most with raw chunks; from there on up
+// to 3 % shorter).  At 64 and 128: what it saves is address arithmetic in the chain's shadow, what it costs is a store of 16 bytes a lane and
+// half group: up to two waves a compute unit (64 KiB chunks, 64 sub-streams) it is 2 to 3 % shorter, products and conversions up to 2 %
+// either way; with three to eight waves 1 to 3 % longer (int8 product of 1024 chunks 46.5 instead of 45.3 us, conversion of 768 57.7
+// instead of 55.9, decode at 128 of 1000 28.4 instead of 27.6).  The bytes alone, which wait for nothing else, gain from it a little longer.
+bool few_again(int mode, uint32_t n_streams, uint64_t waves, uint32_t simds)
+{
+    if (n_streams == 32) return mode == kModeI8 ? waves <= simds : mode != kModeBf16;
+    return mode == kModeI8 ? waves <= simds * 5ull / 8 : waves < simds / 2;
+}
 
 template <int S, int MODE> void launch_one(const ArgsOf<MODE> &a, hipStream_t stream)
 {
@@ -1719,16 +1738,18 @@ template <int S, int MODE> void launch_one(const ArgsOf<MODE> &a, hipStream_t st
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
     const uint64_t waves = grid * (uint64_t)G::kWaves;
     const uint32_t simds = device_simds();
-    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, simds);
-    if constexpr (S == 64 || S == 128)
-        if (few && !few_again(MODE, waves, simds)) {
+    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, simds) || (S == 32 && few_at_32(MODE, waves, a.chunk_bytes, simds));
+    if constexpr (S == 64 || S == 128 || (S == 32 && (MODE == kModeI8 || MODE == kModeBf16)))
+        if (few && !few_again(MODE, S, waves, simds)) {
             hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true, false, false>), dim3(grid), dim3(G::kThreads), 0, stream, a);
             return;
         }
-    if (few)
-        hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);
+    if constexpr (S != 32 || MODE != kModeBf16)
+        if (few) {
+            hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
+            return;
+        }
+    hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN>), dim3(grid), dim3(G::kThreads), 0, stream, a);
 }
 
 // tANS payloads: S >= 64, one chunk per workgroup

@@ -154,3 +154,25 @@ def test_line_for_the_second_copy(decode, S, chunks, units, again):
     c = oc.compress(q, C, S)
     assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape, units=units), q.view(np.uint8).ravel())
     assert ["true>" in kernel for kernel in decode.launched] == [again]
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+def test_32_sub_streams_beyond_a_wavefront_a_simd(decode, order):
+    # bytes without the ring's second copy, products with it, the conversion by the kernel for many wavefronts
+    check_every_mode(decode, order, 32, oc.HUFFMAN, 64, 2560, 16384, 0.0, units=1)
+
+
+@pytest.mark.parametrize("mode,C,chunks,kernel", [
+    (BYTES, 16384, 8, "true"), (BYTES, 16384, 10, "true, false, false"), (BYTES, 16384, 16, "true, false, false"), (BYTES, 16384, 18, ""),
+    (BYTES, 16368, 10, ""), (BF16, 4096, 2, "true, false, false"), (BF16, 4096, 8, "true, false, false"), (BF16, 4096, 10, ""), (BF16, 65536, 10, ""),
+    (PRODUCT, 16384, 10, "true"), (PRODUCT, 16384, 16, "true"), (PRODUCT, 16384, 18, ""), (PRODUCT_INT8, 16384, 10, "true"), (PRODUCT_INT8, 8192, 10, "")])
+def test_lines_at_32_sub_streams(decode, mode, C, chunks, kernel):
+    # by the kernel's last parameters, on a device of four SIMDs
+    cols = C // 2
+    q, scale = oracle_matrix(2 * chunks, cols, synth.matrix_seed(14, 32), False)
+    c = oc.compress(q, C, 32)
+    x = synth.gen_activation_bf16(cols, 5)
+    xq, sx = oq.quantise_vector(oq.bf16_to_f64(x).astype(np.float32))
+    more = {BYTES: (), BF16: (scale,), PRODUCT: (scale, x), PRODUCT_INT8: (scale, np.float32(sx), xq)}[mode]
+    decode("ascending", c, C, 32, oc.HUFFMAN, mode, *q.shape, *more, units=1)
+    assert [k for k in decode.launched if "decode_kernel" in k] == [f"(dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN{kernel and ', ' + kernel}>)"]

@@ -729,6 +729,12 @@ def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, C, chunks, 
     assert np.array_equal(y.cpu().numpy().view(np.uint32), oq.gemv_w8a8(q, scale, xq, sx).view(np.uint32))
 
 
+@pytest.mark.parametrize("chunks,more", [(2048, 1), (4096, 0), (4096, 1)])
+def test_on_both_sides_of_the_lines_at_32_sub_streams(chunks, more):
+    # more than one and up to two wavefronts a SIMD, in chunks from which bytes and products take the kernels for few wavefronts there
+    test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(32, 16384, chunks, more)
+
+
 @pytest.mark.parametrize("S,codec", [(64, oc.HUFFMAN), (64, oc.TANS), (128, oc.HUFFMAN), (256, oc.HUFFMAN), (256, oc.TANS)])
 @pytest.mark.parametrize("cols,C,chunks", [(4096, 12288, 5), (12288, 12288, 4), (8192, 491520, 2), (4096, 8192, 2100),  # whole rows
                                            (5120, 4096, 2100), (5120, 65536, 600), (3072, 10240, 2100), (1024, 9216, 2100), (1024, 5120, 9)])
