@@ -93,6 +93,18 @@ def buffer_access_loops(asm_text: str) -> list:
     return found
 
 
+def generic_lds_addresses(asm_text: str) -> list:
+    """Kernels that make an LDS address of a pointer to any memory, for which they ask whether it is null: the address is then
+    no constant of the kernel, and accesses that could have it as their offset add it up instead, in the decode at each look-up."""
+    found, kernel = [], None
+    for ln in asm_text.split("\n"):
+        m = re.match(r"(_Z\w+):", ln)
+        kernel = m.group(1) if m else kernel
+        if "src_shared_base" in ln and kernel not in found:
+            found.append(kernel)
+    return found
+
+
 def device_assembly(source: str) -> str:
     """The gfx950 assembly of one source, as the build compiles it."""
     flags = [f for f in FLAGS if f not in ("-fPIC", "-shared", "-pthread")]
@@ -132,6 +144,9 @@ def build(force: bool = True, extra=(), want_mix: bool = False) -> str:
             looped = buffer_access_loops(text)
             if looped:
                 raise RuntimeError(f"buffer accesses in loops over their descriptors in {', '.join(looped)}")
+            generic = generic_lds_addresses(text)
+            if generic:
+                raise RuntimeError(f"LDS addresses that are no constants in {', '.join(generic)}")
             if want_mix and "dc_decode_kernel" in text:
                 import json
                 print(json.dumps({"main_loop_instruction_mix": loop_mix(text)}))

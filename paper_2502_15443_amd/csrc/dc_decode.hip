@@ -606,7 +606,7 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 
 
 // The tANS table of a chunk (S >= 64: the workgroup's threads are the chunk's).  front: 4 KiB of LDS not yet
-// in use (the rings); table32: the 2048 entries; cumq: 256 words; wave_sum: one word per wave.  The threads
+// in use (the rings); tbl: the LDS address of the 2048 entries; cumq: 256 words; wave_sum: one word per wave.  The threads
 // read the 256 frequencies, take their prefix sums (value v owns places cum[v] .. cum[v] + q[v] - 1) and mark
 // the first place of every value; then every thread takes 2048/threads consecutive places, finds each
 // place's value, and numbers the place among the places of its value by the order of the states (the places
@@ -619,7 +619,7 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 // Returns false (for every thread alike) when the frequencies do not add up to 2048; nothing is decoded then.
 template <int S>
 __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32_t ct, uint32_t lane, uint32_t wave,
-                                                 uint32_t *front, uint32_t *table32, uint32_t *cumq, uint32_t *wave_sum)
+                                                 uint32_t *front, uint32_t tbl, uint32_t *cumq, uint32_t *wave_sum)
 {
     using G = Geometry<S>;
     constexpr int WAVES = G::kWaves;
@@ -680,7 +680,6 @@ __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32
         tail = hi ? hi : tail;
     }
     uint32_t cur = lanes_last_nonzero_below<false>(tail);
-    const uint32_t tbl = lds_address(table32);
     uint32_t value[EPT], q_of[EPT], from[EPT], k[EPT], most = 0; // of a place: value, its frequency, the place among the value's, the state's number
 #pragma unroll
     for (int i = 0; i < EPT; i++) {
@@ -731,9 +730,10 @@ __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32
 // bit-reversed slot numbers (the stream is read least significant bit first).
 // (With the counters at 256 sub-streams too, the first codes added up by one lane, and marks without their slot, which a comparison and a
 // selection each carry forward, it took 370 instructions there, 215 now: a chunk alone on its compute unit 0.8 instead of 1.2 us.)
-// marks: 2048 words of the rings, SHARED: and of the place of the tables; counts: 16 words a wave at the place of the table (several waves).
+// marks: 2048 words of the rings, SHARED: and of the place of the tables; counts: 16 words a wave at the place of the table (several waves);
+// table: the LDS address of 2048 entries of 16 bits.
 template <int TPC, int WAVES, bool HALVES, bool SHARED>
-__device__ __forceinline__ void build_code_table(uint32_t nib, uint32_t ct, uint32_t wave, uint32_t *marks, uint32_t (*counts)[16], uint16_t *table)
+__device__ __forceinline__ void build_code_table(uint32_t nib, uint32_t ct, uint32_t wave, uint32_t *marks, uint32_t (*counts)[16], uint32_t table)
 {
     constexpr int SPL = 256 / TPC;
     constexpr uint32_t EPT = kTableEntries / TPC; // slots a thread fills
@@ -842,7 +842,7 @@ __device__ __forceinline__ void build_code_table(uint32_t nib, uint32_t ct, uint
     if (SHARED) __syncthreads(); // the marks have been read
     // slot EPT*ct + j in code order = slot bitrev(j) << (11-e) | bitrev(ct) in stream order, EPT = 2^e
     constexpr int E = EPT == 64 ? 6 : EPT == 32 ? 5 : EPT == 16 ? 4 : 3;
-    const uint32_t out = lds_address(table) + 2 * (__brev(ct) >> (32 - (kPeekBits - E)));
+    const uint32_t out = table + 2 * (__brev(ct) >> (32 - (kPeekBits - E)));
 #pragma unroll
     for (uint32_t i = 0; i < EPT; i++) {
         cur = w[i] > cur ? w[i] : cur;
@@ -898,7 +898,6 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(ArgsOf
     // (tANS: 2048 entries of 32 bits, then 256 words of (first place, frequency) and a word per wave)
     constexpr int kTableWords = CODEC == DC_CODEC_TANS ? kTableEntries + 256 + 16 : CPW * kTableEntries / 2;
     __shared__ __attribute__((aligned(4 * kRingStride))) uint32_t lds_all[kFrontWords + kTableWords];
-    uint16_t(*lds_table)[kTableEntries] = reinterpret_cast<uint16_t(*)[kTableEntries]>(lds_all + kFrontWords);
     uint32_t(*lds_counts)[16] = reinterpret_cast<uint32_t(*)[16]>(lds_all + kFrontWords); // [wave][length]
 
     const uint32_t lane = threadIdx.x & 63u;
@@ -943,8 +942,10 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(ArgsOf
     const uint32_t *payload = reinterpret_cast<const uint32_t *>(payload8);
     const bool huff = active && !is_raw;
 
-    uint16_t *tbl = lds_table[sub];
-    const uint32_t tbl_addr = lds_address(tbl);
+    // The chunk's table, as a place in lds_all and not as the address of a pointer: what a pointer to any memory becomes in LDS depends on
+    // whether it is null, and where the compiler does not see through that, the address is no constant and each look-up adds it to
+    // its index: 190 instead of 172 instructions a round of bytes at 64 sub-streams, 219 instead of 200 of tANS at 256.
+    const uint32_t tbl_addr = lds_address(lds_all) + 4 * kFrontWords + 2 * kTableEntries * sub;
     const uint32_t ring_lane = lds_address(lds_all + wave * kRingStride + lane);
     constexpr bool UNI = CPW == 1; // all lanes of the wave belong to one stream set
 
@@ -1054,9 +1055,8 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(ArgsOf
 
     const bool build_table = CODEC == DC_CODEC_TANS ? false : CPW == 1 ? huff : (bool)__any(huff);
     if (CODEC == DC_CODEC_TANS && huff) { // (one chunk per workgroup: the same for all of its threads)
-        uint32_t *table32 = lds_all + kFrontWords;
-        if (!build_tans_table<S>(payload8, ct, lane, wave, lds_all, table32, table32 + kTableEntries,
-                                 table32 + kTableEntries + 256)) {
+        uint32_t *cumq = lds_all + kFrontWords + kTableEntries;
+        if (!build_tans_table<S>(payload8, ct, lane, wave, lds_all, tbl_addr, cumq, cumq + 256)) {
             finish_empty();
             return;
         }
@@ -1066,7 +1066,7 @@ __global__ __launch_bounds__(Geometry<S>::kThreads) void dc_decode_kernel(ArgsOf
         uint32_t *marks = lds_all + sub * kTableEntries;
         constexpr bool SHARED = kFrontWords < CPW * kTableEntries;
         static_assert(!SHARED || (WAVES == 1 && kFrontWords + kTableWords >= CPW * kTableEntries), "room for the marks");
-        build_code_table<TPC, WAVES, CPW == 2, SHARED>(SPL == 1 ? (nib_word >> (4 * (ct & 1))) & 15u : nib_word, ct, wave, marks, lds_counts, tbl);
+        build_code_table<TPC, WAVES, CPW == 2, SHARED>(SPL == 1 ? (nib_word >> (4 * (ct & 1))) & 15u : nib_word, ct, wave, marks, lds_counts, tbl_addr);
     }
 
     // ---- sub-stream set-up, second half: the ring is free now

@@ -36,3 +36,24 @@ def test_the_coders_stores_are_straight(build):
     asm = build.device_assembly(os.path.join(PKG, "csrc", "dc_encode.hip"))
     assert asm.count("buffer_store_dwordx4") >= 6
     assert build.buffer_access_loops(asm) == []
+
+
+GENERIC = """_Zkernel:
+\ts_mov_b64 s[8:9], src_shared_base
+\ts_cmp_lg_u32 s9, -1
+\ts_cselect_b32 s8, 0x1000, -1
+.Lfunc_end0:
+_Zother:
+\ts_endpgm
+"""
+
+
+def test_lds_addresses_of_generic_pointers_are_found(build):
+    assert build.generic_lds_addresses(GENERIC) == ["_Zkernel"]
+
+
+@pytest.mark.parametrize("source", ["dc_decode.hip", "dc_encode.hip"])
+def test_lds_addresses_are_constants(build, source):
+    asm = build.device_assembly(os.path.join(PKG, "csrc", source))
+    assert "ds_read_u16" in asm
+    assert build.generic_lds_addresses(asm) == []
