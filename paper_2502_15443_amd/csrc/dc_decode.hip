@@ -174,8 +174,7 @@ template <bool HALVES, typename T> __device__ __forceinline__ void lanes_add_run
 // FEW: launches of few wavefronts (step_and_decode8_few).  A wave's 4 KiB of ring are followed by 4 KiB that hold the ring's first
 // four words again, so that words behind one another in the stream can be read without a wrap, and four words for blocks that are
 // nobody's.  Where the LDS is busier the second copy costs more than it saves: with four waves to a chunk (4096 x 4096 at
-// 256 sub-streams 14.3 instead of 13.7 us), from some three waves to a compute unit on, and in the conversion at 32 sub-streams (few_again);
-// at 32, 64 and 128 it saves 3 % below.
+// 256 sub-streams 14.3 instead of 13.7 us), and where order_of_work says so.
 constexpr int kMany = 0, kFew = 1, kFewAgain = 2; // the order of a decoder's work: one of the latter two for FEW, kFewAgain with the second copy
 template <int ORDER> struct Ring {
     static constexpr int kStride = ORDER != kMany ? 2048 : kRingWords * 64; // words of LDS a wave
@@ -1701,59 +1700,51 @@ uint32_t device_simds()
     return 0;
 }
 
-// Whether a launch of `waves` wavefronts takes the FEW kernels.  Up to one wavefront a SIMD it is as long as a lane's chain of look-ups, and
-// FEW is up to 19 % shorter, the more the longer the chunks (4 KiB at 256 sub-streams: as long).  The conversion to bf16 at 32
-// sub-streams, whose stores are in each other's way, gains 3 to 7 % up to a quarter of that, in chunks of up to 32 KiB 1 to 3 % up to a
-// half, and loses 4 to 10 % in chunks of 64 KiB from there on.  Up to two wavefronts a SIMD FEW is 2 to 9 % shorter where half of the chunks
-// are raw and between 2 % longer and 7 % shorter where none is; short chunks, in which the set-up counts for more, lose there (4 KiB:
-// 1 to 3 %; bf16 of 16 KiB: 1 to 3 %).  (At 32 sub-streams few_at_32 goes beyond all this.)  At three, where the wavefronts hide each other's look-ups and
-// the LDS is what they wait for, it is longer by 7 to 17 %.
-bool few_wavefronts(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
+// The order of a decoder's work in a launch of `waves` wavefronts.
+// For few of them: up to one a SIMD a launch is as long as a lane's chain of look-ups, and these kernels are up to 19 % shorter, the more the
+// longer the chunks (4 KiB: as long).  Up to two a SIMD they are 2 to 9 % shorter where half of the chunks are raw and between 2 %
+// longer and 7 % shorter where none is; short chunks, in which the set-up counts for more, lose there (4 KiB: 1 to 3 %; bf16 of 16 KiB at
+// 128 and 256 sub-streams: 1 to 3 %), and so does the conversion at 32 sub-streams, whose stores are in each other's way (up to 8 %).  At three a
+// SIMD, where the wavefronts hide each other's look-ups and the LDS is what they wait for, they are 7 to 17 % longer (products at 32
+// sub-streams: up to 10 % shorter where all chunks are coded, up to 4 % longer where half are raw, which the host does not know).
+// The second copy of the ring's first words saves address arithmetic and costs a store of 16 bytes a lane and half group.  At 32
+// sub-streams the conversion is up to 27 % longer with it (2048 chunks of 64 KiB 120.1, without it 105.4 us), products are up to 5 %
+// shorter, bytes up to 7 % shorter up to one wavefront a SIMD and from there on up to 3 % longer.  At 64 and 128 it is worth some
+// percent either way: it costs most where the LDS of a compute unit has a wavefront of each SIMD, or two, and less with some raw chunks.
+// At 128: 1 to 2 % shorter up to three wavefronts to two SIMDs (product of 512 chunks of 64 KiB 30.8, without it 31.5 us), from there on
+// 1 % shorter to 2 % longer.  At 64, bytes: 1 to 3 % shorter up to the same line, but chunks of 16 KiB up to 2.6 % longer from half a
+// wavefront a SIMD on (1024 of them 14.4 / 14.0); those of 64 KiB with one a SIMD are as long where all are coded and 2 %
+// shorter where half are raw.  The conversion: 1 % either way, mostly shorter (640 chunks 55.2 / 56.1, 1024 55.6 / 55.3).
+// Products: up to 2 % shorter up to three wavefronts to four SIMDs, 1 to 2 % longer with one on each (int8 product of 1024 chunks 46.2 / 45.4).
+int order_of_work(int mode, uint32_t n_streams, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
 {
-    const bool bf16 = mode == kModeBf16;
-    if (waves <= simds) return n_streams >= 64 || !bf16 || waves <= (chunk_bytes <= 32768 ? simds / 2 : simds / 4);
-    return n_streams >= 64 && waves <= 2ull * simds && chunk_bytes >= (bf16 ? 32768u : 16384u);
-}
-
-// Launches at 32 sub-streams beyond that line (microseconds before / now).  The conversion, without the second copy of the ring's first words, is up to 13 %
-// shorter up to one wavefront a SIMD (2048 chunks of 64 KiB 120.1 / 105.4, 768 119.5 / 108.0, 1536 of 16 KiB 35.6 / 31.7, of 4 KiB
-// 13.9 / 12.9; half of the chunks raw: up to 3 %), and from there on up to 8 % longer in chunks of up to 32 KiB.  Products and bytes take
-// up to 7 % less up to two wavefronts a SIMD (products of 3072 chunks of 64 KiB 131.9 / 122.2, int8 119.3 / 115.4; bytes of 2560 of
-// 32 KiB 56.7 / 54.7; half raw: 2 % less to 1 % more); chunks of 4 KiB gain nothing.  Beyond two a SIMD products would gain up to 10 %
-// where all chunks are coded and lose up to 4 % where half are raw, which the host does not know.
-bool few_at_32(int mode, uint64_t waves, uint32_t chunk_bytes, uint32_t simds)
-{
-    if (mode == kModeBf16) return waves <= simds;
-    return waves <= 2ull * simds && chunk_bytes >= 16384;
-}
-
-// Whether a launch of few wavefronts keeps the ring's first words a second time.  At 32 sub-streams the conversion never does (with it
-// up to 27 % longer, most where a compute unit has four waves), the products always (without it 1 to 5 % longer up to one wave a SIMD, as
-// long from there on), the bytes up to one wave a SIMD (without it 1 % shorter to 7 % longer there, most with raw chunks; from there on up
-// to 3 % shorter).  At 64 and 128: what it saves is address arithmetic in the chain's shadow, what it costs is a store of 16 bytes a lane and
-// half group: up to two waves a compute unit (64 KiB chunks, 64 sub-streams) it is 2 to 3 % shorter, products and conversions up to 2 %
-// either way; with three to eight waves 1 to 3 % longer (int8 product of 1024 chunks 46.5 instead of 45.3 us, conversion of 768 57.7
-// instead of 55.9, decode at 128 of 1000 28.4 instead of 27.6).  The bytes alone, which wait for nothing else, gain from it a little longer.
-bool few_again(int mode, uint32_t n_streams, uint64_t waves, uint32_t simds)
-{
-    if (n_streams == 32) return mode == kModeI8 ? waves <= simds : mode != kModeBf16;
-    return mode == kModeI8 ? waves <= simds * 5ull / 8 : waves < simds / 2;
+    const bool bytes = mode == kModeI8, bf16 = mode == kModeBf16;
+    const uint64_t two_a_simd = 2ull * simds;
+    if (n_streams == 32) {
+        if (bf16) return waves <= simds ? kFew : kMany;
+        if (waves <= simds) return kFewAgain;
+        return waves > two_a_simd || chunk_bytes < 16384 ? kMany : bytes ? kFew : kFewAgain;
+    }
+    if (waves > simds && (waves > two_a_simd || chunk_bytes < (bf16 ? 32768u : 16384u))) return kMany;
+    if (n_streams == 256) return kFew;
+    if (n_streams == 64 && bf16) return kFewAgain;
+    const uint64_t again = n_streams == 128 || (bytes && chunk_bytes >= 32768) ? simds * 3ull / 2 : bytes ? simds / 2 : simds * 3ull / 4;
+    return waves <= again ? kFewAgain : kFew;
 }
 
 template <int S, int MODE> void launch_one(const ArgsOf<MODE> &a, hipStream_t stream)
 {
     using G = Geometry<S>;
     const uint32_t grid = (uint32_t)((a.n_chunks + G::kChunksPerWave - 1) / G::kChunksPerWave);
-    const uint64_t waves = grid * (uint64_t)G::kWaves;
-    const uint32_t simds = device_simds();
-    const bool few = few_wavefronts(MODE, S, waves, a.chunk_bytes, simds) || (S == 32 && few_at_32(MODE, waves, a.chunk_bytes, simds));
-    if constexpr (S == 64 || S == 128 || (S == 32 && (MODE == kModeI8 || MODE == kModeBf16)))
-        if (few && !few_again(MODE, S, waves, simds)) {
+    const int order = order_of_work(MODE, S, grid * (uint64_t)G::kWaves, a.chunk_bytes, device_simds());
+    constexpr bool BYTES = MODE == kModeI8, BF16 = MODE == kModeBf16;
+    if constexpr (S == 32 ? BYTES || BF16 : S == 64 ? !BF16 : S == 128)
+        if (order == kFew) {
             hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true, false, false>), dim3(grid), dim3(G::kThreads), 0, stream, a);
             return;
         }
-    if constexpr (S != 32 || MODE != kModeBf16)
-        if (few) {
+    if constexpr (S != 32 || !BF16) // (256 sub-streams: the kernel without the copy)
+        if (order != kMany) {
             hipLaunchKernelGGL((dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN, true>), dim3(grid), dim3(G::kThreads), 0, stream, a);
             return;
         }
@@ -1835,7 +1826,7 @@ extern "C" int dc_decompress_chunks_traced(const uint8_t *blob_dev, uint64_t blo
     a.dst_cap = dst_cap;
     a.trace = trace_dev;
     const dim3 grid((uint32_t)n_chunks), block(Geometry<256>::kThreads);
-    if (few_wavefronts(kModeI8, 256, n_chunks * Geometry<256>::kWaves, a.chunk_bytes, device_simds()))
+    if (order_of_work(kModeI8, 256, n_chunks * Geometry<256>::kWaves, a.chunk_bytes, device_simds()) != kMany)
         hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, true, true>), grid, block, 0, static_cast<hipStream_t>(hip_stream), a);
     else
         hipLaunchKernelGGL((dc_decode_kernel<256, kModeI8, DC_CODEC_HUFFMAN, false, true>), grid, block, 0, static_cast<hipStream_t>(hip_stream), a);

@@ -1,16 +1,16 @@
 // The device decoder on the CPU, lane by lane (hip/hip_runtime.h beside this file):
 //   decode ORDER SEED chunk_bytes n_streams codec MODE rows cols SOURCE RESULT [COMPUTE_UNITS]
-//   decode few MODE n_streams waves chunk_bytes simds
+//   decode order MODE n_streams waves chunk_bytes simds
 // MODE: 0 the bytes, 1 bf16 values, 2 product, 3 product with int8 activations, 4 the bytes, traced.  SOURCE: the numbers of chunks and of blob
 // bytes (u64), the table, the blob, row scales (fp32), activations (bf16, or int8 with their scale in fp32 before them).
 // RESULT: what the call writes; standard output: the kernels launched.  COMPUTE_UNITS: of the device (256); 0: no launch is one of few wavefronts.
-// few: whether such a launch takes the kernels for few wavefronts (exit status 1: it does).
+// order: by which kernel such a launch is decoded (exit status 0: for many wavefronts, 1: for few, 2: for few, with the ring's second copy).
 #include "dc_decode.hip"
 
 int main(int argc, char **argv)
 {
-    if (argc == 7 && !strcmp(argv[1], "few"))
-        return few_wavefronts(atoi(argv[2]), (uint32_t)atoi(argv[3]), strtoull(argv[4], nullptr, 10), (uint32_t)atoi(argv[5]), (uint32_t)atoi(argv[6]));
+    if (argc == 7 && !strcmp(argv[1], "order"))
+        return order_of_work(atoi(argv[2]), (uint32_t)atoi(argv[3]), strtoull(argv[4], nullptr, 10), (uint32_t)atoi(argv[5]), (uint32_t)atoi(argv[6]));
     if (argc != 11 && argc != 12) return 2;
     if (argc == 12) lanes::config.compute_units = atoi(argv[11]);
     lanes::config.order = (lanes::Order)atoi(argv[1]);

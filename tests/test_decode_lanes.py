@@ -85,14 +85,21 @@ def test_decoder_of_many_wavefronts(decode, S):
     assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape), q.view(np.uint8).ravel())
 
 
+def order_of_work(decode, *launch):  # mode, sub-streams, wavefronts, bytes a chunk, SIMDs
+    return subprocess.run([decode.exe, "order"] + [str(v) for v in launch]).returncode
+
+
+MANY, FEW, FEW_AGAIN = 0, 1, 2
+
+
 @pytest.mark.parametrize("mode,S,chunk,simds,line", [
-    (BYTES, 32, 65536, 1024, 1024), (BYTES, 256, 4096, 1024, 1024), (BYTES, 256, 16384, 1024, 2048),
-    (PRODUCT, 64, 16368, 1024, 1024), (PRODUCT_INT8, 128, 65536, 1024, 2048),
-    (BF16, 32, 65536, 1024, 256), (BF16, 32, 32768, 1024, 512), (BF16, 64, 16384, 1024, 1024), (BF16, 64, 32768, 1024, 2048),
-    (BYTES, 64, 65536, 128, 256), (BF16, 32, 4096, 128, 64), (BYTES, 64, 65536, 0, 0)])
+    (BYTES, 32, 65536, 1024, 2048), (BYTES, 32, 16368, 1024, 1024), (PRODUCT, 32, 16384, 1024, 2048), (BYTES, 256, 4096, 1024, 1024),
+    (BYTES, 256, 16384, 1024, 2048), (PRODUCT, 64, 16368, 1024, 1024), (PRODUCT_INT8, 128, 65536, 1024, 2048),
+    (BF16, 32, 65536, 1024, 1024), (BF16, 32, 32768, 1024, 1024), (BF16, 64, 16384, 1024, 1024), (BF16, 64, 32768, 1024, 2048),
+    (BYTES, 64, 65536, 128, 256), (BF16, 32, 4096, 128, 128), (BYTES, 64, 65536, 0, 0)])
 def test_line_for_launches_of_few_wavefronts(decode, mode, S, chunk, simds, line):
     # in wavefronts a SIMD of the device, and by what a lane has to decode
-    few = lambda waves: bool(subprocess.run([decode.exe, "few"] + [str(v) for v in (mode, S, waves, chunk, simds)]).returncode)
+    few = lambda waves: order_of_work(decode, mode, S, waves, chunk, simds) != MANY
     assert not few(line + 1) and few(max(1, line // 3)) == few(max(1, line)) == (line > 0)
 
 
@@ -139,21 +146,42 @@ def test_tables_of_extreme_codes(decode, order, S, codec, probabilities):
 
 
 @pytest.mark.parametrize("order", list(ORDERS))
-@pytest.mark.parametrize("S,units", [(64, 1), (128, 2)])
-@pytest.mark.parametrize("rows,cols,C,f", [(4, 4096, 4096, 0.0), (5, 2064, 4096, 0.4)])
-def test_few_wavefronts_that_keep_no_second_copy(decode, order, S, units, rows, cols, C, f):
-    check_every_mode(decode, order, S, oc.HUFFMAN, rows, cols, C, f, units=units)
+@pytest.mark.parametrize("S,rows,cols,C,f", [(64, 4, 4096, 4096, 0.0), (64, 7, 2064, 4096, 0.4),  # a wavefront a SIMD (four): bytes and products
+                                             (128, 32, 4096, 32768, 0.0), (128, 61, 2064, 32768, 0.4)])  # two: every mode
+def test_few_wavefronts_that_keep_no_second_copy(decode, order, S, rows, cols, C, f):
+    check_every_mode(decode, order, S, oc.HUFFMAN, rows, cols, C, f, units=1)
     assert any("true, false, false" in kernel for kernel in decode.launched)
 
 
-@pytest.mark.parametrize("S,chunks,units,again", [(64, 5, 2, True), (64, 6, 2, False), (64, 8, 2, False), (128, 2, 2, True), (128, 3, 2, False),
-                                                  (32, 8, 1, True), (256, 1, 1, True)])  # the latter two have one kernel each
-def test_line_for_the_second_copy(decode, S, chunks, units, again):
-    C = 4096
-    q, _ = oracle_matrix(chunks, C, synth.matrix_seed(13, S), False)
+@pytest.mark.parametrize("mode,S,chunk,simds,line,below,beyond", [
+    (BYTES, 32, 16384, 1024, 1024, FEW_AGAIN, FEW), (BYTES, 64, 65536, 1024, 1536, FEW_AGAIN, FEW), (BYTES, 64, 32768, 64, 96, FEW_AGAIN, FEW),
+    (BYTES, 64, 32752, 1024, 512, FEW_AGAIN, FEW), (BF16, 64, 32768, 1024, 2048, FEW_AGAIN, MANY), (BF16, 64, 4096, 1024, 1024, FEW_AGAIN, MANY),
+    (PRODUCT, 64, 65536, 1024, 768, FEW_AGAIN, FEW), (PRODUCT_INT8, 64, 16384, 1024, 768, FEW_AGAIN, FEW),
+    (BYTES, 128, 16384, 1024, 1536, FEW_AGAIN, FEW), (BF16, 128, 32768, 1024, 1536, FEW_AGAIN, FEW), (PRODUCT, 128, 16384, 1024, 1536, FEW_AGAIN, FEW),
+    (PRODUCT, 32, 16384, 1024, 2048, FEW_AGAIN, MANY), (BF16, 32, 65536, 1024, 1024, FEW, MANY), (BYTES, 256, 16384, 1024, 2048, FEW, MANY)])
+def test_line_for_the_second_copy(decode, mode, S, chunk, simds, line, below, beyond):
+    order = lambda waves: order_of_work(decode, mode, S, waves, chunk, simds)
+    assert (order(1), order(line), order(line + 1)) == (below, below, beyond)
+
+
+@pytest.mark.parametrize("mode,S,C,chunks,kernel", [
+    (BYTES, 64, 4096, 2, "true"), (BYTES, 64, 4096, 3, "true, false, false"), (BYTES, 64, 4096, 5, ""), (BYTES, 64, 32768, 4, "true"),
+    (BF16, 64, 4096, 4, "true"), (BF16, 64, 4096, 5, ""), (PRODUCT_INT8, 64, 4096, 3, "true"), (PRODUCT_INT8, 64, 4096, 4, "true, false, false"),
+    (BYTES, 128, 16384, 3, "true"), (BYTES, 128, 16384, 4, "true, false, false"), (BYTES, 128, 16384, 5, ""), (BF16, 128, 32768, 4, "true, false, false"),
+    (BYTES, 256, 4096, 1, "true"), (BYTES, 256, 4096, 2, "")])
+def test_the_kernel_of_an_order(decode, mode, S, C, chunks, kernel):
+    # by the kernel's last parameters, on a device of four SIMDs
+    cols = C // 2
+    q, scale = oracle_matrix(2 * chunks, cols, synth.matrix_seed(13, S), False)
     c = oc.compress(q, C, S)
-    assert np.array_equal(decode("ascending", c, C, S, oc.HUFFMAN, BYTES, *q.shape, units=units), q.view(np.uint8).ravel())
-    assert ["true>" in kernel for kernel in decode.launched] == [again]
+    x8 = np.ones(cols, np.int8)
+    more = {BYTES: (), BF16: (scale,), PRODUCT_INT8: (scale, np.float32(1), x8)}[mode]
+    got = decode("ascending", c, C, S, oc.HUFFMAN, mode, *q.shape, *more, units=1)
+    want = {BYTES: lambda: q.view(np.uint8).ravel(), BF16: lambda: oq.dequant_bf16(q, scale).view(np.uint8).ravel(),
+            PRODUCT_INT8: lambda: oq.gemv_w8a8(q, scale, x8, np.float32(1)).view(np.uint8).ravel()}[mode]()
+    assert np.array_equal(got.view(np.uint8), want)
+    assert [k for k in decode.launched if "decode_kernel" in k] == [
+        f"(dc_decode_kernel<S, MODE, DC_CODEC_HUFFMAN{kernel and ', ' + kernel}>)"]
 
 
 @pytest.mark.parametrize("order", list(ORDERS))

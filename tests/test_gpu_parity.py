@@ -695,7 +695,7 @@ def test_config1_full_size_bit_exact_and_ratio():
 
 @pytest.mark.parametrize("S,C,chunks", [(32, 4096, 2048), (64, 4096, 1024), (128, 4096, 512), (256, 4096, 256),     # 1024 wavefronts
                                         (64, 16384, 2048), (128, 16384, 1024), (256, 16384, 512),                    # 2048 in longer chunks
-                                        (32, 4096, 1024), (64, 32768, 2048), (256, 32768, 512)])                      # the lines of bf16
+                                        (64, 32768, 2048), (128, 32768, 1024), (256, 32768, 512)])                    # the same of bf16
 @pytest.mark.parametrize("more", [0, 1])
 def test_on_both_sides_of_the_line_for_launches_of_few_wavefronts(S, C, chunks, more):
     # the largest launch of few wavefronts, and one workgroup more; some chunks raw, the last one short
