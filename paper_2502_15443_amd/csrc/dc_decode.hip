@@ -92,8 +92,6 @@ struct DecodeArgs : BytesArgs {
 };
 template <int MODE> using ArgsOf = std::conditional_t<MODE == kModeI8, BytesArgs, DecodeArgs>;
 
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-
 // Sums `val` (float or int32) over runs of consecutive lanes with equal `key` (keys do not decrease with
 // the lane; key 0xFFFFFFFF = lane takes no part) and adds each run's sum to y[key] with one atomic,
 // issued by the last lane of the run.
@@ -614,13 +612,14 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 // with their 11 bits reversed): place p of a value with places a .. e-1 has as many states below it as there are
 // places p' of the value whose reversal is smaller, that is, for every set bit i of p, the places of the value that agree with p
 // below bit i and have bit i clear: those that leave c = p mod 2^i when divided by M = 2^(i+1),
-// (e + M - 1 - c) div M - (a + M - 1 - c) div M of them.  The sums over a and over e are kept in the halves of one word, three
-// operations a bit for both.
+// (e + M - 1 - c) div M - (a + M - 1 - c) div M of them.  The sums over a and over e are kept in the halves of one word, which neither
+// additions nor, with a mask, shifts let into each other: four plain operations a bit for both.
 // (What bounds it: the vector ALU, and registers, which set how many wavefronts run through the whole decode.  All eleven bits of
 // every place were 530 of the 720 vector operations of a wave at 256 sub-streams, whose loop over 64 KiB takes 2400.  Only the bits
 // that can count, with a place's value, frequency, distance and number in a word each, took 217 registers at 64 sub-streams and 107 at
-// 128, where the LDS lets 168 and 96 be used: 2500 chunks of 64 KiB 84 -> 119 us, 12000 of 16 KiB 117 -> 126.  As it is now, 130 and
-// 80 registers: 78.8 and 104.8; 2200 chunks of 64 KiB at 128 sub-streams 66.4 -> 78.4 -> 62.6; at 256 16000 of 4 KiB 84.8 -> 69.4 -> 66.2.)
+// 128, where the LDS lets 168 and 96 be used: 2500 chunks of 64 KiB 84 -> 119 us, 12000 of 16 KiB 117 -> 126.  As it is now, 142 and
+// 82 registers: 77.2 and 102.4; 2200 chunks of 64 KiB at 128 sub-streams 66 -> 78 -> 61.7; at 256 16000 of 4 KiB 84.6 -> 69.2 -> 63.3.
+// The same halves by packed operations of 16 bits, three a bit, take up to 4 % longer: their encoding is twice as long.)
 // Returns false (for every thread alike) when the frequencies do not add up to 2048; nothing is decoded then.
 template <int S>
 __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32_t ct, uint32_t lane, uint32_t wave,
@@ -686,38 +685,38 @@ __device__ __forceinline__ bool build_tans_table(const uint8_t *payload8, uint32
     }
     uint32_t cur = lanes_last_nonzero_below<false>(tail);
     // of a place: its value, the halves a and e, and the sums over them, whose difference will be the number of the place's state
-    u16x2 span[EPT], sum[EPT];
-    uint32_t value[EPT], most = 0;
+    uint32_t value[EPT], span[EPT], sum[EPT], most = 0;
 #pragma unroll
     for (int i = 0; i < EPT; i++) {
         const uint32_t m = (i & 1) ? w16[i / 2] >> 16 : w16[i / 2] & 0xFFFFu;
         cur = m ? m : cur;
         value[i] = (cur - 1) & 255u;
         const uint32_t cq = cumq[value[i]];
-        span[i] = sum[i] = __builtin_bit_cast(u16x2, cq + (cq << 16));
+        span[i] = sum[i] = cq + (cq << 16);
         most = cq > most ? cq : most;
     }
     // Bit b of the place counts where the value has more than 2^b places: of 2^b places in a row no other agrees with this one below
     // bit b.  So the loop ends with the most frequent value that the wave holds; and the lowest bits are the same in every thread.
-    auto all = [](uint32_t v) { return u16x2{(uint16_t)v, (uint16_t)v}; };
+    auto both = [](uint32_t v) { return v << 16 | v; };
     constexpr uint32_t LOW = EPT == 32 ? 5 : EPT == 16 ? 4 : 3; // EPT = 2^LOW
 #pragma unroll
     for (uint32_t b = 0; b < LOW; b++)
 #pragma unroll
         for (uint32_t i = 0; i < (uint32_t)EPT; i++)
-            if (i >> b & 1u) sum[i] += (span[i] + all((2u << b) - 1 - (i & ((1u << b) - 1)))) >> all(b + 1);
+            if (i >> b & 1u) sum[i] += (span[i] + both((2u << b) - 1 - (i & ((1u << b) - 1)))) >> (b + 1) & both(0xFFFFu >> (b + 1));
 #pragma unroll
-    for (uint32_t i = 0; i < (uint32_t)EPT; i++) span[i] -= all(i); // from here on c is what EPT * ct leaves
-#pragma unroll 1
-    for (uint32_t b = LOW; b < (uint32_t)kPeekBits && __any(most >> 16 > 1u << b); b++)
-        if (ct >> (b - LOW) & 1u) {
-            const u16x2 from = all((2u << b) - 1 - EPT * (ct & ((1u << (b - LOW)) - 1))), by = all(b + 1);
+    for (uint32_t i = 0; i < (uint32_t)EPT; i++) span[i] -= both(i); // from here on c is what EPT * ct leaves
 #pragma unroll
-            for (int i = 0; i < EPT; i++) sum[i] += (span[i] + from) >> by;
-        }
+    for (uint32_t b = LOW; b < (uint32_t)kPeekBits; b++) {
+        if (!__any(most >> 16 > 1u << b)) break;
+        const uint32_t from = both((2u << b) - 1 - EPT * (ct & ((1u << (b - LOW)) - 1)));
+        const uint32_t mask = ct >> (b - LOW) & 1u ? both(0xFFFFu >> (b + 1)) : 0u;
+#pragma unroll
+        for (int i = 0; i < EPT; i++) sum[i] += (span[i] + from) >> (b + 1) & mask;
+    }
 #pragma unroll
     for (int i = 0; i < EPT; i++) {
-        const uint32_t p = EPT * ct + i, k = (uint32_t)(uint16_t)(sum[i].y - sum[i].x);
+        const uint32_t p = EPT * ct + i, k = (sum[i] >> 16) - (sum[i] & 0xFFFFu);
         const uint32_t nb = (uint32_t)__builtin_clz(k | 1u) - (31 - kPeekBits);
         const uint32_t base = ((k << nb) - L) & (L - 1);
         *(lds_u32 *)(uintptr_t)(tbl + 4 * (__brev(p) >> (32 - kPeekBits))) = nb | value[i] << 8 | base << 18;
