@@ -226,6 +226,54 @@ struct LeafRanks {
     }
 };
 
+// Package-merge of few leaves (key: ascending, count << 8 | value; n: 2 to kFewLeavesLoaded), as far as leaves_before[j - 1][m], the leaves among the first
+// 2m items of level j.  Thread t owns items 2t and 2t + 1 of a level, the pair that is package t of the next, and searches for the
+// number a of leaves among the 2t items before them.  From level to level items get lighter and a falls, by about half as much each
+// time, so the search begins that far below the last a and is mostly over after a few steps, after none where there are hardly
+// any leaves.  What many leaves take (in the kernel) costs the same whatever their number: the tables of LeafRanks and some
+// four trips to LDS a level.  2048 chunks of 4 KiB with it / with this: 2 values 29.7 / 25.1 us, 16 30.1 / 26.7, 64 30.5 / 27.5, 128 31.3 / 30.1.
+// From 65 leaves on, where more than one wave takes part, it is a chunk's trips to LDS against the compute unit's
+// work: 64 such chunks of 128 values take 15.4 / 15.9, so that there it is for launches of more than four workgroups a compute unit.
+constexpr uint32_t kFewLeaves = 64, kFewLeavesLoaded = 128;
+__device__ __forceinline__ void merge_few(const uint32_t *key, uint32_t n, uint32_t (*packages)[512], uint16_t (*leaves_before)[256])
+{
+    const uint32_t t = threadIdx.x, d = 2 * t;
+    uint32_t size = n, a_last = d < n ? d : n;
+    if (d + 1 < n) packages[0][t] = (key[d] >> 8) + (key[d + 1] >> 8);
+#pragma unroll 1
+    for (uint32_t j = 1; j < kL; j++) {
+        if (n > 64) {
+            __syncthreads();
+        } else { // the first wave has them all
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        const uint32_t *packs = packages[(j - 1) & 1];
+        const uint32_t npk = size / 2;
+        size = n + npk;
+        if (d > size) continue;
+        // the smallest a with leaf a heavier than package d - 1 - a
+        uint32_t a = d > npk ? d - npk : 0, hi = a_last;
+        const uint32_t fall = j < 8 ? 256u >> j : 1u;
+        uint32_t mid = a + fall < hi ? hi - fall : (a + hi) / 2;
+        while (a < hi) {
+            if (key[mid] >> 8 <= packs[d - 1 - mid]) a = mid + 1;
+            else hi = mid;
+            mid = (a + hi) / 2;
+        }
+        a_last = a;
+        leaves_before[j - 1][t] = (uint16_t)a;
+        // items d and d + 1
+        const uint32_t b = d - a, l0 = key[a] >> 8, l1 = key[a + 1] >> 8, p0 = packs[b], p1 = packs[b + 1];
+        const bool leaf0 = a < n && (b >= npk || l0 <= p0);
+        const uint32_t a1 = a + (leaf0 ? 1u : 0u), b1 = b + (leaf0 ? 0u : 1u);
+        const uint32_t l = leaf0 ? l1 : l0, p = leaf0 ? p0 : p1;
+        const bool leaf1 = a1 < n && (b1 >= npk || l <= p);
+        if (d + 1 < size) packages[j & 1][t] = (leaf0 ? l0 : p0) + (leaf1 ? l : p);
+    }
+}
+
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void dc_codes_kernel(EncArgs a)
 {
     // 16 KiB used twice: first the histogram columns, then the tables of the package-merge.
@@ -253,10 +301,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
     if (t < 4) area_bytes[t] = 0;
     chunk_histogram(src, raw, arena, hist);
 
-    for (uint32_t i = t; i < (LeafRanks::kEntries / 2 + 1024) / 4; i += 256) reinterpret_cast<u32x4 *>(lighter)[i] = u32x4{0, 0, 0, 0};
     if (t < LeafRanks::kAtOnce) key[256 + t] = ~0u;
     const uint32_t cnt = hist[t];
     const uint32_t n = (uint32_t)__syncthreads_count(cnt != 0);
+    const bool few = n <= (a.n_chunks > 1024 ? kFewLeavesLoaded : kFewLeaves);
+    if (!few)
+        for (uint32_t i = t; i < (LeafRanks::kEntries / 2 + 1024) / 4; i += 256) reinterpret_cast<u32x4 *>(lighter)[i] = u32x4{0, 0, 0, 0};
     // leaves in order of (count, byte value): sorted in the waves first, then every key finds its place among the other
     // three waves' keys
     {
@@ -279,6 +329,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
 
     if (n == 1) {
         if (t == 0) len_of[key[0] & 0xFFu] = 1;
+    } else if (n >= 2 && few) {
+        merge_few(key, n, items, leaves_before);
     } else if (n >= 2) {
         // Package-merge: level 0 is the sorted leaves; level j is the leaves merged with the pairs of
         // level j-1, a leaf before a package of equal weight.  leaves_before[j][m] = leaves among the
@@ -354,6 +406,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
             const uint32_t l0 = key[a0 < 255 ? a0 : 255] >> 8, l1 = key[a1 < 255 ? a1 : 255] >> 8;
             weight = (v.x ? v.x : l0) + (v.y ? v.y : l1);
         }
+    }
+    if (n >= 2) {
         __syncthreads();
         if (t == 0) {
             uint32_t bought = 2 * n - 2;

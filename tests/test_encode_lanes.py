@@ -96,3 +96,28 @@ def test_code_lengths_of_constructed_counts(encode, order, counts):
     used, status, table, blob = encode(order, 5, data, C, S)
     assert status == 0 and used == want.blob.size
     assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
+
+
+@pytest.mark.parametrize("order", list(ORDERS))
+@pytest.mark.parametrize("leaves", [2, 3, 63, 64, 65, 66, 128, 129])  # on both sides of the lines up to which a chunk has few
+def test_code_lengths_of_few_leaves(encode, order, leaves):
+    r = np.random.default_rng(leaves)
+    counts = [np.full(leaves, 5), 1 + r.integers(0, 40, leaves), np.minimum(1 + (1.3 ** np.arange(leaves)).astype(int), 900)]
+    parts = [np.concatenate([bytes_with_counts(c, leaves), np.zeros(4096, np.uint8)])[:8192] for c in counts]
+    C = 8192
+    data = np.concatenate([np.resize(p, C) for p in parts])
+    want = oc.compress(data, C, 64)
+    used, status, table, blob = encode(order, 5, data, C, 64)
+    assert status == 0 and used == want.blob.size
+    assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
+
+
+@pytest.mark.parametrize("chunks", [1024, 1025])
+def test_code_lengths_of_few_leaves_in_many_chunks(encode, chunks):
+    # beyond 1024 chunks more leaves are few
+    C = 256
+    data = np.random.default_rng(chunks).integers(0, 110, chunks * C - 3).astype(np.uint8)
+    want = oc.compress(data, C, 64)
+    used, status, table, blob = encode("shuffled", 5, data, C, 64)
+    assert status == 0 and used == want.blob.size
+    assert np.array_equal(table, want.table) and np.array_equal(blob, want.blob)
