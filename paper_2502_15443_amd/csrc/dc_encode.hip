@@ -495,7 +495,8 @@ __device__ __forceinline__ float lanes_smallest(float v)
 // after, a value that got its one state for being present has count < R, and there are more of the former than steps, which
 // are the sum of their shares' fractions less what the others were given.  So the steps go to the `steps` largest ratios, found
 // through the smallest of them, bit by bit.  Ratios are below 1024 and two of them differ by 1 / (2048 * 2048) or more, so
-// that their fixed-point quotients of 22 bits (grant_key) stand in the same order, and only equal ones are equal.
+// that their fixed-point quotients of 22 bits (grant_key) stand in the same order, and only equal ones are equal.  Four bits a turn, without
+// branches, until no more keys are left than steps.
 // (One step at a time, a reduction over the lanes each: the whole call 77 us on 688 chunks of 64 KiB and 65 on 1024 of 16 KiB
 // where it now takes 69 and 40.)
 __device__ __forceinline__ uint32_t grant_key(uint32_t count, uint32_t q, uint32_t raw)
@@ -506,13 +507,18 @@ __device__ __forceinline__ uint32_t grant_key(uint32_t count, uint32_t q, uint32
 __device__ __forceinline__ void grant_states(const uint32_t key[4], uint32_t q[4], uint32_t steps)
 {
     uint32_t last = 0; // the smallest key that gains: the largest that `steps` keys are not below
-    for (uint32_t bit = 1u << 31; bit > 0; bit >>= 1) {
-        uint32_t n = 0;
+    uint32_t gain = 0; // how many keys are not below it
+#pragma unroll 1
+    for (int at = 28; at >= 0 && gain != steps; at -= 4)
 #pragma unroll
-        for (int i = 0; i < 4; i++) n += (uint32_t)__popcll(__ballot(key[i] >= (last | bit)));
-        if (n >= steps) last |= bit;
-        if (n == steps) break; // the keys from here on are those that gain
-    }
+        for (int j = 3; j >= 0; j--) {
+            const uint32_t next = last | 1u << (at + j);
+            uint32_t n = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) n += (uint32_t)__popcll(__ballot(key[i] >= next));
+            last = n >= steps ? next : last;
+            gain = n >= steps ? n : gain;
+        }
 #pragma unroll
     for (int i = 0; i < 4; i++) steps -= (uint32_t)__popcll(__ballot(key[i] > last)); // what is left for keys equal to it
 #pragma unroll
@@ -607,13 +613,16 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
         const uint32_t share = (cnt << kTansBits) / raw; // cnt is at most 2^20
         const uint32_t q0 = cnt ? (share ? share : 1u) : 0u;
         nq[t] = q0;
-        cumq[t] = grant_key(cnt, q0, raw); // by all threads, two divisions each
         const uint32_t incl = lanes_prefix_sum<false>(q0);
         if (lane == 63) wave_sum[wave] = incl;
     }
     __syncthreads();
+    const int32_t diff = (int32_t)kTansL - (int32_t)(wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]);
+    if (diff > 0) { // the ratios, two divisions each, by all threads
+        cumq[t] = grant_key(hist[t], nq[t], raw);
+        __syncthreads();
+    }
     if (wave == 0) {
-        const int32_t diff = (int32_t)kTansL - (int32_t)(wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3]);
         uint32_t c[4], q[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -657,9 +666,10 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
     }
     __syncthreads();
     // ---- states: place p is state rev11(p); the states of a value in ascending order are numbered q, q + 1, ...
-    // Thread t takes places 8t .. 8t + 7; the number of place p among the places a .. a + q - 1 of its value is q
+    // Thread t takes places 8t .. 8t + 7; the number of place p among the places a .. e - 1 of its value is q
     // plus, for every set bit i of p, the places of the value that agree with p below bit i and have bit i
-    // clear: (q + M - 1 - ((p - a - 2^i) mod M)) div M with M = 2^(i+1).
+    // clear: (e + M - 1 - c) div M - (a + M - 1 - c) div M with M = 2^(i+1), c = p mod 2^i.  The sums over a and e are kept in
+    // the halves of one word, which neither additions nor, with a mask, shifts let into each other.
     {
         const uint4 m4 = *reinterpret_cast<const uint4 *>(marks + 8 * t);
         const uint32_t w16[4] = {m4.x, m4.y, m4.z, m4.w};
@@ -671,39 +681,41 @@ __global__ __launch_bounds__(256) void dc_tans_model_kernel(EncArgs a)
             tail = hi ? hi : tail;
         }
         uint32_t cur = lanes_last_nonzero_below<false>(tail);
-        uint32_t first[8], q[8], off[8], rank[8], most = 0;
+        uint32_t first[8], span[8], sum[8], most = 0;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
             const uint32_t m = (i & 1) ? w16[i / 2] >> 16 : w16[i / 2] & 0xFFFFu;
             cur = m ? m : cur;
             const uint32_t cq = cumq[(cur - 1) & 255u];
             first[i] = cq & 0xFFFFu;
-            q[i] = cq >> 16;
-            off[i] = 8 * t + i - first[i];
-            rank[i] = 0;
-            most = q[i] > most ? q[i] : most;
+            span[i] = cq + (cq << 16);
+            sum[i] = 0;
+            most = cq > most ? cq : most;
         }
         // A bit counts only where the value has more places than the bit's weight (of 2^b places in a row no two agree below bit b), so
-        // the most frequent value of the wave ends the loop; of the lowest three it is known which are set.  (All eleven bits of all places, with the
-        // ratios above worked out by one wave: 45 MB in chunks of 8 KiB 83.2 instead of 79.4 us, 64 KiB 67.2 instead of 66.6, at 128 sub-streams 77.8
-        // instead of 76.0.)
-        auto count_bit = [&](uint32_t b, int i) {
-            const uint32_t M = 2u << b;
-            rank[i] += (q[i] + M - 1 - ((off[i] - (1u << b)) & (M - 1))) >> (b + 1);
-        };
+        // the most frequent value of the wave ends the count; of the lowest three it is known which are set.  (All eleven bits of all
+        // places, then those that count in a loop with a branch a thread, then as here, with the ratios above by one wave, by all threads always, where
+        // they are asked for: 66 chunks of 8 KiB 15.6 / 15.9 / 15.4 us, of one value 13.4 / 14.2 / 13.9; 2048 of 4 KiB 33.4 / 33.8 / 32.4.)
+        auto both = [](uint32_t v) { return v << 16 | v; };
+        auto halved = [&](uint32_t v, uint32_t by) { return v >> by & both(0xFFFFu >> by); };
 #pragma unroll
         for (uint32_t b = 0; b < 3; b++)
 #pragma unroll
-            for (int i = 0; i < 8; i++)
-                if ((uint32_t)i >> b & 1u) count_bit(b, i);
-#pragma unroll 1
-        for (uint32_t b = 3; b < kTansBits && __any(most > 1u << b); b++)
-            if (t >> (b - 3) & 1u)
+            for (uint32_t i = 0; i < 8; i++)
+                if (i >> b & 1u) sum[i] += halved(span[i] + both((2u << b) - 1 - (i & ((1u << b) - 1))), b + 1);
 #pragma unroll
-                for (int i = 0; i < 8; i++) count_bit(b, i);
+        for (uint32_t i = 0; i < 8; i++) span[i] -= both(i);
+#pragma unroll
+        for (uint32_t b = 3; b < kTansBits; b++) {
+            if (!__any(most >> 16 > 1u << b)) break;
+            const uint32_t from = both((2u << b) - 1 - 8 * (t & ((1u << (b - 3)) - 1)));
+            const uint32_t mask = t >> (b - 3) & 1u ? both(0xFFFFu >> (b + 1)) : 0u;
+#pragma unroll
+            for (int i = 0; i < 8; i++) sum[i] += (span[i] + from) >> (b + 1) & mask;
+        }
 #pragma unroll
         for (int i = 0; i < 8; i++)
-            state_of[(first[i] + rank[i]) & (kTansL - 1)] = (uint16_t)(kTansL + (__brev(8 * t + i) >> (32 - kTansBits)));
+            state_of[(first[i] + (sum[i] >> 16) - (sum[i] & 0xFFFFu)) & (kTansL - 1)] = (uint16_t)(kTansL + (__brev(8 * t + i) >> (32 - kTansBits)));
     }
     __syncthreads();
 
