@@ -301,12 +301,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void d
     if (t < 4) area_bytes[t] = 0;
     chunk_histogram(src, raw, arena, hist);
 
+    for (uint32_t i = t; i < (LeafRanks::kEntries / 2 + 1024) / 4; i += 256) reinterpret_cast<u32x4 *>(lighter)[i] = u32x4{0, 0, 0, 0};
     if (t < LeafRanks::kAtOnce) key[256 + t] = ~0u;
     const uint32_t cnt = hist[t];
     const uint32_t n = (uint32_t)__syncthreads_count(cnt != 0);
     const bool few = n <= (a.n_chunks > 1024 ? kFewLeavesLoaded : kFewLeaves);
-    if (!few)
-        for (uint32_t i = t; i < (LeafRanks::kEntries / 2 + 1024) / 4; i += 256) reinterpret_cast<u32x4 *>(lighter)[i] = u32x4{0, 0, 0, 0};
     // leaves in order of (count, byte value): sorted in the waves first, then every key finds its place among the other
     // three waves' keys
     {
