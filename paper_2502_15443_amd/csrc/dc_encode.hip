@@ -231,7 +231,7 @@ struct LeafRanks {
 // number a of leaves among the 2t items before them.  From level to level items get lighter and a falls, by about half as much each
 // time, so the search begins that far below the last a and is mostly over after a few steps, after none where there are hardly
 // any leaves.  What many leaves take (in the kernel) costs the same whatever their number: the tables of LeafRanks and some
-// four trips to LDS a level.  2048 chunks of 4 KiB with it / with this: 2 values 29.7 / 25.1 us, 16 30.1 / 26.7, 64 30.5 / 27.5, 128 31.3 / 30.1.
+// four trips to LDS a level.  2048 chunks of 4 KiB with it / with this: 2 values 29.7 / 25.4 us, 16 30.2 / 27.1, 64 30.5 / 27.9, 128 31.3 / 30.3; 20 of 64 values 15.08 / 15.13.
 // From 65 leaves on, where more than one wave takes part, it is a chunk's trips to LDS against the compute unit's
 // work: 64 such chunks of 128 values take 15.4 / 15.9, so that there it is for launches of more than four workgroups a compute unit.
 constexpr uint32_t kFewLeaves = 64, kFewLeavesLoaded = 128;

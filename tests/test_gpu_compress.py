@@ -380,7 +380,7 @@ def test_device_compress_of_few_values(values, chunks):
 
 
 def test_device_compress_of_two_values_is_shorter_than_of_all():
-    """2048 chunks of 4 KiB: with 2 values there is hardly a package to merge, 0.77 of the time that 256 take (25.1 and 32.6 us).  With the tables of
+    """2048 chunks of 4 KiB: with 2 values there is hardly a package to merge, 0.77 of the time that 256 take (25.4 and 32.9 us).  With the tables of
     the packages' ranks built for either it was 0.90."""
     print("case dev two values", flush=True)
     C, chunks = 4096, 2048
